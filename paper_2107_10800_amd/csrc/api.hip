@@ -537,7 +537,8 @@ int fmm_pair(arb_ctx *ctx, hipStream_t s, int N, const double *pos, const float4
         std::string msg;
         const auto t0 = std::chrono::steady_clock::now();
         const int rc = arb::fmm_build(F, s, N, pos, hi, lo, ctx->opt.a, ctx->opt.fmm_order,
-                                      ctx->opt.fmm_levels, ctx->opt.fmm_leaf, 1, &msg);
+                                      ctx->opt.fmm_levels, ctx->opt.fmm_leaf, 1,
+                                      ctx->opt.wall != 0, &msg);
         if (rc) return fail(ctx, rc, msg);
         F.build_ms =
             std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0)
@@ -623,7 +624,7 @@ int body_mobility_dev(arb_ctx *ctx, hipStream_t s, const double *x6, double scal
             const auto t0 = std::chrono::steady_clock::now();
             const int rc = arb::fmm_build(F, s, M, ctx->pos.as<double>(), ctx->hi.as<float4>(),
                                           ctx->lo.as<float4>(), ctx->opt.a, ctx->opt.fmm_order,
-                                          ctx->opt.fmm_levels, ctx->opt.fmm_leaf, 2, &msg);
+                                          ctx->opt.fmm_levels, ctx->opt.fmm_leaf, 2, false, &msg);
             if (rc) return fail(ctx, rc, msg);
             F.build_ms = std::chrono::duration<double, std::milli>(
                              std::chrono::steady_clock::now() - t0)

@@ -76,14 +76,31 @@ constexpr int kFmmDefaultOrder = 6;
 
 // octree and proxy buffers of the fast product; cells of all levels 0..L in
 // Morton order, level l at [lvl[l], lvl[l+1])
+// M2L entries of one (level, target minus source cell offset, above the wall the
+// target cells' height): columns [first, first + count) of FmmState::cols (source
+// cell, slot)
+struct FmmBatch {
+    int first, count, level, tz, dx, dy, dz, pad;
+};
+// M2L runs over chunks of target cells (counted from level 2's first), so that the
+// slots of a chunk's entries stay within kFmmSlotBytes
+struct FmmChunk {
+    int cell0, cell1, batch0, batch1, slot0;
+};
+constexpr int64_t kFmmSlotBytes = (int64_t)256 << 20;
+
 struct FmmHostCache;  // host buffers of the tree build, kept between builds (fmm.hip)
 struct FmmState {
     std::shared_ptr<FmmHostCache> host;
-    DevBuf perm, cc, rng, parent, kids, il_ptr, il, near_ptr, nearl, work, tab, shi, slo, slam,
+    DevBuf perm, cc, rng, parent, kids, near_ptr, nearl, work, tab, shi, slo, slam,
         qhat, v, slam2, qhat2, v2;  // second channel: the torques of single-blob bodies
-    DevBuf vsplit;  // M2L sums of the parts of split interaction lists (splits > 1)
+    // M2L: sparse listed cells per cell, slots per cell, columns and batches of the
+    // dense entries, the entries' results
+    DevBuf sp_ptr, sp, slot_ptr, cols, batches, slots;
+    std::vector<FmmChunk> chunks;
+    DevBuf vsplit;  // M2L sums of the parts of split sparse lists (splits > 1)
     int N = 0, L = 0, n = 0, P = 0, ncell = 0, nleaf = 0, nwork = 0, channels = 1;
-    int splits = 1;  // M2L work items per cell
+    int splits = 1;  // M2L work items per cell (sparse part)
     int64_t n_il = 0, n_near_pairs = 0;  // interaction-list entries, direct pairs
     int64_t n_m2l_pairs = 0;             // M2L pair evaluations per product
     std::vector<int> lvl;
@@ -96,11 +113,15 @@ struct FmmState {
 // prep_positions makes them); order = Chebyshev points per direction (0: the
 // default), levels = leaf level (0: chosen, from leaf, the mean blobs per leaf
 // aimed at, or when leaf = 0 the level with the fewest pair evaluations);
-// channels = 2 adds the torque channel of single-blob bodies.  Returns 0 or an
+// channels = 2 adds the torque channel of single-blob bodies; wall: the products
+// will be above the wall.  Returns 0 or an
 // ARB_E_* code with *msg set.
 int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const float4 *hi,
-              const float4 *lo, double a, int order, int levels, int leaf, int channels,
+              const float4 *lo, double a, int order, int levels, int leaf, int channels, bool wall,
               std::string *msg);
+// v of every cell of levels 2..L from its interaction list (fmm_m2l.hip); channels =
+// 1: forces, 2: forces and torques (a tree built with channels = 2)
+void fmm_m2l(const FmmState &F, hipStream_t s, int channels, bool wall, bool fp64);
 // partial[c][i] (3 x N, original order) = the approximation of M_{a=1} lambda,
 // M in units of 1/(8 pi eta) with positions in units of a; fp64: lambda and
 // every sum in double (linear in lambda to double rounding), else in float

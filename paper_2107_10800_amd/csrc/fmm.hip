@@ -29,12 +29,10 @@
 //   M2M  the parent's qhat from its children's proxies (exact: the parent's
 //        Lagrange polynomials have degree n-1 and the children interpolate
 //        them exactly);
-//   M2L  v^c_k = sum_{c' in IL(c)} sum_m M(t^c_k, s^c'_m) qhat^c'_m, matrix-free
-//        with the FP32 pair function (one workgroup per cell, lane groups of
-//        one lane per target proxy taking listed cells in turn, the source
-//        proxies of each listed cell staged in LDS; a listed cell with fewer
-//        blobs than proxies enters with its blobs, n^3 |c'| pairs instead of
-//        n^6);
+//   M2L  v^c_k = sum_{c' in IL(c)} sum_m M(t^c_k, s^c'_m) qhat^c'_m with FP32 tensor
+//        values (fmm_m2l.hip): batches of equal (level, offset, height) on the
+//        matrix cores; a listed cell with fewer blobs than proxies enters with
+//        its blobs, n^3 |c'| pairs instead of n^6;
 //   L2L  the children's v gain the parent's interpolant at their proxies;
 //   near + L2P  direct sums over the adjacent leaves (hi/lo split positions,
 //        float runs promoted to double, as in the dense FP32 kernel) plus
@@ -62,29 +60,13 @@
 #include <thread>
 #include <type_traits>
 
-#include "rot_device.h"
+#include "fmm_device.h"
 
 namespace arb {
 
 namespace {
 
-constexpr int kTabNode = 0, kTabDen = kFmmMaxOrder, kTabT1 = 2 * kFmmMaxOrder;
-constexpr int kTabSize = 2 * kFmmMaxOrder + 2 * kFmmMaxOrder * kFmmMaxOrder;
 constexpr int kNearBlock = 64;
-constexpr int kFmmRun = 32;
-
-template <class A>
-using Vec4 = std::conditional_t<std::is_same_v<A, float>, float4, double4>;
-
-template <class A>
-__device__ __forceinline__ Vec4<A> vec4(A x, A y, A z) {
-    Vec4<A> r;
-    r.x = x;
-    r.y = y;
-    r.z = z;
-    r.w = A(0);
-    return r;
-}
 
 // free-space RPY coefficients c1, c2 (units of a) of M = c1 I + c2 r r^T
 __device__ __forceinline__ void free_coef(float r2, float rinv, float &c1, float &c2) {
@@ -131,60 +113,12 @@ __device__ __forceinline__ void pair_acc(float dx, float dy, float dz, float dxy
     }
 }
 
-struct Geo {
-    double ox, oy, oz, S;  // root cube in units of a
-    int n, P;
-};
-
-__device__ __forceinline__ void load_tab(const float *__restrict__ g, float *tab) {
-    for (int i = threadIdx.x; i < kTabSize; i += blockDim.x) tab[i] = g[i];
-    __syncthreads();
-}
-
-// the item of this workgroup when the launch has round_up(items, 8 kXcdChunk)
-// workgroups: consecutive workgroups are dealt round-robin to the 8 XCDs, so
-// this gives each XCD runs of kXcdChunk consecutive items (neighbouring cells in
-// Morton order, which read the same leaves and multipole weights, share its
-// L2), the runs dealt round-robin to keep the XCDs' loads even; -1 past the end
-constexpr int kXcdChunk = 16;
-__device__ __forceinline__ int xcd_item(int items) {
-    const int x = blockIdx.x % 8, j = blockIdx.x / 8;
-    const int it = (j / kXcdChunk) * 8 * kXcdChunk + x * kXcdChunk + j % kXcdChunk;
-    return it < items ? it : -1;
-}
-
 // Lagrange polynomial l_k(u) at the Chebyshev points (product form)
 __device__ __forceinline__ float lag(const float *tab, int n, int k, float u) {
     float p = tab[kTabDen + k];
     for (int j = 0; j < n; ++j)
         if (j != k) p *= u - tab[kTabNode + j];
     return p;
-}
-
-// a double split into float hi + lo
-struct F2 {
-    float h, l;
-};
-__device__ __forceinline__ F2 split(double x) {
-    const float h = (float)x;
-    return F2{h, (float)(x - (double)h)};
-}
-
-__device__ __forceinline__ double centre(double o, double side, int i) {
-    return o + ((double)i + 0.5) * side;
-}
-
-// v of the cells of split interaction lists: the parts' sums, added in the
-// order of the parts (m values of 3 P doubles per cell)
-__global__ void fmm_split_sum_kernel(int64_t m, int splits, int P3,
-                                     const double *__restrict__ vpart, double *__restrict__ v) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const int64_t c = i / P3, r = i - c * P3;
-    const double *p = vpart + c * splits * P3 + r;
-    double t = 0.0;
-    for (int j = 0; j < splits; ++j) t += p[(int64_t)j * P3];
-    v[i] = t;
 }
 
 __global__ void fmm_sort_pos_kernel(int N, const int *__restrict__ perm,
@@ -308,130 +242,6 @@ __global__ __launch_bounds__(kFmmMaxP) void fmm_m2m_kernel(Geo g, const float *_
         qz += fz;
     }
     if (act) qhat[(size_t)c * P + k] = vec4<A>((A)qx, (A)qy, (A)qz);
-}
-
-// v of every cell of levels 2..L over its interaction list: `groups` lane
-// groups of P (one lane per target proxy) take interaction-list entries in
-// turn, so that groups * P fills the workgroup's waves; the groups' sums meet
-// in LDS at the end
-template <bool WALL, class A>
-__global__ __launch_bounds__(kFmmMaxP) void fmm_m2l_kernel(
-    Geo g, const float *__restrict__ tabg, const int4 *__restrict__ cc,
-    const int *__restrict__ il_ptr, const int *__restrict__ il, int cell0, int items, int groups,
-    int splits,
-    const int2 *__restrict__ rng, const float4 *__restrict__ shi, const float4 *__restrict__ slo,
-    const Vec4<A> *__restrict__ slam, const Vec4<A> *__restrict__ qhat, double *__restrict__ v,
-    double *__restrict__ vpart) {
-    const int item = xcd_item(items);
-    if (item < 0) return;
-    // LDS sized by the host: the sources of `groups` listed cells (offsets from
-    // the cell's centre and charges), the groups' sums, the table
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int n = g.n, P = g.P;
-    const int GP = groups * P;  // <= kFmmMaxP
-    Vec4<A> *s_q = reinterpret_cast<Vec4<A> *>(lds);
-    float4 *s_off = reinterpret_cast<float4 *>(s_q + GP);
-    double *s_acc = reinterpret_cast<double *>(s_off + GP);
-    float *tab = reinterpret_cast<float *>(s_acc + 3 * (GP - P));
-    load_tab(tabg, tab);
-    // a cell's interaction list may be split over `splits` consecutive items,
-    // each of which stores its part's sum at its own place in vpart
-    const int c = cell0 + item / splits, part = item % splits;
-    const int tid = threadIdx.x;
-    const int4 ct = cc[c];
-    const double side = ldexp(g.S, -ct.w), w = 0.5 * side;
-    const bool act = tid < GP;
-    const int gi = act ? tid / P : 0;
-    const int k = act ? tid - gi * P : 0;
-    const int kx = k / (n * n), ky = (k / n) % n, kz = k % n;
-    const float okx = (float)(w * tab[kTabNode + kx]), oky = (float)(w * tab[kTabNode + ky]),
-                okz = (float)(w * tab[kTabNode + kz]);
-    const double czt = centre(g.oz, side, ct.z);
-    const float zi = (float)(czt + w * tab[kTabNode + kz]);  // target proxy height
-    const TargetZ<float> zsc = target_z(zi);
-    double ux = 0.0, uy = 0.0, uz = 0.0;
-    const int b0 = il_ptr[c], len = il_ptr[c + 1] - b0;
-    const int e1 = b0 + (int)((int64_t)len * (part + 1) / splits);
-    for (int e0 = b0 + (int)((int64_t)len * part / splits); e0 < e1; e0 += groups) {
-        __syncthreads();
-        // a listed cell with fewer blobs than proxies enters with its blobs,
-        // the others with their proxies (offsets w xi) and multipole weights
-        for (int t = tid; t < GP; t += blockDim.x) {
-            const int gg = t / P, m = t - gg * P;
-            if (e0 + gg >= e1) continue;
-            const int sc = il[e0 + gg];
-            const int2 r = rng[sc];
-            if (r.y - r.x < P) {
-                if (m < r.y - r.x) {
-                    const int4 cs = cc[sc];
-                    const F2 cx = split(centre(g.ox, side, cs.x)),
-                             cy = split(centre(g.oy, side, cs.y)),
-                             cz = split(centre(g.oz, side, cs.z));
-                    const float4 h = shi[r.x + m], l = slo[r.x + m];
-                    s_off[t] = make_float4((h.x - cx.h) + (l.x - cx.l), (h.y - cy.h) + (l.y - cy.l),
-                                           (h.z - cz.h) + (l.z - cz.l), 0.f);
-                    s_q[t] = slam[r.x + m];
-                }
-            } else {
-                const int mx = m / (n * n), my = (m / n) % n, mz = m % n;
-                s_off[t] = make_float4((float)(w * tab[kTabNode + mx]),
-                                       (float)(w * tab[kTabNode + my]),
-                                       (float)(w * tab[kTabNode + mz]), 0.f);
-                s_q[t] = qhat[(size_t)sc * P + m];
-            }
-        }
-        __syncthreads();
-        const int e = e0 + gi;
-        if (!act || e >= e1) continue;
-        const int sc = il[e];
-        const int4 cs = cc[sc];
-        const int cnt = min(P, rng[sc].y - rng[sc].x);
-        // target proxy minus source cell centre, from the integer offset
-        const float ax = (float)((double)(ct.x - cs.x) * side) + okx;
-        const float ay = (float)((double)(ct.y - cs.y) * side) + oky;
-        const float az = (float)((double)(ct.z - cs.z) * side) + okz;
-        const float zc = (float)centre(g.oz, side, cs.z);
-        const float4 *so = s_off + gi * P;
-        const Vec4<A> *sq = s_q + gi * P;
-        for (int m0 = 0; m0 < cnt; m0 += kFmmRun) {
-            const int m1 = min(m0 + kFmmRun, cnt);
-            A fx = 0, fy = 0, fz = 0;
-            for (int m = m0; m < m1; ++m) {
-                const float4 o = so[m];
-                const Vec4<A> q = sq[m];
-                const float dx = ax - o.x, dy = ay - o.y, dz = az - o.z;
-                const float dxy2 = fmaf(dx, dx, dy * dy);
-                const float zj = zc + o.z;
-                const float h2 = 2.f * zj;
-                pair_acc<WALL, A>(dx, dy, dz, dxy2, zsc, zi, zj, h2, -(h2 * h2), q.x, q.y, q.z, fx,
-                                  fy, fz);
-            }
-            ux += fx;
-            uy += fy;
-            uz += fz;
-        }
-    }
-    // the groups' sums, added in group order
-    __syncthreads();
-    if (act && gi > 0) {
-        double *a = s_acc + 3 * (tid - P);
-        a[0] = ux;
-        a[1] = uy;
-        a[2] = uz;
-    }
-    __syncthreads();
-    if (act && gi == 0) {
-        for (int gg = 1; gg < groups; ++gg) {
-            const double *a = s_acc + 3 * ((gg - 1) * P + k);
-            ux += a[0];
-            uy += a[1];
-            uz += a[2];
-        }
-        double *o = splits == 1 ? v + ((size_t)c * P + k) * 3 : vpart + ((size_t)item * P + k) * 3;
-        o[0] = ux;
-        o[1] = uy;
-        o[2] = uz;
-    }
 }
 
 // the children at one level gain the parent's interpolant at their proxies (NO
@@ -605,122 +415,6 @@ __device__ __forceinline__ void rot_acc(float dx, float dy, float dz, float r2, 
     }
 }
 
-// M2L of the generalised tensor (unbounded), lane groups as in fmm_m2l_kernel
-template <class A>
-__global__ __launch_bounds__(kFmmMaxP) void fmm_m2l6_kernel(
-    Geo g, const float *__restrict__ tabg, const int4 *__restrict__ cc,
-    const int *__restrict__ il_ptr, const int *__restrict__ il, int cell0, int items, int groups,
-    int splits,
-    const int2 *__restrict__ rng, const float4 *__restrict__ shi, const float4 *__restrict__ slo,
-    const Vec4<A> *__restrict__ sf, const Vec4<A> *__restrict__ st,
-    const Vec4<A> *__restrict__ qf, const Vec4<A> *__restrict__ qt, double *__restrict__ vu,
-    double *__restrict__ vw, double *__restrict__ vpart) {
-    const int item = xcd_item(items);
-    if (item < 0) return;
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int n = g.n, P = g.P;
-    const int GP = groups * P;  // <= kFmmMaxP
-    Vec4<A> *s_qf = reinterpret_cast<Vec4<A> *>(lds);
-    Vec4<A> *s_qt = s_qf + GP;
-    float4 *s_off = reinterpret_cast<float4 *>(s_qt + GP);
-    double *s_acc = reinterpret_cast<double *>(s_off + GP);
-    float *tab = reinterpret_cast<float *>(s_acc + 6 * (GP - P));
-    load_tab(tabg, tab);
-    // a cell's interaction list may be split over `splits` consecutive items,
-    // each of which stores its part's sum at its own place in vpart
-    const int c = cell0 + item / splits, part = item % splits;
-    const int tid = threadIdx.x;
-    const int4 ct = cc[c];
-    const double side = ldexp(g.S, -ct.w), w = 0.5 * side;
-    const bool act = tid < GP;
-    const int gi = act ? tid / P : 0;
-    const int k = act ? tid - gi * P : 0;
-    const int kx = k / (n * n), ky = (k / n) % n, kz = k % n;
-    const float okx = (float)(w * tab[kTabNode + kx]), oky = (float)(w * tab[kTabNode + ky]),
-                okz = (float)(w * tab[kTabNode + kz]);
-    double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    const int b0 = il_ptr[c], len = il_ptr[c + 1] - b0;
-    const int e1 = b0 + (int)((int64_t)len * (part + 1) / splits);
-    for (int e0 = b0 + (int)((int64_t)len * part / splits); e0 < e1; e0 += groups) {
-        __syncthreads();
-        // sparse listed cells enter with their bodies, the others with proxies
-        for (int t = tid; t < GP; t += blockDim.x) {
-            const int gg = t / P, m = t - gg * P;
-            if (e0 + gg >= e1) continue;
-            const int sc = il[e0 + gg];
-            const int2 r = rng[sc];
-            if (r.y - r.x < P) {
-                if (m < r.y - r.x) {
-                    const int4 cs = cc[sc];
-                    const F2 cx = split(centre(g.ox, side, cs.x)),
-                             cy = split(centre(g.oy, side, cs.y)),
-                             cz = split(centre(g.oz, side, cs.z));
-                    const float4 h = shi[r.x + m], l = slo[r.x + m];
-                    s_off[t] = make_float4((h.x - cx.h) + (l.x - cx.l), (h.y - cy.h) + (l.y - cy.l),
-                                           (h.z - cz.h) + (l.z - cz.l), 0.f);
-                    s_qf[t] = sf[r.x + m];
-                    s_qt[t] = st[r.x + m];
-                }
-            } else {
-                const int mx = m / (n * n), my = (m / n) % n, mz = m % n;
-                s_off[t] = make_float4((float)(w * tab[kTabNode + mx]),
-                                       (float)(w * tab[kTabNode + my]),
-                                       (float)(w * tab[kTabNode + mz]), 0.f);
-                const size_t q = (size_t)sc * P + m;
-                s_qf[t] = qf[q];
-                s_qt[t] = qt[q];
-            }
-        }
-        __syncthreads();
-        const int e = e0 + gi;
-        if (!act || e >= e1) continue;
-        const int sc = il[e];
-        const int4 cs = cc[sc];
-        const int cnt = min(P, rng[sc].y - rng[sc].x);
-        const float ax = (float)((double)(ct.x - cs.x) * side) + okx;
-        const float ay = (float)((double)(ct.y - cs.y) * side) + oky;
-        const float az = (float)((double)(ct.z - cs.z) * side) + okz;
-        const Vec4<A> *qfg = s_qf + gi * P, *qtg = s_qt + gi * P;
-        const float4 *so = s_off + gi * P;
-        for (int m0 = 0; m0 < cnt; m0 += kFmmRun) {
-            const int m1 = min(m0 + kFmmRun, cnt);
-            A f6[6] = {0, 0, 0, 0, 0, 0};
-            for (int m = m0; m < m1; ++m) {
-                const float4 o = so[m];
-                const float dx = ax - o.x, dy = ay - o.y, dz = az - o.z;
-                rot_acc<A>(dx, dy, dz, fmaf(dz, dz, fmaf(dx, dx, dy * dy)), qfg[m], qtg[m], f6);
-            }
-#pragma unroll
-            for (int j = 0; j < 6; ++j) acc[j] += f6[j];
-        }
-    }
-    __syncthreads();
-    if (act && gi > 0) {
-#pragma unroll
-        for (int j = 0; j < 6; ++j) s_acc[6 * (tid - P) + j] = acc[j];
-    }
-    __syncthreads();
-    if (act && gi == 0) {
-        for (int gg = 1; gg < groups; ++gg)
-#pragma unroll
-            for (int j = 0; j < 6; ++j) acc[j] += s_acc[6 * ((gg - 1) * P + k) + j];
-        double *ou, *ow;
-        if (splits == 1) {
-            ou = vu + ((size_t)c * P + k) * 3;
-            ow = vw + ((size_t)c * P + k) * 3;
-        } else {
-            ou = vpart + ((size_t)item * P + k) * 3;
-            ow = ou + (size_t)items * P * 3;
-        }
-        ou[0] = acc[0];
-        ou[1] = acc[1];
-        ou[2] = acc[2];
-        ow[0] = acc[3];
-        ow[1] = acc[4];
-        ow[2] = acc[5];
-    }
-}
-
 // direct sums of the generalised tensor over adjacent leaves plus both
 // channels' interpolants; partial[j][body] (6 x M, original order)
 template <class A>
@@ -834,8 +528,6 @@ inline int compact3(uint64_t x) {  // every third bit -> 21 bits (inverse of spr
     x = (x | (x >> 32)) & 0x1fffffull;
     return (int)x;
 }
-
-int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
 // host threads for the O(N) steps of the tree build: at most 16 (one GPU's
 // share of the host), one per 65,536 blobs; the environment variable
@@ -1034,40 +726,10 @@ void CellHash::build(const uint64_t *k, int n, int base, int threads) {
     });
 }
 
-// work items per cell in M2L: one, or up to 8 when there are too few cells to
-// fill the chip (about 2,048 items wanted)
+// work items per cell of M2L's sparse part: one, or up to 8 when there are too few
+// cells to fill the chip (about 2,048 items wanted)
 int m2l_splits(int cells) {
     return std::max(1, std::min(8, (2048 + cells - 1) / std::max(cells, 1)));
-}
-
-// calls f with the order n (2..kFmmMaxOrder, checked when the options are
-// read) as a compile-time constant, for the kernels whose loops unroll over it
-template <class F> void with_order(int n, F &&f) {
-    static_assert(kFmmMaxOrder == 8, "cases 2..8");
-    switch (n) {
-    case 2: f(std::integral_constant<int, 2>{}); break;
-    case 3: f(std::integral_constant<int, 3>{}); break;
-    case 4: f(std::integral_constant<int, 4>{}); break;
-    case 5: f(std::integral_constant<int, 5>{}); break;
-    case 6: f(std::integral_constant<int, 6>{}); break;
-    case 7: f(std::integral_constant<int, 7>{}); break;
-    default: f(std::integral_constant<int, 8>{}); break;
-    }
-}
-
-// M2L lane groups per workgroup: the count (up to 8 within 512 lanes) that
-// leaves the fewest idle lanes in its waves
-int m2l_groups(int P) {
-    int groups = 1;
-    double best = 0.0;
-    for (int gq = 1; gq <= 8 && gq * P <= kFmmMaxP; ++gq) {
-        const double util = (double)(gq * P) / round_up(gq * P, kWave);
-        if (util > best + 1e-9) {
-            best = util;
-            groups = gq;
-        }
-    }
-    return groups;
 }
 
 }  // namespace
@@ -1098,6 +760,16 @@ struct HostArr {
         return p.get();
     }
 };
+// M2L's work (fmm_m2l.hip): per cell of levels 2..L the sparse listed cells and the
+// slots of its dense entries, the dense entries grouped into batches, and the
+// chunks of cells that share the slots' memory
+struct M2LGroups {
+    std::vector<int> sp_ptr, sp, slot_ptr, count, zidx;
+    std::vector<int2> cols;
+    std::vector<FmmBatch> batches;
+    std::vector<FmmChunk> chunks;
+    int max_slots = 0;  // of a chunk
+};
 struct PlanScratch {
     HostArr<int> crd, idx, idx2;
     HostArr<uint64_t> key, key2;
@@ -1111,6 +783,7 @@ struct PlanScratch {
 struct arb::FmmHostCache {
     PlanScratch scratch;
     FmmPlan plan;
+    M2LGroups m2l;
     double *hpos = nullptr;
     size_t hpos_n = 0;
     FmmHostCache() = default;
@@ -1526,8 +1199,103 @@ int fmm_plan(FmmPlan &pl, PlanScratch &sc, int N, const double *h, double a, int
     return 0;
 }
 
+// Groups the interaction lists for M2L.  Entries whose listed cell holds at least P
+// blobs are dense: they get a slot each, numbered in list order within a chunk of
+// target cells, and are sorted (counting sort, stable) by the key that fixes the
+// tensor between the two proxy grids: the level, the cells' offset and, above the
+// wall, the target cell's height.  Equal keys make batches of at most max_cols
+// columns.
+static void group_m2l(const FmmPlan &pl, bool wall, int max_cols, int64_t chunk_slots,
+                      M2LGroups &G) {
+    G.sp.clear();
+    G.cols.clear();
+    G.batches.clear();
+    G.chunks.clear();
+    G.max_slots = 0;
+    const int cell0 = pl.L >= 2 ? pl.lvl[2] : pl.ncell, nc = pl.ncell - cell0, P = pl.P;
+    G.sp_ptr.assign((size_t)nc + 1, 0);
+    G.slot_ptr.assign((size_t)nc + 1, 0);
+    auto dense = [&](int sc) { return pl.rng[sc].y - pl.rng[sc].x >= P; };
+    for (int i = 0; i < nc; ++i) {
+        int d = 0;
+        for (int e = pl.il_ptr[cell0 + i]; e < pl.il_ptr[cell0 + i + 1]; ++e) {
+            if (dense(pl.il[e]))
+                ++d;
+            else
+                G.sp.push_back(pl.il[e]);
+        }
+        G.sp_ptr[i + 1] = (int)G.sp.size();
+        G.slot_ptr[i + 1] = G.slot_ptr[i] + d;
+    }
+    G.cols.resize((size_t)G.slot_ptr[nc]);
+    for (int a = 0; a < nc;) {
+        int b = a + 1;
+        while (b < nc && G.slot_ptr[b + 1] - G.slot_ptr[a] <= chunk_slots) ++b;
+        FmmChunk ch{a, b, (int)G.batches.size(), 0, G.slot_ptr[a]};
+        int out = G.slot_ptr[a];
+        for (int x = a; x < b;) {  // the cells of one level
+            const int l = pl.cc[cell0 + x].w;
+            int y = x + 1;
+            while (y < b && pl.cc[cell0 + y].w == l) ++y;
+            // the heights that occur, numbered
+            int z0 = pl.cc[cell0 + x].z, z1 = z0, nz = 1;
+            if (wall) {
+                for (int i = x; i < y; ++i) {
+                    z0 = std::min(z0, pl.cc[cell0 + i].z);
+                    z1 = std::max(z1, pl.cc[cell0 + i].z);
+                }
+                G.zidx.assign((size_t)(z1 - z0 + 1), -1);
+                nz = 0;
+                for (int i = x; i < y; ++i) {
+                    int &zi = G.zidx[pl.cc[cell0 + i].z - z0];
+                    if (zi < 0) zi = nz++;
+                }
+            }
+            auto key = [&](const int4 &t, const int4 &s) {
+                const int d = ((t.x - s.x + 3) * 7 + (t.y - s.y + 3)) * 7 + (t.z - s.z + 3);
+                return (wall ? G.zidx[t.z - z0] : 0) * 343 + d;
+            };
+            G.count.assign((size_t)nz * 343 + 1, 0);
+            for (int i = x; i < y; ++i)
+                for (int e = pl.il_ptr[cell0 + i]; e < pl.il_ptr[cell0 + i + 1]; ++e)
+                    if (dense(pl.il[e])) ++G.count[key(pl.cc[cell0 + i], pl.cc[pl.il[e]]) + 1];
+            for (int k = 0; k < nz * 343; ++k) G.count[k + 1] += G.count[k];
+            const int base = out;
+            out += G.count[nz * 343];
+            for (int i = x; i < y; ++i) {
+                int slot = G.slot_ptr[i] - ch.slot0;
+                for (int e = pl.il_ptr[cell0 + i]; e < pl.il_ptr[cell0 + i + 1]; ++e) {
+                    const int sc = pl.il[e];
+                    if (!dense(sc)) continue;
+                    const int at = base + G.count[key(pl.cc[cell0 + i], pl.cc[sc])]++;
+                    G.cols[at] = make_int2(sc, slot++);
+                }
+            }
+            // count[k] is now the end of key k's entries
+            for (int zi = 0, k0 = 0; zi < nz; ++zi) {
+                int tz = 0;
+                if (wall)
+                    while (G.zidx[tz] != zi) ++tz;
+                for (int d = 0; d < 343; ++d) {
+                    const int k1 = G.count[zi * 343 + d];
+                    for (int f = k0; f < k1; f += max_cols)
+                        G.batches.push_back(FmmBatch{base + f, std::min(max_cols, k1 - f), l,
+                                                     wall ? z0 + tz : 0, d / 49 - 3,
+                                                     (d / 7) % 7 - 3, d % 7 - 3, 0});
+                    k0 = k1;
+                }
+            }
+            x = y;
+        }
+        ch.batch1 = (int)G.batches.size();
+        G.max_slots = std::max(G.max_slots, G.slot_ptr[b] - G.slot_ptr[a]);
+        G.chunks.push_back(ch);
+        a = b;
+    }
+}
+
 int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const float4 *hi,
-              const float4 *lo, double a, int order, int levels, int leaf, int channels,
+              const float4 *lo, double a, int order, int levels, int leaf, int channels, bool wall,
               std::string *msg) {
     F.N = 0;
     F.ready = false;
@@ -1572,8 +1340,6 @@ int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const fl
               up(F.rng, pl.rng.data(), pl.rng.size() * sizeof(int2)) &&
               up(F.parent, pl.parent.data(), pl.parent.size() * sizeof(int)) &&
               up(F.kids, pl.kids.data(), pl.kids.size() * sizeof(int2)) &&
-              up(F.il_ptr, pl.il_ptr.data(), pl.il_ptr.size() * sizeof(int)) &&
-              up(F.il, pl.il.data(), pl.il.size() * sizeof(int)) &&
               up(F.near_ptr, pl.near_ptr.data(), pl.near_ptr.size() * sizeof(int)) &&
               up(F.nearl, pl.nearl.data(), pl.nearl.size() * sizeof(int)) &&
               up(F.work, pl.work.data(), pl.work.size() * sizeof(int2)) &&
@@ -1587,6 +1353,17 @@ int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const fl
                (F.slam2.ensure((size_t)N * sizeof(double4)) == hipSuccess &&
                 F.qhat2.ensure((size_t)ncell * P * sizeof(double4)) == hipSuccess &&
                 F.v2.ensure((size_t)ncell * P * 3 * sizeof(double)) == hipSuccess));
+    // M2L's batches: 32 columns, 16 with the torque channel; slots of a chunk bounded
+    M2LGroups &mg = hc.m2l;
+    const int64_t slot_doubles = 3 * (int64_t)P * channels;
+    group_m2l(pl, wall, channels == 2 ? 16 : 32,
+              std::max<int64_t>(1, kFmmSlotBytes / (slot_doubles * 8)), mg);
+    ok = ok && up(F.sp_ptr, mg.sp_ptr.data(), mg.sp_ptr.size() * sizeof(int)) &&
+         up(F.sp, mg.sp.data(), mg.sp.size() * sizeof(int)) &&
+         up(F.slot_ptr, mg.slot_ptr.data(), mg.slot_ptr.size() * sizeof(int)) &&
+         up(F.cols, mg.cols.data(), mg.cols.size() * sizeof(int2)) &&
+         up(F.batches, mg.batches.data(), mg.batches.size() * sizeof(FmmBatch)) &&
+         F.slots.ensure((size_t)mg.max_slots * slot_doubles * sizeof(double)) == hipSuccess;
     const int nc_m2l = pl.L >= 2 ? pl.lvl[pl.L + 1] - pl.lvl[2] : 0;
     const int splits = nc_m2l > 0 ? m2l_splits(nc_m2l) : 1;
     ok = ok && (splits == 1 ||
@@ -1604,6 +1381,7 @@ int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const fl
     }
     F.L = pl.L;
     F.lvl = pl.lvl;
+    F.chunks = mg.chunks;
     F.splits = splits;
     F.o[0] = pl.o[0] / a;
     F.o[1] = pl.o[1] / a;
@@ -1640,22 +1418,7 @@ void fmm_run(const FmmState &F, hipStream_t s, const double *lam, double *partia
                 fmm_m2m_kernel<A, decltype(o)::value><<<F.lvl[l + 1] - F.lvl[l], B, 0, s>>>(
                     g, tab, F.cc.as<int4>(), F.kids.as<int2>(), F.lvl[l], qhat);
         });
-        const int groups = m2l_groups(P);
-        const size_t lds = (size_t)groups * P * (sizeof(Vec4<A>) + sizeof(float4)) +
-                           (size_t)3 * (groups - 1) * P * sizeof(double) +
-                           kTabSize * sizeof(float);
-        const int nc = F.lvl[L + 1] - F.lvl[2], splits = F.splits;
-        fmm_m2l_kernel<WALL, A><<<round_up(nc * splits, 8 * kXcdChunk), round_up(groups * P, kWave),
-                                  lds, s>>>(
-            g, tab, F.cc.as<int4>(), F.il_ptr.as<int>(), F.il.as<int>(), F.lvl[2], nc * splits,
-            groups, splits,
-            F.rng.as<int2>(), F.shi.as<float4>(), F.slo.as<float4>(), slam, qhat,
-            F.v.as<double>(), F.vsplit.as<double>());
-        if (splits > 1) {
-            const int64_t m = (int64_t)nc * P * 3;
-            fmm_split_sum_kernel<<<(unsigned)((m + 255) / 256), 256, 0, s>>>(
-                m, splits, P * 3, F.vsplit.as<double>(), F.v.as<double>() + (size_t)F.lvl[2] * P * 3);
-        }
+        fmm_m2l(F, s, 1, WALL, std::is_same_v<A, double>);
         with_order(F.n, [&](auto o) {
             for (int l = 3; l <= L; ++l)
                 fmm_l2l_kernel<decltype(o)::value><<<F.lvl[l + 1] - F.lvl[l], B, 0, s>>>(
@@ -1709,24 +1472,7 @@ void fmm_run6(const FmmState &F, hipStream_t s, const double *x6, double inv_a, 
                     fmm_m2m_kernel<A, decltype(o)::value><<<F.lvl[l + 1] - F.lvl[l], B, 0, s>>>(
                         g, tab, F.cc.as<int4>(), F.kids.as<int2>(), F.lvl[l], ch ? qt : qf);
         });
-        const int groups = m2l_groups(P);
-        const size_t lds = (size_t)groups * P * (2 * sizeof(Vec4<A>) + sizeof(float4)) +
-                           (size_t)6 * (groups - 1) * P * sizeof(double) +
-                           kTabSize * sizeof(float);
-        const int nc = F.lvl[L + 1] - F.lvl[2], splits = F.splits;
-        fmm_m2l6_kernel<A><<<round_up(nc * splits, 8 * kXcdChunk), round_up(groups * P, kWave), lds,
-                             s>>>(
-            g, tab, F.cc.as<int4>(), F.il_ptr.as<int>(), F.il.as<int>(), F.lvl[2], nc * splits,
-            groups, splits,
-            F.rng.as<int2>(), F.shi.as<float4>(), F.slo.as<float4>(), sf, st, qf, qt, vu, vw,
-            F.vsplit.as<double>());
-        if (splits > 1) {
-            const int64_t m = (int64_t)nc * P * 3;
-            for (int ch = 0; ch < 2; ++ch)
-                fmm_split_sum_kernel<<<(unsigned)((m + 255) / 256), 256, 0, s>>>(
-                    m, splits, P * 3, F.vsplit.as<double>() + ch * (size_t)nc * splits * P * 3,
-                    (ch ? vw : vu) + (size_t)F.lvl[2] * P * 3);
-        }
+        fmm_m2l(F, s, 2, false, std::is_same_v<A, double>);
         with_order(F.n, [&](auto o) {
             for (int l = 3; l <= L; ++l)
                 for (int ch = 0; ch < 2; ++ch)

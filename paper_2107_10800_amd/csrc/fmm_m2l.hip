@@ -1,0 +1,555 @@
+// M2L of the fast product (fmm.hip): v^c_k = sum over the interaction list of c of
+// the pair tensor between c's proxies and the listed cell's, or its blobs when it
+// holds fewer blobs than proxies.  Two kernels share the work:
+//
+//  * listed cells with their proxies ("dense" entries).  The tensor between two
+//    proxy grids depends only on the level, the cells' integer offset and, above
+//    the wall, the target cell's height, so the entries with the same key are one
+//    matrix (3 n^3 x 3 n^3, 6 n^3 with torques) against many columns: a
+//    contraction, done on the matrix cores.  The host groups the entries by key
+//    into batches of at most 16 CT columns; a wavefront holds 16 target proxies
+//    against the batch's columns.  At each step every lane evaluates the tensor
+//    of one pair (proxy l mod 16 of the tile, source proxy 4 st + l / 16) once, and
+//    its 9 entries (30 with torques) are the A operands of one matrix instruction
+//    each per 16 columns, in the instruction's own lane layout, so nothing is
+//    exchanged between lanes.  Each column's result goes to a slot of its own, and
+//    fmm_m2l_sum_kernel adds a cell's slots in list order: no atomics, products
+//    repeat bit for bit.
+//    Bound by the matrix cores: 9 instructions of 1,024 FMAs (30 with torques) per 64
+//    pairs and 16 columns, against about 60 VALU instructions to form the operands,
+//    shared by up to 32 columns.  8,192 bacteria (94,550 dense entries, n = 6): 1.17 ms
+//    = 68 TFLOP/s; pair by pair on the VALU these entries took about 6.8 ms.  Diatom
+//    colonies, double sums: 0.99 ms (2.5 ms before); 4,096 shells with torques 2.2 ms
+//    (4.1 ms).
+//  * sparse entries (P2L): the blobs of a cell's sparse listed cells, strung
+//    together and dealt evenly to lane groups of n^2 lanes, each lane holding the
+//    n target proxies of one (x, y), so that the differences in the plane are
+//    formed once per blob and lane.  VALU-bound: 2.6 ms for 1.48e9 pairs of the
+//    bacteria (5.7e11 pairs/s).
+//
+// Every pair is well separated (r > 2a: cells at least a side apart, side >= 2a, and
+// proxies inside their cells), so the overlap branch is left out.
+#include <algorithm>
+
+#include "fmm_device.h"
+
+namespace arb {
+
+namespace {
+
+typedef float accf __attribute__((ext_vector_type(4)));
+typedef double accd __attribute__((ext_vector_type(4)));
+template <class A>
+using Acc = std::conditional_t<std::is_same_v<A, float>, accf, accd>;
+
+__device__ __forceinline__ accf mfma16(float a, float b, accf c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ accd mfma16(double a, double b, accd c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+// row of accumulator element e in lane l (column l mod 16)
+__device__ __forceinline__ int acc_row(int l, int e, float) { return 4 * (l >> 4) + e; }
+__device__ __forceinline__ int acc_row(int l, int e, double) { return 4 * e + (l >> 4); }
+
+// wall pair coefficients of a well-separated pair, float
+__device__ __forceinline__ PairCoef<float> wall_coef(float dx, float dy, float dz, float zi,
+                                                     const TargetZ<float> &zs, float zj,
+                                                     float &Rz) {
+    constexpr CoefF cf = kUnitCoefF;
+    const float dxy2 = fmaf(dx, dx, dy * dy);
+    const float rinv = rsq_f32(fmaf(dz, dz, dxy2));
+    Rz = zi + zj;
+    const float h2 = 2.f * zj;
+    return wall_pair_coef<float, CoefF, false>(0.f, rinv, dxy2, zs, zj, h2, -(h2 * h2), Rz,
+                                               rsq_f32(fmaf(Rz, Rz, dxy2)), cf);
+}
+
+// the 3 x 3 tensor (row-major) of a well-separated pair: coefficients in float,
+// entries in A
+template <bool WALL, class A>
+__device__ __forceinline__ void entries3(float dx, float dy, float dz, float zi,
+                                         const TargetZ<float> &zs, float zj, A *m) {
+    if constexpr (WALL) {
+        float Rzf;
+        const PairCoef<float> w = wall_coef(dx, dy, dz, zi, zs, zj, Rzf);
+        const A x = (A)dx, y = (A)dy, z = (A)dz, R = (A)Rzf, b = (A)w.b, c2 = (A)w.c2;
+        const A px = (c2 + b) * x, py = (c2 + b) * y;
+        const A q = fma(c2, z, b * R);
+        const A qc = q + (A)w.c, qd = q + (A)w.d;
+        m[0] = fma(px, x, (A)w.cA);
+        m[1] = m[3] = px * y;
+        m[4] = fma(py, y, (A)w.cA);
+        m[2] = x * qc;
+        m[5] = y * qc;
+        m[6] = x * qd;
+        m[7] = y * qd;
+        m[8] = fma(R, fma(b, R, (A)w.c + (A)w.d), fma(c2 * z, z, (A)w.cAe));
+    } else {
+        constexpr CoefF cf = kUnitCoefF;
+        const float rinv = rsq_f32(fmaf(dz, dz, fmaf(dx, dx, dy * dy)));
+        const float rinv2 = rinv * rinv, rinv3 = rinv * rinv2;
+        const A c1 = (A)fmaf(cf.k1, rinv3, rinv), c2 = (A)fmaf(-cf.k2, rinv3 * rinv2, rinv3);
+        const A x = (A)dx, y = (A)dy, z = (A)dz;
+        const A px = c2 * x, py = c2 * y;
+        m[0] = fma(px, x, c1);
+        m[4] = fma(py, y, c1);
+        m[8] = fma(c2 * z, z, c1);
+        m[1] = m[3] = px * y;
+        m[2] = m[6] = px * z;
+        m[5] = m[7] = py * z;
+    }
+}
+
+// generalised tensor of a well-separated pair: translation and rotation blocks
+// (symmetric: xx, xy, xz, yy, yz, zz) and the couplings c_r r
+template <class A>
+__device__ __forceinline__ void entries6(float dx, float dy, float dz, A *tr, A *ro, A *e) {
+    constexpr RotCoef<float> c = kUnitRotCoef;
+    const float rinv = rsq_f32(fmaf(dz, dz, fmaf(dx, dx, dy * dy)));
+    const float rinv2 = rinv * rinv, rinv3 = rinv * rinv2, rinv5 = rinv3 * rinv2;
+    const A c1 = (A)fmaf(c.k1, rinv3, rinv), c2 = (A)fmaf(-c.k2, rinv5, rinv3);
+    const A cr = (A)rinv3, d1 = (A)(-0.5f * rinv3), d2 = (A)(1.5f * rinv5);
+    const A x = (A)dx, y = (A)dy, z = (A)dz;
+    e[0] = cr * x;
+    e[1] = cr * y;
+    e[2] = cr * z;
+    const A px = c2 * x, py = c2 * y, sx = d2 * x, sy = d2 * y;
+    tr[0] = fma(px, x, c1);
+    tr[1] = px * y;
+    tr[2] = px * z;
+    tr[3] = fma(py, y, c1);
+    tr[4] = py * z;
+    tr[5] = fma(c2 * z, z, c1);
+    ro[0] = fma(sx, x, d1);
+    ro[1] = sx * y;
+    ro[2] = sx * z;
+    ro[3] = fma(sy, y, d1);
+    ro[4] = sy * z;
+    ro[5] = fma(d2 * z, z, d1);
+}
+
+// shape of the dense kernel for order n: wavefronts of a workgroup (a 16-proxy
+// target tile each), workgroups per batch, sources per staged chunk
+template <int NO>
+struct DenseShape {
+    static constexpr int P = NO * NO * NO, tiles = (P + 15) / 16;
+    static constexpr int waves = tiles <= 8 ? tiles : (NO == 6 ? 7 : 8);
+    static constexpr int groups = (tiles + waves - 1) / waves;
+    static constexpr int KB = P >= kFmmRun ? kFmmRun : (P + 3) / 4 * 4;
+    static constexpr int threads = 64 * waves;
+};
+
+// One workgroup: `waves` target tiles of a batch's columns.  The sources' weights
+// go through LDS in chunks of KB proxies, double-buffered, the next chunk in
+// flight in registers; float sums run over one chunk and are promoted to double
+// (kFmmRun sources, as in the direct sums).
+template <bool WALL, int CH, class A, int CT, int NO>
+__global__ __launch_bounds__(DenseShape<NO>::threads) void fmm_m2l_dense_kernel(
+    Geo g, const float *__restrict__ tabg, const FmmBatch *__restrict__ batches, int items,
+    const int2 *__restrict__ cols, const Vec4<A> *__restrict__ qf, const Vec4<A> *__restrict__ qt,
+    double *__restrict__ slots) {
+    using Sh = DenseShape<NO>;
+    constexpr int P = Sh::P, KB = Sh::KB, NC = 16 * CT, NB = 3 * CH, RS = NC + 1;
+    constexpr int T = Sh::threads, NPF = (KB * NC + T - 1) / T;
+    constexpr bool F32 = std::is_same_v<A, float>;
+    const int item = xcd_item(items);
+    if (item < 0) return;
+    __shared__ float tab[kTabSize];
+    __shared__ float4 s_off[P];
+    __shared__ int s_src[NC];
+    __shared__ A s_b[2][KB][NB][RS];
+    load_tab(tabg, tab);
+    const FmmBatch b = batches[item / Sh::groups];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const double side = ldexp(g.S, -b.level), w = 0.5 * side;
+    if (tid < NC) s_src[tid] = tid < b.count ? cols[b.first + tid].x : -1;
+    for (int m = tid; m < P; m += T)
+        s_off[m] = make_float4((float)(w * tab[kTabNode + m / (NO * NO)]),
+                               (float)(w * tab[kTabNode + (m / NO) % NO]),
+                               (float)(w * tab[kTabNode + m % NO]), 0.f);
+    __syncthreads();
+    // the staged chunk, one (proxy, column) per thread and turn; zero weights
+    // past the proxies and the columns
+    Vec4<A> pf[NPF], pt[CH == 2 ? NPF : 1];
+    auto fetch = [&](int m0) {
+#pragma unroll
+        for (int r = 0; r < NPF; ++r) {
+            const int t = r * T + tid, m = m0 + t % KB, col = t / KB;
+            const int sc = col < NC ? s_src[col] : -1;
+            const bool ok = sc >= 0 && m < P;
+            pf[r] = vec4<A>(0, 0, 0);
+            if (ok) pf[r] = qf[(size_t)sc * P + m];
+            if constexpr (CH == 2) {
+                pt[r] = vec4<A>(0, 0, 0);
+                if (ok) pt[r] = qt[(size_t)sc * P + m];
+            }
+        }
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int r = 0; r < NPF; ++r) {
+            const int t = r * T + tid, m = t % KB, col = t / KB;
+            if (col >= NC) continue;
+            s_b[buf][m][0][col] = pf[r].x;
+            s_b[buf][m][1][col] = pf[r].y;
+            s_b[buf][m][2][col] = pf[r].z;
+            if constexpr (CH == 2) {
+                s_b[buf][m][3][col] = pt[r].x;
+                s_b[buf][m][4][col] = pt[r].y;
+                s_b[buf][m][5][col] = pt[r].z;
+            }
+        }
+    };
+    // this lane's target proxy (A operand row l mod 16 of the wavefront's tile)
+    const int tile = (item % Sh::groups) * Sh::waves + wv;
+    const int k = min(tile * 16 + (lane & 15), P - 1);
+    const float4 ok4 = s_off[k];
+    const float ax = (float)((double)b.dx * side) + ok4.x;
+    const float ay = (float)((double)b.dy * side) + ok4.y;
+    const float az = (float)((double)b.dz * side) + ok4.z;
+    const float zi =
+        (float)(centre(g.oz, side, b.tz) + w * (double)tab[kTabNode + k % NO]);
+    const TargetZ<float> zs = target_z(zi);
+    const float zc = (float)centre(g.oz, side, b.tz - b.dz);
+    const int kq = lane >> 4, cl = lane & 15;
+    const bool two = CT > 1 && b.count > 16;
+    Acc<A> acc[CT][NB] = {};
+    double sum[F32 ? CT : 1][F32 ? NB : 1][4] = {};
+    fetch(0);
+    stage(0);
+    __syncthreads();
+    int buf = 0;
+    for (int m0 = 0; m0 < P; m0 += KB, buf ^= 1) {
+        if (m0 + KB < P) fetch(m0 + KB);
+        const int steps = min(KB, P - m0 + 3) / 4;
+        for (int st = 0; st < steps; ++st) {
+            const int ml = 4 * st + kq;
+            const float4 o = s_off[min(m0 + ml, P - 1)];
+            const float dx = ax - o.x, dy = ay - o.y, dz = az - o.z;
+            const A(*bb)[RS] = s_b[buf][ml];
+            if constexpr (CH == 1) {
+                A m[9];
+                entries3<WALL, A>(dx, dy, dz, zi, zs, zc + o.z, m);
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    if (ct > 0 && !two) break;
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) {
+                        const A bv = bb[j][16 * ct + cl];
+#pragma unroll
+                        for (int i = 0; i < 3; ++i)
+                            acc[ct][i] = mfma16(m[3 * i + j], bv, acc[ct][i]);
+                    }
+                }
+            } else {
+                A tr[6], ro[6], e[3];
+                entries6<A>(dx, dy, dz, tr, ro, e);
+                constexpr int sy[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
+                A bv[6];
+#pragma unroll
+                for (int j = 0; j < 6; ++j) bv[j] = bb[j][cl];
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        acc[0][i] = mfma16(tr[sy[i][j]], bv[j], acc[0][i]);
+                        acc[0][3 + i] = mfma16(ro[sy[i][j]], bv[3 + j], acc[0][3 + i]);
+                    }
+                // u += t x e, w += f x e:  (v x e)_i = v_{i+1} e_{i+2} - v_{i+2} e_{i+1}
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
+                    acc[0][i] = mfma16(e[i2], bv[3 + i1], acc[0][i]);
+                    acc[0][3 + i] = mfma16(e[i2], bv[i1], acc[0][3 + i]);
+                    acc[0][i] = mfma16(-e[i1], bv[3 + i2], acc[0][i]);
+                    acc[0][3 + i] = mfma16(-e[i1], bv[i2], acc[0][3 + i]);
+                }
+            }
+        }
+        if constexpr (F32) {
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) sum[ct][i][q] += (double)acc[ct][i][q];
+                    acc[ct][i] = Acc<A>{};
+                }
+        }
+        if (m0 + KB < P) {
+            stage(buf ^ 1);
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+        const int col = 16 * ct + cl;
+        if (col >= b.count) continue;
+        double *o = slots + (size_t)cols[b.first + col].y * (3 * CH * P);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = tile * 16 + acc_row(lane, q, A(0));
+            if (row >= P) continue;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                double v;
+                if constexpr (F32)
+                    v = sum[ct][i][q];
+                else
+                    v = acc[ct][i][q];
+                o[(size_t)(i / 3) * 3 * P + 3 * row + i % 3] = v;
+            }
+        }
+    }
+}
+
+// lanes, lane groups and staged blobs of the sparse kernel for order n: n^2 lanes
+// per group, at most kFmmRun staged blobs per group
+constexpr int kP2LBlock = 256;
+template <int NO>
+struct SparseShape {
+    static constexpr int P = NO * NO * NO, lanes = NO * NO, groups = kP2LBlock / lanes;
+    static constexpr int chunk = groups * kFmmRun < kP2LBlock ? groups * kFmmRun : kP2LBlock;
+};
+constexpr int kMaxListed = 189;  // cells of an interaction list (6^3 - 3^3)
+static_assert(kMaxListed <= kP2LBlock, "one list entry per thread");
+
+// the blobs of the sparse listed cells of one target cell; a cell's blobs may be
+// split over `splits` consecutive items, each with a place of its own in vpart
+template <bool WALL, int CH, class A, int NO>
+__global__ __launch_bounds__(kP2LBlock) void fmm_p2l_kernel(
+    Geo g, const float *__restrict__ tabg, const int4 *__restrict__ cc,
+    const int *__restrict__ sp_ptr, const int *__restrict__ sp, int cell0, int items, int splits,
+    const int2 *__restrict__ rng, const float4 *__restrict__ shi, const float4 *__restrict__ slo,
+    const Vec4<A> *__restrict__ sf, const Vec4<A> *__restrict__ st, double *__restrict__ vu,
+    double *__restrict__ vw, double *__restrict__ vpart) {
+    using Sh = SparseShape<NO>;
+    constexpr int P = Sh::P, C = Sh::chunk, NB = 3 * CH;
+    constexpr bool F32 = std::is_same_v<A, float>;
+    const int item = xcd_item(items);
+    if (item < 0) return;
+    __shared__ float tab[kTabSize];
+    __shared__ int s_start[kMaxListed], s_pre[kMaxListed + 1], s_wave[kP2LBlock / kWave];
+    __shared__ float4 s_off[C];
+    __shared__ Vec4<A> s_f[C], s_t[CH == 2 ? C : 1];
+    __shared__ double s_sum[NB][P];
+    load_tab(tabg, tab);
+    const int tid = threadIdx.x;
+    const int ci = item / splits, part = item % splits, c = cell0 + ci;
+    const int4 ct = cc[c];
+    const double side = ldexp(g.S, -ct.w), w = 0.5 * side;
+    const int e0 = sp_ptr[ci], ne = sp_ptr[ci + 1] - e0;
+    for (int i = tid; i < NB * P; i += kP2LBlock) s_sum[i / P][i % P] = 0.0;
+    // prefix sums of the listed cells' blob counts (one list entry per thread)
+    {
+        int v = 0;
+        if (tid < ne) {
+            const int2 r = rng[sp[e0 + tid]];
+            s_start[tid] = r.x;
+            v = r.y - r.x;
+        }
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int u = __shfl_up(v, off);
+            if ((tid & 63) >= off) v += u;
+        }
+        if ((tid & 63) == 63) s_wave[tid >> 6] = v;
+        __syncthreads();
+        for (int q = 0; q < (tid >> 6); ++q) v += s_wave[q];
+        if (tid < ne) s_pre[tid + 1] = v;
+        if (tid == 0) s_pre[0] = 0;
+    }
+    __syncthreads();
+    const int total = s_pre[ne];
+    const int j1 = (int)((int64_t)total * (part + 1) / splits);
+    const int grp = tid / Sh::lanes, kxy = tid % Sh::lanes;
+    const bool act = grp < Sh::groups;
+    const float okx = (float)(w * tab[kTabNode + kxy / NO]),
+                oky = (float)(w * tab[kTabNode + kxy % NO]);
+    const double cx = centre(g.ox, side, ct.x), cy = centre(g.oy, side, ct.y),
+                 cz = centre(g.oz, side, ct.z);
+    const F2 hx = split(cx), hy = split(cy), hz = split(cz);
+    float okz[NO], zi[NO];
+#pragma unroll
+    for (int kz = 0; kz < NO; ++kz) {
+        okz[kz] = (float)(w * tab[kTabNode + kz]);
+        zi[kz] = (float)(cz + w * (double)tab[kTabNode + kz]);
+    }
+    // double sums: float runs are promoted after each chunk
+    A run[NO][NB] = {};
+    double sum[F32 ? NO : 1][F32 ? NB : 1] = {};
+    for (int j0 = (int)((int64_t)total * part / splits); j0 < j1; j0 += C) {
+        const int cnt = min(C, j1 - j0);
+        __syncthreads();
+        if (tid < cnt) {
+            // the listed cell that holds blob j0 + tid of the string
+            int lo = 0, up = ne;
+            while (up - lo > 1) {
+                const int mid = (lo + up) >> 1;
+                if (s_pre[mid] <= j0 + tid)
+                    lo = mid;
+                else
+                    up = mid;
+            }
+            const int j = s_start[lo] + (j0 + tid - s_pre[lo]);
+            const float4 h = shi[j], l = slo[j];
+            // offset from the target cell's centre, and the blob's height
+            s_off[tid] = make_float4((h.x - hx.h) + (l.x - hx.l), (h.y - hy.h) + (l.y - hy.l),
+                                     (h.z - hz.h) + (l.z - hz.l), h.z + l.z);
+            s_f[tid] = sf[j];
+            if constexpr (CH == 2) s_t[tid] = st[j];
+        }
+        __syncthreads();
+        if (!act) continue;
+        for (int s = grp; s < cnt; s += Sh::groups) {
+            const float4 o = s_off[s];
+            const Vec4<A> F = s_f[s];
+            const float dx = okx - o.x, dy = oky - o.y;
+            if constexpr (CH == 1) {
+#pragma unroll
+                for (int kz = 0; kz < NO; ++kz) {
+                    const float dz = okz[kz] - o.z;
+                    if constexpr (WALL) {
+                        float Rz;
+                        const PairCoef<float> pc =
+                            wall_coef(dx, dy, dz, zi[kz], target_z(zi[kz]), o.w, Rz);
+                        const PairCoef<A> pa{(A)pc.cA, (A)pc.cAe, (A)pc.c2, (A)pc.b,
+                                             (A)pc.c,  (A)pc.d,   (A)pc.e,  (A)pc.h2};
+                        wall_pair_apply<A>(pa, pa.c, pa.d, (A)dx, (A)dy, (A)dz, (A)Rz, F.x, F.y,
+                                           F.z, run[kz][0], run[kz][1], run[kz][2]);
+                    } else {
+                        constexpr CoefF cf = kUnitCoefF;
+                        const float rinv = rsq_f32(fmaf(dz, dz, fmaf(dx, dx, dy * dy)));
+                        const float rinv2 = rinv * rinv, rinv3 = rinv * rinv2;
+                        const A c1 = (A)fmaf(cf.k1, rinv3, rinv);
+                        const A c2 = (A)fmaf(-cf.k2, rinv3 * rinv2, rinv3);
+                        const A t = c2 * fma((A)dx, F.x, fma((A)dy, F.y, (A)dz * F.z));
+                        run[kz][0] = fma(c1, F.x, fma(t, (A)dx, run[kz][0]));
+                        run[kz][1] = fma(c1, F.y, fma(t, (A)dy, run[kz][1]));
+                        run[kz][2] = fma(c1, F.z, fma(t, (A)dz, run[kz][2]));
+                    }
+                }
+            } else {
+                const Vec4<A> Tq = s_t[s];
+#pragma unroll
+                for (int kz = 0; kz < NO; ++kz) {
+                    constexpr RotCoef<float> rc = kUnitRotCoef;
+                    const float dz = okz[kz] - o.z;
+                    const float rinv = rsq_f32(fmaf(dz, dz, fmaf(dx, dx, dy * dy)));
+                    const float rinv2 = rinv * rinv, rinv3 = rinv * rinv2, rinv5 = rinv3 * rinv2;
+                    const RotTerms<A> kt{(A)fmaf(rc.k1, rinv3, rinv), (A)fmaf(-rc.k2, rinv5, rinv3),
+                                         (A)rinv3, (A)(-0.5f * rinv3), (A)(1.5f * rinv5)};
+                    rot_one_way<A>(kt, (A)dx, (A)dy, (A)dz, F.x, F.y, F.z, Tq.x, Tq.y, Tq.z,
+                                   run[kz]);
+                }
+            }
+        }
+        if constexpr (F32) {
+#pragma unroll
+            for (int kz = 0; kz < NO; ++kz)
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    sum[kz][i] += (double)run[kz][i];
+                    run[kz][i] = 0.f;
+                }
+        }
+    }
+    // the groups' sums, added in group order
+    for (int gr = 0; gr < Sh::groups; ++gr) {
+        if (grp == gr) {
+#pragma unroll
+            for (int kz = 0; kz < NO; ++kz)
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    if constexpr (F32)
+                        s_sum[i][kxy * NO + kz] += sum[kz][i];
+                    else
+                        s_sum[i][kxy * NO + kz] += run[kz][i];
+                }
+        }
+        __syncthreads();
+    }
+    for (int i = tid; i < 3 * P; i += kP2LBlock) {
+        if (splits == 1) {
+            vu[(size_t)c * 3 * P + i] = s_sum[i % 3][i / 3];
+            if constexpr (CH == 2) vw[(size_t)c * 3 * P + i] = s_sum[3 + i % 3][i / 3];
+        } else {
+            double *o = vpart + (size_t)item * NB * P + i;
+            o[0] = s_sum[i % 3][i / 3];
+            if constexpr (CH == 2) o[3 * P] = s_sum[3 + i % 3][i / 3];
+        }
+    }
+}
+
+// v of the cells [c0, c0 + gridDim.x) (counted from cell0): the sparse part, or
+// its split parts in order, plus the cell's slots in list order
+__global__ __launch_bounds__(256) void fmm_m2l_sum_kernel(int cell0, int c0, int P3, int channels,
+                                                          int splits,
+                                                          const int *__restrict__ slot_ptr,
+                                                          int slot0,
+                                                          const double *__restrict__ slots,
+                                                          const double *__restrict__ vpart,
+                                                          double *__restrict__ vu,
+                                                          double *__restrict__ vw) {
+    const int ci = c0 + blockIdx.x, W = P3 * channels;
+    const int s0 = slot_ptr[ci] - slot0, s1 = slot_ptr[ci + 1] - slot0;
+    for (int i = blockIdx.y * 256 + threadIdx.x; i < W; i += 256 * gridDim.y) {
+        double *v = (i < P3 ? vu : vw) + (size_t)(cell0 + ci) * P3 + i % P3;
+        double t = 0.0;
+        if (splits == 1)
+            t = *v;
+        else
+            for (int j = 0; j < splits; ++j) t += vpart[((size_t)ci * splits + j) * W + i];
+        const double *s = slots + (size_t)s0 * W + i;
+#pragma unroll 4
+        for (int j = s0; j < s1; ++j, s += W) t += *s;
+        *v = t;
+    }
+}
+
+template <bool WALL, int CH, class A>
+void run_m2l(const FmmState &F, hipStream_t s) {
+    const int P = F.P, L = F.L;
+    const Geo g{F.o[0], F.o[1], F.o[2], F.S, F.n, P};
+    const float *tab = F.tab.as<float>();
+    const Vec4<A> *sf = F.slam.as<Vec4<A>>(), *st = F.slam2.as<Vec4<A>>();
+    const Vec4<A> *qf = F.qhat.as<Vec4<A>>(), *qt = F.qhat2.as<Vec4<A>>();
+    double *vu = F.v.as<double>(), *vw = F.v2.as<double>();
+    const int cell0 = F.lvl[2], nc = F.lvl[L + 1] - cell0, splits = F.splits;
+    with_order(F.n, [&](auto o) {
+        constexpr int NO = decltype(o)::value;
+        fmm_p2l_kernel<WALL, CH, A, NO>
+            <<<round_up(nc * splits, 8 * kXcdChunk), kP2LBlock, 0, s>>>(
+                g, tab, F.cc.as<int4>(), F.sp_ptr.as<int>(), F.sp.as<int>(), cell0, nc * splits,
+                splits, F.rng.as<int2>(), F.shi.as<float4>(), F.slo.as<float4>(), sf, st, vu, vw,
+                F.vsplit.as<double>());
+        using Sh = DenseShape<NO>;
+        for (const FmmChunk &ch : F.chunks) {
+            const int items = (ch.batch1 - ch.batch0) * Sh::groups;
+            if (items > 0)
+                fmm_m2l_dense_kernel<WALL, CH, A, (CH == 1 ? 2 : 1), NO>
+                    <<<round_up(items, 8 * kXcdChunk), Sh::threads, 0, s>>>(
+                        g, tab, F.batches.as<FmmBatch>() + ch.batch0, items, F.cols.as<int2>(), qf,
+                        qt, F.slots.as<double>());
+            if (items > 0 || splits > 1)
+                fmm_m2l_sum_kernel<<<dim3(ch.cell1 - ch.cell0, (3 * P * CH + 255) / 256), 256, 0,
+                                     s>>>(cell0, ch.cell0, 3 * P, CH, splits,
+                                          F.slot_ptr.as<int>(), ch.slot0, F.slots.as<double>(),
+                                          F.vsplit.as<double>(), vu, vw);
+        }
+    });
+}
+
+}  // namespace
+
+void fmm_m2l(const FmmState &F, hipStream_t s, int channels, bool wall, bool fp64) {
+    if (channels == 2) {
+        fp64 ? run_m2l<false, 2, double>(F, s) : run_m2l<false, 2, float>(F, s);
+    } else if (wall) {
+        fp64 ? run_m2l<true, 1, double>(F, s) : run_m2l<true, 1, float>(F, s);
+    } else {
+        fp64 ? run_m2l<false, 1, double>(F, s) : run_m2l<false, 1, float>(F, s);
+    }
+}
+
+}  // namespace arb

@@ -62,6 +62,40 @@ def test_matches_the_oracle_of_the_approximation(N, box, wall, n, L):
         assert approx > 10 * err          # the comparison resolves the approximation
 
 
+# (N, wall, n, L): M2L's batches at the edges of their tiles: one 16-proxy tile partly
+# filled (n = 2: 8 proxies, n = 3: 27), full ones (n = 4: 64), a last tile of 8 (n = 6)
+# and of 7 (n = 7) proxies; batches of 1 to 32 columns (16 with torques), and blobs
+# crowded towards one side so that dense and sparse listed cells occur side by side
+@pytest.mark.parametrize("N,wall,n,L", [(260, False, 2, 3), (300, True, 2, 3), (900, False, 3, 3),
+                                        (1500, True, 4, 2), (6000, False, 6, 2),
+                                        (3500, True, 6, 2), (5000, False, 7, 2)])
+def test_m2l_batches_against_the_oracle(N, wall, n, L):
+    rng = np.random.default_rng(N + n)
+    pos = rng.uniform(0, 1, (N, 3))
+    pos[:, 0] **= 2
+    pos = pos * np.array([60.0, 60.0, 15.0]) + np.array([0, 0, 1.5])
+    lam = rng.standard_normal((N, 3))
+    ref = fastsum.fmm_apply(pos, lam, 1.0, 1.0, wall, n, L)
+    for prec in (arb.ARB_FP64, arb.ARB_FP32C):
+        err = np.abs(fmm(pos, lam, wall, n, L, precision=prec) - ref).max() / np.abs(ref).max()
+        print(f"m2l batches N={N} wall={wall} n={n} L={L} precision {prec}: {err:.1e}", flush=True)
+        assert err <= 1e-5
+    if wall or n > 4:
+        return
+    F = rng.standard_normal((N, 6))
+    wl = W.Workload("loose", 1.0, 1.0, False, np.zeros((N, 3)), np.arange(N + 1, dtype=np.int32),
+                    pos, np.tile([1.0, 0, 0, 0], (N, 1)), F, extra=dict(single_blob=True))
+    ref = fastsum.fmm_apply(pos, F, 1.0, 1.0, False, n, L, kernel=rot_kernel(1.0, 1.0))
+    for prec in (arb.ARB_FP64, arb.ARB_FP32C):
+        ctx = arb.context_for(wl, precision=prec, pair_kernel=arb.ARB_PAIR_FMM, fmm_order=n,
+                              fmm_levels=L)
+        try:
+            uw = arb.arb_body_mobility_apply(ctx, F)
+        finally:
+            arb.arb_destroy(ctx)
+        assert np.abs(uw - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("wall", [False, True])
 def test_direct_sum_when_no_level_separates(wall):
     """fmm_levels = 1, a cluster narrower than 8a (no level with side >= 2a
