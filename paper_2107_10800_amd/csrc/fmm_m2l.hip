@@ -17,15 +17,15 @@
 //    repeat bit for bit.
 //    Bound by the matrix cores: 9 instructions of 1,024 FMAs (30 with torques) per 64
 //    pairs and 16 columns, against about 60 VALU instructions to form the operands,
-//    shared by up to 32 columns.  8,192 bacteria (94,550 dense entries, n = 6): 1.17 ms
-//    = 68 TFLOP/s; pair by pair on the VALU these entries took about 6.8 ms.  Diatom
-//    colonies, double sums: 0.99 ms (2.5 ms before); 4,096 shells with torques 2.2 ms
+//    shared by up to 32 columns.  8,192 bacteria (94,550 dense entries, n = 6): 1.03 ms
+//    = 77 TFLOP/s; pair by pair on the VALU these entries took about 6.8 ms.  Diatom
+//    colonies, double sums: 0.90 ms (2.5 ms before); 4,096 shells with torques 1.86 ms
 //    (4.1 ms).
 //  * sparse entries (P2L): the blobs of a cell's sparse listed cells, strung
 //    together and dealt evenly to lane groups of n^2 lanes, each lane holding the
-//    n target proxies of one (x, y), so that the differences in the plane are
-//    formed once per blob and lane.  VALU-bound: 2.6 ms for 1.48e9 pairs of the
-//    bacteria (5.7e11 pairs/s).
+//    KZ target proxies of one (x, y), so that the differences in the plane are
+//    formed once per blob and lane.  VALU-bound: 2.05 ms for 1.48e9 pairs of the
+//    bacteria (7.2e11 pairs/s).
 //
 // Every pair is well separated (r > 2a: cells at least a side apart, side >= 2a, and
 // proxies inside their cells), so the overlap branch is left out.
@@ -129,126 +129,113 @@ __device__ __forceinline__ void entries6(float dx, float dy, float dz, A *tr, A 
     ro[5] = fma(d2 * z, z, d1);
 }
 
-// shape of the dense kernel for order n: wavefronts of a workgroup (a 16-proxy
-// target tile each), workgroups per batch, sources per staged chunk
-template <int NO>
-struct DenseShape {
-    static constexpr int P = NO * NO * NO, tiles = (P + 15) / 16;
-    static constexpr int waves = tiles <= 8 ? tiles : (NO == 6 ? 7 : 8);
-    static constexpr int groups = (tiles + waves - 1) / waves;
-    static constexpr int KB = P >= kFmmRun ? kFmmRun : (P + 3) / 4 * 4;
-    static constexpr int threads = 64 * waves;
-};
+// One wavefront: a tile of 16 target proxies against a batch's columns, independent of
+// the others of its workgroup (no barrier: with the weights staged in LDS by the
+// workgroup, barriers and the uneven share of tiles per SIMD left the matrix cores
+// idle half the time).  The weights are read straight in the B operand's layout,
+// 4 consecutive proxies of 16 cells at a time (64-byte runs), the next step's in
+// flight while this one's are used; the tiles of a batch run side by side and share
+// them in the caches.  Float sums run over kFmmRun sources and are promoted to
+// double, as in the direct sums.
+constexpr int kDenseWaves = 4;
 
-// One workgroup: `waves` target tiles of a batch's columns.  The sources' weights
-// go through LDS in chunks of KB proxies, double-buffered, the next chunk in
-// flight in registers; float sums run over one chunk and are promoted to double
-// (kFmmRun sources, as in the direct sums).
 template <bool WALL, int CH, class A, int CT, int NO>
-__global__ __launch_bounds__(DenseShape<NO>::threads) void fmm_m2l_dense_kernel(
-    Geo g, const float *__restrict__ tabg, const FmmBatch *__restrict__ batches, int items,
-    const int2 *__restrict__ cols, const Vec4<A> *__restrict__ qf, const Vec4<A> *__restrict__ qt,
-    double *__restrict__ slots) {
-    using Sh = DenseShape<NO>;
-    constexpr int P = Sh::P, KB = Sh::KB, NC = 16 * CT, NB = 3 * CH, RS = NC + 1;
-    constexpr int T = Sh::threads, NPF = (KB * NC + T - 1) / T;
+__global__ __launch_bounds__(64 * kDenseWaves) __attribute__((amdgpu_waves_per_eu(4)))
+void fmm_m2l_dense_kernel(
+    Geo g, const float *__restrict__ tabg, const FmmBatch *__restrict__ batches, int tasks,
+    int items, const int2 *__restrict__ cols, const Vec4<A> *__restrict__ qf,
+    const Vec4<A> *__restrict__ qt, double *__restrict__ slots) {
+    constexpr int P = NO * NO * NO, tiles = (P + 15) / 16, NB = 3 * CH;
+    constexpr int steps = (P + 3) / 4, run = kFmmRun / 4;
     constexpr bool F32 = std::is_same_v<A, float>;
     const int item = xcd_item(items);
     if (item < 0) return;
     __shared__ float tab[kTabSize];
-    __shared__ float4 s_off[P];
-    __shared__ int s_src[NC];
-    __shared__ A s_b[2][KB][NB][RS];
+    __shared__ float4 s_off[kDenseWaves][P];
     load_tab(tabg, tab);
-    const FmmBatch b = batches[item / Sh::groups];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int task = item * kDenseWaves + wv;
+    if (task >= tasks) return;  // the whole wavefront; no barrier follows
+    const FmmBatch b = batches[task / tiles];
     const double side = ldexp(g.S, -b.level), w = 0.5 * side;
-    if (tid < NC) s_src[tid] = tid < b.count ? cols[b.first + tid].x : -1;
-    for (int m = tid; m < P; m += T)
-        s_off[m] = make_float4((float)(w * tab[kTabNode + m / (NO * NO)]),
-                               (float)(w * tab[kTabNode + (m / NO) % NO]),
-                               (float)(w * tab[kTabNode + m % NO]), 0.f);
-    __syncthreads();
-    // the staged chunk, one (proxy, column) per thread and turn; zero weights
-    // past the proxies and the columns
-    Vec4<A> pf[NPF], pt[CH == 2 ? NPF : 1];
-    auto fetch = [&](int m0) {
-#pragma unroll
-        for (int r = 0; r < NPF; ++r) {
-            const int t = r * T + tid, m = m0 + t % KB, col = t / KB;
-            const int sc = col < NC ? s_src[col] : -1;
-            const bool ok = sc >= 0 && m < P;
-            pf[r] = vec4<A>(0, 0, 0);
-            if (ok) pf[r] = qf[(size_t)sc * P + m];
-            if constexpr (CH == 2) {
-                pt[r] = vec4<A>(0, 0, 0);
-                if (ok) pt[r] = qt[(size_t)sc * P + m];
-            }
-        }
-    };
-    auto stage = [&](int buf) {
-#pragma unroll
-        for (int r = 0; r < NPF; ++r) {
-            const int t = r * T + tid, m = t % KB, col = t / KB;
-            if (col >= NC) continue;
-            s_b[buf][m][0][col] = pf[r].x;
-            s_b[buf][m][1][col] = pf[r].y;
-            s_b[buf][m][2][col] = pf[r].z;
-            if constexpr (CH == 2) {
-                s_b[buf][m][3][col] = pt[r].x;
-                s_b[buf][m][4][col] = pt[r].y;
-                s_b[buf][m][5][col] = pt[r].z;
-            }
-        }
-    };
-    // this lane's target proxy (A operand row l mod 16 of the wavefront's tile)
-    const int tile = (item % Sh::groups) * Sh::waves + wv;
-    const int k = min(tile * 16 + (lane & 15), P - 1);
-    const float4 ok4 = s_off[k];
+    float4 *off = s_off[wv];
+    for (int m = lane; m < P; m += 64)
+        off[m] = make_float4((float)(w * tab[kTabNode + m / (NO * NO)]),
+                             (float)(w * tab[kTabNode + (m / NO) % NO]),
+                             (float)(w * tab[kTabNode + m % NO]), 0.f);
+    __builtin_amdgcn_wave_barrier();  // LDS of one wavefront completes in order
+    // this lane's target proxy (A operand row l mod 16 of the tile)
+    const int tile = task % tiles;
+    const int kq = lane >> 4, cl = lane & 15;
+    const int k = min(tile * 16 + cl, P - 1);
+    const float4 ok4 = off[k];
     const float ax = (float)((double)b.dx * side) + ok4.x;
     const float ay = (float)((double)b.dy * side) + ok4.y;
     const float az = (float)((double)b.dz * side) + ok4.z;
-    const float zi =
-        (float)(centre(g.oz, side, b.tz) + w * (double)tab[kTabNode + k % NO]);
+    const float zi = (float)(centre(g.oz, side, b.tz) + w * (double)tab[kTabNode + k % NO]);
     const TargetZ<float> zs = target_z(zi);
     const float zc = (float)centre(g.oz, side, b.tz - b.dz);
-    const int kq = lane >> 4, cl = lane & 15;
     const bool two = CT > 1 && b.count > 16;
+    // a column past the batch's last reads the last one's weights (its results are
+    // not stored)
+    const Vec4<A> *src[CT], *srt[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+        const size_t q = (size_t)cols[b.first + min(16 * ct + cl, b.count - 1)].x * P;
+        src[ct] = qf + q;
+        srt[ct] = CH == 2 ? qt + q : nullptr;
+    }
+    Vec4<A> bf[CT], bt[CH == 2 ? CT : 1];
+    auto fetch = [&](int st) {
+        const int m = 4 * st + kq;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            if (ct > 0 && !two) break;
+            bf[ct] = src[ct][min(m, P - 1)];
+            if constexpr (CH == 2) bt[ct] = srt[ct][min(m, P - 1)];
+        }
+        if (P % 4 != 0 && m >= P) {  // no source proxy: zero weights
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                bf[ct] = vec4<A>(0, 0, 0);
+                if constexpr (CH == 2) bt[ct] = vec4<A>(0, 0, 0);
+            }
+        }
+    };
     Acc<A> acc[CT][NB] = {};
     double sum[F32 ? CT : 1][F32 ? NB : 1][4] = {};
     fetch(0);
-    stage(0);
-    __syncthreads();
-    int buf = 0;
-    for (int m0 = 0; m0 < P; m0 += KB, buf ^= 1) {
-        if (m0 + KB < P) fetch(m0 + KB);
-        const int steps = min(KB, P - m0 + 3) / 4;
-        for (int st = 0; st < steps; ++st) {
-            const int ml = 4 * st + kq;
-            const float4 o = s_off[min(m0 + ml, P - 1)];
+#pragma unroll 1
+    for (int st0 = 0; st0 < steps; st0 += run) {
+#pragma unroll 1
+        for (int st = st0; st < min(st0 + run, steps); ++st) {
+            Vec4<A> f[CT], t[CH == 2 ? CT : 1];
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                f[ct] = bf[ct];
+                if constexpr (CH == 2) t[ct] = bt[ct];
+            }
+            if (st + 1 < steps) fetch(st + 1);
+            const float4 o = off[min(4 * st + kq, P - 1)];
             const float dx = ax - o.x, dy = ay - o.y, dz = az - o.z;
-            const A(*bb)[RS] = s_b[buf][ml];
             if constexpr (CH == 1) {
                 A m[9];
                 entries3<WALL, A>(dx, dy, dz, zi, zs, zc + o.z, m);
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
                     if (ct > 0 && !two) break;
+                    const A bv[3] = {f[ct].x, f[ct].y, f[ct].z};
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        const A bv = bb[j][16 * ct + cl];
+                    for (int j = 0; j < 3; ++j)
 #pragma unroll
                         for (int i = 0; i < 3; ++i)
-                            acc[ct][i] = mfma16(m[3 * i + j], bv, acc[ct][i]);
-                    }
+                            acc[ct][i] = mfma16(m[3 * i + j], bv[j], acc[ct][i]);
                 }
             } else {
                 A tr[6], ro[6], e[3];
                 entries6<A>(dx, dy, dz, tr, ro, e);
                 constexpr int sy[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
-                A bv[6];
-#pragma unroll
-                for (int j = 0; j < 6; ++j) bv[j] = bb[j][cl];
+                const A bv[6] = {f[0].x, f[0].y, f[0].z, t[0].x, t[0].y, t[0].z};
 #pragma unroll
                 for (int j = 0; j < 3; ++j)
 #pragma unroll
@@ -277,10 +264,6 @@ __global__ __launch_bounds__(DenseShape<NO>::threads) void fmm_m2l_dense_kernel(
                     acc[ct][i] = Acc<A>{};
                 }
         }
-        if (m0 + KB < P) {
-            stage(buf ^ 1);
-            __syncthreads();
-        }
     }
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
@@ -304,33 +287,42 @@ __global__ __launch_bounds__(DenseShape<NO>::threads) void fmm_m2l_dense_kernel(
     }
 }
 
-// lanes, lane groups and staged blobs of the sparse kernel for order n: n^2 lanes
-// per group, at most kFmmRun staged blobs per group
-constexpr int kP2LBlock = 256;
+// shape of the sparse kernel for order n: KZ proxies of one (x, y) per lane, n^3 / KZ
+// lanes per group, as many groups as fill the workgroup's wavefronts, at most
+// kFmmRun staged blobs per group.  KZ = n, but half of it at n = 6 and 8: the KZ
+// pairs are independent chains, and the 128 registers of 4 wavefronts per SIMD hold
+// three of them side by side (2.05 ms on the bacteria) but not six, which the
+// compiler then runs one after the other (2.60 ms; so do 5 or 6 wavefronts per SIMD:
+// 2.47 ms).  Workgroups are whole multiples of 4 wavefronts: 6 load two of the four
+// SIMDs twice as much (3.30 ms).
 template <int NO>
 struct SparseShape {
-    static constexpr int P = NO * NO * NO, lanes = NO * NO, groups = kP2LBlock / lanes;
-    static constexpr int chunk = groups * kFmmRun < kP2LBlock ? groups * kFmmRun : kP2LBlock;
+    static constexpr int P = NO * NO * NO, KZ = NO == 6 || NO == 8 ? NO / 2 : NO;
+    static constexpr int lanes = P / KZ;
+    static constexpr int block = NO == 6 ? 512 : 256, groups = block / lanes;
+    static constexpr int chunk = groups * kFmmRun < block ? groups * kFmmRun : block;
 };
 constexpr int kMaxListed = 189;  // cells of an interaction list (6^3 - 3^3)
-static_assert(kMaxListed <= kP2LBlock, "one list entry per thread");
+static_assert(kMaxListed <= 256, "one list entry per thread");
 
 // the blobs of the sparse listed cells of one target cell; a cell's blobs may be
 // split over `splits` consecutive items, each with a place of its own in vpart
 template <bool WALL, int CH, class A, int NO>
-__global__ __launch_bounds__(kP2LBlock) void fmm_p2l_kernel(
+__global__ __launch_bounds__(SparseShape<NO>::block)
+__attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 : 3)))
+void fmm_p2l_kernel(
     Geo g, const float *__restrict__ tabg, const int4 *__restrict__ cc,
     const int *__restrict__ sp_ptr, const int *__restrict__ sp, int cell0, int items, int splits,
     const int2 *__restrict__ rng, const float4 *__restrict__ shi, const float4 *__restrict__ slo,
     const Vec4<A> *__restrict__ sf, const Vec4<A> *__restrict__ st, double *__restrict__ vu,
     double *__restrict__ vw, double *__restrict__ vpart) {
     using Sh = SparseShape<NO>;
-    constexpr int P = Sh::P, C = Sh::chunk, NB = 3 * CH;
+    constexpr int P = Sh::P, C = Sh::chunk, NB = 3 * CH, KZ = Sh::KZ, block = Sh::block;
     constexpr bool F32 = std::is_same_v<A, float>;
     const int item = xcd_item(items);
     if (item < 0) return;
     __shared__ float tab[kTabSize];
-    __shared__ int s_start[kMaxListed], s_pre[kMaxListed + 1], s_wave[kP2LBlock / kWave];
+    __shared__ int s_start[kMaxListed], s_pre[kMaxListed + 1], s_wave[block / kWave];
     __shared__ float4 s_off[C];
     __shared__ Vec4<A> s_f[C], s_t[CH == 2 ? C : 1];
     __shared__ double s_sum[NB][P];
@@ -340,7 +332,7 @@ __global__ __launch_bounds__(kP2LBlock) void fmm_p2l_kernel(
     const int4 ct = cc[c];
     const double side = ldexp(g.S, -ct.w), w = 0.5 * side;
     const int e0 = sp_ptr[ci], ne = sp_ptr[ci + 1] - e0;
-    for (int i = tid; i < NB * P; i += kP2LBlock) s_sum[i / P][i % P] = 0.0;
+    for (int i = tid; i < NB * P; i += block) s_sum[i / P][i % P] = 0.0;
     // prefix sums of the listed cells' blob counts (one list entry per thread)
     {
         int v = 0;
@@ -362,22 +354,23 @@ __global__ __launch_bounds__(kP2LBlock) void fmm_p2l_kernel(
     __syncthreads();
     const int total = s_pre[ne];
     const int j1 = (int)((int64_t)total * (part + 1) / splits);
-    const int grp = tid / Sh::lanes, kxy = tid % Sh::lanes;
+    // proxies k0 .. k0 + KZ - 1 of this lane: one (x, y), consecutive z
+    const int grp = tid / Sh::lanes, k0 = tid % Sh::lanes * KZ, kxy = k0 / NO, kz0 = k0 % NO;
     const bool act = grp < Sh::groups;
     const float okx = (float)(w * tab[kTabNode + kxy / NO]),
                 oky = (float)(w * tab[kTabNode + kxy % NO]);
     const double cx = centre(g.ox, side, ct.x), cy = centre(g.oy, side, ct.y),
                  cz = centre(g.oz, side, ct.z);
     const F2 hx = split(cx), hy = split(cy), hz = split(cz);
-    float okz[NO], zi[NO];
+    float okz[KZ], zi[KZ];
 #pragma unroll
-    for (int kz = 0; kz < NO; ++kz) {
-        okz[kz] = (float)(w * tab[kTabNode + kz]);
-        zi[kz] = (float)(cz + w * (double)tab[kTabNode + kz]);
+    for (int kz = 0; kz < KZ; ++kz) {
+        okz[kz] = (float)(w * tab[kTabNode + kz0 + kz]);
+        zi[kz] = (float)(cz + w * (double)tab[kTabNode + kz0 + kz]);
     }
     // double sums: float runs are promoted after each chunk
-    A run[NO][NB] = {};
-    double sum[F32 ? NO : 1][F32 ? NB : 1] = {};
+    A run[KZ][NB] = {};
+    double sum[F32 ? KZ : 1][F32 ? NB : 1] = {};
     for (int j0 = (int)((int64_t)total * part / splits); j0 < j1; j0 += C) {
         const int cnt = min(C, j1 - j0);
         __syncthreads();
@@ -401,13 +394,14 @@ __global__ __launch_bounds__(kP2LBlock) void fmm_p2l_kernel(
         }
         __syncthreads();
         if (!act) continue;
+#pragma unroll 1
         for (int s = grp; s < cnt; s += Sh::groups) {
             const float4 o = s_off[s];
             const Vec4<A> F = s_f[s];
             const float dx = okx - o.x, dy = oky - o.y;
             if constexpr (CH == 1) {
 #pragma unroll
-                for (int kz = 0; kz < NO; ++kz) {
+                for (int kz = 0; kz < KZ; ++kz) {
                     const float dz = okz[kz] - o.z;
                     if constexpr (WALL) {
                         float Rz;
@@ -432,7 +426,7 @@ __global__ __launch_bounds__(kP2LBlock) void fmm_p2l_kernel(
             } else {
                 const Vec4<A> Tq = s_t[s];
 #pragma unroll
-                for (int kz = 0; kz < NO; ++kz) {
+                for (int kz = 0; kz < KZ; ++kz) {
                     constexpr RotCoef<float> rc = kUnitRotCoef;
                     const float dz = okz[kz] - o.z;
                     const float rinv = rsq_f32(fmaf(dz, dz, fmaf(dx, dx, dy * dy)));
@@ -446,7 +440,7 @@ __global__ __launch_bounds__(kP2LBlock) void fmm_p2l_kernel(
         }
         if constexpr (F32) {
 #pragma unroll
-            for (int kz = 0; kz < NO; ++kz)
+            for (int kz = 0; kz < KZ; ++kz)
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
                     sum[kz][i] += (double)run[kz][i];
@@ -458,18 +452,18 @@ __global__ __launch_bounds__(kP2LBlock) void fmm_p2l_kernel(
     for (int gr = 0; gr < Sh::groups; ++gr) {
         if (grp == gr) {
 #pragma unroll
-            for (int kz = 0; kz < NO; ++kz)
+            for (int kz = 0; kz < KZ; ++kz)
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
                     if constexpr (F32)
-                        s_sum[i][kxy * NO + kz] += sum[kz][i];
+                        s_sum[i][k0 + kz] += sum[kz][i];
                     else
-                        s_sum[i][kxy * NO + kz] += run[kz][i];
+                        s_sum[i][k0 + kz] += run[kz][i];
                 }
         }
         __syncthreads();
     }
-    for (int i = tid; i < 3 * P; i += kP2LBlock) {
+    for (int i = tid; i < 3 * P; i += block) {
         if (splits == 1) {
             vu[(size_t)c * 3 * P + i] = s_sum[i % 3][i / 3];
             if constexpr (CH == 2) vw[(size_t)c * 3 * P + i] = s_sum[3 + i % 3][i / 3];
@@ -519,18 +513,18 @@ void run_m2l(const FmmState &F, hipStream_t s) {
     with_order(F.n, [&](auto o) {
         constexpr int NO = decltype(o)::value;
         fmm_p2l_kernel<WALL, CH, A, NO>
-            <<<round_up(nc * splits, 8 * kXcdChunk), kP2LBlock, 0, s>>>(
+            <<<round_up(nc * splits, 8 * kXcdChunk), SparseShape<NO>::block, 0, s>>>(
                 g, tab, F.cc.as<int4>(), F.sp_ptr.as<int>(), F.sp.as<int>(), cell0, nc * splits,
                 splits, F.rng.as<int2>(), F.shi.as<float4>(), F.slo.as<float4>(), sf, st, vu, vw,
                 F.vsplit.as<double>());
-        using Sh = DenseShape<NO>;
         for (const FmmChunk &ch : F.chunks) {
-            const int items = (ch.batch1 - ch.batch0) * Sh::groups;
+            const int tasks = (ch.batch1 - ch.batch0) * ((NO * NO * NO + 15) / 16);
+            const int items = (tasks + kDenseWaves - 1) / kDenseWaves;
             if (items > 0)
                 fmm_m2l_dense_kernel<WALL, CH, A, (CH == 1 ? 2 : 1), NO>
-                    <<<round_up(items, 8 * kXcdChunk), Sh::threads, 0, s>>>(
-                        g, tab, F.batches.as<FmmBatch>() + ch.batch0, items, F.cols.as<int2>(), qf,
-                        qt, F.slots.as<double>());
+                    <<<round_up(items, 8 * kXcdChunk), 64 * kDenseWaves, 0, s>>>(
+                        g, tab, F.batches.as<FmmBatch>() + ch.batch0, tasks, items,
+                        F.cols.as<int2>(), qf, qt, F.slots.as<double>());
             if (items > 0 || splits > 1)
                 fmm_m2l_sum_kernel<<<dim3(ch.cell1 - ch.cell0, (3 * P * CH + 255) / 256), 256, 0,
                                      s>>>(cell0, ch.cell0, 3 * P, CH, splits,
