@@ -4,7 +4,7 @@ import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["pair.hip", "pair_sym.hip", "bodies.hip", "precond.hip", "krylov.hip", "correct.hip", "reconstruct.hip", "rot_pair.hip", "fmm.hip", "fmm_m2l.hip", "mlp.hip",
+SOURCES = ["pair.hip", "pair_sym.hip", "bodies.hip", "precond.hip", "krylov.hip", "correct.hip", "reconstruct.hip", "rot_pair.hip", "fmm.hip", "fmm_m2l.hip", "fmm_near.hip", "mlp.hip",
            "small.hip", "noalloc.hip", "api.hip"]
 LIB = os.path.join(HERE, "libarb.so")
 

@@ -87,6 +87,9 @@ struct FmmBatch {
 struct FmmChunk {
     int cell0, cell1, batch0, batch1, slot0;
 };
+// most near-field slots (24 bytes each; about 17 per blob in a layer of leaves, 60 in
+// space) of a tree that sums pairs both ways
+constexpr int64_t kFmmNearSlots = (int64_t)256 << 20;
 constexpr int64_t kFmmSlotBytes = (int64_t)256 << 20;
 
 struct FmmHostCache;  // host buffers of the tree build, kept between builds (fmm.hip)
@@ -94,10 +97,15 @@ struct FmmState {
     std::shared_ptr<FmmHostCache> host;
     DevBuf perm, cc, rng, parent, kids, near_ptr, nearl, work, tab, shi, slo, slam,
         qhat, v, slam2, qhat2, v2;  // second channel: the torques of single-blob bodies
-    // M2L: sparse listed cells per cell, slots per cell, columns and batches of the
+    // M2L: sparse listed cells per cell and the cells' order, slots per cell, columns and batches of the
     // dense entries, the entries' results
-    DevBuf sp_ptr, sp, slot_ptr, cols, batches, slots;
+    DevBuf sp_ptr, sp, sp_order, slot_ptr, cols, batches, slots;
     std::vector<FmmChunk> chunks;
+    // near field: blocks of targets, per leaf the slots other blocks fill for it, each
+    // blob's own sums, the slots
+    DevBuf blocks, in_ptr, in, own, near_slots;
+    int n_blocks = 0;
+    bool near_sym = false;  // both directions of a pair at once (slots)
     DevBuf vsplit;  // M2L sums of the parts of split sparse lists (splits > 1)
     int N = 0, L = 0, n = 0, P = 0, ncell = 0, nleaf = 0, nwork = 0, channels = 1;
     int splits = 1;  // M2L work items per cell (sparse part)
@@ -122,6 +130,10 @@ int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const fl
 // v of every cell of levels 2..L from its interaction list (fmm_m2l.hip); channels =
 // 1: forces, 2: forces and torques (a tree built with channels = 2)
 void fmm_m2l(const FmmState &F, hipStream_t s, int channels, bool wall, bool fp64);
+// direct sums over adjacent leaves plus the leaves' interpolants (fmm_near.hip):
+// partial[c][i] in the original blob order
+void fmm_near(const FmmState &F, hipStream_t s, int channels, bool wall, bool fp64,
+              double *partial);
 // partial[c][i] (3 x N, original order) = the approximation of M_{a=1} lambda,
 // M in units of 1/(8 pi eta) with positions in units of a; fp64: lambda and
 // every sum in double (linear in lambda to double rounding), else in float

@@ -34,9 +34,10 @@
 //        matrix cores; a listed cell with fewer blobs than proxies enters with
 //        its blobs, n^3 |c'| pairs instead of n^6;
 //   L2L  the children's v gain the parent's interpolant at their proxies;
-//   near + L2P  direct sums over the adjacent leaves (hi/lo split positions,
-//        float runs promoted to double, as in the dense FP32 kernel) plus
-//        sum_k S^leaf_k(x_i) v^leaf_k, written in the original blob order.
+//   near + L2P  direct sums over the adjacent leaves (fmm_near.hip: hi/lo split
+//        positions, float runs promoted to double, each pair once for both
+//        directions) plus sum_k S^leaf_k(x_i) v^leaf_k, written in the original
+//        blob order.
 // With L <= 1 there is no interaction list: one cell, the direct sum.
 // Single-blob bodies (Sec. 2.4): the generalised tensor, with the forces and
 // the torques / a in two channels through P2M, M2M and L2L; M2L and the near
@@ -67,51 +68,6 @@ namespace arb {
 namespace {
 
 constexpr int kNearBlock = 64;
-
-// free-space RPY coefficients c1, c2 (units of a) of M = c1 I + c2 r r^T
-__device__ __forceinline__ void free_coef(float r2, float rinv, float &c1, float &c2) {
-    constexpr CoefF c = kUnitCoefF;
-    const float rinv2 = rinv * rinv, rinv3 = rinv * rinv2;
-    c1 = fmaf(c.k1, rinv3, rinv);
-    c2 = fmaf(-c.k2, rinv3 * rinv2, rinv3);
-    ARB_IF_ANY_OVERLAP(r2 <= c.four_a2)
-    if (r2 <= c.four_a2) {
-        const float rv = r2 > 0.f ? rinv : 0.f;
-        c1 = fmaf(-c.n2, r2 * rv, c.n1);
-        c2 = rv * c.n3;
-    }
-    ARB_END_IF_ANY
-}
-
-// acc += M(d) l for one pair: tensor coefficients in float, applied in A
-template <bool WALL, class A>
-__device__ __forceinline__ void pair_acc(float dx, float dy, float dz, float dxy2,
-                                         const TargetZ<float> &zsc, float zi, float zj, float h2,
-                                         float mh22, A lx, A ly, A lz, A &ax, A &ay, A &az) {
-    constexpr CoefF cf = kUnitCoefF;
-    const float r2 = fmaf(dz, dz, dxy2);
-    const float rinv = rsq_f32(r2);
-    if constexpr (WALL) {
-        const float Rz = zi + zj;
-        const float Ri = rsq_f32(fmaf(Rz, Rz, dxy2));
-        const PairCoef<float> pc =
-            wall_pair_coef<float>(r2, rinv, dxy2, zsc, zj, h2, mh22, Rz, Ri, cf);
-        if constexpr (std::is_same_v<A, float>) {
-            wall_pair_apply<float>(pc, pc.c, pc.d, dx, dy, dz, Rz, lx, ly, lz, ax, ay, az);
-        } else {
-            const PairCoef<double> pd{pc.cA, pc.cAe, pc.c2, pc.b, pc.c, pc.d, pc.e, pc.h2};
-            wall_pair_apply<double>(pd, pd.c, pd.d, dx, dy, dz, Rz, lx, ly, lz, ax, ay, az);
-        }
-    } else {
-        float c1, c2;
-        free_coef(r2, rinv, c1, c2);
-        const A rl = fma((A)dx, lx, fma((A)dy, ly, (A)dz * lz));
-        const A t = (A)c2 * rl;
-        ax = fma((A)c1, lx, fma(t, (A)dx, ax));
-        ay = fma((A)c1, ly, fma(t, (A)dy, ay));
-        az = fma((A)c1, lz, fma(t, (A)dz, az));
-    }
-}
 
 // Lagrange polynomial l_k(u) at the Chebyshev points (product form)
 __device__ __forceinline__ float lag(const float *tab, int n, int k, float u) {
@@ -289,102 +245,6 @@ __global__ __launch_bounds__(kFmmMaxP) void fmm_l2l_kernel(Geo g, const float *_
     o[2] += sz;
 }
 
-// direct sums over the adjacent leaves plus the leaf's interpolant; one
-// workgroup per (leaf, run of 64 targets); output in the original blob order
-template <bool WALL, class A>
-__global__ __launch_bounds__(kNearBlock) void fmm_near_kernel(
-    Geo g, const float *__restrict__ tabg, int N, int far, const int4 *__restrict__ cc,
-    const int2 *__restrict__ rng, const int *__restrict__ near_ptr, const int *__restrict__ near,
-    int leaf0, const int2 *__restrict__ work, int items, const int *__restrict__ perm,
-    const float4 *__restrict__ shi, const float4 *__restrict__ slo,
-    const Vec4<A> *__restrict__ slam, const double *__restrict__ v, double *__restrict__ partial) {
-    const int item = xcd_item(items);
-    if (item < 0) return;
-    __shared__ float tab[kTabSize];
-    __shared__ float4 s_hi[kNearBlock], s_lo[kNearBlock];
-    __shared__ Vec4<A> s_lam[kNearBlock];
-    load_tab(tabg, tab);
-    const int tid = threadIdx.x;
-    const int2 wk = work[item];
-    const int c = wk.x;
-    const int2 tr = rng[c];
-    const int i = wk.y + tid;
-    const bool act = i < tr.y;
-    const int ic = act ? i : tr.y - 1;
-    const float4 th = shi[ic], tl = slo[ic];
-    const float zi = th.z + tl.z;
-    const TargetZ<float> zsc = target_z(zi);
-    double ux = 0.0, uy = 0.0, uz = 0.0;
-    const int lf = c - leaf0;
-    const int e1 = near_ptr[lf + 1];
-    for (int e = near_ptr[lf]; e < e1; ++e) {
-        const int2 sr = rng[near[e]];
-        for (int j0 = sr.x; j0 < sr.y; j0 += kNearBlock) {
-            const int j = j0 + tid;
-            __syncthreads();
-            if (j < sr.y) {
-                s_hi[tid] = shi[j];
-                s_lo[tid] = slo[j];
-                s_lam[tid] = slam[j];
-            }
-            __syncthreads();
-            const int cnt = min(kNearBlock, sr.y - j0);
-            for (int k0 = 0; k0 < cnt; k0 += kFmmRun) {
-                const int k1 = min(k0 + kFmmRun, cnt);
-                A ax = 0, ay = 0, az = 0;
-                for (int k = k0; k < k1; ++k) {
-                    const float4 sh = s_hi[k], sl = s_lo[k];
-                    const Vec4<A> L = s_lam[k];
-                    const float dx = (th.x - sh.x) + (tl.x - sl.x);
-                    const float dy = (th.y - sh.y) + (tl.y - sl.y);
-                    const float dz = (th.z - sh.z) + (tl.z - sl.z);
-                    const float dxy2 = fmaf(dx, dx, dy * dy);
-                    pair_acc<WALL, A>(dx, dy, dz, dxy2, zsc, zi, sh.z, sh.w, sl.w, L.x, L.y, L.z,
-                                      ax, ay, az);
-                }
-                ux += ax;
-                uy += ay;
-                uz += az;
-            }
-        }
-    }
-    if (far) {
-        const int n = g.n;
-        const int4 ci = cc[c];
-        const double side = ldexp(g.S, -ci.w);
-        const F2 cx = split(centre(g.ox, side, ci.x)), cy = split(centre(g.oy, side, ci.y)),
-                 cz = split(centre(g.oz, side, ci.z));
-        const float iw = (float)(2.0 / side);
-        const float px = ((th.x - cx.h) + (tl.x - cx.l)) * iw;
-        const float py = ((th.y - cy.h) + (tl.y - cy.l)) * iw;
-        const float pz = ((th.z - cz.h) + (tl.z - cz.l)) * iw;
-        const double *vc = v + (size_t)c * g.P * 3;
-        double sx = 0.0, sy = 0.0, sz = 0.0;
-        for (int kx = 0; kx < n; ++kx) {
-            const float a = lag(tab, n, kx, px);
-            for (int ky = 0; ky < n; ++ky) {
-                const float b = a * lag(tab, n, ky, py);
-                for (int kz = 0; kz < n; ++kz) {
-                    const double wk = (double)(b * lag(tab, n, kz, pz));
-                    const double *pv = vc + 3 * ((kx * n + ky) * n + kz);
-                    sx = fma(wk, pv[0], sx);
-                    sy = fma(wk, pv[1], sy);
-                    sz = fma(wk, pv[2], sz);
-                }
-            }
-        }
-        ux += sx;
-        uy += sy;
-        uz += sz;
-    }
-    if (act) {
-        const size_t o = (size_t)perm[i];
-        partial[o] = ux;
-        partial[(size_t)N + o] = uy;
-        partial[2 * (size_t)N + o] = uz;
-    }
-}
-
 // ---------------------------------------------------------------- single-blob bodies
 // Generalised forces (f, tau) in two channels, f and tau / a (units of a), each
 // carried by the channel-wise P2M, M2M and L2L kernels above; M2L and the near
@@ -399,111 +259,6 @@ __global__ void fmm_gather6_kernel(int M, const int *__restrict__ perm,
     const double *x = x6 + 6 * (size_t)perm[k];
     sf[k] = vec4<A>((A)x[0], (A)x[1], (A)x[2]);
     st[k] = vec4<A>((A)(x[3] * inv_a), (A)(x[4] * inv_a), (A)(x[5] * inv_a));
-}
-
-// acc += N(d) (f, t): tensor coefficients in float (a = 1), applied in A
-template <class A>
-__device__ __forceinline__ void rot_acc(float dx, float dy, float dz, float r2, const Vec4<A> &f,
-                                        const Vec4<A> &t, A *acc) {
-    const float rinv = rsq_f32(r2);
-    const RotTerms<float> kf = rot_terms<float>(r2, rinv, kUnitRotCoef);
-    if constexpr (std::is_same_v<A, float>) {
-        rot_one_way<float>(kf, dx, dy, dz, f.x, f.y, f.z, t.x, t.y, t.z, acc);
-    } else {
-        const RotTerms<double> kd{kf.c1, kf.c2, kf.cr, kf.d1, kf.d2};
-        rot_one_way<double>(kd, dx, dy, dz, f.x, f.y, f.z, t.x, t.y, t.z, acc);
-    }
-}
-
-// direct sums of the generalised tensor over adjacent leaves plus both
-// channels' interpolants; partial[j][body] (6 x M, original order)
-template <class A>
-__global__ __launch_bounds__(kNearBlock) void fmm_near6_kernel(
-    Geo g, const float *__restrict__ tabg, int M, int far, const int4 *__restrict__ cc,
-    const int2 *__restrict__ rng, const int *__restrict__ near_ptr, const int *__restrict__ near,
-    int leaf0, const int2 *__restrict__ work, int items, const int *__restrict__ perm,
-    const float4 *__restrict__ shi, const float4 *__restrict__ slo, const Vec4<A> *__restrict__ sf,
-    const Vec4<A> *__restrict__ st, const double *__restrict__ vu, const double *__restrict__ vw,
-    double *__restrict__ partial) {
-    const int item = xcd_item(items);
-    if (item < 0) return;
-    __shared__ float tab[kTabSize];
-    __shared__ float4 s_hi[kNearBlock], s_lo[kNearBlock];
-    __shared__ Vec4<A> s_f[kNearBlock], s_t[kNearBlock];
-    load_tab(tabg, tab);
-    const int tid = threadIdx.x;
-    const int2 wk = work[item];
-    const int c = wk.x;
-    const int2 tr = rng[c];
-    const int i = wk.y + tid;
-    const bool act = i < tr.y;
-    const int ic = act ? i : tr.y - 1;
-    const float4 th = shi[ic], tl = slo[ic];
-    double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    const int lf = c - leaf0;
-    const int e1 = near_ptr[lf + 1];
-    for (int e = near_ptr[lf]; e < e1; ++e) {
-        const int2 sr = rng[near[e]];
-        for (int j0 = sr.x; j0 < sr.y; j0 += kNearBlock) {
-            const int j = j0 + tid;
-            __syncthreads();
-            if (j < sr.y) {
-                s_hi[tid] = shi[j];
-                s_lo[tid] = slo[j];
-                s_f[tid] = sf[j];
-                s_t[tid] = st[j];
-            }
-            __syncthreads();
-            const int cnt = min(kNearBlock, sr.y - j0);
-            for (int k0 = 0; k0 < cnt; k0 += kFmmRun) {
-                const int k1 = min(k0 + kFmmRun, cnt);
-                A f6[6] = {0, 0, 0, 0, 0, 0};
-                for (int k = k0; k < k1; ++k) {
-                    const float4 sh = s_hi[k], sl = s_lo[k];
-                    const float dx = (th.x - sh.x) + (tl.x - sl.x);
-                    const float dy = (th.y - sh.y) + (tl.y - sl.y);
-                    const float dz = (th.z - sh.z) + (tl.z - sl.z);
-                    rot_acc<A>(dx, dy, dz, fmaf(dz, dz, fmaf(dx, dx, dy * dy)), s_f[k], s_t[k],
-                               f6);
-                }
-#pragma unroll
-                for (int jj = 0; jj < 6; ++jj) acc[jj] += f6[jj];
-            }
-        }
-    }
-    if (far) {
-        const int n = g.n;
-        const int4 ci = cc[c];
-        const double side = ldexp(g.S, -ci.w);
-        const F2 cx = split(centre(g.ox, side, ci.x)), cy = split(centre(g.oy, side, ci.y)),
-                 cz = split(centre(g.oz, side, ci.z));
-        const float iw = (float)(2.0 / side);
-        const float px = ((th.x - cx.h) + (tl.x - cx.l)) * iw;
-        const float py = ((th.y - cy.h) + (tl.y - cy.l)) * iw;
-        const float pz = ((th.z - cz.h) + (tl.z - cz.l)) * iw;
-        const double *pu = vu + (size_t)c * g.P * 3, *pw = vw + (size_t)c * g.P * 3;
-        for (int kx = 0; kx < n; ++kx) {
-            const float a = lag(tab, n, kx, px);
-            for (int ky = 0; ky < n; ++ky) {
-                const float b = a * lag(tab, n, ky, py);
-                for (int kz = 0; kz < n; ++kz) {
-                    const double wk2 = (double)(b * lag(tab, n, kz, pz));
-                    const int q = 3 * ((kx * n + ky) * n + kz);
-                    acc[0] = fma(wk2, pu[q], acc[0]);
-                    acc[1] = fma(wk2, pu[q + 1], acc[1]);
-                    acc[2] = fma(wk2, pu[q + 2], acc[2]);
-                    acc[3] = fma(wk2, pw[q], acc[3]);
-                    acc[4] = fma(wk2, pw[q + 1], acc[4]);
-                    acc[5] = fma(wk2, pw[q + 2], acc[5]);
-                }
-            }
-        }
-    }
-    if (act) {
-        const size_t o = (size_t)perm[i];
-#pragma unroll
-        for (int jj = 0; jj < 6; ++jj) partial[(size_t)jj * M + o] = acc[jj];
-    }
 }
 
 // ---------------------------------------------------------------- host tree
@@ -764,11 +519,18 @@ struct HostArr {
 // slots of its dense entries, the dense entries grouped into batches, and the
 // chunks of cells that share the slots' memory
 struct M2LGroups {
-    std::vector<int> sp_ptr, sp, slot_ptr, count, zidx;
+    std::vector<int> sp_ptr, sp, sp_order, slot_ptr, count, zidx;
     std::vector<int2> cols;
     std::vector<FmmBatch> batches;
     std::vector<FmmChunk> chunks;
     int max_slots = 0;  // of a chunk
+};
+// the near field's work (fmm_near.hip): blocks of targets (leaf, first target,
+// targets, first slot) and, per leaf, the slots that other blocks fill for it
+struct NearBlocks {
+    std::vector<int4> blocks;
+    std::vector<int> in_ptr, in;
+    int64_t slots = 0;  // blobs' worth of slots (3 doubles each)
 };
 struct PlanScratch {
     HostArr<int> crd, idx, idx2;
@@ -784,6 +546,7 @@ struct arb::FmmHostCache {
     PlanScratch scratch;
     FmmPlan plan;
     M2LGroups m2l;
+    NearBlocks near;
     double *hpos = nullptr;
     size_t hpos_n = 0;
     FmmHostCache() = default;
@@ -1199,6 +962,19 @@ int fmm_plan(FmmPlan &pl, PlanScratch &sc, int N, const double *h, double a, int
     return 0;
 }
 
+// Work items longest first when there are so few that the last ones to start decide
+// when a launch ends (a few per compute unit; with more, neighbours stay together for
+// the caches): cost[k] of item k, the order in `order`
+constexpr int kSortItems = 16384;
+template <class V>
+static void longest_first(const std::vector<V> &cost, std::vector<int> &order) {
+    order.resize(cost.size());
+    for (size_t k = 0; k < cost.size(); ++k) order[k] = (int)k;
+    if (cost.size() <= kSortItems)
+        std::stable_sort(order.begin(), order.end(),
+                         [&](int a, int b) { return cost[a] > cost[b]; });
+}
+
 // Groups the interaction lists for M2L.  Entries whose listed cell holds at least P
 // blobs are dense: they get a slot each, numbered in list order within a chunk of
 // target cells, and are sorted (counting sort, stable) by the key that fixes the
@@ -1226,6 +1002,13 @@ static void group_m2l(const FmmPlan &pl, bool wall, int max_cols, int64_t chunk_
         }
         G.sp_ptr[i + 1] = (int)G.sp.size();
         G.slot_ptr[i + 1] = G.slot_ptr[i] + d;
+    }
+    {
+        std::vector<int> blobs((size_t)nc);
+        for (int i = 0; i < nc; ++i)
+            for (int e = G.sp_ptr[i]; e < G.sp_ptr[i + 1]; ++e)
+                blobs[i] += pl.rng[G.sp[e]].y - pl.rng[G.sp[e]].x;
+        longest_first(blobs, G.sp_order);
     }
     G.cols.resize((size_t)G.slot_ptr[nc]);
     for (int a = 0; a < nc;) {
@@ -1294,6 +1077,55 @@ static void group_m2l(const FmmPlan &pl, bool wall, int max_cols, int64_t chunk_
     }
 }
 
+// Blocks of at most kNearBlock targets of one leaf; with sym, the slots of each block: one
+// per adjacent leaf after its own (in cell order), |leaf| blobs each.
+static void near_blocks(const FmmPlan &pl, bool sym, NearBlocks &B) {
+    const int leaf0 = pl.lvl[pl.L];
+    std::vector<int4> blocks;
+    std::vector<int64_t> cost;
+    B.blocks.clear();
+    B.in.clear();
+    B.in_ptr.assign((size_t)pl.nleaf + 1, 0);
+    B.slots = 0;
+    for (int c = leaf0; c < leaf0 + pl.nleaf; ++c) {
+        int64_t per_block = 0, visited = 0;
+        int after = 0;
+        for (int e = pl.near_ptr[c - leaf0]; e < pl.near_ptr[c - leaf0 + 1]; ++e) {
+            const int q = pl.nearl[e], m = pl.rng[q].y - pl.rng[q].x;
+            if (!sym || q >= c) visited += m;
+            if (sym && q > c) {
+                per_block += m;
+                ++after;
+            }
+        }
+        const int2 r = pl.rng[c];
+        for (int t = r.x; t < r.y; t += kNearBlock) {
+            blocks.push_back(make_int4(c, t, std::min(kNearBlock, r.y - t), (int)B.slots));
+            cost.push_back(visited);
+            B.slots += per_block;
+            if (after)
+                for (int e = pl.near_ptr[c - leaf0]; e < pl.near_ptr[c - leaf0 + 1]; ++e)
+                    if (pl.nearl[e] > c) ++B.in_ptr[pl.nearl[e] - leaf0 + 1];
+        }
+    }
+    std::vector<int> order;
+    longest_first(cost, order);
+    for (int k : order) B.blocks.push_back(blocks[k]);
+    if (!sym || B.slots > kFmmNearSlots) return;
+    for (int q = 0; q < pl.nleaf; ++q) B.in_ptr[q + 1] += B.in_ptr[q];
+    B.in.resize((size_t)B.in_ptr[pl.nleaf]);
+    std::vector<int> next(B.in_ptr.begin(), B.in_ptr.end() - 1);
+    for (const int4 &b : B.blocks) {
+        int at = b.w;
+        for (int e = pl.near_ptr[b.x - leaf0]; e < pl.near_ptr[b.x - leaf0 + 1]; ++e) {
+            const int q = pl.nearl[e];
+            if (q <= b.x) continue;
+            B.in[next[q - leaf0]++] = at;
+            at += pl.rng[q].y - pl.rng[q].x;
+        }
+    }
+}
+
 int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const float4 *hi,
               const float4 *lo, double a, int order, int levels, int leaf, int channels, bool wall,
               std::string *msg) {
@@ -1353,6 +1185,20 @@ int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const fl
                (F.slam2.ensure((size_t)N * sizeof(double4)) == hipSuccess &&
                 F.qhat2.ensure((size_t)ncell * P * sizeof(double4)) == hipSuccess &&
                 F.v2.ensure((size_t)ncell * P * 3 * sizeof(double)) == hipSuccess));
+    // near field: both directions of a pair at once for the 3-component tensor; one way,
+    // without slots, with torques or when the slots would outgrow kFmmNearSlots
+    NearBlocks &nb = hc.near;
+    bool near_sym = channels == 1;
+    near_blocks(pl, near_sym, nb);
+    if (near_sym && nb.slots > kFmmNearSlots) {
+        near_sym = false;
+        near_blocks(pl, false, nb);
+    }
+    ok = ok && up(F.blocks, nb.blocks.data(), nb.blocks.size() * sizeof(int4)) &&
+         up(F.in_ptr, nb.in_ptr.data(), nb.in_ptr.size() * sizeof(int)) &&
+         up(F.in, nb.in.data(), nb.in.size() * sizeof(int)) &&
+         F.own.ensure((size_t)N * 3 * channels * sizeof(double)) == hipSuccess &&
+         F.near_slots.ensure((size_t)nb.slots * 3 * sizeof(double)) == hipSuccess;
     // M2L's batches: 32 columns, 16 with the torque channel; slots of a chunk bounded
     M2LGroups &mg = hc.m2l;
     const int64_t slot_doubles = 3 * (int64_t)P * channels;
@@ -1360,6 +1206,7 @@ int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const fl
               std::max<int64_t>(1, kFmmSlotBytes / (slot_doubles * 8)), mg);
     ok = ok && up(F.sp_ptr, mg.sp_ptr.data(), mg.sp_ptr.size() * sizeof(int)) &&
          up(F.sp, mg.sp.data(), mg.sp.size() * sizeof(int)) &&
+         up(F.sp_order, mg.sp_order.data(), mg.sp_order.size() * sizeof(int)) &&
          up(F.slot_ptr, mg.slot_ptr.data(), mg.slot_ptr.size() * sizeof(int)) &&
          up(F.cols, mg.cols.data(), mg.cols.size() * sizeof(int2)) &&
          up(F.batches, mg.batches.data(), mg.batches.size() * sizeof(FmmBatch)) &&
@@ -1390,6 +1237,8 @@ int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const fl
     F.ncell = pl.ncell;
     F.nleaf = pl.nleaf;
     F.nwork = (int)pl.work.size();
+    F.n_blocks = (int)nb.blocks.size();
+    F.near_sym = near_sym;
     F.n_il = (int64_t)pl.il.size();
     F.n_m2l_pairs = pl.n_m2l_pairs;
     F.n_near_pairs = pl.n_near_pairs;
@@ -1425,11 +1274,7 @@ void fmm_run(const FmmState &F, hipStream_t s, const double *lam, double *partia
                     g, tab, F.cc.as<int4>(), F.parent.as<int>(), F.lvl[l], F.v.as<double>());
         });
     }
-    fmm_near_kernel<WALL, A><<<round_up(F.nwork, 8 * kXcdChunk), kNearBlock, 0, s>>>(
-        g, tab, N, L >= 2 ? 1 : 0, F.cc.as<int4>(), F.rng.as<int2>(), F.near_ptr.as<int>(),
-        F.nearl.as<int>(), F.lvl[L], F.work.as<int2>(), F.nwork, F.perm.as<int>(),
-        F.shi.as<float4>(),
-        F.slo.as<float4>(), slam, F.v.as<double>(), partial);
+    fmm_near(F, s, 1, WALL, std::is_same_v<A, double>, partial);
 }
 
 }  // namespace
@@ -1480,11 +1325,7 @@ void fmm_run6(const FmmState &F, hipStream_t s, const double *x6, double inv_a, 
                         g, tab, F.cc.as<int4>(), F.parent.as<int>(), F.lvl[l], ch ? vw : vu);
         });
     }
-    fmm_near6_kernel<A><<<round_up(F.nwork, 8 * kXcdChunk), kNearBlock, 0, s>>>(
-        g, tab, M, L >= 2 ? 1 : 0, F.cc.as<int4>(), F.rng.as<int2>(), F.near_ptr.as<int>(),
-        F.nearl.as<int>(), F.lvl[L], F.work.as<int2>(), F.nwork, F.perm.as<int>(),
-        F.shi.as<float4>(),
-        F.slo.as<float4>(), sf, st, vu, vw, partial);
+    fmm_near(F, s, 2, false, std::is_same_v<A, double>, partial);
 }
 
 }  // namespace

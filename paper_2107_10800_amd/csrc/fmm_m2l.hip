@@ -312,7 +312,8 @@ __global__ __launch_bounds__(SparseShape<NO>::block)
 __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 : 3)))
 void fmm_p2l_kernel(
     Geo g, const float *__restrict__ tabg, const int4 *__restrict__ cc,
-    const int *__restrict__ sp_ptr, const int *__restrict__ sp, int cell0, int items, int splits,
+    const int *__restrict__ sp_ptr, const int *__restrict__ sp, const int *__restrict__ order,
+    int cell0, int items, int splits,
     const int2 *__restrict__ rng, const float4 *__restrict__ shi, const float4 *__restrict__ slo,
     const Vec4<A> *__restrict__ sf, const Vec4<A> *__restrict__ st, double *__restrict__ vu,
     double *__restrict__ vw, double *__restrict__ vpart) {
@@ -328,7 +329,7 @@ void fmm_p2l_kernel(
     __shared__ double s_sum[NB][P];
     load_tab(tabg, tab);
     const int tid = threadIdx.x;
-    const int ci = item / splits, part = item % splits, c = cell0 + ci;
+    const int ci = order[item / splits], part = item % splits, c = cell0 + ci;
     const int4 ct = cc[c];
     const double side = ldexp(g.S, -ct.w), w = 0.5 * side;
     const int e0 = sp_ptr[ci], ne = sp_ptr[ci + 1] - e0;
@@ -353,6 +354,13 @@ void fmm_p2l_kernel(
     }
     __syncthreads();
     const int total = s_pre[ne];
+    if (total == 0 && splits == 1) {
+        for (int i = tid; i < 3 * P; i += block) {
+            vu[(size_t)c * 3 * P + i] = 0.0;
+            if constexpr (CH == 2) vw[(size_t)c * 3 * P + i] = 0.0;
+        }
+        return;
+    }
     const int j1 = (int)((int64_t)total * (part + 1) / splits);
     // proxies k0 .. k0 + KZ - 1 of this lane: one (x, y), consecutive z
     const int grp = tid / Sh::lanes, k0 = tid % Sh::lanes * KZ, kxy = k0 / NO, kz0 = k0 % NO;
@@ -468,7 +476,7 @@ void fmm_p2l_kernel(
             vu[(size_t)c * 3 * P + i] = s_sum[i % 3][i / 3];
             if constexpr (CH == 2) vw[(size_t)c * 3 * P + i] = s_sum[3 + i % 3][i / 3];
         } else {
-            double *o = vpart + (size_t)item * NB * P + i;
+            double *o = vpart + ((size_t)ci * splits + part) * NB * P + i;
             o[0] = s_sum[i % 3][i / 3];
             if constexpr (CH == 2) o[3 * P] = s_sum[3 + i % 3][i / 3];
         }
@@ -514,7 +522,8 @@ void run_m2l(const FmmState &F, hipStream_t s) {
         constexpr int NO = decltype(o)::value;
         fmm_p2l_kernel<WALL, CH, A, NO>
             <<<round_up(nc * splits, 8 * kXcdChunk), SparseShape<NO>::block, 0, s>>>(
-                g, tab, F.cc.as<int4>(), F.sp_ptr.as<int>(), F.sp.as<int>(), cell0, nc * splits,
+                g, tab, F.cc.as<int4>(), F.sp_ptr.as<int>(), F.sp.as<int>(), F.sp_order.as<int>(), cell0,
+                nc * splits,
                 splits, F.rng.as<int2>(), F.shi.as<float4>(), F.slo.as<float4>(), sf, st, vu, vw,
                 F.vsplit.as<double>());
         for (const FmmChunk &ch : F.chunks) {

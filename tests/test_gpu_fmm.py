@@ -96,6 +96,57 @@ def test_m2l_batches_against_the_oracle(N, wall, n, L):
         assert np.abs(uw - ref).max() <= 1e-5 * np.abs(ref).max()
 
 
+def leaves_of(counts, rng):
+    """counts[i] blobs in cell i of a row of 8 x 1 x 1 cells of side 10 (leaf level 3 of a
+    cube of side 80); the corner blobs span the cube."""
+    pos = [np.array([[0.0, 0.0, 2.0], [80.0, 80.0, 82.0]])]
+    for i, m in enumerate(counts):
+        pos.append(rng.uniform(0.2, 9.8, (m, 3)) + np.array([10.0 * i, 0.0, 2.0]))
+    return np.vstack(pos)
+
+
+# the near field's blocks at the edges of their tiles: leaves of 1 to 257 blobs side by
+# side (targets and source tiles of 1, 63, 64, 65, 128, 129 and 257), every leaf level
+# including the direct sum of a single leaf
+@pytest.mark.parametrize("L", [0, 3])
+@pytest.mark.parametrize("wall", [False, True])
+def test_near_field_blocks_at_their_edges(wall, L):
+    rng = np.random.default_rng(21 + L)
+    pos = leaves_of([1, 63, 64, 65, 257, 128, 129, 2], rng)
+    lam = rng.standard_normal((len(pos), 3))
+    ref = fastsum.fmm_apply(pos, lam, 1.0, 1.0, wall, 2, L) if L else \
+        rpy.mobility_apply(pos, lam, 1.0, 1.0, wall)
+    for prec in (arb.ARB_FP64, arb.ARB_FP32C):
+        u = [fmm(pos, lam, wall, 2, L or 1, precision=prec) for _ in range(2)]
+        assert np.array_equal(u[0], u[1])
+        assert np.abs(u[0] - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+def test_products_share_a_tree_with_torques():
+    """The translational product of single-blob bodies runs on the tree of the
+    generalised one (no slots: the near field one way), before and after it."""
+    rng = np.random.default_rng(5)
+    pos = leaves_of([65, 40, 64, 3, 0, 70, 129, 20], rng)
+    M = len(pos)
+    F = rng.standard_normal((M, 6))
+    wl = W.Workload("loose", 1.0, 1.0, False, np.zeros((M, 3)), np.arange(M + 1, dtype=np.int32),
+                    pos, np.tile([1.0, 0, 0, 0], (M, 1)), F, extra=dict(single_blob=True))
+    ref3 = fastsum.fmm_apply(pos, F[:, :3], 1.0, 1.0, False, 2, 3)
+    ref6 = fastsum.fmm_apply(pos, F, 1.0, 1.0, False, 2, 3, kernel=rot_kernel(1.0, 1.0))
+    for prec in (arb.ARB_FP64, arb.ARB_FP32C):
+        ctx = arb.context_for(wl, precision=prec, pair_kernel=arb.ARB_PAIR_FMM, fmm_order=2,
+                              fmm_levels=3)
+        try:
+            first = arb.arb_mobility_apply(ctx, F[:, :3]).reshape(-1, 3)
+            uw = arb.arb_body_mobility_apply(ctx, F)
+            after = arb.arb_mobility_apply(ctx, F[:, :3]).reshape(-1, 3)
+        finally:
+            arb.arb_destroy(ctx)
+        for u in (first, after):
+            assert np.abs(u - ref3).max() <= 1e-5 * np.abs(ref3).max()
+        assert np.abs(uw - ref6).max() <= 1e-5 * np.abs(ref6).max()
+
+
 @pytest.mark.parametrize("wall", [False, True])
 def test_direct_sum_when_no_level_separates(wall):
     """fmm_levels = 1, a cluster narrower than 8a (no level with side >= 2a
