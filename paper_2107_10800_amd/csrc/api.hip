@@ -411,26 +411,37 @@ int sym_worklist(arb_ctx *ctx, hipStream_t s, int N, int R, int precision) {
     return 0;
 }
 
+// sizes whose product runs in one launch, whatever the shape
+bool small_pair(const arb_ctx *ctx, int N) {
+    return N <= arb::kSmallPairN && ctx->opt.pair_kernel != ARB_PAIR_SYMMETRIC;
+}
+
+// launch shape of the ring kernel (mid sizes), reported as the symmetric kernel's -1
+constexpr int kRingShape = -1000;
+
 // one pair product; shape > 0: target-parallel kernel with that many source
-// slices; shape < 0: symmetric kernel with -shape source tiles per work item
-int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double4 *p64, const float4 *hi,
-             const float4 *lo, const float4 *box, const int *perm, const double *lam, double *out,
-             const double *U, const int *bob,
-             const double *dvec, int precision, bool wall, int shape) {
-    const bool sym = shape < 0;
-    // small systems take the run-sliced target-parallel kernel whatever the shape
-    const bool small = N <= arb::kSmallPairN && ctx->opt.pair_kernel != ARB_PAIR_SYMMETRIC;
+// slices; shape < 0: symmetric kernel with -shape source tiles per work item, or the
+// ring kernel; raw_pos: loose blobs whose positions need not be prepared (small_pair)
+int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const double4 *p64,
+             const float4 *hi, const float4 *lo, const float4 *box, const int *perm,
+             const double *lam, double *out, const double *U, const int *bob, const double *dvec,
+             int precision, bool wall, int shape) {
+    // FP32 sums are in units of the blob radius: M(a) = M_{a=1}(r / a) / a
+    const double scale = 1.0 / (8.0 * arb::kPi * ctx->opt.eta) /
+                         (precision == ARB_FP32C ? ctx->opt.a : 1.0);
+    const bool small = small_pair(ctx, N);
+    const bool ring = !small && shape == kRingShape;
+    const bool sym = !small && !ring && shape < 0;
     int used = 1;
-    if (small) {
-        const int runs = (N + arb::kSmallRun - 1) / arb::kSmallRun;
-        HIPCHK(ctx->partial.ensure((size_t)runs * 3 * N * sizeof(double)));
+    if (ring) {
+        HIPCHK(ctx->partial.ensure((size_t)arb::pair_ring_slices(N) * 3 * N * sizeof(double)));
     } else if (sym) {
         TRY(sym_worklist(ctx, s, N, -shape, precision));
         HIPCHK(ctx->partial.ensure((size_t)3 * N * sizeof(double)));
-    } else {
+        arb::pair_sym_clear(s, N, ctx->partial.as<double>());
+    } else if (!small) {
         HIPCHK(ctx->partial.ensure((size_t)shape * 3 * N * sizeof(double)));
     }
-    if (sym && !small) arb::pair_sym_clear(s, N, ctx->partial.as<double>());
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->prof) {
         HIPCHK(hipEventCreate(&e0));
@@ -438,8 +449,11 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double4 *p64, const float
         HIPCHK(hipEventRecord(e0, s));
     }
     if (small)
-        used = arb::pair_partial_small(s, precision, wall, N, p64, hi, lo, lam, perm, ctx->opt.a,
-                                       ctx->partial.as<double>());
+        arb::pair_small(s, precision, wall, N, raw_pos, p64, hi, lo, lam, perm, ctx->opt.a, scale,
+                        out, U, bob, dvec);
+    else if (ring)
+        used = arb::pair_ring(s, precision, wall, N, p64, hi, lo, box, lam, perm, ctx->opt.a,
+                              ctx->partial.as<double>());
     else if (sym)
         arb::pair_sym(s, precision, wall, N, p64, hi, lo, box, lam, perm, ctx->opt.a,
                       ctx->sym_work[precision == ARB_FP32C].as<int4>(),
@@ -451,10 +465,8 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double4 *p64, const float
         HIPCHK(hipEventRecord(e1, s));
         ctx->prof_ev.emplace_back(e0, e1);
     }
-    // FP32 sums are in units of the blob radius: M(a) = M_{a=1}(r / a) / a
-    const double scale = 1.0 / (8.0 * arb::kPi * ctx->opt.eta) /
-                         (precision == ARB_FP32C ? ctx->opt.a : 1.0);
-    arb::pair_reduce(s, N, used, ctx->partial.as<double>(), scale, out, U, bob, dvec, perm);
+    if (!small)
+        arb::pair_reduce(s, N, used, ctx->partial.as<double>(), scale, out, U, bob, dvec, perm);
     return 0;
 }
 
@@ -503,7 +515,8 @@ int choose_slices(arb_ctx *ctx, hipStream_t s, int N, const double4 *p64, const 
             float tmin = 1e30f;
             for (int rep = 0, reps = 5; rep < reps; ++rep) {
                 HIPCHK(hipEventRecord(e0, s));
-                TRY(run_pair(ctx, s, N, p64, hi, lo, box, perm, lam, ctx->tune_out.as<double>(),
+                TRY(run_pair(ctx, s, N, nullptr, p64, hi, lo, box, perm, lam,
+                             ctx->tune_out.as<double>(),
                              nullptr, nullptr, nullptr, precision, wall, c));
                 HIPCHK(hipEventRecord(e1, s));
                 HIPCHK(hipEventSynchronize(e1));
@@ -519,8 +532,10 @@ int choose_slices(arb_ctx *ctx, hipStream_t s, int N, const double4 *p64, const 
         }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
-    } else if (sym_ok && kind == 2) {
+    } else if (kind == ARB_PAIR_SYMMETRIC) {
         best = -4;
+    } else if (kind == ARB_PAIR_AUTO && N > arb::kSmallPairN) {
+        best = kRingShape;
     }
     ctx->slice_cache[key] = best;
     *shape = best;
@@ -581,7 +596,7 @@ int ctx_pair(arb_ctx *ctx, hipStream_t s, const double *lam, double *out, const 
     const int *perm = so ? ctx->pperm.as<int>() : nullptr;
     int sl = 0;
     TRY(choose_slices(ctx, s, ctx->N, p64, hi, lo, box, perm, lam, precision, wall, &sl));
-    return run_pair(ctx, s, ctx->N, p64, hi, lo, box, perm, lam, out, U,
+    return run_pair(ctx, s, ctx->N, nullptr, p64, hi, lo, box, perm, lam, out, U,
                     ctx->body_of_blob.as<int>(), ctx->dvec.as<double>(), precision, wall, sl);
 }
 
@@ -1507,7 +1522,8 @@ int arb_get_slices(const arb_ctx *ctx, int n_blobs) {
         const int64_t key = (int64_t)n_blobs * 4 + prec * 2 + (ctx->opt.wall ? 1 : 0);
         if (prec == ctx->opt.precision) {
             auto it = ctx->slice_cache.find(key);
-            if (it != ctx->slice_cache.end()) return it->second;
+            if (it != ctx->slice_cache.end())
+                return it->second == kRingShape ? -1 : it->second;
         }
     }
     return heuristic_slices(n_blobs);
@@ -1740,6 +1756,12 @@ int arb_rpy_apply_dev(arb_ctx *ctx, int N, const double *pos_dev, const double *
     if (N == 0) return ARB_OK;
     HIPCHK(hipSetDevice(ctx->opt.device));
     hipStream_t s = pick(ctx, stream);
+    if (small_pair(ctx, N) && ctx->opt.pair_kernel != ARB_PAIR_FMM) {
+        TRY(run_pair(ctx, s, N, pos_dev, nullptr, nullptr, nullptr, nullptr, nullptr, lambda_dev,
+                     u_dev, nullptr, nullptr, nullptr, ctx->opt.precision, ctx->opt.wall != 0, 1));
+        HIPCHK(hipGetLastError());
+        return ARB_OK;
+    }
     const size_t ntb = 2 * (size_t)((N + 63) / 64);
     HIPCHK(ctx->s_pos.ensure((size_t)N * (sizeof(double4) + 2 * sizeof(float4)) +
                              ntb * sizeof(float4)));
@@ -1760,8 +1782,8 @@ int arb_rpy_apply_dev(arb_ctx *ctx, int N, const double *pos_dev, const double *
     int sl = 0;
     TRY(choose_slices(ctx, s, N, p64, hi, lo, box, nullptr, lambda_dev, ctx->opt.precision, wall,
                       &sl));
-    TRY(run_pair(ctx, s, N, p64, hi, lo, box, nullptr, lambda_dev, u_dev, nullptr, nullptr, nullptr,
-                 ctx->opt.precision, wall, sl));
+    TRY(run_pair(ctx, s, N, nullptr, p64, hi, lo, box, nullptr, lambda_dev, u_dev, nullptr, nullptr,
+                 nullptr, ctx->opt.precision, wall, sl));
     HIPCHK(hipGetLastError());
     return ARB_OK;
     ARB_GUARD_END(ctx)

@@ -164,15 +164,22 @@ int noalloc_setup(int device);
 // source slices of the target-parallel kernel when none are given: doubled while
 // the grid stays within about 2,048 workgroups and every slice keeps a tile
 int heuristic_slices(int N);
-// returns the number of slices written (clamped to the tile count)
-// small systems: target-parallel sums over runs of kSmallRun sources, one 64-lane
-// workgroup per (64 targets, run); partial holds ceil(N / kSmallRun) slices;
-// returns that count
+// small systems: the whole product in one launch, out as pair_reduce writes it;
+// raw_pos (may be null): loose blobs' positions (3N, units of length) instead of the
+// prepared arrays
 constexpr int kSmallPairN = 1024;
-constexpr int kSmallRun = 16;
-int pair_partial_small(hipStream_t s, int precision, bool wall, int N, const double4 *p64,
-                       const float4 *hi, const float4 *lo, const double *lam, const int *perm,
-                       double a, double *partial);
+void pair_small(hipStream_t s, int precision, bool wall, int N, const double *raw_pos,
+                const double4 *p64, const float4 *hi, const float4 *lo, const double *lam,
+                const int *perm, double a, double scale, double *out, const double *U,
+                const int *body_of_blob, const double *dvec);
+// mid sizes (pair_sym.hip): each unordered pair once, ordered sums in
+// pair_ring_slices(N) slices of partial (returned)
+constexpr int kRingPairN = 8192;
+int pair_ring_slices(int N);
+int pair_ring(hipStream_t s, int precision, bool wall, int N, const double4 *p64,
+              const float4 *hi, const float4 *lo, const float4 *box, const double *lam,
+              const int *perm, double a, double *partial);
+// target-parallel sums; returns the number of slices written (clamped to the tile count)
 // positions in the order of perm (may be null), lambda in blob order, partial in
 // the positions' order
 int pair_partial(hipStream_t s, int precision, bool wall, int N, const double4 *p64,

@@ -25,6 +25,8 @@
 // results are deterministic.  FP32C: positions (in units of a) are split hi +
 // lo floats so that differences keep ~double accuracy; sums are float over
 // runs of 32 sources and double across runs.
+#include <type_traits>
+
 #include "rpy_device.h"
 
 namespace arb {
@@ -197,24 +199,13 @@ __global__ __launch_bounds__(kTile) void pair_f64_kernel(int N, const double4 *_
     }
 }
 
-// partial in the pair kernels' order (entry k = blob perm[k]); out in blob order
-__global__ void pair_reduce_kernel(int N, int slices, const double *__restrict__ partial,
-                                   double scale, double *__restrict__ out,
-                                   const double *__restrict__ U, const int *__restrict__ bob,
-                                   const double *__restrict__ dvec, const int *__restrict__ perm) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N) return;
-    const int i = perm ? perm[k] : k;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (int s = 0; s < slices; ++s) {
-        const size_t base = (size_t)s * 3 * N + k;
-        s0 += partial[base];
-        s1 += partial[base + N];
-        s2 += partial[base + 2 * (size_t)N];
-    }
-    s0 *= scale;
-    s1 *= scale;
-    s2 *= scale;
+// out_i = scale * s - (K U)_i for one blob (the K term only if U)
+__device__ __forceinline__ void reduce_store(int i, double scale, const double *s,
+                                             double *__restrict__ out,
+                                             const double *__restrict__ U,
+                                             const int *__restrict__ bob,
+                                             const double *__restrict__ dvec) {
+    double s0 = s[0] * scale, s1 = s[1] * scale, s2 = s[2] * scale;
     if (U) {
         // subtract (K U)_i = u_p + w_p x d_i  (Eq. no-slip)
         const double *Up = U + 6 * (size_t)bob[i];
@@ -226,6 +217,44 @@ __global__ void pair_reduce_kernel(int N, int slices, const double *__restrict__
     out[3 * i] = s0;
     out[3 * i + 1] = s1;
     out[3 * i + 2] = s2;
+}
+
+// partial in the pair kernels' order (entry k = blob perm[k]); out in blob order
+__global__ void pair_reduce_kernel(int N, int slices, const double *__restrict__ partial,
+                                   double scale, double *__restrict__ out,
+                                   const double *__restrict__ U, const int *__restrict__ bob,
+                                   const double *__restrict__ dvec, const int *__restrict__ perm) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= N) return;
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int sl = 0; sl < slices; ++sl)
+        for (int c = 0; c < 3; ++c) s[c] += partial[((size_t)sl * 3 + c) * N + k];
+    reduce_store(perm ? perm[k] : k, scale, s, out, U, bob, dvec);
+}
+
+// many slices: 64 blobs per workgroup, its 8 wavefronts taking the slices in turn; their
+// sums meet in LDS in wavefront order
+constexpr int kReduceWaves = 8;
+__global__ __launch_bounds__(64 * kReduceWaves) void pair_reduce_wide_kernel(
+    int N, int slices, const double *__restrict__ partial, double scale, double *__restrict__ out,
+    const double *__restrict__ U, const int *__restrict__ bob, const double *__restrict__ dvec,
+    const int *__restrict__ perm) {
+    __shared__ double red[kReduceWaves][3][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int k = blockIdx.x * 64 + lane;
+    double s[3] = {0.0, 0.0, 0.0};
+    if (k < N) {
+#pragma unroll 4
+        for (int sl = w; sl < slices; sl += kReduceWaves)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) s[c] += partial[((size_t)sl * 3 + c) * N + k];
+    }
+    for (int c = 0; c < 3; ++c) red[w][c][lane] = s[c];
+    __syncthreads();
+    if (w > 0 || k >= N) return;
+    for (int q = 1; q < kReduceWaves; ++q)
+        for (int c = 0; c < 3; ++c) s[c] += red[q][c][lane];
+    reduce_store(perm ? perm[k] : k, scale, s, out, U, bob, dvec);
 }
 
 __global__ void wall_check_kernel(int N, const double4 *__restrict__ p64, double a,
@@ -250,109 +279,121 @@ int heuristic_slices(int N) {
     return s;
 }
 
-// Small systems (N <= kSmallPairN, e.g. a 20-rod filament of 80 blobs): one
-// 64-lane workgroup per (64 targets, run of kSmallRun sources), sources read
-// straight from memory, so that a product of a few thousand pairs spreads over
-// N/64 x N/16 wavefronts instead of one workgroup; partial[run][c][i], reduced in
-// run order by pair_reduce (deterministic).
-template <bool WALL>
-__global__ __launch_bounds__(64) void pair_small_f64_kernel(int N, const double4 *__restrict__ p64,
-                                                            const double *__restrict__ lam,
-                                                            const int *__restrict__ perm, CoefD c,
-                                                            double *__restrict__ partial) {
-    const int i = blockIdx.x * 64 + threadIdx.x;
-    const int ic = i < N ? i : N - 1;
-    const double4 ti = p64[ic];
-    const TargetZ<double> zsc = target_z(ti.z);
-    double ux = 0.0, uy = 0.0, uz = 0.0;
-    const int j0 = blockIdx.y * kSmallRun, j1 = min(j0 + kSmallRun, N);
-    for (int j = j0; j < j1; ++j) {
-        const double4 sj = p64[j];
-        const size_t b = 3 * (size_t)(perm ? perm[j] : j);
-        const double lx = lam[b], ly = lam[b + 1], lz = lam[b + 2];
-        const double dx = ti.x - sj.x, dy = ti.y - sj.y, dz = ti.z - sj.z;
-        const double dxy2 = fma(dx, dx, dy * dy);
-        const double r2 = fma(dz, dz, dxy2);
-        const double rinv = rsq_f64(r2);
-        if (WALL) {
-            const double Rz = ti.z + sj.z;
-            const double Ri = rsq_f64(fma(Rz, Rz, dxy2));
-            const PairCoef<double> w =
-                wall_pair_coef<double>(r2, rinv, dxy2, zsc, sj.z, sj.w, -(sj.w * sj.w), Rz, Ri, c);
-            wall_pair_apply<double>(w, w.c, w.d, dx, dy, dz, Rz, lx, ly, lz, ux, uy, uz);
+// Small systems (N <= kSmallPairN): the whole product in one launch.  A wavefront
+// takes one target, its lanes the sources in turn (at most 16 each), and adds them by
+// lane exchanges; the last step of pair_reduce (scale, K U) follows in its first lane.
+// Deterministic.  Latency-bound: with a launch each for the positions (RAW: loose
+// blobs, prepared here per pair), the pair sums in runs of 16 sources and their
+// reduction, 300 blobs took 15.8 us a product, against 4.8 us.
+template <bool WALL, bool F32, bool RAW>
+__global__ __launch_bounds__(256) void pair_small_kernel(
+    int N, const double *__restrict__ pos, double inv_a, const double4 *__restrict__ p64,
+    const float4 *__restrict__ hi, const float4 *__restrict__ lo, const double *__restrict__ lam,
+    const int *__restrict__ perm, CoefD c, double scale, double *__restrict__ out,
+    const double *__restrict__ U, const int *__restrict__ bob, const double *__restrict__ dvec) {
+    const int lane = threadIdx.x & 63;
+    const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (k >= N) return;  // the whole wavefront
+    // entry j as prep_positions makes it
+    auto load32 = [&](int j, float4 &h, float4 &l) {
+        if (RAW) {
+            const double x = pos[3 * j] * inv_a, y = pos[3 * j + 1] * inv_a,
+                         z = pos[3 * j + 2] * inv_a;
+            h.x = (float)x;
+            h.y = (float)y;
+            h.z = (float)z;
+            h.w = 2.f * h.z;
+            l = make_float4((float)(x - (double)h.x), (float)(y - (double)h.y),
+                            (float)(z - (double)h.z), -(h.w * h.w));
         } else {
-            rpy_free<double>(dx, dy, dz, r2, rinv, lx, ly, lz, c, ux, uy, uz);
+            h = hi[j];
+            l = lo[j];
         }
-    }
-    if (i < N) {
-        const size_t base = (size_t)blockIdx.y * 3 * N + i;
-        partial[base] = ux;
-        partial[base + N] = uy;
-        partial[base + 2 * (size_t)N] = uz;
-    }
-}
-
-template <bool WALL>
-__global__ __launch_bounds__(64) void pair_small_f32c_kernel(int N, const float4 *__restrict__ hi,
-                                                             const float4 *__restrict__ lo,
-                                                             const double *__restrict__ lam,
-                                                             const int *__restrict__ perm,
-                                                             double *__restrict__ partial) {
-    constexpr CoefF c = kUnitCoefF;
-    const int i = blockIdx.x * 64 + threadIdx.x;
-    const int ic = i < N ? i : N - 1;
-    const float4 th = hi[ic], tl = lo[ic];
-    const float zi = th.z + tl.z;
-    const TargetZ<float> zsc = target_z(zi);
-    float ax = 0.f, ay = 0.f, az = 0.f;  // one float run of at most kSmallRun sources
-    const int j0 = blockIdx.y * kSmallRun, j1 = min(j0 + kSmallRun, N);
-    for (int j = j0; j < j1; ++j) {
-        const float4 sh = hi[j], sl = lo[j];
-        const size_t b = 3 * (size_t)(perm ? perm[j] : j);
-        const float Lx = (float)lam[b], Ly = (float)lam[b + 1], Lz = (float)lam[b + 2];
-        const float dx = (th.x - sh.x) + (tl.x - sl.x);
-        const float dy = (th.y - sh.y) + (tl.y - sl.y);
-        const float dz = (th.z - sh.z) + (tl.z - sl.z);
-        const float dxy2 = fmaf(dx, dx, dy * dy);
-        const float r2 = fmaf(dz, dz, dxy2);
-        const float rinv = rsq_f32(r2);
-        if (WALL) {
-            const float Rz = zi + sh.z;
-            const float Ri = rsq_f32(fmaf(Rz, Rz, dxy2));
-            const PairCoef<float> w =
-                wall_pair_coef<float>(r2, rinv, dxy2, zsc, sh.z, sh.w, sl.w, Rz, Ri, c);
-            wall_pair_apply<float>(w, w.c, w.d, dx, dy, dz, Rz, Lx, Ly, Lz, ax, ay, az);
-        } else {
-            rpy_free<float>(dx, dy, dz, r2, rinv, Lx, Ly, Lz, c, ax, ay, az);
+    };
+    double u[3] = {0.0, 0.0, 0.0};
+    if constexpr (F32) {
+        constexpr CoefF cf = kUnitCoefF;
+        float4 th, tl;
+        load32(k, th, tl);
+        const float zi = th.z + tl.z;
+        const TargetZ<float> zsc = target_z(zi);
+        float ax = 0.f, ay = 0.f, az = 0.f;  // at most kSmallPairN / 64 = 16 sources
+        for (int j = lane; j < N; j += 64) {
+            float4 sh, sl;
+            load32(j, sh, sl);
+            const size_t b = 3 * (size_t)(perm ? perm[j] : j);
+            const float Lx = (float)lam[b], Ly = (float)lam[b + 1], Lz = (float)lam[b + 2];
+            const float dx = (th.x - sh.x) + (tl.x - sl.x);
+            const float dy = (th.y - sh.y) + (tl.y - sl.y);
+            const float dz = (th.z - sh.z) + (tl.z - sl.z);
+            const float dxy2 = fmaf(dx, dx, dy * dy);
+            const float r2 = fmaf(dz, dz, dxy2);
+            const float rinv = rsq_f32(r2);
+            if (WALL) {
+                const float Rz = zi + sh.z;
+                const float Ri = rsq_f32(fmaf(Rz, Rz, dxy2));
+                const PairCoef<float> w =
+                    wall_pair_coef<float>(r2, rinv, dxy2, zsc, sh.z, sh.w, sl.w, Rz, Ri, cf);
+                wall_pair_apply<float>(w, w.c, w.d, dx, dy, dz, Rz, Lx, Ly, Lz, ax, ay, az);
+            } else {
+                rpy_free<float>(dx, dy, dz, r2, rinv, Lx, Ly, Lz, cf, ax, ay, az);
+            }
         }
-    }
-    if (i < N) {
-        const size_t base = (size_t)blockIdx.y * 3 * N + i;
-        partial[base] = (double)ax;
-        partial[base + N] = (double)ay;
-        partial[base + 2 * (size_t)N] = (double)az;
-    }
-}
-
-int pair_partial_small(hipStream_t s, int precision, bool wall, int N, const double4 *p64,
-                       const float4 *hi, const float4 *lo, const double *lam, const int *perm,
-                       double a, double *partial) {
-    if (N <= 0) return 0;
-    const int runs = (N + kSmallRun - 1) / kSmallRun;
-    dim3 grid((N + 63) / 64, runs);
-    if (precision == ARB_FP32C) {
-        if (wall)
-            pair_small_f32c_kernel<true><<<grid, 64, 0, s>>>(N, hi, lo, lam, perm, partial);
-        else
-            pair_small_f32c_kernel<false><<<grid, 64, 0, s>>>(N, hi, lo, lam, perm, partial);
+        u[0] = (double)ax;
+        u[1] = (double)ay;
+        u[2] = (double)az;
     } else {
-        const CoefD c = make_coef<CoefD, double>(a);
-        if (wall)
-            pair_small_f64_kernel<true><<<grid, 64, 0, s>>>(N, p64, lam, perm, c, partial);
-        else
-            pair_small_f64_kernel<false><<<grid, 64, 0, s>>>(N, p64, lam, perm, c, partial);
+        auto load64 = [&](int j) {
+            if (!RAW) return p64[j];
+            const double z = pos[3 * j + 2];
+            return make_double4(pos[3 * j], pos[3 * j + 1], z, 2.0 * z);
+        };
+        const double4 ti = load64(k);
+        const TargetZ<double> zsc = target_z(ti.z);
+        for (int j = lane; j < N; j += 64) {
+            const double4 sj = load64(j);
+            const size_t b = 3 * (size_t)(perm ? perm[j] : j);
+            const double lx = lam[b], ly = lam[b + 1], lz = lam[b + 2];
+            const double dx = ti.x - sj.x, dy = ti.y - sj.y, dz = ti.z - sj.z;
+            const double dxy2 = fma(dx, dx, dy * dy);
+            const double r2 = fma(dz, dz, dxy2);
+            const double rinv = rsq_f64(r2);
+            if (WALL) {
+                const double Rz = ti.z + sj.z;
+                const double Ri = rsq_f64(fma(Rz, Rz, dxy2));
+                const PairCoef<double> w = wall_pair_coef<double>(
+                    r2, rinv, dxy2, zsc, sj.z, sj.w, -(sj.w * sj.w), Rz, Ri, c);
+                wall_pair_apply<double>(w, w.c, w.d, dx, dy, dz, Rz, lx, ly, lz, u[0], u[1], u[2]);
+            } else {
+                rpy_free<double>(dx, dy, dz, r2, rinv, lx, ly, lz, c, u[0], u[1], u[2]);
+            }
+        }
     }
-    return runs;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) u[q] += __shfl_xor(u[q], off);
+    if (lane == 0) reduce_store(perm ? perm[k] : k, scale, u, out, U, bob, dvec);
+}
+
+void pair_small(hipStream_t s, int precision, bool wall, int N, const double *raw_pos,
+                const double4 *p64, const float4 *hi, const float4 *lo, const double *lam,
+                const int *perm, double a, double scale, double *out, const double *U,
+                const int *body_of_blob, const double *dvec) {
+    if (N <= 0) return;
+    const CoefD c = make_coef<CoefD, double>(a);
+    auto go = [&](auto w, auto f, auto r) {
+        pair_small_kernel<decltype(w)::value, decltype(f)::value, decltype(r)::value>
+            <<<nblk(N, 4), 256, 0, s>>>(N, raw_pos, 1.0 / a, p64, hi, lo, lam, perm, c, scale, out,
+                                        U, body_of_blob, dvec);
+    };
+    auto go2 = [&](auto w, auto f) {
+        raw_pos ? go(w, f, std::true_type{}) : go(w, f, std::false_type{});
+    };
+    auto go1 = [&](auto w) {
+        precision == ARB_FP32C ? go2(w, std::true_type{}) : go2(w, std::false_type{});
+    };
+    wall ? go1(std::true_type{}) : go1(std::false_type{});
 }
 
 int pair_partial(hipStream_t s, int precision, bool wall, int N, const double4 *p64,
@@ -382,8 +423,13 @@ void pair_reduce(hipStream_t s, int N, int slices, const double *partial, double
                  double *out, const double *U, const int *body_of_blob, const double *dvec,
                  const int *perm) {
     if (N <= 0) return;
-    pair_reduce_kernel<<<nblk(N, 256), 256, 0, s>>>(N, slices, partial, scale, out, U,
-                                                      body_of_blob, dvec, perm);
+    // from 8 slices on one thread per blob is a chain of loads over too few wavefronts
+    if (slices >= kReduceWaves)
+        pair_reduce_wide_kernel<<<nblk(N, 64), 64 * kReduceWaves, 0, s>>>(
+            N, slices, partial, scale, out, U, body_of_blob, dvec, perm);
+    else
+        pair_reduce_kernel<<<nblk(N, 256), 256, 0, s>>>(N, slices, partial, scale, out, U,
+                                                          body_of_blob, dvec, perm);
 }
 
 int pair_wall_violation(hipStream_t s, int N, const double4 *p64, double a, int *flag_dev,

@@ -247,3 +247,30 @@ def test_coincident_blobs_and_empty_input(kind, prec):
     uo = rpy.mobility_apply(pos, cl["lam"], 1.0, 1.0, True)
     assert np.all(np.isfinite(u))
     assert rel(u, uo) <= TOL[prec]
+
+
+# products without atomics or slices of the caller's choice: one launch up to 1,024 blobs
+# (one wavefront per target: 64 lanes, part of them, several turns), the ring of 64-blob
+# tiles from 1,025 to 8,191 (odd and even numbers of tiles, where the opposite tile counts
+# once; 4, 2 and 1 wavefronts per tile; a last tile of 1 blob and a full one)
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 1024, 1025, 1088, 2048, 2049, 4096, 4161, 5824, 8191])
+@pytest.mark.parametrize("wall", [False, True])
+@pytest.mark.parametrize("prec", [arb.ARB_FP64, arb.ARB_FP32C])
+def test_small_and_mid_sizes(n, wall, prec):
+    a, eta = 0.8, 1.3
+    cl = W.random_blobs(n, seed=300 + n, box=8.0 + n ** 0.5, zlo=1.0, zhi=9.0)
+    rng = np.random.default_rng(n)
+    tg = np.unique(np.concatenate([[0, n - 1, n // 2, min(63, n - 1)], rng.integers(0, n, 40)]))
+    uo = rpy.mobility_apply(cl["pos"], cl["lam"], a, eta, wall, targets=tg)
+    loose = arb.arb_create(precision=prec, wall=wall, a=a, eta=eta)
+    state = arb.context_for(W.loose_blobs(cl["pos"], a=a, eta=eta, wall=wall), precision=prec)
+    try:
+        print(f"pair n={n} wall={wall} prec={prec}", flush=True)
+        for f in (lambda: arb.arb_rpy_apply(loose, cl["pos"], cl["lam"]),
+                  lambda: arb.arb_mobility_apply(state, cl["lam"])):
+            u = f()
+            assert np.array_equal(u, f())
+            assert rel(u.reshape(n, 3)[tg], uo) <= TOL[prec]
+    finally:
+        arb.arb_destroy(loose)
+        arb.arb_destroy(state)
