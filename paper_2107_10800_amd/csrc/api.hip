@@ -966,7 +966,7 @@ double now_ms() {
 // ---------------------------------------------------------------- GMRES (Sec. 3.1)
 struct Krylov {
     int64_t n;
-    int m, nch;
+    int m;
     double *b, *r, *z, *w, *V, *H, *cs, *sn, *g, *sv, *part, *h1, *h2, *sc;
     double *steps;  // gmres_small_cycle's per-step figures (2 m + 1)
 };
@@ -976,7 +976,6 @@ int krylov_buffers(arb_ctx *ctx, Krylov &K) {
     const int m = ctx->opt.restart;
     K.n = n;
     K.m = m;
-    K.nch = (int)((n + 2047) / 2048);
     HIPCHK(ctx->kb.ensure(n * sizeof(double)));
     HIPCHK(ctx->kr.ensure(n * sizeof(double)));
     HIPCHK(ctx->kz.ensure(n * sizeof(double)));
@@ -989,7 +988,7 @@ int krylov_buffers(arb_ctx *ctx, Krylov &K) {
     HIPCHK(ctx->kg.ensure((size_t)(m + 2) * sizeof(double)));
     HIPCHK(ctx->khcol.ensure((size_t)(2 * (m + 2) + 16) * sizeof(double)));
     HIPCHK(ctx->ksv.ensure((size_t)(m + 1) * sizeof(double)));
-    HIPCHK(ctx->kpart.ensure((size_t)(m + 1) * K.nch * sizeof(double)));
+    HIPCHK(ctx->kpart.ensure(2 * (size_t)(m + 1) * arb::cgs_blocks(n) * sizeof(double)));
     HIPCHK(ctx->ksteps.ensure((size_t)(2 * m + 2) * sizeof(double)));
     K.b = ctx->kb.as<double>();
     K.r = ctx->kr.as<double>();
@@ -1070,8 +1069,7 @@ arb::SmallSystem small_system(arb_ctx *ctx) {
 }
 
 int dev_norm(arb_ctx *ctx, hipStream_t s, Krylov &K, const double *x, int slot, double *out) {
-    arb::multidot(s, K.n, 1, x, K.n, x, K.part, K.sc + slot);
-    HIPCHK(hipMemcpyAsync(ctx->pinned, K.sc + slot, sizeof(double), hipMemcpyDeviceToHost, s));
+    arb::vector_norm(s, K.n, x, K.part, 0, nullptr, K.sc + slot, ctx->pinned);
     HIPCHK(hipStreamSynchronize(s));
     *out = std::sqrt(ctx->pinned[0]);
     return 0;
@@ -1163,10 +1161,9 @@ int gmres_core(arb_ctx *ctx, hipStream_t s, Krylov &K, const double *rhs, double
     auto push = [&](double v) {
         if (inf->history_len < 1024) inf->history[inf->history_len++] = v;
     };
-    auto read_norm = [&](const double *x, int slot, double *out) -> int {
-        arb::multidot(s, n, 1, x, n, x, K.part, K.sc + slot);
-        arb::g_init(s, m, K.sc + slot, K.g, K.sc + 3);  // g = [norm, 0, ...], sc[3] = norm
-        HIPCHK(hipMemcpyAsync(pin, K.sc + 3, sizeof(double), hipMemcpyDeviceToHost, s));
+    // g = [norm, 0, ...], sc[3] = norm
+    auto read_norm = [&](const double *x, double *out) -> int {
+        arb::vector_norm(s, n, x, K.part, m, K.g, K.sc + 2, pin);
         HIPCHK(hipStreamSynchronize(s));
         *out = pin[0];
         return 0;
@@ -1174,14 +1171,13 @@ int gmres_core(arb_ctx *ctx, hipStream_t s, Krylov &K, const double *rhs, double
     // work counts (a replayed graph runs the same product and apply as step())
     auto count_product = [&]() { ++(prec == ARB_FP64 ? inf->products_fp64 : inf->products_fp32); };
     const bool graphs = ctx->opt.graphs == 0 && !ctx->prof;
-    const bool small = n <= arb::kSmallArnoldi;
     // a whole cycle in one launch of one workgroup (stopping test on the device)
     const bool one_launch = !left && small_cycle_ok(ctx, prec, n);
     arb::SmallSystem SS;
     if (one_launch) SS = small_system(ctx);
     for (;;) {
         double beta = 0.0;
-        TRY(read_norm(K.r, 2, &beta));
+        TRY(read_norm(K.r, &beta));
         if (!std::isfinite(beta)) return fail(ctx, ARB_E_NAN, "GMRES residual is not finite");
         *res = beta;
         push(beta * hist_scale);
@@ -1193,7 +1189,7 @@ int gmres_core(arb_ctx *ctx, hipStream_t s, Krylov &K, const double *rhs, double
             TRY(precond_apply(ctx, s, K.r, K.z));
             ++inf->precond_applies;
             double bz = 0.0;
-            TRY(read_norm(K.z, 2, &bz));
+            TRY(read_norm(K.z, &bz));
             if (!std::isfinite(bz) || bz == 0.0)
                 return fail(ctx, ARB_E_NAN, "preconditioned residual is not finite or zero");
             target = tol_abs / beta * bz;
@@ -1213,19 +1209,10 @@ int gmres_core(arb_ctx *ctx, hipStream_t s, Krylov &K, const double *rhs, double
                 TRY(precond_apply(ctx, s, vj, K.z));
                 TRY(system_apply(ctx, s, K.z, K.w, prec));
             }
-            if (small) {
-                arb::arnoldi_small(s, n, j, m, K.V, n, K.w, K.H, K.cs, K.sn, K.g, K.sc + 5);
-            } else {
-                // classical Gram-Schmidt, twice
-                arb::multidot(s, n, j + 1, K.V, n, K.w, K.part, K.h1);
-                arb::gemv_sub(s, n, j + 1, K.V, n, K.h1, K.w);
-                arb::multidot(s, n, j + 1, K.V, n, K.w, K.part, K.h2);
-                arb::gemv_sub(s, n, j + 1, K.V, n, K.h2, K.w);
-                arb::multidot(s, n, 1, K.w, n, K.w, K.part, K.sc + 4);
-                arb::arnoldi_post(s, j, m, K.h1, K.h2, K.sc + 4, K.H, K.cs, K.sn, K.g, K.sc + 5);
-            }
-            HIPCHK(hipMemcpyAsync(pin_step + 2 * j, K.sc + 5, 2 * sizeof(double),
-                                  hipMemcpyDeviceToHost, s));
+            // classical Gram-Schmidt twice and the Givens update; h_{j+1,j} and the
+            // estimate go to the step's pinned slot
+            arb::arnoldi_step(s, n, j, m, K.V, K.w, K.part, K.h1, K.h2, K.H, K.cs, K.sn,
+                              K.g, K.sc + 5, pin_step + 2 * j);
             return 0;
         };
         auto launch = [&](int j) -> int {

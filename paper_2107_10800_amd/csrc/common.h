@@ -363,26 +363,27 @@ void learned_correction(hipStream_t s, int M, const int *type, const double *tNt
                         const double *R9, const double *Nw, double *out, int *bad);
 
 // Dense helpers for the Krylov solver (FP64, Sec. 3.1)
-void multidot(hipStream_t s, int64_t n, int k, const double *V, int64_t ldv, const double *w,
-              double *partial, double *h);
-void gemv_sub(hipStream_t s, int64_t n, int k, const double *V, int64_t ldv, const double *h,
-              double *w);
+// workgroups of a launch over n unknowns (entries of a row of partial sums)
+int cgs_blocks(int64_t n);
+// out[0] = ||x||^2; with g: g = [||x||, 0, ...] (m + 1 entries) and out[1] = ||x||; host[0]
+// (pinned memory) = ||x||^2, or ||x|| with g
+void vector_norm(hipStream_t s, int64_t n, const double *x, double *partial, int m, double *g,
+                 double *out, double *host);
 void gemv_set(hipStream_t s, int64_t n, int k, const double *V, int64_t ldv, const double *h,
               double *out);
 void scale_copy(hipStream_t s, int64_t n, const double *x, const double *alpha_dev, double *y);
 void axpby(hipStream_t s, int64_t n, double a, const double *x, double b, double *y);
-// largest system (unknowns) whose Arnoldi orthogonalisation runs in one
-// workgroup (arnoldi_small), and the largest restart length
+// largest system (unknowns) whose Arnoldi orthogonalisation runs in one workgroup and
+// launch, and the largest restart length
 constexpr int kSmallArnoldi = 4096;
 constexpr int kMaxRestart = 256;
-// CGS2 + norm + Givens update of Arnoldi step j for n <= kSmallArnoldi in one
-// launch: w is orthogonalised in place; out[0] = ||w||, out[1] = |g[j+1]|
-void arnoldi_small(hipStream_t s, int64_t n, int j, int m, const double *V, int64_t ldv,
-                   double *w, double *Hbar, double *cs, double *sn, double *g, double *out);
-void arnoldi_post(hipStream_t s, int j, int m, const double *h1, const double *h2,
-                  const double *hn2, double *Hbar, double *cs, double *sn, double *g,
-                  double *out);
-void g_init(hipStream_t s, int m, const double *beta2, double *g, double *beta);
+// Arnoldi step j: w orthogonalised in place against V_0..V_j (leading dimension n) by
+// classical Gram-Schmidt twice (coefficients h1, h2), the Givens update of Hbar, cs, sn
+// and g; out[0] = ||w||, out[1] = |g[j+1]|, both also to host (pinned memory); partial:
+// 2 (m + 1) cgs_blocks(n) doubles
+void arnoldi_step(hipStream_t s, int64_t n, int j, int m, const double *V, double *w,
+                  double *partial, double *h1, double *h2, double *Hbar, double *cs, double *sn,
+                  double *g, double *out, double *host);
 void upper_solve(hipStream_t s, int k, int m, const double *Hbar, const double *g, double *sv);
 void rhs_assemble(hipStream_t s, int N, int M, int Nc, const double *us, const double *F,
                   const double *B, double *b);

@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) void pair_small_kernel(
         }
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
+    for (int off = 1; off < 64; off <<= 1)
 #pragma unroll
         for (int q = 0; q < 3; ++q) u[q] += __shfl_xor(u[q], off);
     if (lane == 0) reduce_store(perm ? perm[k] : k, scale, u, out, U, bob, dvec);
