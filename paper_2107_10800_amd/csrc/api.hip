@@ -725,6 +725,7 @@ arb::PrecondDev pc_view(arb_ctx *ctx) {
     P.status = ctx->status.as<int>();
     P.tmp = ctx->pctmp.as<double>();
     P.learned = ctx->pc_learned ? 1 : 0;
+    if (!ctx->pc_learned) P.fuse = ctx->pc_fuse;
     P.type = ctx->body_type_d.as<int>();
     P.tmat_off = ctx->t_mat_off.as<int64_t>();
     P.tz_off = ctx->t_z_off.as<int64_t>();
@@ -937,12 +938,22 @@ int precond_build_exact(arb_ctx *ctx, hipStream_t s) {
     if (st[0])
         return fail(ctx, ARB_E_NOT_SPD,
                     "blob mobility of body " + std::to_string(st[0] - 1) + " is not positive definite");
+    ctx->pc_fuse = arb::precond_fuse(ctx->n_asm, ctx->h_asm_body_ptr.data(),
+                                     ctx->h_asm_bodies.data(), ctx->h_asm_row_ptr.data(),
+                                     ctx->h_blob_off.data());
     ctx->pc_built = true;
     ctx->pc_pinv = st[1] + st[3];
     return ctx->pc_pinv ? ARB_W_PINV_USED : ARB_OK;
 }
 
-int precond_apply(arb_ctx *ctx, hipStream_t s, const double *r, double *z) {
+// whether precond_apply can scale its input on the way (r / alpha, stored to v)
+bool precond_scales(const arb_ctx *ctx) {
+    return ctx->opt.precond == ARB_PC_BLOCK && ctx->opt.model == ARB_MODEL_MULTIBLOB &&
+           ctx->pc_fuse.rows && !ctx->pc_learned;
+}
+
+int precond_apply(arb_ctx *ctx, hipStream_t s, const double *r, double *z,
+                  const double *alpha = nullptr, double *v = nullptr) {
     const int64_t n = n_unknowns(ctx);
     if (ctx->opt.precond == ARB_PC_NONE) {
         HIPCHK(hipMemcpyAsync(z, r, n * sizeof(double), hipMemcpyDeviceToDevice, s));
@@ -953,7 +964,7 @@ int precond_apply(arb_ctx *ctx, hipStream_t s, const double *r, double *z) {
         arb::precond_apply_single(s, P, ctx->zero_off.as<int>(), ctx->zero_off64.as<int64_t>(), r,
                                   z);
     else
-        arb::precond_apply(s, P, ctx->N, r, z);
+        arb::precond_apply(s, P, ctx->N, r, z, alpha, v);
     return 0;
 }
 
@@ -1085,7 +1096,7 @@ std::vector<long long> graph_key(arb_ctx *ctx, const Krylov &K, int prec) {
     auto it = ctx->slice_cache.find(skey);
     return {(long long)arb::alloc_generation().load(), (long long)K.n, K.m, prec,
             ctx->opt.precond, ctx->opt.left_precond, ctx->psorted ? 1 : 0, ctx->pc_learned ? 1 : 0,
-            ctx->pc_lcorr ? 1 : 0, ctx->N, ctx->M,
+            ctx->pc_lcorr ? 1 : 0, ctx->pc_fuse.rows, ctx->N, ctx->M,
             ctx->Nc, ctx->n_asm, it == ctx->slice_cache.end() ? 0 : it->second,
             (long long)(intptr_t)K.V, (long long)(intptr_t)ctx->pinned, ctx->fmm.version};
 }
@@ -1201,8 +1212,13 @@ int gmres_core(arb_ctx *ctx, hipStream_t s, Krylov &K, const double *rhs, double
         // pair launch), the others replay a graph captured once per j
         auto step = [&](int j) -> int {
             double *vj = K.V + (size_t)j * n;
-            if (j > 0) arb::scale_copy(s, n, K.w, K.sc + 5, vj);  // v_j = w / h_{j,j-1}
-            if (left) {
+            const bool scale_on_the_way = j > 0 && !left && precond_scales(ctx);
+            if (j > 0 && !scale_on_the_way)
+                arb::scale_copy(s, n, K.w, K.sc + 5, vj);  // v_j = w / h_{j,j-1}
+            if (scale_on_the_way) {
+                TRY(precond_apply(ctx, s, K.w, K.z, K.sc + 5, vj));
+                TRY(system_apply(ctx, s, K.z, K.w, prec));
+            } else if (left) {
                 TRY(system_apply(ctx, s, vj, K.z, prec));
                 TRY(precond_apply(ctx, s, K.z, K.w));
             } else {

@@ -219,6 +219,11 @@ void C_apply(hipStream_t s, int Nc, const int *row_p, const int *row_q, const do
 void euler_update(hipStream_t s, int M, const double *U, double dt, double *q, double *theta);
 
 // Block-diagonal preconditioner (Sec. 3.1)
+// largest assembly, when all are small enough for the one-launch apply (rows 0: not)
+struct PcFuse {
+    int rows = 0, bodies = 0, cons = 0;  // blob rows, bodies, constraint rows
+};
+
 struct PrecondDev {
     int M = 0, A = 0;
     const int *blob_off = nullptr;     // M+1
@@ -245,6 +250,7 @@ struct PrecondDev {
     int *status = nullptr;    // [0] not-SPD body+1, [1] G~ pinv count, [2] below wall,
                               // [3] N~ with dropped eigenvalues
     double *tmp = nullptr;    // apply scratch: U-hat (6M)
+    PcFuse fuse;              // exact blocks of small assemblies: apply in one launch
     // learned variant: per-type body-frame blocks rotated by R_p
     int learned = 0;
     const int *type = nullptr;
@@ -356,7 +362,11 @@ hipError_t precond_factor(hipStream_t s, const PrecondDev &P, const double *dvec
 bool precond_factor_in_place(int max_m);
 int64_t precond_dinv_size(int64_t n_blobs, int M);
 hipError_t precond_assembly(hipStream_t s, const PrecondDev &P);
-void precond_apply(hipStream_t s, const PrecondDev &P, int N, const double *r, double *z);
+// z = P^-1 r; alpha, v (P.fuse.rows only): z = P^-1 (r / alpha), v = r / alpha
+void precond_apply(hipStream_t s, const PrecondDev &P, int N, const double *r, double *z,
+                   const double *alpha = nullptr, double *v = nullptr);
+PcFuse precond_fuse(int A, const int *body_ptr, const int *bodies, const int *row_ptr,
+                    const int *blob_off);  // host arrays
 void rotate_body_mobility(hipStream_t s, int M, const int *type, const double *tNt,
                           const double *R9, double *Nt);
 void learned_correction(hipStream_t s, int M, const int *type, const double *tNt,
@@ -518,6 +528,7 @@ struct arb_ctx {
     bool pc_learned = false;
     bool pc_lcorr = false;  // learned body mobility with the consistent blob-block correction
     int pc_pinv = 0;
+    arb::PcFuse pc_fuse;  // of the exact blocks
 
     // device buffers
     arb::DevBuf blob_off, body_of_blob, r_ref, q, theta, R9, pos, dvec, p64, hi, lo,

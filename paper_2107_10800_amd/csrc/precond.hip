@@ -1150,42 +1150,241 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
     return s;
 }
 
-__global__ __launch_bounds__(256) void pc_apply1_kernel(
+// Row i of M_pp^-1 x, the part k = [k0, k1) of its sum.  The apply kernels give a row
+// several threads, each a part, so that a workgroup keeps enough loads in flight: with
+// one thread per row it waited on its m loads (51 us for the 2,000-odd plates of 64
+// diatom colonies, 43 us with parts).
+__device__ __forceinline__ double row_part(const double *__restrict__ Mi, int m, int i, int k0,
+                                           int k1, const double *x) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = k0; k < k1; ++k) s += Mi[(size_t)k * m + i] * x[k];
+    return s;
+}
+
+constexpr int kApply = 1024;  // threads of the apply kernels
+
+__global__ __launch_bounds__(kApply) void pc_apply1_kernel(
     int N, const int *__restrict__ blob_off, const int64_t *__restrict__ mat_off,
     const int64_t *__restrict__ z_off, const double *__restrict__ minv,
     const double *__restrict__ Zbuf, const double *__restrict__ Nt, const double *__restrict__ r,
     double *__restrict__ z, double *__restrict__ uhat) {
     __shared__ double x[kMaxM];
-    __shared__ double red[8];
+    __shared__ double part[kApply];
     __shared__ double w6[6];
-    const int p = blockIdx.x;
+    const int p = blockIdx.x, tid = threadIdx.x;
     const int b0 = blob_off[p], m = 3 * (blob_off[p + 1] - b0);
     const double *Mi = minv + mat_off[p];
     const double *Z = Zbuf + z_off[p];
     const double *rl = r + 3 * (size_t)b0;
-    for (int i = threadIdx.x; i < m; i += blockDim.x) x[i] = rl[i];
+    for (int i = tid; i < m; i += kApply) x[i] = rl[i];
     __syncthreads();
     // t = Minv r_lam (Minv symmetric: column access is coalesced)
-    for (int i = threadIdx.x; i < m; i += blockDim.x) {
-        double s = 0.0;
-        for (int k = 0; k < m; ++k) s += Mi[(size_t)k * m + i] * x[k];
-        z[3 * (size_t)b0 + i] = s;
+    const int ks = kApply / m;  // parts per row (0: more rows than threads)
+    if (ks < 2) {
+        for (int i = tid; i < m; i += kApply)
+            z[3 * (size_t)b0 + i] = row_part(Mi, m, i, 0, m, x);
+    } else {
+        const int g = tid / m, i = tid - g * m;
+        if (g < ks) part[tid] = row_part(Mi, m, i, m * g / ks, m * (g + 1) / ks, x);
     }
-    // Z^T r_lam
-    double acc[6] = {0, 0, 0, 0, 0, 0};
-    for (int i = threadIdx.x; i < m; i += blockDim.x)
-        for (int c = 0; c < 6; ++c) acc[c] += Z[(size_t)i * 6 + c] * x[i];
-    for (int c = 0; c < 6; ++c) {
-        const double s = block_sum(acc[c], red);
-        if (threadIdx.x == 0) w6[c] = s + r[3 * (size_t)N + 6 * (size_t)p + c];
+    // Z^T r_lam + r_U, a wavefront per component
+    const int lane = tid % kWave, w = tid / kWave;
+    if (w < 6) {
+        double s = 0.0;
+        for (int i = lane; i < m; i += kWave) s += Z[(size_t)i * 6 + w] * x[i];
+        for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        if (lane == 0) w6[w] = s + r[3 * (size_t)N + 6 * (size_t)p + w];
     }
     __syncthreads();
-    if (threadIdx.x < 6) {
+    if (ks >= 2 && tid < m) {
+        double s = part[tid];
+        for (int g = 1; g < ks; ++g) s += part[g * m + tid];
+        z[3 * (size_t)b0 + tid] = s;
+    }
+    if (tid < 6) {
         const double *Nb = Nt + 36 * (size_t)p;
         double s = 0.0;
-        for (int c = 0; c < 6; ++c) s += Nb[threadIdx.x * 6 + c] * w6[c];
-        uhat[6 * (size_t)p + threadIdx.x] = -s;
+        for (int c = 0; c < 6; ++c) s += Nb[tid * 6 + c] * w6[c];
+        uhat[6 * (size_t)p + tid] = -s;
     }
+}
+
+// The whole apply of small assemblies in one launch, in place of the three kernels
+// around it, which stay for assemblies beyond the limits (precond_fuse: what LDS holds
+// and one thread per row covers).  An assembly is taken by gridDim.y workgroups: each
+// repeats the short chain Z^T r, U^, phi, U (a few kB of Z, N~, C, G~) and does its
+// share of the rows of M_pp^-1 r + Z U, whose blocks are the traffic (590 kB for a 42-
+// and an 80-blob body).  About 10 us of dependent loads and barriers up to 256
+// workgroups, then bound by the blocks' bandwidth.  With alpha, r / alpha is applied and
+// stored to v: GMRES scales its new basis vector here.  Against three kernels and the
+// scaling (launches without their gaps): 16 bacteria 27.0 -> 10.7 us, 100 37.9 -> 18.6
+// (59 MB, 3.2 TB/s), 1,024 150.7 -> 142.0 (600 MB, 4.2 TB/s), 1,000 free 42-blob shells
+// 38.5 -> 26.2.
+constexpr int kFuseBlocks = 256;  // workgroups an apply is split into (100 bacteria with
+                                  // 500: 26.7 us, with 1,000: 40.5: the chain is repeated)
+constexpr int kFuseRows = 1024, kFuseBodies = 32, kFuseCons = 64;
+
+__host__ __device__ inline size_t fuse_doubles(const PcFuse &f, int threads) {
+    return (size_t)f.rows + threads + 18 * f.bodies + (size_t)f.cons * (14 + f.cons);
+}
+
+__global__ __launch_bounds__(kApply) void pc_apply_asm_kernel(
+    int N, int M, PrecondDev P, const double *__restrict__ r, const double *__restrict__ alpha,
+    double *__restrict__ v, double *__restrict__ z) {
+    extern __shared__ double lds[];
+    __shared__ int s_p[kFuseBodies], s_row[kFuseBodies + 1], s_b[kFuseBodies];
+    __shared__ int s_rows[kFuseCons], s_side[kFuseCons][2];  // rows; their bodies, local
+    const int T = blockDim.x;
+    double *x = lds, *part = x + P.fuse.rows, *y = part + T, *ph = y + P.fuse.cons;
+    double(*ru)[6] = reinterpret_cast<double(*)[6]>(ph + P.fuse.cons);
+    double(*w6)[6] = ru + P.fuse.bodies, (*uh)[6] = w6 + P.fuse.bodies;
+    double(*cr)[12] = reinterpret_cast<double(*)[12]>(uh + P.fuse.bodies);
+    double *G = cr[P.fuse.cons];
+    const int a = blockIdx.x, tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+    const bool first = blockIdx.y == 0;  // writes z_U, z_phi and their part of v
+    const int bp = P.asm_body_ptr[a], nb = P.asm_body_ptr[a + 1] - bp;
+    const int r0 = P.asm_row_ptr[a], na = P.asm_row_ptr[a + 1] - r0;
+    const size_t off_u = 3 * (size_t)N, off_phi = off_u + 6 * (size_t)M;
+    const double al = alpha ? alpha[0] : 1.0;
+    auto load = [&](size_t i, bool mine) {
+        double t = r[i];
+        if (alpha) {
+            t /= al;
+            if (mine) v[i] = t;
+        }
+        return t;
+    };
+    if (w == 0) {  // the bodies' rows, numbered through
+        int m = 0;
+        if (lane < nb) {
+            const int p = P.asm_bodies[bp + lane];
+            s_p[lane] = p;
+            s_b[lane] = 3 * P.blob_off[p];
+            m = 3 * P.blob_off[p + 1] - s_b[lane];
+        }
+        for (int off = 1; off < kFuseBodies; off <<= 1) {
+            const int u = __shfl_up(m, off);
+            if (lane >= off) m += u;
+        }
+        if (lane < nb) s_row[lane + 1] = m;
+        if (lane == 0) s_row[0] = 0;
+    }
+    if (tid < na) s_rows[tid] = P.asm_rows[r0 + tid];
+    for (int e = tid; e < na * na; e += T) G[e] = P.G[P.asm_mat_off[a] + e];
+    __syncthreads();
+    const int mt = s_row[nb];
+    const int i0 = mt * blockIdx.y / gridDim.y, nr = mt * (blockIdx.y + 1) / gridDim.y - i0;
+    auto body_of = [&](int row) {  // body that holds blob row `row`
+        int b = 0;
+        while (s_row[b + 1] <= row) ++b;
+        return b;
+    };
+    for (int i = tid; i < mt; i += T) {
+        const int b = body_of(i);
+        x[i] = load((size_t)s_b[b] + (i - s_row[b]), i >= i0 && i < i0 + nr);
+    }
+    // a thread per (body, component) and per constraint row.  All that the chain below
+    // reads is loaded here: its steps then wait on barriers only, not on memory
+    const int eb = tid / 6, ec = tid - 6 * eb;
+    double Nb[6];
+    if (eb < nb) {
+        ru[eb][ec] = load(off_u + 6 * (size_t)s_p[eb] + ec, first);
+        for (int c = 0; c < 6; ++c) Nb[c] = P.Nt[36 * (size_t)s_p[eb] + 6 * ec + c];
+    }
+    if (tid < na) y[tid] = load(off_phi + s_rows[tid], first);
+    for (int e = tid; e < 12 * na; e += T)
+        cr[e / 12][e % 12] = P.crow[12 * (size_t)s_rows[e / 12] + e % 12];
+    for (int e = tid; e < 2 * na; e += T) {
+        const int p = (e & 1) ? P.row_q[s_rows[e / 2]] : P.row_p[s_rows[e / 2]];
+        int q = -1;
+        if (p >= 0)
+            for (q = 0; s_p[q] != p;) ++q;
+        s_side[e / 2][e & 1] = q;
+    }
+    __syncthreads();
+    // parts of t = M_pp^-1 r_lam
+    const int ks = nr ? min(T / nr, 16) : 0, g = nr ? tid / nr : 0, row = tid - g * nr;
+    int b = 0, il = 0;
+    if (g < ks) {
+        b = body_of(i0 + row);
+        il = i0 + row - s_row[b];
+        const int m = s_row[b + 1] - s_row[b];
+        part[tid] = row_part(P.minv + P.mat_off[s_p[b]], m, il, m * g / ks, m * (g + 1) / ks,
+                             x + s_row[b]);
+    }
+    // Z^T r_lam + r_U, a wavefront per (body, component)
+    for (int e = w; e < 6 * nb; e += T / kWave) {
+        const int q = e / 6, c = e % 6, m = s_row[q + 1] - s_row[q];
+        const double *Z = P.Z + P.z_off[s_p[q]];
+        double s = 0.0;
+        for (int i = lane; i < m; i += kWave) s += Z[(size_t)i * 6 + c] * x[s_row[q] + i];
+        for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        if (lane == 0) w6[q][c] = s + ru[q][c];
+    }
+    __syncthreads();
+    if (eb < nb) {  // U^
+        double s = 0.0;
+        for (int c = 0; c < 6; ++c) s += Nb[c] * w6[eb][c];
+        uh[eb][ec] = -s;
+    }
+    __syncthreads();
+    if (tid < na) {
+        const int q = s_side[tid][1];
+        const double *Up = uh[s_side[tid][0]];
+        double s = 0.0;
+        for (int u = 0; u < 6; ++u) s += cr[tid][u] * Up[u];
+        if (q >= 0)
+            for (int u = 0; u < 6; ++u) s += cr[tid][6 + u] * uh[q][u];
+        y[tid] -= s;
+    }
+    __syncthreads();
+    if (tid < na) {
+        double s = 0.0;
+        for (int l = 0; l < na; ++l) s += G[tid * na + l] * y[l];
+        ph[tid] = s;
+        if (first) z[off_phi + s_rows[tid]] = s;
+    }
+    __syncthreads();
+    if (eb < nb) {  // f = C^T phi per body
+        double s = 0.0;
+        for (int t = 0; t < na; ++t)
+            for (int side = 0; side < 2; ++side)
+                if (s_side[t][side] == eb) s += ph[t] * cr[t][6 * side + ec];
+        w6[eb][ec] = s;
+    }
+    __syncthreads();
+    if (eb < nb) {  // U = U^ + N~ f
+        double s = uh[eb][ec];
+        for (int c = 0; c < 6; ++c) s += Nb[c] * w6[eb][c];
+        ru[eb][ec] = s;
+        if (first) z[off_u + 6 * (size_t)s_p[eb] + ec] = s;
+    }
+    __syncthreads();
+    if (tid < nr) {
+        double s = part[tid];
+        for (int q = 1; q < ks; ++q) s += part[q * nr + tid];
+        const double *Z = P.Z + P.z_off[s_p[b]] + (size_t)il * 6;
+        double d = 0.0;
+        for (int c = 0; c < 6; ++c) d += Z[c] * ru[b][c];
+        z[(size_t)s_b[b] + il] = s + d;
+    }
+}
+
+PcFuse precond_fuse(int A, const int *body_ptr, const int *bodies, const int *row_ptr,
+                    const int *blob_off) {
+    PcFuse f;
+    for (int a = 0; a < A; ++a) {
+        int64_t rows = 0;
+        for (int e = body_ptr[a]; e < body_ptr[a + 1]; ++e)
+            rows += 3 * (int64_t)(blob_off[bodies[e] + 1] - blob_off[bodies[e]]);
+        const int nb = body_ptr[a + 1] - body_ptr[a], na = row_ptr[a + 1] - row_ptr[a];
+        if (nb > kFuseBodies || na > kFuseCons || rows > kFuseRows) return PcFuse();
+        f.rows = std::max(f.rows, (int)rows);
+        f.bodies = std::max(f.bodies, nb);
+        f.cons = std::max(f.cons, na);
+    }
+    return f;
 }
 
 __global__ __launch_bounds__(256) void pc_apply2_kernel(
@@ -1887,14 +2086,25 @@ hipError_t precond_assembly(hipStream_t s, const PrecondDev &P) {
     return hipGetLastError();
 }
 
-void precond_apply(hipStream_t s, const PrecondDev &P, int N, const double *r, double *z) {
+void precond_apply(hipStream_t s, const PrecondDev &P, int N, const double *r, double *z,
+                   const double *alpha, double *v) {
     if (P.M <= 0) return;
+    if (P.fuse.rows) {
+        // a workgroup per compute unit while the assemblies are few.  From two per unit
+        // on, short assemblies take 256 threads each, so that more are resident (1,000
+        // shells of 42 blobs: 26.2 us, with 1,024 threads 38.5)
+        const int split = std::min(16, std::max(1, kFuseBlocks / P.A));
+        const int T = P.A >= 512 && P.fuse.rows <= 256 ? 256 : kApply;
+        pc_apply_asm_kernel<<<dim3(P.A, split), T, fuse_doubles(P.fuse, T) * sizeof(double), s>>>(
+            N, P.M, P, r, alpha, v, z);
+        return;
+    }
     if (P.learned)
         pc_apply1_learned_kernel<<<P.M, 256, 0, s>>>(N, P.blob_off, P.type, P.tmat_off, P.tz_off,
                                                      P.tminv, P.tZ, P.R9, P.Nt, P.lcorr, r, z,
                                                      P.tmp, P.stmp);
     else
-        pc_apply1_kernel<<<P.M, 256, 0, s>>>(N, P.blob_off, P.mat_off, P.z_off, P.minv, P.Z, P.Nt,
+        pc_apply1_kernel<<<P.M, kApply, 0, s>>>(N, P.blob_off, P.mat_off, P.z_off, P.minv, P.Z, P.Nt,
                                              r, z, P.tmp);
     if (P.A > 0)
         pc_apply2_kernel<<<P.A, 256, 0, s>>>(N, P.M, P.asm_row_ptr, P.asm_rows, P.asm_mat_off,

@@ -342,6 +342,41 @@ def test_preconditioner_large_bodies(n_helix):
         arb.arb_destroy(ctx)
 
 
+@pytest.mark.parametrize("bodies_,blobs,rows", [
+    (1, 1, 0), (1, 341, 0), (1, 342, 0),     # 1,023 and 1,026 blob rows
+    (11, 31, 3), (11, 32, 3),                # the same, over a chain
+    (22, 4, 3), (23, 4, 3),                  # 63 and 66 constraint rows
+    (32, 3, 2), (33, 3, 2),                  # 32 and 33 bodies
+    (512, 3, 0), (300, 4, 0)])               # many assemblies: workgroups of 256, of 1,024
+def test_preconditioner_apply_at_its_limits(bodies_, blobs, rows):
+    # a chain of curved bodies (rows per link; 0: no links), just inside and just
+    # beyond what the one-launch apply takes
+    k = np.arange(blobs)
+    body = np.stack([1.5 * np.cos(k), 1.5 * np.sin(k), 1.1 * (k - 0.5 * (blobs - 1))], 1)
+    q = np.zeros((bodies_, 3))
+    q[:, 0] = 7.0 * np.arange(bodies_)
+    theta = np.tile([1.0, 0.0, 0.0, 0.0], (bodies_, 1))
+    L = W._links(bodies_ - 1 if rows else 0)
+    for n in range(len(L["pq"])):
+        L["pq"][n] = (n, n + 1)
+        L["dl_p"][n, 0], L["dl_q"][n, 0], L["nproj"][n] = 3.5, -3.5, rows
+    rng = np.random.default_rng(bodies_)
+    wl = W.Workload("limits", 1.0, 1.0, False, np.tile(body, (bodies_, 1)),
+                    np.arange(bodies_ + 1, dtype=np.int32) * blobs, q, theta,
+                    rng.standard_normal((bodies_, 6)), **L)
+    print(f"apply: {bodies_} bodies of {blobs} blobs, {wl.n_rows} rows", flush=True)
+    S = system.assemble(wl)
+    P = precond.BlockPreconditioner(wl, S["r"], S["C"])
+    ctx = arb.context_for(wl, precision=arb.ARB_FP64, tol=1e-10)
+    try:
+        arb.arb_precond_build(ctx)
+        for _ in range(2):
+            r = rng.standard_normal(wl.n_unknowns)
+            assert rel(arb.arb_precond_apply(ctx, r), P.apply(r)) <= 1e-11
+    finally:
+        arb.arb_destroy(ctx)
+
+
 @pytest.mark.parametrize("name,prec", [("filament", arb.ARB_FP64), ("bacteria4", arb.ARB_FP32C),
                                        ("diatoms2", arb.ARB_FP64)])
 def test_graph_replays_match_plain_launches(name, prec):
