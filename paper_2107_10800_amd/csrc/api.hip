@@ -425,20 +425,32 @@ constexpr int kRingShape = -1000;
 int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const double4 *p64,
              const float4 *hi, const float4 *lo, const float4 *box, const int *perm,
              const double *lam, double *out, const double *U, const int *bob, const double *dvec,
-             int precision, bool wall, int shape) {
+             int precision, bool wall, int shape, const arb::SaddleRows &rows = arb::SaddleRows()) {
     // FP32 sums are in units of the blob radius: M(a) = M_{a=1}(r / a) / a
     const double scale = 1.0 / (8.0 * arb::kPi * ctx->opt.eta) /
                          (precision == ARB_FP32C ? ctx->opt.a : 1.0);
     const bool small = small_pair(ctx, N);
     const bool ring = !small && shape == kRingShape;
     const bool sym = !small && !ring && shape < 0;
+    bool sym_clean = true;
     int used = 1;
     if (ring) {
         HIPCHK(ctx->partial.ensure((size_t)arb::pair_ring_slices(N) * 3 * N * sizeof(double)));
     } else if (sym) {
         TRY(sym_worklist(ctx, s, N, -shape, precision));
-        HIPCHK(ctx->partial.ensure((size_t)3 * N * sizeof(double)));
-        arb::pair_sym_clear(s, N, ctx->partial.as<double>());
+        // the sums' buffer is left zero by the reduction of the product before.  A clear
+        // that is only recorded (a captured first product) does not count as done
+        const size_t bytes = (size_t)3 * N * sizeof(double);
+        if (ctx->sym_sums.bytes < bytes) ctx->sym_dirty = true;
+        HIPCHK(ctx->sym_sums.ensure(bytes));
+        if (ctx->sym_dirty) {
+            arb::pair_sym_clear(s, ctx->sym_sums.bytes / sizeof(double),
+                                ctx->sym_sums.as<double>());
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            HIPCHK(hipStreamIsCapturing(s, &cs));
+            sym_clean = cs == hipStreamCaptureStatusNone;
+        }
+        ctx->sym_dirty = true;
     } else if (!small) {
         HIPCHK(ctx->partial.ensure((size_t)shape * 3 * N * sizeof(double)));
     }
@@ -450,14 +462,14 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const do
     }
     if (small)
         arb::pair_small(s, precision, wall, N, raw_pos, p64, hi, lo, lam, perm, ctx->opt.a, scale,
-                        out, U, bob, dvec);
+                        out, U, bob, dvec, rows);
     else if (ring)
         used = arb::pair_ring(s, precision, wall, N, p64, hi, lo, box, lam, perm, ctx->opt.a,
                               ctx->partial.as<double>());
     else if (sym)
         arb::pair_sym(s, precision, wall, N, p64, hi, lo, box, lam, perm, ctx->opt.a,
                       ctx->sym_work[precision == ARB_FP32C].as<int4>(),
-                      ctx->sym_n_work[precision == ARB_FP32C], ctx->partial.as<double>());
+                      ctx->sym_n_work[precision == ARB_FP32C], ctx->sym_sums.as<double>());
     else
         used = arb::pair_partial(s, precision, wall, N, p64, hi, lo, lam, perm, ctx->opt.a, shape,
                                  ctx->partial.as<double>());
@@ -466,7 +478,9 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const do
         ctx->prof_ev.emplace_back(e0, e1);
     }
     if (!small)
-        arb::pair_reduce(s, N, used, ctx->partial.as<double>(), scale, out, U, bob, dvec, perm);
+        arb::pair_reduce(s, N, used, (sym ? ctx->sym_sums : ctx->partial).as<double>(), sym, scale,
+                         out, U, bob, dvec, perm, rows);
+    if (sym) ctx->sym_dirty = !sym_clean;
     return 0;
 }
 
@@ -546,7 +560,8 @@ int choose_slices(arb_ctx *ctx, hipStream_t s, int N, const double4 *p64, const 
 // changed (or when asked), then out = M lambda - K U as run_pair writes it
 int fmm_pair(arb_ctx *ctx, hipStream_t s, int N, const double *pos, const float4 *hi,
              const float4 *lo, const double *lam, double *out, const double *U, const int *bob,
-             const double *dvec, bool rebuild, int precision) {
+             const double *dvec, bool rebuild, int precision,
+             const arb::SaddleRows &rows = arb::SaddleRows()) {
     arb::FmmState &F = ctx->fmm;
     if (rebuild || F.dirty || !F.ready || F.N != N) {
         std::string msg;
@@ -576,16 +591,17 @@ int fmm_pair(arb_ctx *ctx, hipStream_t s, int N, const double *pos, const float4
     // sums in units of the blob radius: M(a) = M_{a=1}(r / a) / a
     const double scale = 1.0 / (8.0 * arb::kPi * ctx->opt.eta) / ctx->opt.a;
     if (N > 0)
-        arb::pair_reduce(s, N, 1, ctx->partial.as<double>(), scale, out, U, bob, dvec, nullptr);
+        arb::pair_reduce(s, N, 1, ctx->partial.as<double>(), false, scale, out, U, bob, dvec,
+                         nullptr, rows);
     return 0;
 }
 
 int ctx_pair(arb_ctx *ctx, hipStream_t s, const double *lam, double *out, const double *U,
-             int precision) {
+             int precision, const arb::SaddleRows &rows = arb::SaddleRows()) {
     if (ctx->opt.pair_kernel == ARB_PAIR_FMM)
         return fmm_pair(ctx, s, ctx->N, ctx->pos.as<double>(), ctx->hi.as<float4>(),
                         ctx->lo.as<float4>(), lam, out, U, ctx->body_of_blob.as<int>(),
-                        ctx->dvec.as<double>(), false, precision);
+                        ctx->dvec.as<double>(), false, precision, rows);
     const bool wall = ctx->opt.wall != 0;
     // the state's positions in the pair kernels' order (pair_order)
     const bool so = ctx->psorted;
@@ -597,7 +613,7 @@ int ctx_pair(arb_ctx *ctx, hipStream_t s, const double *lam, double *out, const 
     int sl = 0;
     TRY(choose_slices(ctx, s, ctx->N, p64, hi, lo, box, perm, lam, precision, wall, &sl));
     return run_pair(ctx, s, ctx->N, nullptr, p64, hi, lo, box, perm, lam, out, U,
-                    ctx->body_of_blob.as<int>(), ctx->dvec.as<double>(), precision, wall, sl);
+                    ctx->body_of_blob.as<int>(), ctx->dvec.as<double>(), precision, wall, sl, rows);
 }
 
 // out = A y (Eq. linear_system)
@@ -609,13 +625,22 @@ int system_apply(arb_ctx *ctx, hipStream_t s, const double *y, double *out, int 
         return single_blob_system_apply(ctx, s, y, out, precision);
     const int N = ctx->N, M = ctx->M;
     const double *lam = y, *U = y + 3 * (size_t)N, *phi = y + 3 * (size_t)N + 6 * (size_t)M;
-    TRY(ctx_pair(ctx, s, lam, out, U, precision));
-    arb::KT_CT_apply(s, M, ctx->blob_off.as<int>(), ctx->dvec.as<double>(), lam, -1.0,
-                     ctx->brow_ptr.as<int>(), ctx->brow_ent.as<int>(), ctx->crow.as<double>(),
-                     ctx->Nc > 0 ? phi : nullptr, out + 3 * (size_t)N);
-    arb::C_apply(s, ctx->Nc, ctx->row_p.as<int>(), ctx->row_q.as<int>(), ctx->crow.as<double>(), U,
-                 out + 3 * (size_t)N + 6 * (size_t)M);
-    return 0;
+    arb::SaddleRows R;
+    R.M = M;
+    R.Nc = ctx->Nc;
+    R.blob_off = ctx->blob_off.as<int>();
+    R.brow_ptr = ctx->brow_ptr.as<int>();
+    R.brow_ent = ctx->brow_ent.as<int>();
+    R.row_p = ctx->row_p.as<int>();
+    R.row_q = ctx->row_q.as<int>();
+    R.dvec = ctx->dvec.as<double>();
+    R.crow = ctx->crow.as<double>();
+    R.lam = lam;
+    R.U = U;
+    R.phi = ctx->Nc > 0 ? phi : nullptr;
+    R.out_u = out + 3 * (size_t)N;
+    R.out_phi = out + 3 * (size_t)N + 6 * (size_t)M;
+    return ctx_pair(ctx, s, lam, out, U, precision, R);
 }
 
 // generalised RPY product N x6 (6M) scaled into out = base + scale' N x6, with the

@@ -8,7 +8,7 @@
 //  constraint_rows lab-frame row coefficients of C and B (Eq. dg, App. A)
 //  C_apply         (C U)_k
 //  euler_update    q += dt u, theta <- theta_{w dt} . theta (Sec. 2.1, Sec. 4.3)
-#include "common.h"
+#include "saddle_device.h"
 
 namespace arb {
 
@@ -59,11 +59,6 @@ __global__ void K_kernel(int N, const int *__restrict__ bob, const double *__res
     for (int k = 0; k < 3; ++k) out[3 * (size_t)i + k] = Up[k] + c[k];
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
 // one wavefront per body; blockDim = 256 -> 4 bodies per block
 __global__ __launch_bounds__(256) void KT_CT_kernel(
     int M, const int *__restrict__ blob_off, const double *__restrict__ dvec,
@@ -73,34 +68,7 @@ __global__ __launch_bounds__(256) void KT_CT_kernel(
     const int lane = threadIdx.x & (kWave - 1);
     const int p = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     if (p >= M) return;  // whole wavefront exits together
-    double f[6] = {0, 0, 0, 0, 0, 0};
-    if (lam) {
-        for (int i = blob_off[p] + lane; i < blob_off[p + 1]; i += kWave) {
-            const double l0 = lam[3 * (size_t)i], l1 = lam[3 * (size_t)i + 1],
-                         l2 = lam[3 * (size_t)i + 2];
-            const double d0 = dvec[3 * (size_t)i], d1 = dvec[3 * (size_t)i + 1],
-                         d2 = dvec[3 * (size_t)i + 2];
-            f[0] += l0;
-            f[1] += l1;
-            f[2] += l2;
-            f[3] += d1 * l2 - d2 * l1;
-            f[4] += d2 * l0 - d0 * l2;
-            f[5] += d0 * l1 - d1 * l0;
-        }
-    }
-    for (int k = 0; k < 6; ++k) f[k] = sign * wave_sum(f[k]);
-    if (lane == 0) {
-        if (phi) {
-            for (int e = brow_ptr[p]; e < brow_ptr[p + 1]; ++e) {
-                const int ent = brow_ent[e];
-                const int row = ent >> 1, side = ent & 1;
-                const double *c = crow + 12 * (size_t)row + 6 * side;
-                const double ph = phi[row];
-                for (int k = 0; k < 6; ++k) f[k] += ph * c[k];
-            }
-        }
-        for (int k = 0; k < 6; ++k) out[6 * (size_t)p + k] = f[k];
-    }
+    kt_ct_row(p, lane, blob_off, dvec, lam, sign, brow_ptr, brow_ent, crow, phi, out);
 }
 
 // row kinds: 0 = projected link row, 1 = general row
@@ -164,16 +132,7 @@ __global__ void C_kernel(int Nc, const int *__restrict__ row_p, const int *__res
                          double *__restrict__ out) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= Nc) return;
-    const double *c = crow + 12 * (size_t)k;
-    const double *Up = U + 6 * (size_t)row_p[k];
-    double s = 0.0;
-    for (int a = 0; a < 6; ++a) s += c[a] * Up[a];
-    const int q = row_q[k];
-    if (q >= 0) {
-        const double *Uq = U + 6 * (size_t)q;
-        for (int a = 0; a < 6; ++a) s += c[6 + a] * Uq[a];
-    }
-    out[k] = s;
+    out[k] = c_row(k, row_p, row_q, crow, U);
 }
 
 __global__ void euler_kernel(int M, const double *__restrict__ U, double dt, double *__restrict__ q,

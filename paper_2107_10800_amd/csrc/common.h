@@ -164,6 +164,16 @@ int noalloc_setup(int device);
 // source slices of the target-parallel kernel when none are given: doubled while
 // the grid stays within about 2,048 workgroups and every slice keeps a tile
 int heuristic_slices(int N);
+// the rigid-body rows of the saddle operator (Eq. linear_system), done by the launch that
+// finishes the pair product: out_u = -K^T lambda + C^T phi, out_phi = C U (M = Nc = 0: none)
+struct SaddleRows {
+    int M = 0, Nc = 0;
+    const int *blob_off = nullptr, *brow_ptr = nullptr, *brow_ent = nullptr;
+    const int *row_p = nullptr, *row_q = nullptr;
+    const double *dvec = nullptr, *crow = nullptr;
+    const double *lam = nullptr, *U = nullptr, *phi = nullptr;  // phi null: no rows
+    double *out_u = nullptr, *out_phi = nullptr;
+};
 // small systems: the whole product in one launch, out as pair_reduce writes it;
 // raw_pos (may be null): loose blobs' positions (3N, units of length) instead of the
 // prepared arrays
@@ -171,7 +181,7 @@ constexpr int kSmallPairN = 1024;
 void pair_small(hipStream_t s, int precision, bool wall, int N, const double *raw_pos,
                 const double4 *p64, const float4 *hi, const float4 *lo, const double *lam,
                 const int *perm, double a, double scale, double *out, const double *U,
-                const int *body_of_blob, const double *dvec);
+                const int *body_of_blob, const double *dvec, const SaddleRows &R);
 // mid sizes (pair_sym.hip): each unordered pair once, ordered sums in
 // pair_ring_slices(N) slices of partial (returned)
 constexpr int kRingPairN = 8192;
@@ -185,15 +195,16 @@ int pair_ring(hipStream_t s, int precision, bool wall, int N, const double4 *p64
 int pair_partial(hipStream_t s, int precision, bool wall, int N, const double4 *p64,
                   const float4 *hi, const float4 *lo, const double *lam, const int *perm,
                   double a, int slices, double *partial);
-// out_i = scale * sum_s partial[s][c][i]  -  (K U)_i   (the K term only if U != nullptr)
-void pair_reduce(hipStream_t s, int N, int slices, const double *partial, double scale,
+// out_i = scale * sum_s partial[s][c][i]  -  (K U)_i   (the K term only if U != nullptr),
+// and the rows R in the same launch; clear: partial is zeroed on the way
+void pair_reduce(hipStream_t s, int N, int slices, double *partial, bool clear, double scale,
                  double *out, const double *U, const int *body_of_blob, const double *dvec,
-                 const int *perm);
+                 const int *perm, const SaddleRows &R);
 int pair_wall_violation(hipStream_t s, int N, const double4 *p64, double a, int *flag_dev,
                         int *flag_host);
 // symmetric pair sums, FP32 (hi/lo) or FP64 (p64) (pair_sym.hip): u [3][N]
-// unscaled, accumulated into u (cleared first by pair_sym_clear)
-void pair_sym_clear(hipStream_t s, int N, double *u);
+// unscaled, accumulated into u, which is zero before (pair_sym_clear, pair_reduce's clear)
+void pair_sym_clear(hipStream_t s, size_t n, double *u);
 void pair_sym(hipStream_t s, int precision, bool wall, int N, const double4 *p64,
               const float4 *hi, const float4 *lo, const float4 *box, const double *lam,
               const int *perm, double a, const int4 *work, int n_work, double *u);
@@ -566,6 +577,8 @@ struct arb_ctx {
     int64_t ky_n = 0;
     // single-blob model: M+1 zero offsets (no blobs in the preconditioner's body
     // stage), partial sums of the generalised RPY product, C^T phi
+    arb::DevBuf sym_sums;    // sums of the symmetric product, zero between products
+    bool sym_dirty = true;   // ... unless a product did not end
     arb::DevBuf zero_off, zero_off64, rot_partial, rot_ct, rot_work;
     int rot_work_M = -1, rot_n_work = 0;
     // the initial state of a midpoint step

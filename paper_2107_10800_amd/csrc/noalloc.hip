@@ -99,7 +99,8 @@ static int rpy_apply_noalloc(arb_ctx *ctx, int N, const double *pos_dev,
     // FP32 sums are in units of the blob radius: M(a) = M_{a=1}(r / a) / a
     const double scale = 1.0 / (8.0 * arb::kPi * ctx->opt.eta) /
                          (ctx->opt.precision == ARB_FP32C ? ctx->opt.a : 1.0);
-    arb::pair_reduce(s, N, used, partial, scale, u_dev, nullptr, nullptr, nullptr, nullptr);
+    arb::pair_reduce(s, N, used, partial, false, scale, u_dev, nullptr, nullptr, nullptr, nullptr,
+                     arb::SaddleRows());
     e = hipGetLastError();
     if (e != hipSuccess)
         return fail(ctx, ARB_E_DEVICE, std::string("pair launch: ") + hipGetErrorString(e));

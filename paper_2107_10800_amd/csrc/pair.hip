@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "rpy_device.h"
+#include "saddle_device.h"
 
 namespace arb {
 
@@ -219,16 +220,23 @@ __device__ __forceinline__ void reduce_store(int i, double scale, const double *
     out[3 * i + 2] = s2;
 }
 
-// partial in the pair kernels' order (entry k = blob perm[k]); out in blob order
-__global__ void pair_reduce_kernel(int N, int slices, const double *__restrict__ partial,
-                                   double scale, double *__restrict__ out,
-                                   const double *__restrict__ U, const int *__restrict__ bob,
-                                   const double *__restrict__ dvec, const int *__restrict__ perm) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+// partial in the pair kernels' order (entry k = blob perm[k]); out in blob order.  The
+// workgroups beyond the blobs' do the rigid-body rows R.  clear: partial is zero
+// afterwards, which saves the symmetric product a launch (3.5 us) before its sums.
+__global__ __launch_bounds__(256) void pair_reduce_kernel(
+    int N, int slices, double *__restrict__ partial, bool clear, double scale,
+    double *__restrict__ out, const double *__restrict__ U, const int *__restrict__ bob,
+    const double *__restrict__ dvec, const int *__restrict__ perm, SaddleRows R) {
+    const int nb = (N + 255) / 256;
+    if ((int)blockIdx.x >= nb) return saddle_rows(R, blockIdx.x - nb);
+    const int k = blockIdx.x * 256 + threadIdx.x;
     if (k >= N) return;
     double s[3] = {0.0, 0.0, 0.0};
     for (int sl = 0; sl < slices; ++sl)
         for (int c = 0; c < 3; ++c) s[c] += partial[((size_t)sl * 3 + c) * N + k];
+    if (clear)
+        for (int sl = 0; sl < slices; ++sl)
+            for (int c = 0; c < 3; ++c) partial[((size_t)sl * 3 + c) * N + k] = 0.0;
     reduce_store(perm ? perm[k] : k, scale, s, out, U, bob, dvec);
 }
 
@@ -238,8 +246,10 @@ constexpr int kReduceWaves = 8;
 __global__ __launch_bounds__(64 * kReduceWaves) void pair_reduce_wide_kernel(
     int N, int slices, const double *__restrict__ partial, double scale, double *__restrict__ out,
     const double *__restrict__ U, const int *__restrict__ bob, const double *__restrict__ dvec,
-    const int *__restrict__ perm) {
+    const int *__restrict__ perm, SaddleRows R) {
     __shared__ double red[kReduceWaves][3][64];
+    const int nb = (N + 63) / 64;
+    if ((int)blockIdx.x >= nb) return saddle_rows(R, blockIdx.x - nb);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int k = blockIdx.x * 64 + lane;
     double s[3] = {0.0, 0.0, 0.0};
@@ -290,7 +300,10 @@ __global__ __launch_bounds__(256) void pair_small_kernel(
     int N, const double *__restrict__ pos, double inv_a, const double4 *__restrict__ p64,
     const float4 *__restrict__ hi, const float4 *__restrict__ lo, const double *__restrict__ lam,
     const int *__restrict__ perm, CoefD c, double scale, double *__restrict__ out,
-    const double *__restrict__ U, const int *__restrict__ bob, const double *__restrict__ dvec) {
+    const double *__restrict__ U, const int *__restrict__ bob, const double *__restrict__ dvec,
+    SaddleRows R) {
+    const int nb = (N + 3) / 4;
+    if ((int)blockIdx.x >= nb) return saddle_rows(R, blockIdx.x - nb);
     const int lane = threadIdx.x & 63;
     const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (k >= N) return;  // the whole wavefront
@@ -379,13 +392,14 @@ __global__ __launch_bounds__(256) void pair_small_kernel(
 void pair_small(hipStream_t s, int precision, bool wall, int N, const double *raw_pos,
                 const double4 *p64, const float4 *hi, const float4 *lo, const double *lam,
                 const int *perm, double a, double scale, double *out, const double *U,
-                const int *body_of_blob, const double *dvec) {
+                const int *body_of_blob, const double *dvec, const SaddleRows &R) {
     if (N <= 0) return;
     const CoefD c = make_coef<CoefD, double>(a);
     auto go = [&](auto w, auto f, auto r) {
         pair_small_kernel<decltype(w)::value, decltype(f)::value, decltype(r)::value>
-            <<<nblk(N, 4), 256, 0, s>>>(N, raw_pos, 1.0 / a, p64, hi, lo, lam, perm, c, scale, out,
-                                        U, body_of_blob, dvec);
+            <<<nblk(N, 4) + saddle_blocks(R, 256), 256, 0, s>>>(N, raw_pos, 1.0 / a, p64, hi, lo,
+                                                                lam, perm, c, scale, out, U,
+                                                                body_of_blob, dvec, R);
     };
     auto go2 = [&](auto w, auto f) {
         raw_pos ? go(w, f, std::true_type{}) : go(w, f, std::false_type{});
@@ -419,17 +433,18 @@ int pair_partial(hipStream_t s, int precision, bool wall, int N, const double4 *
     return slices;
 }
 
-void pair_reduce(hipStream_t s, int N, int slices, const double *partial, double scale,
+void pair_reduce(hipStream_t s, int N, int slices, double *partial, bool clear, double scale,
                  double *out, const double *U, const int *body_of_blob, const double *dvec,
-                 const int *perm) {
+                 const int *perm, const SaddleRows &R) {
     if (N <= 0) return;
     // from 8 slices on one thread per blob is a chain of loads over too few wavefronts
-    if (slices >= kReduceWaves)
-        pair_reduce_wide_kernel<<<nblk(N, 64), 64 * kReduceWaves, 0, s>>>(
-            N, slices, partial, scale, out, U, body_of_blob, dvec, perm);
+    constexpr int kWide = 64 * kReduceWaves;
+    if (slices >= kReduceWaves && !clear)
+        pair_reduce_wide_kernel<<<nblk(N, 64) + saddle_blocks(R, kWide), kWide, 0, s>>>(
+            N, slices, partial, scale, out, U, body_of_blob, dvec, perm, R);
     else
-        pair_reduce_kernel<<<nblk(N, 256), 256, 0, s>>>(N, slices, partial, scale, out, U,
-                                                          body_of_blob, dvec, perm);
+        pair_reduce_kernel<<<nblk(N, 256) + saddle_blocks(R, 256), 256, 0, s>>>(
+            N, slices, partial, clear, scale, out, U, body_of_blob, dvec, perm, R);
 }
 
 int pair_wall_violation(hipStream_t s, int N, const double4 *p64, double a, int *flag_dev,

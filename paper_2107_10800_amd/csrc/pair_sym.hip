@@ -579,11 +579,10 @@ int pair_ring(hipStream_t s, int precision, bool wall, int N, const double4 *p64
     return pair_ring_slices(N);
 }
 
-// u = 0 (3N doubles) before the symmetric kernel adds into it
-void pair_sym_clear(hipStream_t s, int N, double *u) {
-    if (N <= 0) return;
-    const size_t n3 = 3 * (size_t)N;
-    zero_kernel<<<(unsigned)((n3 + 255) / 256), 256, 0, s>>>(n3, u);
+// u = 0 (n doubles) before the symmetric kernel first adds into it
+void pair_sym_clear(hipStream_t s, size_t n, double *u) {
+    if (n == 0) return;
+    zero_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, u);
 }
 
 // u (layout [3][N], FP64) += sum over all pairs, unscaled (units 1/(8 pi eta))

@@ -1152,8 +1152,8 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
 
 // Row i of M_pp^-1 x, the part k = [k0, k1) of its sum.  The apply kernels give a row
 // several threads, each a part, so that a workgroup keeps enough loads in flight: with
-// one thread per row it waited on its m loads (51 us for the 2,000-odd plates of 64
-// diatom colonies, 43 us with parts).
+// one thread per row it waited on its m loads (51 us for the 1,591 plates of 64 diatom
+// colonies, 43 us with parts).
 __device__ __forceinline__ double row_part(const double *__restrict__ Mi, int m, int i, int k0,
                                            int k1, const double *x) {
     double s = 0.0;

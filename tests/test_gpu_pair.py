@@ -274,3 +274,18 @@ def test_small_and_mid_sizes(n, wall, prec):
     finally:
         arb.arb_destroy(loose)
         arb.arb_destroy(state)
+
+
+# the symmetric product leaves the buffer of its sums zero for the next one: products of
+# two sizes in turn, the larger first and last
+@pytest.mark.parametrize("prec", [arb.ARB_FP64, arb.ARB_FP32C])
+def test_symmetric_products_in_turn(prec):
+    ctx = arb.arb_create(precision=prec, wall=True, a=0.8, eta=1.3,
+                         pair_kernel=arb.ARB_PAIR_SYMMETRIC)
+    try:
+        for n in (300, 70, 70, 300, 520, 300):
+            cl = W.random_blobs(n, seed=n, box=8.0 + n ** 0.5, zlo=1.0, zhi=9.0)
+            uo = rpy.mobility_apply(cl["pos"], cl["lam"], 0.8, 1.3, True)
+            assert rel(arb.arb_rpy_apply(ctx, cl["pos"], cl["lam"]), uo.ravel()) <= TOL[prec]
+    finally:
+        arb.arb_destroy(ctx)

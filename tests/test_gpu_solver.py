@@ -117,6 +117,28 @@ def test_preconditioner(case):
     assert rel(arb.arb_precond_apply(ctx, r), P.apply(r)) <= 1e-11
 
 
+@pytest.mark.parametrize("n_bact,kernel", [
+    (8, arb.ARB_PAIR_AUTO), (9, arb.ARB_PAIR_AUTO), (9, arb.ARB_PAIR_TARGET),
+    (9, arb.ARB_PAIR_SYMMETRIC), (9, arb.ARB_PAIR_FMM)])
+def test_saddle_rows_of_each_product(n_bact, kernel):
+    # the body and constraint rows ride on each product's last launch: 976 and 1,098
+    # blobs of 16 and 18 bodies, 48 and 54 rows
+    wl = W.bacteria(n_bact=n_bact, side=90.0, seed=n_bact)
+    S = system.assemble(wl)
+    y = np.random.default_rng(n_bact).standard_normal(S["A"].shape[0])
+    z = S["A"] @ y
+    n3 = 3 * wl.N
+    ctx = arb.context_for(wl, precision=arb.ARB_FP64, pair_kernel=kernel)
+    try:
+        for _ in range(2):
+            g = arb.arb_system_apply(ctx, y)
+            assert rel(g[n3:], z[n3:]) <= 1e-12
+            if kernel != arb.ARB_PAIR_FMM:
+                assert rel(g, z) <= 1e-12
+    finally:
+        arb.arb_destroy(ctx)
+
+
 def test_gmres_solve(case):
     name, wl, S, ctx = case
     us = wl.u_slip
