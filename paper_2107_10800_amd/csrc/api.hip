@@ -723,6 +723,8 @@ arb::PrecondDev pc_view(arb_ctx *ctx) {
     P.M = ctx->M;
     P.A = ctx->n_asm;
     P.blob_off = ctx->blob_off.as<int>();
+    P.order = ctx->body_order.as<int>();
+    P.n_large = ctx->n_large;
     P.mat_off = ctx->mat_off.as<int64_t>();
     P.z_off = ctx->z_off.as<int64_t>();
     P.asm_body_ptr = ctx->asm_body_ptr.as<int>();
@@ -1592,6 +1594,18 @@ int arb_set_bodies(arb_ctx *ctx, int M, const int32_t *blob_offset, const double
     hipStream_t s = ctx->stream;
     TRY(upload(ctx, ctx->blob_off, ctx->h_blob_off.data(), M + 1, s));
     TRY(upload(ctx, ctx->body_of_blob, ctx->h_body_of_blob.data(), N, s));
+    // launches of a workgroup per body take the largest first: in the bodies' order the
+    // fixed round of workgroups over XCDs and shader engines can give one engine all of
+    // them (alternating sizes: 42- and 80-blob bodies), and the rest waits
+    std::vector<int> order(M);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+        return blob_offset[x + 1] - blob_offset[x] > blob_offset[y + 1] - blob_offset[y];
+    });
+    TRY(upload(ctx, ctx->body_order, order.data(), M, s));
+    ctx->n_large = (int)std::count_if(order.begin(), order.end(), [&](int p) {
+        return 3 * (blob_offset[p + 1] - blob_offset[p]) > arb::kSweepSmall;
+    });
     TRY(upload(ctx, ctx->r_ref, ctx->h_r_ref.data(), 3 * (size_t)N, s));
     TRY(upload(ctx, ctx->body_type_d, ctx->h_body_type.data(), M, s));
     HIPCHK(hipStreamSynchronize(s));

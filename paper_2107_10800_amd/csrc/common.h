@@ -235,9 +235,14 @@ struct PcFuse {
     int rows = 0, bodies = 0, cons = 0;  // blob rows, bodies, constraint rows
 };
 
+// rows up to which the block sweep takes its small instance
+constexpr int kSweepSmall = 144;
+
 struct PrecondDev {
     int M = 0, A = 0;
     const int *blob_off = nullptr;     // M+1
+    const int *order = nullptr;        // M bodies, most blobs first (null: as they come)
+    int n_large = 0;                   // those of more than kSweepSmall rows
     const int64_t *mat_off = nullptr;  // M+1, doubles
     const int64_t *z_off = nullptr;    // M+1, doubles (18 n_p per body)
     const int *asm_body_ptr = nullptr, *asm_bodies = nullptr;
@@ -540,9 +545,10 @@ struct arb_ctx {
     bool pc_lcorr = false;  // learned body mobility with the consistent blob-block correction
     int pc_pinv = 0;
     arb::PcFuse pc_fuse;  // of the exact blocks
+    int n_large = 0;      // bodies of more than kSweepSmall rows
 
     // device buffers
-    arb::DevBuf blob_off, body_of_blob, r_ref, q, theta, R9, pos, dvec, p64, hi, lo,
+    arb::DevBuf blob_off, body_order, body_of_blob, r_ref, q, theta, R9, pos, dvec, p64, hi, lo,
         partial, row_p, row_q, row_kind, row_src, row_m, dl_p, dl_q, dldot_p, dldot_q, proj,
         gcoef, grhs, crow, Bc, brow_ptr, brow_ent, asm_body_ptr, asm_bodies, asm_row_ptr,
         asm_rows, asm_mat_off, mat_off, z_off, mats, minv, ldiag, dinv, Z, Nt, G, S, status, pctmp, lcorr, stmp,

@@ -101,16 +101,17 @@ __device__ __forceinline__ int sym_pinv_serial(double *S, double *V, int n, doub
     return dropped;
 }
 
-__global__ __launch_bounds__(256) void pc_assemble_kernel(const int *__restrict__ blob_off,
+__global__ __launch_bounds__(256) void pc_assemble_kernel(const int *__restrict__ order,
+                                                          const int *__restrict__ blob_off,
                                                           const int64_t *__restrict__ mat_off,
                                                           const double *__restrict__ pos, CoefD c,
                                                           double scale, int wall, double a,
                                                           double *__restrict__ mats,
                                                           int *__restrict__ status) {
-    const int p = blockIdx.x;
+    const int p = order ? order[blockIdx.x] : blockIdx.x;
     const int b0 = blob_off[p], n = blob_off[p + 1] - b0, m = 3 * n;
     double *A = mats + mat_off[p];
-    for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
+    for (int idx = blockIdx.y * 256 + threadIdx.x; idx < n * n; idx += 256 * gridDim.y) {
         const int i = idx / n, j = idx - (idx / n) * n;
         const double *xi = pos + 3 * (size_t)(b0 + i);
         const double *xj = pos + 3 * (size_t)(b0 + j);
@@ -256,6 +257,10 @@ struct MatBatch {
     int *status;
     int *fail;
     double rel_tol;
+    // matrix of a workgroup, largest first (may be null; the sweep's).  Workgroups go
+    // round XCDs and shader engines in a fixed order, which gave every other engine all
+    // the large matrices when sizes alternate (512 bacteria: 537 us, sorted 416)
+    const int *order;
 };
 __device__ __forceinline__ int mat_rows(const MatBatch &B, int p) {
     return B.scale * (B.off[p + 1] - B.off[p]);
@@ -653,52 +658,55 @@ __device__ __forceinline__ double K_entry(const double *d, int a, int c) {
     return b == 0 ? d[1] : -d[0];
 }
 
-// out = R^-1 for a symmetric positive definite 6 x 6 R by Cholesky (R = L L^T,
-// X = L^-1, R^-1 = X^T X; L and X are 36-double scratch, row-major); false,
-// with out untouched, when a pivot falls to 1e-8 of the largest diagonal entry
-// or below (then the caller takes the pseudo-inverse, which is the inverse
-// whenever this succeeds)
-__device__ inline bool chol_inv6(const double *R, double *L, double *X, double *out) {
+// X = L^-1 of a symmetric positive definite 6 x 6 R = L L^T (R^-1 = X^T X); false when a
+// pivot falls to 1e-8 of the largest diagonal entry or below (then the caller takes the
+// pseudo-inverse, which is the inverse whenever this succeeds).
+// Lane c < 6 gets column c of L^-1 (zeros above the diagonal); the factor itself is
+// computed by every lane, in registers.
+__device__ __forceinline__ bool chol_inv6(const double *R, int c, double *X) {
     double dmax = 0.0;
+#pragma unroll
     for (int i = 0; i < 6; ++i) dmax = fmax(dmax, R[i * 6 + i]);
     const double tol = 1e-8 * dmax;
+    double L[6][6];
+    bool ok = true;
+#pragma unroll
     for (int j = 0; j < 6; ++j) {
         double d = R[j * 6 + j];
-        for (int k = 0; k < j; ++k) d -= L[j * 6 + k] * L[j * 6 + k];
-        if (!(d > tol)) return false;
-        L[j * 6 + j] = sqrt(d);
+#pragma unroll
+        for (int k = 0; k < j; ++k) d -= L[j][k] * L[j][k];
+        ok &= d > tol;
+        L[j][j] = sqrt(d);
+#pragma unroll
         for (int i = j + 1; i < 6; ++i) {
             double v = R[i * 6 + j];
-            for (int k = 0; k < j; ++k) v -= L[i * 6 + k] * L[j * 6 + k];
-            L[i * 6 + j] = v / L[j * 6 + j];
+#pragma unroll
+            for (int k = 0; k < j; ++k) v -= L[i][k] * L[j][k];
+            L[i][j] = v / L[j][j];
         }
     }
-    for (int c = 0; c < 6; ++c)
-        for (int i = 0; i < 6; ++i) {
-            if (i < c) {
-                X[i * 6 + c] = 0.0;
-                continue;
-            }
-            double v = i == c ? 1.0 : 0.0;
-            for (int k = c; k < i; ++k) v -= L[i * 6 + k] * X[k * 6 + c];
-            X[i * 6 + c] = v / L[i * 6 + i];
-        }
-    for (int i = 0; i < 6; ++i)
-        for (int j = 0; j < 6; ++j) {
-            double v = 0.0;
-            for (int k = max(i, j); k < 6; ++k) v += X[k * 6 + i] * X[k * 6 + j];
-            out[i * 6 + j] = v;
-        }
-    return true;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        double v = i == c ? 1.0 : 0.0;
+#pragma unroll
+        for (int k = 0; k < i; ++k) v -= L[i][k] * X[k];
+        X[i] = v / L[i][i];
+    }
+    return ok;
 }
 
 // Per body: Z = M^-1 K (m x 6) and N~ = (K^T M^-1 K)^-1 (Sec. 3.1).  Thread r
 // takes row r of Z (M^-1 is symmetric, so the row is read as column r:
 // consecutive threads read consecutive addresses) and adds K_r^T Z_r to its
 // partial R = K^T Z (the 21 entries of the upper triangle); the partials are
-// summed over the wavefronts, then N~ = R^-1 by Cholesky; when R is singular (a
-// rod of collinear blobs) R is stored and flagged for pc_body_pinv_kernel.
-__global__ __launch_bounds__(256) void pc_body_kernel(const int *__restrict__ blob_off,
+// summed over the wavefronts, then N~ = R^-1 by Cholesky, in registers and a lane per
+// column; when R is singular (a rod of collinear blobs) R is stored and flagged for
+// pc_body_pinv_kernel.  A few bodies wait on their loads, many are bound by M^-1 (512
+// bacteria: 301 MB): with five blobs' loads in flight a row, and the factor in registers
+// instead of one thread's LDS, 33 -> 21 us for 16 bacteria, 101 -> 85 for 512 (3.6 TB/s).
+// Four threads a row: 181 us, too few workgroups fit a compute unit.
+__global__ __launch_bounds__(256) void pc_body_kernel(const int *__restrict__ order,
+                                                      const int *__restrict__ blob_off,
                                                       const int64_t *__restrict__ mat_off,
                                                       const int64_t *__restrict__ z_off,
                                                       const double *__restrict__ minv,
@@ -708,8 +716,9 @@ __global__ __launch_bounds__(256) void pc_body_kernel(const int *__restrict__ bl
                                                       int *__restrict__ body_pinv,
                                                       int *__restrict__ status) {
     __shared__ double red[4][21];
-    __shared__ double S6[36], V6[36], L6[36];  // R, then Cholesky scratch
-    const int p = blockIdx.x;
+    __shared__ double S6[36], V6[36];  // R, L^-1
+    __shared__ int singular;
+    const int p = order ? order[blockIdx.x] : blockIdx.x;
     if (status[0] != 0) return;
     const int b0 = blob_off[p], n = blob_off[p + 1] - b0, m = 3 * n;
     const double *Mi = minv + mat_off[p];
@@ -721,6 +730,7 @@ __global__ __launch_bounds__(256) void pc_body_kernel(const int *__restrict__ bl
     for (int r = threadIdx.x; r < m; r += blockDim.x) {
         double z[6] = {0, 0, 0, 0, 0, 0};
         const double *col = Mi + r;
+#pragma unroll 5
         for (int i = 0; i < n; ++i) {
             const double m0 = col[(size_t)(3 * i) * m], m1 = col[(size_t)(3 * i + 1) * m],
                          m2 = col[(size_t)(3 * i + 2) * m];
@@ -754,21 +764,29 @@ __global__ __launch_bounds__(256) void pc_body_kernel(const int *__restrict__ bl
         if (lane == 0) red[w][e] = v;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int e = 0;
-        for (int c1 = 0; c1 < 6; ++c1)
-            for (int c2 = c1; c2 < 6; ++c2, ++e) {
-                double v = 0.0;
-                for (int k = 0; k < (int)(blockDim.x >> 6); ++k) v += red[k][e];
-                S6[c1 * 6 + c2] = v;
-                S6[c2 * 6 + c1] = v;
-            }
-        double *out = Nt + 36 * (size_t)p;
-        const bool ok = chol_inv6(S6, L6, V6, out);
-        if (!ok)  // R for pc_body_pinv_kernel
-            for (int k = 0; k < 36; ++k) out[k] = S6[k];
-        body_pinv[p] = ok ? 0 : 1;
+    if (threadIdx.x < 36) {
+        const int i = threadIdx.x / 6, j = threadIdx.x % 6, c1 = min(i, j), c2 = max(i, j);
+        const int e = c1 * 6 - c1 * (c1 - 1) / 2 + c2 - c1;
+        double v = 0.0;
+        for (int k = 0; k < (int)(blockDim.x >> 6); ++k) v += red[k][e];
+        S6[threadIdx.x] = v;
     }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        double X[6];
+        const bool ok = chol_inv6(S6, threadIdx.x, X);
+        for (int i = 0; i < 6; ++i) V6[i * 6 + threadIdx.x] = X[i];
+        if (threadIdx.x == 0) singular = !ok;
+    }
+    __syncthreads();
+    if (threadIdx.x < 36) {
+        const int i = threadIdx.x / 6, j = threadIdx.x % 6;
+        double v = 0.0;
+        for (int k = max(i, j); k < 6; ++k) v += V6[k * 6 + i] * V6[k * 6 + j];
+        // singular: R for pc_body_pinv_kernel
+        Nt[36 * (size_t)p + threadIdx.x] = singular ? S6[threadIdx.x] : v;
+    }
+    if (threadIdx.x == 0) body_pinv[p] = singular;
 }
 
 // N~_p = R_p^+ (symmetric pseudo-inverse, eigenvalues below 1e-12 of the largest
@@ -1165,14 +1183,14 @@ __device__ __forceinline__ double row_part(const double *__restrict__ Mi, int m,
 constexpr int kApply = 1024;  // threads of the apply kernels
 
 __global__ __launch_bounds__(kApply) void pc_apply1_kernel(
-    int N, const int *__restrict__ blob_off, const int64_t *__restrict__ mat_off,
+    int N, const int *__restrict__ order, const int *__restrict__ blob_off, const int64_t *__restrict__ mat_off,
     const int64_t *__restrict__ z_off, const double *__restrict__ minv,
     const double *__restrict__ Zbuf, const double *__restrict__ Nt, const double *__restrict__ r,
     double *__restrict__ z, double *__restrict__ uhat) {
     __shared__ double x[kMaxM];
     __shared__ double part[kApply];
     __shared__ double w6[6];
-    const int p = blockIdx.x, tid = threadIdx.x;
+    const int p = order ? order[blockIdx.x] : blockIdx.x, tid = threadIdx.x;
     const int b0 = blob_off[p], m = 3 * (blob_off[p + 1] - b0);
     const double *Mi = minv + mat_off[p];
     const double *Z = Zbuf + z_off[p];
@@ -1719,88 +1737,197 @@ void precond_assemble(hipStream_t s, const PrecondDev &P, const double *pos, dou
                       bool wall) {
     if (P.M <= 0) return;
     const CoefD c = make_coef<CoefD, double>(a);
-    pc_assemble_kernel<<<P.M, 256, 0, s>>>(P.blob_off, P.mat_off, pos, c, 1.0 / (8 * kPi * eta),
-                                           wall ? 1 : 0, a, P.mats, P.status);
+    // a few bodies: several workgroups each
+    const int parts = std::min(16, std::max(1, 1024 / P.M));
+    pc_assemble_kernel<<<dim3(P.M, parts), 256, 0, s>>>(P.order, P.blob_off, P.mat_off, pos, c,
+                                                        1.0 / (8 * kPi * eta), wall ? 1 : 0, a,
+                                                        P.mats, P.status);
 }
 
 // SPD inverse of each matrix of the batch by the symmetric block sweep (block
 // Gauss-Jordan elimination without pivoting, which positive definite matrices
 // allow; the pivot blocks are the Schur complements of the Cholesky
 // factorisation), out of place, for matrices of at most kSwRows rows.  One
-// workgroup of 512 threads per matrix holds its lower triangle in registers as
-// 16 x 16 tiles in the matrix-core accumulator layout: tile t = (ti, tj), tj <= ti,
-// counted row by row, belongs to wavefront t % 8 (slot t / 8).  Rows beyond m
-// are padded with the identity.  Sweeping block k with P = A_kk^-1 takes, with
-// the values before the step,
+// workgroup per matrix holds its lower triangle in registers as 16 x 16 tiles in the
+// matrix-core accumulator layout: tile t = (ti, tj), tj <= ti, counted row by row,
+// belongs to wavefront t % WAVES (slot t / WAVES).  Rows beyond m are padded with the
+// identity.  Sweeping block k with P = A_kk^-1 takes, with the values before the step,
 //   A_ij -= A_ik P A_kj (i, j != k),   A_ik <- A_ik P,   A_kk <- -P,
-// which keeps the matrix symmetric; after the last block it holds -A^-1.  Per
-// step: the block column k is copied to LDS (C_r = A_rk, the tiles of row k
-// transposed); one wavefront inverts D = A_kk in place there by Gauss-Jordan
-// steps, testing each pivot (the Cholesky pivots, L_ii^2)
-// against rel_tol * (largest diagonal entry) as pc_potrf does and storing
-// sqrt(pivot) as diag(L) when asked; W_r = C_r P is formed on the matrix cores
-// (wavefront r % 8 takes block row r); every wavefront then updates its tiles on the
-// matrix cores, A_ij -= W_i C_j^T.  The flop count equals that of factor,
-// triangular inverse and product (m^3 in all), with the matrix read once and
-// its inverse (both triangles) written once.  Dynamic LDS: C and W, 16 nb rows
-// of kSwLd doubles each.
+// which keeps the matrix symmetric; after the last block it holds -A^-1.  Per step:
+// W_r = C_r P (C_r = A_rk) is formed on the matrix cores, block row r by wavefront
+// r % WAVES; then every wavefront updates its tiles there, A_ij -= W_i C_j^T.  The
+// next step's serial part runs under that update: the wavefront that holds A_k+1,k+1
+// updates it first and inverts it in registers (sweep_invert16), and the tiles of
+// block column k+1 go to the other C buffer as they are updated, so a step has two
+// barriers.  The flop count equals that of factor, triangular inverse and product
+// (m^3 in all), with the matrix read once and its inverse (both triangles) written
+// once.  Dynamic LDS: two C, W, and two each of P, P^T and A_kk, 16 nb or 16 rows of
+// kSwLd doubles.
+// Bound by the matrix cores and by memory in turn: one 240-row matrix takes 118 us (51 at
+// the FP64 peak of one compute unit; 159 with the inverse between barriers and a branch
+// per tile), of which the updates are 12,000 of 15,400 cycles a step, two wavefronts to a
+// SIMD.  16 wavefronts spill (114 us, 534 for 512 bacteria against 541 then).  512 bacteria
+// (a 126- and a 240-row matrix each): 688 -> 399 us, most of it from the order
+// (MatBatch::order).
 constexpr int kSwRows = 256;
-constexpr int kSwThreads = 512;
-constexpr int kSwWaves = kSwThreads / 64;
 constexpr int kSwLd = 17;
 // matrices of at most kSwSmall tile rows (144 rows) take an instance with fewer
 // registers, two or more workgroups per compute unit
-constexpr int kSwSmall = 9;
+constexpr int kSwSmall = kSweepSmall / 16;
+constexpr int kSwMaxWaves = 8;
 
 size_t sweep_lds_bytes(int max_m) {
     const int nb = (max_m + 15) / 16;
-    return 2 * (size_t)16 * nb * kSwLd * sizeof(double);
+    return (size_t)16 * (std::max(3 * nb, kSwMaxWaves) + 6) * kSwLd * sizeof(double);
 }
 
-// NBMAX: the most tile rows this instance holds; matrices of at most nb_lo tile
-// rows (or more than NBMAX) are skipped
-template <int NBMAX>
-__global__ __launch_bounds__(kSwThreads) void pc_sweep_kernel(MatBatch B, int nb_lo) {
-    constexpr int kSwSlots = (NBMAX * (NBMAX + 1) / 2 + kSwWaves - 1) / kSwWaves;
+// lane Q of each row of 16 lanes, to the whole row
+template <int Q>
+__device__ __forceinline__ double row_bcast(double x) {
+    return __builtin_amdgcn_update_dpp(0.0, x, 0x150 + Q, 0xf, 0xf, true);
+}
+
+// row G of 16 lanes, to all four rows
+template <int G>
+__device__ __forceinline__ unsigned all_rows(unsigned x) {
+    const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    const unsigned y = h[G >> 1];
+    const auto r = __builtin_amdgcn_permlane16_swap(y, y, false, false);
+    return r[G & 1];
+}
+
+// D_Q,c in every row of lanes, and its entry Q
+template <int Q>
+__device__ __forceinline__ void sweep_pivot_row(const double *d, double &row, double &piv) {
+    row = __hiloint2double(all_rows<Q & 3>(__double2hiint(d[Q >> 2])),
+                           all_rows<Q & 3>(__double2loint(d[Q >> 2])));
+    piv = row_bcast<Q>(row);
+}
+
+// one pivot of sweep_invert16; row, piv, ip = 1 / piv of this pivot, then of the next,
+// whose row is updated first: its reciprocal's chain runs under the other rows' updates
+template <int Q>
+__device__ __forceinline__ void sweep_pivot(double *d, int lr, int lc, double tol, bool &bad,
+                                            double &mypiv, double &row, double &piv, double &ip) {
+    // a failed pivot is recorded, the (meaningless) steps still run
+    bad |= !(piv > tol);
+    mypiv = lr == 0 && lc == Q ? piv : mypiv;
+    // pivot row scaled, pivot column scaled and negated, the rest eliminated: the pivot
+    // column takes the elimination's form with 0 in place of the entry
+    const double rq = lc == Q ? ip : row * ip;
+    auto eliminate = [&](int e) {
+        const double el = fma(-row_bcast<Q>(d[e]), rq, lc == Q ? 0.0 : d[e]);
+        d[e] = e == (Q >> 2) && lr == (Q & 3) ? rq : el;
+    };
+    constexpr int kNext = Q < 15 ? Q + 1 : Q, e0 = kNext >> 2;
+    eliminate(e0);
+    if (Q < 15) sweep_pivot_row<kNext>(d, row, piv);
+    __builtin_amdgcn_sched_barrier(0);
+    // 1 / piv: the hardware estimate and two Newton steps
+    ip = __builtin_amdgcn_rcp(piv);
+    eliminate((e0 + 1) & 3);
+    double t = fma(-piv, ip, 1.0);
+    ip = fma(t, ip, ip);
+    eliminate((e0 + 2) & 3);
+    t = fma(-piv, ip, 1.0);
+    ip = fma(t, ip, ip);
+    eliminate((e0 + 3) & 3);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// D <- D^-1 by Gauss-Jordan steps in one wavefront, lane l holding D[4 e + l / 16][l % 16]:
+// lane moves only (through LDS, which every pivot wrote and read again, a block took
+// about 5 us).  Lane q < 16 gets pivot q; false if a pivot was not above tol.
+template <int... Q>
+__device__ __forceinline__ bool sweep_invert16(double *d, int lr, int lc, double tol,
+                                               double &mypiv, std::integer_sequence<int, Q...>) {
+    bool bad = false;
+    double row, piv;
+    sweep_pivot_row<0>(d, row, piv);
+    double ip = __builtin_amdgcn_rcp(piv);
+    ip = fma(fma(-piv, ip, 1.0), ip, ip);
+    ip = fma(fma(-piv, ip, 1.0), ip, ip);
+    (sweep_pivot<Q>(d, lr, lc, tol, bad, mypiv, row, piv, ip), ...);
+    return !bad;
+}
+
+// NBMAX: the most tile rows this instance holds (matrices of more are skipped)
+template <int NBMAX, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, NBMAX <= kSwSmall ? 4 : 2) void pc_sweep_kernel(MatBatch B) {
+    constexpr int kSwSlots = (NBMAX * (NBMAX + 1) / 2 + WAVES - 1) / WAVES;
+    // slots without a branch between them
+    constexpr int kRun = 3;
     extern __shared__ double sw_lds[];
     __shared__ int fail;
     __shared__ double piv_tol;
-    __shared__ double red[kSwWaves];
-    const int p = blockIdx.x;
+    __shared__ double red[WAVES];
+    const int p = B.order ? B.order[blockIdx.x] : blockIdx.x;
     if (mat_skip(B, p)) return;
     const int m = mat_rows(B, p);
     const int nb = (m + 15) >> 4, T = nb * (nb + 1) / 2;
-    if (nb <= nb_lo || nb > NBMAX) return;
-    double *Cb = sw_lds;                            // C_r = A_rk, 16 nb x kSwLd
-    double *Wb = sw_lds + (size_t)16 * nb * kSwLd;  // W_r = C_r P
+    if (nb == 0 || nb > NBMAX) return;
+    const int buf = 16 * nb * kSwLd;
+    // LDS, in doubles: C_r = A_rk of this and the next step, -W_r, P (even and odd
+    // steps), P^T (the same), A_kk of the next step (the same) before its update by this one
+    const int oW = 2 * buf, oP = oW + buf, oT = oP + 32 * kSwLd, oD = oT + 32 * kSwLd;
     const double *A = B.mats + B.mat_off[p];
     double *Out = B.out + B.mat_off[p];
     const int tid = threadIdx.x, l = tid & 63, lr = l >> 4, lc = l & 15;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // this wavefront's tiles: row i of tile t is the largest with i (i + 1) / 2 <= t
-    int ti[kSwSlots], tj[kSwSlots];
+    // this wavefront's tiles t0 .. t0 + nt - 1, row by row; row | column << 8 in scalar
+    // registers.  Wavefront 0 inverts the diagonal blocks and takes what the others leave
+    const int per = min(kSwSlots, (T + WAVES - 2) / (WAVES - 1));
+    const int t0 = min(T, (w > 0 ? w - 1 : WAVES - 1) * per), nt = min(per, T - t0);
+    int tij[kSwSlots];
+    int li = 255, lj = 255;  // lane s: the tile of slot s (255: none)
+    {
+        int i = 0, j = t0;
+        for (; j > i; ++i) j -= i + 1;
 #pragma unroll
-    for (int s = 0; s < kSwSlots; ++s) {
-        const int t = w + kSwWaves * s;
-        int i = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
-        i += (i + 1) * (i + 2) / 2 <= t;
-        i -= i * (i + 1) / 2 > t;
-        ti[s] = i;
-        tj[s] = t - i * (i + 1) / 2;
+        for (int s = 0; s < kSwSlots; ++s) {
+            tij[s] = __builtin_amdgcn_readfirstlane(i | j << 8);
+            if (l == s && s < nt) {
+                li = i;
+                lj = j;
+            }
+            if (++j > i) {
+                j = 0;
+                ++i;
+            }
+        }
     }
-    // load the lower triangle (the upper part of diagonal tiles by symmetry)
+    // load the lower triangle (the upper part of diagonal tiles by symmetry), from offsets
+    // clamped into the matrix, a run of slots at a time (a branch, an address and a wait
+    // per entry took 17 us of 160)
     mfma_acc acc[kSwSlots];
     double dloc = 0.0;
+    unsigned o_diag[4];  // entry (4 e + lr, lc) of a diagonal tile, taken from below
 #pragma unroll
-    for (int s = 0; s < kSwSlots; ++s) {
-        if (w + kSwWaves * s >= T) continue;
+    for (int e = 0; e < 4; ++e) o_diag[e] = max(4 * e + lr, lc) * m + min(4 * e + lr, lc);
+    const unsigned o_tile = lr * m + lc;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int r = 16 * ti[s] + 4 * e + lr, c = 16 * tj[s] + lc;
-            double v = r == c ? 1.0 : 0.0;
-            if (r < m && c < m) v = c <= r ? A[(size_t)r * m + c] : A[(size_t)c * m + r];
-            acc[s][e] = v;
-            if (r == c && r < m) dloc = fmax(dloc, v);
+    for (int s0 = 0; s0 < kSwSlots; s0 += kRun) {
+        if (s0 >= nt) continue;
+#pragma unroll
+        for (int s = s0; s < kSwSlots && s < s0 + kRun; ++s) {
+            const int i = min(tij[s] & 255, nb - 1), j = min(tij[s] >> 8, nb - 1);
+            const unsigned at = 16 * (i * m + j), last = m * m - 1 - at;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc[s][e] = A[at + min(i == j ? o_diag[e] : o_tile + 4 * e * m, last)];
+        }
+#pragma unroll
+        for (int s = s0; s < kSwSlots && s < s0 + kRun; ++s) {
+            const int i = tij[s] & 255, j = tij[s] >> 8;
+            if (i >= nb - 1)  // the last tile row: the identity beyond m
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (16 * i + 4 * e + lr >= m || 16 * j + lc >= m)
+                        acc[s][e] = i == j && 4 * e + lr == lc ? 1.0 : 0.0;
+            if (i == j && i < nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (4 * e + lr == lc && 16 * i + lc < m) dloc = fmax(dloc, acc[s][e]);
         }
     }
     if (B.rel_tol > 0.0) {
@@ -1812,104 +1939,123 @@ __global__ __launch_bounds__(kSwThreads) void pc_sweep_kernel(MatBatch B, int nb
     if (tid == 0) {
         double dmax = 0.0;
         if (B.rel_tol > 0.0)
-            for (int q = 0; q < kSwWaves; ++q) dmax = fmax(dmax, red[q]);
+            for (int q = 0; q < WAVES; ++q) dmax = fmax(dmax, red[q]);
         piv_tol = B.rel_tol * dmax;
     }
-    for (int k = 0; k < nb; ++k) {
-        double *Dk = Cb + (size_t)16 * k * kSwLd;  // rows of C holding D = A_kk, then P
-        __syncthreads();  // the previous step's reads of C and W are done
-        // 1. block column k: C_r = A_rk (tiles (r, k), r >= k, and (k, r)^T, r < k)
+    // lane offsets into rows and columns of a 16 x 16 LDS block.  They pass through an
+    // empty asm every step: hoisted out of the loop, two addresses a tile would spill
+    int o_row = lc * kSwLd + lr, o_col = lr * kSwLd + lc;
+    // tiles after step k - 1: those of block column k to its buffer, A_k+1,k+1 to where
+    // wavefront 0 takes it up
+    auto publish = [&](int k) __attribute__((always_inline)) {
+        const bool diag = li == lj && li == k + 1;
+        // as rows of the buffer (i, k), or transposed (k, j)
+        const bool col = lj == k || diag;
+        const uint64_t sel = __ballot(diag || (li == k) != (lj == k));
+        const int base = diag ? oD + 16 * (li & 1) * kSwLd
+                              : (k & 1) * buf + 16 * (col ? li : lj) * kSwLd;
+        const uint64_t cols = __ballot(col);
+        const int o_diff = o_col - o_row;
 #pragma unroll
         for (int s = 0; s < kSwSlots; ++s) {
-            if (w + kSwWaves * s >= T) continue;
-            if (tj[s] == k) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Cb[(16 * ti[s] + 4 * e + lr) * kSwLd + lc] = acc[s][e];
-            } else if (ti[s] == k) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Cb[(16 * tj[s] + lc) * kSwLd + 4 * e + lr] = acc[s][e];
+            const int at = __builtin_amdgcn_readlane(base, s);
+            const bool c = cols >> s & 1;
+            double *q = sw_lds + at + o_row + (c ? o_diff : 0);
+            const int st = c ? 4 * kSwLd : 4;
+            if (sel >> s & 1) {
+                q[0] = acc[s][0];
+                q[st] = acc[s][1];
+                q[2 * st] = acc[s][2];
+                q[3 * st] = acc[s][3];
             }
         }
+    };
+    // wavefront 0: A_kk, its update by the step before (none before the first), P
+    auto invert = [&](int k) __attribute__((always_inline)) {
+        const double *D = sw_lds + oD + 16 * (k & 1) * kSwLd + o_col;
+        mfma_acc x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = D[4 * e * kSwLd];
+        if (k > 0) {
+            const double *W = sw_lds + oW + 16 * k * kSwLd + o_row;
+            const double *C = sw_lds + ((k - 1) & 1) * buf + 16 * k * kSwLd + o_row;
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) x = mfma_f64_16x16x4(W[4 * kk], C[4 * kk], x);
+        }
+        double d[4] = {x[0], x[1], x[2], x[3]};
+        double mypiv = 1.0;  // lane q < 16: pivot q
+        const bool ok = sweep_invert16(d, lr, lc, piv_tol, mypiv,
+                                       std::make_integer_sequence<int, 16>());
+        double *P = sw_lds + oP + 16 * (k & 1) * kSwLd + o_col;
+        double *PT = sw_lds + oT + 16 * (k & 1) * kSwLd + o_row;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            P[4 * e * kSwLd] = d[e];
+            PT[4 * e] = d[e];
+        }
+        if (B.ldiag && l < 16 && 16 * k + l < m)
+            B.ldiag[B.scale * (int64_t)B.off[p] + 16 * k + l] = sqrt(mypiv);
+        if (!ok && l == 0) fail = 1;  // checked at the end: a way out of the loop costs 40
+    };                                // copies of accumulators a step
+    publish(0);
+    publish(-1);
+    __syncthreads();
+    if (w == 0) invert(0);
+    for (int k = 0; k < nb; ++k) {
+        double *C = sw_lds + (k & 1) * buf;
         __syncthreads();
-        // 2. P = D^-1 by Gauss-Jordan in wavefront 0, in place in the LDS rows of C
-        // that hold D (no later use of C_k): lane l keeps D[4e + l/16][l%16] in
-        // registers and publishes it after every pivot; one wavefront's LDS
-        // operations complete in order, so each pivot reads the previous one's
-        // values (the fences keep the compiler from reordering them)
-        if (w == 0) {
-            const double tol = piv_tol;
-            double d[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) d[e] = Dk[(4 * e + lr) * kSwLd + lc];
-            bool bad = false;
-            double mypiv = 1.0;  // lane q < 16: pivot q
-#pragma unroll 1
-            for (int q = 0; q < 16; ++q) {
-                const double piv = Dk[q * kSwLd + q];
-                const double rqc = Dk[q * kSwLd + lc];  // D_q,c
-                double cq[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) cq[e] = Dk[(4 * e + lr) * kSwLd + q];  // D_r,q
-                // a failed pivot is recorded, the (meaningless) steps still run
-                bad |= !(piv > tol);
-                mypiv = l == q ? piv : mypiv;
-                // 1 / piv: the hardware estimate and two Newton steps
-                double ip = __builtin_amdgcn_rcp(piv);
-                ip = fma(fma(-piv, ip, 1.0), ip, ip);
-                ip = fma(fma(-piv, ip, 1.0), ip, ip);
-                const double rq = rqc * ip;
+        asm volatile("" : "+v"(o_row), "+v"(o_col));
+        // W_r = C_r P (stored negated), block row r by wavefront r % WAVES; block k of
+        // both: -I
+        for (int r = w; r < nb; r += WAVES) {
+            double *W = sw_lds + oW + 16 * r * kSwLd + o_col;
+            if (r == k) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    // pivot row scaled, pivot column scaled and negated, the rest
-                    // eliminated; selects, no branches
-                    const bool rowq = 4 * e + lr == q, colq = lc == q;
-                    const double sc = d[e] * ip, el = fma(-cq[e], rq, d[e]);
-                    d[e] = rowq ? (colq ? ip : sc) : (colq ? -sc : el);
+                    const double v = 4 * e + lr == lc ? -1.0 : 0.0;
+                    W[4 * e * kSwLd] = v;
+                    C[(16 * r + 4 * e) * kSwLd + o_col] = v;
                 }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Dk[(4 * e + lr) * kSwLd + lc] = d[e];
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                continue;
             }
-            if (B.ldiag && l < 16 && 16 * k + l < m)
-                B.ldiag[B.scale * (int64_t)B.off[p] + 16 * k + l] = sqrt(mypiv);
-            if (bad && l == 0) fail = 1;
-        }
-        __syncthreads();
-        if (fail) break;
-        // 3. W_r = C_r P, block row r by wavefront r % kSwWaves
-        for (int r = w; r < nb; r += kSwWaves) {
-            if (r == k) continue;
+            const double *P = sw_lds + oP + 16 * (k & 1) * kSwLd + o_col;
             mfma_acc x = {};
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk)
-                x = mfma_f64_16x16x4(Cb[(16 * r + lc) * kSwLd + 4 * kk + lr],
-                                     Dk[(4 * kk + lr) * kSwLd + lc], x);
+                x = mfma_f64_16x16x4(C[16 * r * kSwLd + 4 * kk + o_row], P[4 * kk * kSwLd], x);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) Wb[(16 * r + 4 * e + lr) * kSwLd + lc] = x[e];
+            for (int e = 0; e < 4; ++e) W[4 * e * kSwLd] = -x[e];
         }
         __syncthreads();
-        // 4. the tiles: A_ij -= W_i C_j^T; A_ik <- W_i; A_kj <- W_j^T; A_kk <- -P
+        // A_k+1,k+1 and its inverse; the tiles: A_ij -= W_i C_j^T.  Those of row and
+        // column k start from 0 and have -I as one factor (exact): A_ik <- W_i I,
+        // A_kj <- I W_j^T, A_kk <- -I P, so that a run of slots has no branch (a branch
+        // per tile cost 1,200 cycles a tile, against 256 of its products)
+        if (w == 0 && k + 1 < nb) invert(k + 1);
+        const uint64_t zero = __ballot(li == k || lj == k);
+        const int offA = oW + 16 * li * kSwLd;
+        const int offB = li != k   ? (k & 1) * buf + 16 * lj * kSwLd
+                         : lj != k ? oW + 16 * lj * kSwLd
+                                   : oT + 16 * (k & 1) * kSwLd;
 #pragma unroll
-        for (int s = 0; s < kSwSlots; ++s) {
-            if (w + kSwWaves * s >= T) continue;
-            const int i = ti[s], j = tj[s];
-            if (i != k && j != k) {
+        for (int s0 = 0; s0 < kSwSlots; s0 += kRun) {
+            if (s0 >= nt) continue;
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk)
-                    acc[s] = mfma_f64_16x16x4(-Wb[(16 * i + lc) * kSwLd + 4 * kk + lr],
-                                              Cb[(16 * j + lc) * kSwLd + 4 * kk + lr], acc[s]);
-            } else if (i != k) {
+            for (int q = 0; q < kRun; ++q) {
+                const int s = s0 + q;
+                if (s >= kSwSlots) continue;
+                const bool z = zero >> s & 1;
+                const double *qa = sw_lds + __builtin_amdgcn_readlane(offA, s) + o_row;
+                const double *qb = sw_lds + __builtin_amdgcn_readlane(offB, s) + o_row;
+                mfma_acc x;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[s][e] = Wb[(16 * i + 4 * e + lr) * kSwLd + lc];
-            } else if (j != k) {
+                for (int e = 0; e < 4; ++e) x[e] = z ? 0.0 : acc[s][e];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[s][e] = Wb[(16 * j + lc) * kSwLd + 4 * e + lr];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[s][e] = -Dk[(4 * e + lr) * kSwLd + lc];
+                for (int kk = 0; kk < 4; ++kk) x = mfma_f64_16x16x4(qa[4 * kk], qb[4 * kk], x);
+                acc[s] = x;
             }
         }
+        publish(k + 1);
     }
     if (fail) {
         if (tid == 0) {
@@ -1920,51 +2066,69 @@ __global__ __launch_bounds__(kSwThreads) void pc_sweep_kernel(MatBatch B, int nb
         }
         return;
     }
-    // A^-1 = -(the tiles), both triangles
+    // A^-1 = -(the tiles), both triangles; the upper one through LDS, so that both are
+    // written in rows of 128 bytes
+    __syncthreads();
+    double *tr = sw_lds + 16 * w * kSwLd;
 #pragma unroll
     for (int s = 0; s < kSwSlots; ++s) {
-        if (w + kSwWaves * s >= T) continue;
+        if (s >= nt) continue;
+        const int i = 16 * (tij[s] & 255), j = 16 * (tij[s] >> 8);
+        const bool whole = i + 16 <= m;
+        double *lo = Out + ((size_t)i * m + j);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int r = 16 * ti[s] + 4 * e + lr, c = 16 * tj[s] + lc;
-            if (r < m && c < m) {
-                Out[(size_t)r * m + c] = -acc[s][e];
-                if (ti[s] != tj[s]) Out[(size_t)c * m + r] = -acc[s][e];
-            }
+            const double v = -acc[s][e];
+            if (whole || (i + 4 * e + lr < m && j + lc < m)) lo[o_tile + 4 * e * m] = v;
+            tr[4 * e * kSwLd + o_col] = v;
         }
+        if (i == j) continue;
+        asm volatile("" ::: "memory");
+        double *up = Out + ((size_t)j * m + i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double v = tr[4 * e + o_row];
+            if (whole || i + lc < m) up[o_tile + 4 * e * m] = v;
+        }
+        asm volatile("" ::: "memory");
     }
 }
 
 bool precond_factor_in_place(int max_m) { return max_m > kSwRows; }
 
-// the sweep over a batch of count matrices of at most max_m <= kSwRows rows: the
-// small instance when every matrix fits it, else the large one for all of them
-// (one launch keeps small and large matrices interleaved over the compute units;
-// two launches measured slower on the bacteria)
-static hipError_t launch_sweep(hipStream_t s, const MatBatch &B, int count, int max_m) {
+template <int NBMAX, int WAVES>
+static hipError_t launch_sweep_as(hipStream_t s, const MatBatch &B, int count, int max_m) {
     const size_t lds = sweep_lds_bytes(max_m);
-    if (max_m <= 16 * kSwSmall) {
-        const hipError_t e = hipFuncSetAttribute((const void *)pc_sweep_kernel<kSwSmall>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)lds);
-        if (e != hipSuccess) return e;
-        pc_sweep_kernel<kSwSmall><<<count, kSwThreads, lds, s>>>(B, 0);
-    } else {
-        const hipError_t e = hipFuncSetAttribute((const void *)pc_sweep_kernel<kSwRows / 16>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)lds);
-        if (e != hipSuccess) return e;
-        pc_sweep_kernel<kSwRows / 16><<<count, kSwThreads, lds, s>>>(B, 0);
-    }
+    const hipError_t e = hipFuncSetAttribute((const void *)pc_sweep_kernel<NBMAX, WAVES>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    pc_sweep_kernel<NBMAX, WAVES><<<count, 64 * WAVES, lds, s>>>(B);
     return hipSuccess;
+}
+
+// the sweep over a batch of count matrices of at most max_m <= kSwRows rows, n_large of
+// them (the first of B.order) beyond the small instance: the small instance when every
+// matrix fits it, else the large one for all of them in one launch (small matrices then
+// run beside the large ones), else, when both kinds fill the chip, one launch of each:
+// two small ones share a compute unit (512 bacteria: 416 us in one
+// launch, 399 in two)
+static hipError_t launch_sweep(hipStream_t s, MatBatch B, int count, int max_m, int n_large) {
+    constexpr int kUnits = 256;  // compute units, one large matrix each
+    if (max_m <= 16 * kSwSmall) return launch_sweep_as<kSwSmall, 8>(s, B, count, max_m);
+    if (!B.order || n_large < kUnits || count - n_large < kUnits)
+        return launch_sweep_as<kSwRows / 16, 8>(s, B, count, max_m);
+    const hipError_t e = launch_sweep_as<kSwRows / 16, 8>(s, B, n_large, max_m);
+    if (e != hipSuccess) return e;
+    B.order += n_large;
+    return launch_sweep_as<kSwSmall, 8>(s, B, count - n_large, 16 * kSwSmall);
 }
 
 hipError_t precond_factor(hipStream_t s, const PrecondDev &P, const double *dvec, int max_m) {
     if (P.M <= 0) return hipSuccess;
     if (max_m <= kSwRows) {
         const MatBatch B{P.blob_off, 3, P.mat_off, P.mats, P.ldiag, P.dinv, P.minv, P.status,
-                         nullptr, 0.0};
-        const hipError_t e = launch_sweep(s, B, P.M, max_m);
+                         nullptr, 0.0, P.order};
+        const hipError_t e = launch_sweep(s, B, P.M, max_m, P.n_large);
         if (e != hipSuccess) return e;
     } else if (max_m <= kFastMaxM) {
         const int nbk = (max_m + kNB - 1) / kNB;
@@ -1974,7 +2138,7 @@ hipError_t precond_factor(hipStream_t s, const PrecondDev &P, const double *dvec
         if (e != hipSuccess) return e;
         const int nt = (max_m + 63) / 64;
         const MatBatch B{P.blob_off, 3, P.mat_off, P.mats, P.ldiag, P.dinv, P.minv, P.status,
-                         nullptr, 0.0};
+                         nullptr, 0.0, nullptr};
         pc_potrf_kernel<<<P.M, 256, 0, s>>>(B);
         pc_trtri_kernel<<<dim3(nbk, P.M), 256, lds_i, s>>>(B);
         pc_lauum_kernel<<<dim3(nt * (nt + 1) / 2, P.M), 256, 0, s>>>(B);
@@ -1984,8 +2148,8 @@ hipError_t precond_factor(hipStream_t s, const PrecondDev &P, const double *dvec
                                               P.status);
         pc_restore_diag_kernel<<<P.M, 256, 0, s>>>(P.blob_off, P.mat_off, P.mats, P.ldiag);
     }
-    pc_body_kernel<<<P.M, 256, 0, s>>>(P.blob_off, P.mat_off, P.z_off, P.minv, dvec, P.Z, P.Nt,
-                                       P.body_pinv, P.status);
+    pc_body_kernel<<<P.M, 256, 0, s>>>(P.order, P.blob_off, P.mat_off, P.z_off, P.minv, dvec, P.Z,
+                                       P.Nt, P.body_pinv, P.status);
     pc_body_pinv_kernel<<<(P.M + 63) / 64, 64, 0, s>>>(P.M, P.body_pinv, P.Nt, P.status);
     return hipGetLastError();
 }
@@ -2072,9 +2236,9 @@ hipError_t precond_assembly(hipStream_t s, const PrecondDev &P) {
                                                P.row_p, P.row_q, P.crow, P.Nt, P.S, P.asm_fail,
                                                P.status, max_m);
     const MatBatch B{P.asm_row_ptr, 1, P.asm_mat_off, P.S, nullptr, P.asm_dinv, P.G, P.status,
-                     P.asm_fail, 1e-12};
+                     P.asm_fail, 1e-12, nullptr};
     if (sweep) {
-        e = launch_sweep(s, B, P.A, max_m);
+        e = launch_sweep(s, B, P.A, max_m, 0);
         if (e != hipSuccess) return e;
     } else {
         pc_potrf_kernel<<<P.A, 256, 0, s>>>(B);
@@ -2104,8 +2268,8 @@ void precond_apply(hipStream_t s, const PrecondDev &P, int N, const double *r, d
                                                      P.tminv, P.tZ, P.R9, P.Nt, P.lcorr, r, z,
                                                      P.tmp, P.stmp);
     else
-        pc_apply1_kernel<<<P.M, kApply, 0, s>>>(N, P.blob_off, P.mat_off, P.z_off, P.minv, P.Z, P.Nt,
-                                             r, z, P.tmp);
+        pc_apply1_kernel<<<P.M, kApply, 0, s>>>(N, P.order, P.blob_off, P.mat_off, P.z_off, P.minv,
+                                                P.Z, P.Nt, r, z, P.tmp);
     if (P.A > 0)
         pc_apply2_kernel<<<P.A, 256, 0, s>>>(N, P.M, P.asm_row_ptr, P.asm_rows, P.asm_mat_off,
                                              P.row_p, P.row_q, P.crow, P.G, r, P.tmp, z);

@@ -364,6 +364,40 @@ def test_preconditioner_large_bodies(n_helix):
         arb.arb_destroy(ctx)
 
 
+@pytest.mark.parametrize("sizes", [
+    (3, 5, 6, 11, 16, 17, 48),                           # the small instance, 1 to 9 tile rows
+    (3, 80, 5, 85, 48, 49, 6, 64, 17, 81),               # up to 16 tile rows, small ones beside
+    (49, 6) * 256])                                      # a launch for each kind
+def test_block_inverses_of_every_tile_count(sizes):
+    # free bodies: the apply of each is its own block's, compared with the oracle's
+    # preconditioner of that body alone
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    body = lambda n: np.stack([1.5 * np.cos(np.arange(n)), 1.5 * np.sin(np.arange(n)),
+                               1.1 * (np.arange(n) - 0.5 * (n - 1))], 1)
+    M = len(sizes)
+    q = np.zeros((M, 3))
+    q[:, 0] = 7.0 * np.arange(M)
+    theta = np.tile([1.0, 0.0, 0.0, 0.0], (M, 1))
+    mk = lambda ps: W.Workload("tiles", 1.0, 1.0, False, np.vstack([body(sizes[p]) for p in ps]),
+                               np.concatenate([[0], np.cumsum([sizes[p] for p in ps])])
+                               .astype(np.int32), q[ps], theta[ps], np.zeros((len(ps), 6)),
+                               **W._links(0))
+    wl = mk(list(range(M)))
+    r = np.random.default_rng(M).standard_normal(wl.n_unknowns)
+    ctx = arb.context_for(wl, precision=arb.ARB_FP64)
+    try:
+        assert arb.arb_precond_build(ctx) in (arb.ARB_OK, arb.ARB_W_PINV_USED)
+        z = arb.arb_precond_apply(ctx, r)
+    finally:
+        arb.arb_destroy(ctx)
+    for p in (range(M) if M < 20 else (0, 1, 255, 256, 510, 511)):
+        one = mk([p])
+        S = system.assemble(one)
+        sel = np.r_[3 * off[p]:3 * off[p + 1], 3 * wl.N + 6 * p:3 * wl.N + 6 * p + 6]
+        zo = precond.BlockPreconditioner(one, S["r"], S["C"]).apply(r[sel])
+        assert rel(z[sel], zo) <= 1e-11, (p, sizes[p])
+
+
 @pytest.mark.parametrize("bodies_,blobs,rows", [
     (1, 1, 0), (1, 341, 0), (1, 342, 0),     # 1,023 and 1,026 blob rows
     (11, 31, 3), (11, 32, 3),                # the same, over a chain
