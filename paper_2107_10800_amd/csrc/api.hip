@@ -4,6 +4,7 @@
 // krylov.hip and correct.hip.
 #include <algorithm>
 #include <chrono>
+#include <climits>
 #include <cmath>
 #include <cstring>
 #include <numeric>
@@ -723,7 +724,7 @@ arb::PrecondDev pc_view(arb_ctx *ctx) {
     P.M = ctx->M;
     P.A = ctx->n_asm;
     P.blob_off = ctx->blob_off.as<int>();
-    P.order = ctx->body_order.as<int>();
+    if (ctx->sorted_bodies) P.order = ctx->body_of_blob.as<int>() + ctx->N;
     P.n_large = ctx->n_large;
     P.mat_off = ctx->mat_off.as<int64_t>();
     P.z_off = ctx->z_off.as<int64_t>();
@@ -1100,8 +1101,18 @@ arb::SmallSystem small_system(arb_ctx *ctx) {
         S.n_g += na * na;
     }
     S.n_brow_ent = ctx->n_brow_ent;
-    int tpt = 1;  // threads per target: the 512 threads in about one pass
-    while (tpt < 64 && 2 * tpt * S.N <= 512) tpt *= 2;
+    // threads per target: least pair sums on the busiest SIMD over the passes of the
+    // workgroup's threads (80 blobs: 25 with 16 threads a target, 40 with the 4 of one pass)
+    constexpr int kT = arb::kSmallCycleThreads;
+    int tpt = 1;
+    for (int t = 1, best = INT_MAX; t <= 64; t *= 2) {
+        const int threads = t * S.N, each = (S.N + t - 1) / t;
+        const int turns = threads / kT * (kT / 256) + (threads % kT + 255) / 256;
+        if (turns * each < best) {
+            best = turns * each;
+            tpt = t;
+        }
+    }
     S.tpt = tpt;
     return S;
 }
@@ -1593,19 +1604,20 @@ int arb_set_bodies(arb_ctx *ctx, int M, const int32_t *blob_offset, const double
         ctx->h_body_type.assign(M, 0);
     hipStream_t s = ctx->stream;
     TRY(upload(ctx, ctx->blob_off, ctx->h_blob_off.data(), M + 1, s));
-    TRY(upload(ctx, ctx->body_of_blob, ctx->h_body_of_blob.data(), N, s));
     // launches of a workgroup per body take the largest first: in the bodies' order the
     // fixed round of workgroups over XCDs and shader engines can give one engine all of
     // them (alternating sizes: 42- and 80-blob bodies), and the rest waits
     std::vector<int> order(M);
     std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-        return blob_offset[x + 1] - blob_offset[x] > blob_offset[y + 1] - blob_offset[y];
-    });
-    TRY(upload(ctx, ctx->body_order, order.data(), M, s));
-    ctx->n_large = (int)std::count_if(order.begin(), order.end(), [&](int p) {
-        return 3 * (blob_offset[p + 1] - blob_offset[p]) > arb::kSweepSmall;
-    });
+    const auto size = [&](int p) { return blob_offset[p + 1] - blob_offset[p]; };
+    const auto larger = [&](int x, int y) { return size(x) > size(y); };
+    ctx->sorted_bodies = !std::is_sorted(order.begin(), order.end(), larger);
+    if (ctx->sorted_bodies) std::stable_sort(order.begin(), order.end(), larger);
+    std::vector<int> bob_order(ctx->h_body_of_blob);  // one upload: the order follows
+    bob_order.insert(bob_order.end(), order.begin(), order.end());
+    TRY(upload(ctx, ctx->body_of_blob, bob_order.data(), bob_order.size(), s));
+    ctx->n_large = (int)std::count_if(order.begin(), order.end(),
+                                      [&](int p) { return 3 * size(p) > arb::kSweepSmall; });
     TRY(upload(ctx, ctx->r_ref, ctx->h_r_ref.data(), 3 * (size_t)N, s));
     TRY(upload(ctx, ctx->body_type_d, ctx->h_body_type.data(), M, s));
     HIPCHK(hipStreamSynchronize(s));

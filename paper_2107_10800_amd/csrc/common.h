@@ -308,7 +308,7 @@ struct SmallLayout {
     size_t vs, zs, ws, us, w6, yv, p64, dvec, minv, Z, Nt, G, crow, mat_off, z_off, asm_mat_off,
         ints;
     size_t bob, blob_off, brow_ptr, brow_ent, row_p, row_q, asm_row_ptr, asm_rows, slot_a, perm,
-        n_ints;
+        n_ints, vl;
     size_t bytes;
 };
 __host__ __device__ inline SmallLayout small_layout(const SmallSystem &S) {
@@ -358,10 +358,19 @@ __host__ __device__ inline SmallLayout small_layout(const SmallSystem &S) {
     L.perm = q;
     q += S.perm ? S.N : 0;
     L.n_ints = q;
-    L.bytes = 8 * L.ints + 4 * L.n_ints;
+    L.vl = L.ints + (L.n_ints + 3) / 4 * 2;
+    L.bytes = 8 * L.vl;
     return L;
 }
+constexpr int kSmallCycleThreads = 512;
 constexpr size_t kSmallCycleLds = 144 * 1024;  // arena limit (bytes)
+// basis vectors (of m + 1) that fit the arena behind the rest
+__host__ __device__ inline int small_basis_in_lds(const SmallSystem &S, int m) {
+    const size_t b = small_layout(S).bytes;
+    if (b >= kSmallCycleLds) return 0;
+    const size_t fit = (kSmallCycleLds - b) / (8 * (size_t)S.n);
+    return fit < (size_t)m + 1 ? (int)fit : m + 1;
+}
 constexpr int kSmallCycleN = 128;      // blobs
 constexpr int kSmallCycleRows = 64;    // rows of the largest assembly
 // Arnoldi steps 0 .. budget-1 of one cycle from v_0 = V[0..n) (Hbar, cs, sn, g as
@@ -546,9 +555,11 @@ struct arb_ctx {
     int pc_pinv = 0;
     arb::PcFuse pc_fuse;  // of the exact blocks
     int n_large = 0;      // bodies of more than kSweepSmall rows
+    bool sorted_bodies = false;  // the N entries of body_of_blob are followed by the
+                                 // bodies, largest first
 
     // device buffers
-    arb::DevBuf blob_off, body_order, body_of_blob, r_ref, q, theta, R9, pos, dvec, p64, hi, lo,
+    arb::DevBuf blob_off, body_of_blob, r_ref, q, theta, R9, pos, dvec, p64, hi, lo,
         partial, row_p, row_q, row_kind, row_src, row_m, dl_p, dl_q, dldot_p, dldot_q, proj,
         gcoef, grhs, crow, Bc, brow_ptr, brow_ent, asm_body_ptr, asm_bodies, asm_row_ptr,
         asm_rows, asm_mat_off, mat_off, z_off, mats, minv, ldiag, dinv, Z, Nt, G, S, status, pctmp, lcorr, stmp,

@@ -850,71 +850,50 @@ __device__ void asm_stage_rows(int r0, int na, const int *__restrict__ asm_rows,
     }
 }
 
-// Column l of the lower triangle of S_a = C_a N~ C_a^T from the staged rows, by
-// the calling thread: t_side = N~_b c_l,side for the bodies b of row l, then
-// S_kl = sum of c_k,side' . t_side over the side pairs on the same body, k >= l.
-// store(k, value) receives every entry.  The rows are visited from k = 0 (the
-// threads of a wavefront store row k together, at consecutive addresses); rows
-// above the diagonal are skipped.
-template <class F>
-__device__ __forceinline__ void asm_column(int l, int na, const double *cl, const int *bl,
-                                           const double *__restrict__ Nt, F &&store) {
-    double t[2][6];
-    int bs[2];
-#pragma unroll
-    for (int sd = 0; sd < 2; ++sd) {
-        bs[sd] = bl[2 * l + sd];
-        const double *c = cl + 12 * l + 6 * sd;
-        const double *Nb = Nt + 36 * (size_t)max(bs[sd], 0);
-#pragma unroll
-        for (int u = 0; u < 6; ++u) {
-            double v = 0.0;
-            if (bs[sd] >= 0)
-#pragma unroll
-                for (int w = 0; w < 6; ++w) v += Nb[u * 6 + w] * c[w];
-            t[sd][u] = v;
-        }
-    }
-    for (int k = 0; k < na; ++k) {
-        if (k < l) continue;
-        const int b0 = bl[2 * k], b1 = bl[2 * k + 1];
-        double sum = 0.0;
-#pragma unroll
-        for (int sk = 0; sk < 2; ++sk) {
-            const int bk = sk ? b1 : b0;
-            if (bk < 0) continue;
-            const double *c = cl + 12 * k + 6 * sk;
-#pragma unroll
-            for (int sd = 0; sd < 2; ++sd)
-                if (bk == bs[sd])
-#pragma unroll
-                    for (int u = 0; u < 6; ++u) sum += c[u] * t[sd][u];
-        }
-        store(k, sum);
-    }
-}
-
 // the lower triangle of the assemblies' S_a for the blocked kernels (assemblies of
-// at most kFastMaxM rows; the factorisation reads no other entries).  Dynamic LDS:
-// the staged rows, 12 doubles and 2 ints per row of the largest assembly.
-__global__ __launch_bounds__(256) void pc_asm_form_kernel(
+// at most kFastMaxM rows; the factorisation reads no other entries): N~_b c for both
+// sides of each row, then an entry per thread, the sum over the side pairs on the same
+// body (a thread per column took 56 us for 64 diatom colonies, this 25).  Dynamic LDS:
+// the staged rows and N~_b c, 24 doubles and 2 ints per row of the largest assembly.
+constexpr int kAsmForm = 1024;
+__global__ __launch_bounds__(kAsmForm) void pc_asm_form_kernel(
     const int *__restrict__ asm_row_ptr, const int *__restrict__ asm_rows,
     const int64_t *__restrict__ asm_mat_off, const int *__restrict__ row_p,
     const int *__restrict__ row_q, const double *__restrict__ crow, const double *__restrict__ Nt,
     double *__restrict__ Sbuf, int *__restrict__ fail, const int *__restrict__ status,
     int max_rows) {
     extern __shared__ double sm[];
-    double *cl = sm;
-    int *bl = reinterpret_cast<int *>(sm + 12 * (size_t)max_rows);
-    const int a = blockIdx.x;
+    double *cl = sm, *tl = cl + 12 * (size_t)max_rows;  // N~_b c for both sides of each row
+    int *bl = reinterpret_cast<int *>(tl + 12 * (size_t)max_rows);
+    const int a = blockIdx.x, tid = threadIdx.x;
     const int r0 = asm_row_ptr[a], na = asm_row_ptr[a + 1] - r0;
-    if (threadIdx.x == 0) fail[a] = 0;
+    if (tid == 0) fail[a] = 0;
     if (na == 0 || status[0] != 0) return;
     asm_stage_rows(r0, na, asm_rows, row_p, row_q, crow, cl, bl);
     __syncthreads();
+    for (int idx = tid; idx < 12 * na; idx += kAsmForm) {
+        const int l = idx / 12, sd = (idx / 6) & 1, u = idx % 6;
+        const int b = bl[2 * l + sd];
+        double v = 0.0;
+        if (b >= 0)
+            for (int w = 0; w < 6; ++w) v += Nt[36 * (size_t)b + u * 6 + w] * cl[12 * l + 6 * sd + w];
+        tl[idx] = v;
+    }
+    __syncthreads();
     double *S = Sbuf + asm_mat_off[a];
-    for (int l = threadIdx.x; l < na; l += blockDim.x)
-        asm_column(l, na, cl, bl, Nt, [&](int k, double v) { S[(size_t)k * na + l] = v; });
+    for (int k = tid / kWave; k < na; k += kAsmForm / kWave)
+        for (int l = tid % kWave; l <= k; l += kWave) {
+            double sum = 0.0;
+            for (int sk = 0; sk < 2; ++sk) {
+                const int bk = bl[2 * k + sk];
+                if (bk < 0) continue;
+                for (int sl = 0; sl < 2; ++sl)
+                    if (bl[2 * l + sl] == bk)
+                        for (int u = 0; u < 6; ++u)
+                            sum += cl[12 * k + 6 * sk + u] * tl[12 * l + 6 * sl + u];
+            }
+            S[(size_t)k * na + l] = sum;
+        }
 }
 
 // assemblies whose S_a failed the Cholesky pivot test: S_a formed again and its
@@ -938,7 +917,7 @@ __global__ __launch_bounds__(256) void pc_asm_pinv_kernel(
     }
 }
 
-// Assemblies of at most kAsmSmall rows, one workgroup of 1,024 threads each,
+// Assemblies of at most kAsmSmall rows, one workgroup of 256 threads each,
 // everything in LDS (dynamic: S and E, n (n + 1) doubles each, the staged rows and
 // N~_b c per row, for n rows of the largest assembly):
 //   S = C_a N~ C_a^T (lower triangle, an entry per thread);
@@ -947,10 +926,13 @@ __global__ __launch_bounds__(256) void pc_asm_pinv_kernel(
 //   the same row operations applied to the identity in E, which becomes the unit
 //   lower triangular factor E with E S E^T = D (the final pivots);
 //   G~ = S^-1 = E^T D^-1 E, each entry by one thread.
-// A failed pivot flags the assembly for the pseudo-inverse kernel.
-constexpr int kAsmSmall = 64;
-constexpr int kAsmThreads = 1024;
+// A failed pivot flags the assembly for the pseudo-inverse kernel.  A barrier and a
+// division per pivot: 14 us at 12 rows, where forming S and the block sweep take 13 and a
+// launch more; at 27 rows 26.5 us against 16, at 63 91 against 26.
+constexpr int kAsmSmall = 16;
+constexpr int kAsmThreads = 256;
 constexpr int kAsmSlots = kAsmSmall * kAsmSmall / kAsmThreads;  // rows per thread
+constexpr int kAsmStep = kAsmThreads / kAsmSmall;
 __global__ __launch_bounds__(kAsmThreads) void pc_asm_small_kernel(
     const int *__restrict__ asm_row_ptr, const int *__restrict__ asm_rows,
     const int64_t *__restrict__ asm_mat_off, const int *__restrict__ row_p,
@@ -970,7 +952,7 @@ __global__ __launch_bounds__(kAsmThreads) void pc_asm_small_kernel(
     if (na == 0 || status[0] != 0) return;
     asm_stage_rows(r0, na, asm_rows, row_p, row_q, crow, cl, bl);
     for (int idx = tid; idx < kAsmSmall * kAsmSmall; idx += kAsmThreads) {
-        const int i = idx >> 6, c = idx & 63;
+        const int i = idx / kAsmSmall, c = idx % kAsmSmall;
         if (i < na && c <= i) E[i * ld + c] = i == c ? 1.0 : 0.0;
     }
     __syncthreads();
@@ -986,7 +968,7 @@ __global__ __launch_bounds__(kAsmThreads) void pc_asm_small_kernel(
     }
     __syncthreads();
     for (int idx = tid; idx < kAsmSmall * kAsmSmall; idx += kAsmThreads) {
-        const int k = idx >> 6, l = idx & 63;
+        const int k = idx / kAsmSmall, l = idx % kAsmSmall;
         if (k >= na || l > k) continue;
         double sum = 0.0;
         for (int sk = 0; sk < 2; ++sk) {
@@ -1009,7 +991,7 @@ __global__ __launch_bounds__(kAsmThreads) void pc_asm_small_kernel(
     // thread tid owns column c = tid % 64 of rows i = tid / 64 + 16 q (q < kAsmSlots):
     // the column-c entries of row j are read once per pivot, the rows' entries all
     // issued before they are updated
-    const int c = tid & 63, i0 = tid >> 6;
+    const int c = tid % kAsmSmall, i0 = tid / kAsmSmall;
     for (int j = 0; j < na; ++j) {
         const double d = S[j * ld + j];
         if (!(d > tol)) {  // the same value for every thread: a uniform exit
@@ -1026,13 +1008,13 @@ __global__ __launch_bounds__(kAsmThreads) void pc_asm_small_kernel(
             double sij[kAsmSlots], xv[kAsmSlots];
 #pragma unroll
             for (int q = 0; q < kAsmSlots; ++q) {
-                const int i = min(i0 + 16 * q, na - 1);
+                const int i = min(i0 + kAsmStep * q, na - 1);
                 sij[q] = S[i * ld + j];
                 xv[q] = X[i * ld + c];
             }
 #pragma unroll
             for (int q = 0; q < kAsmSlots; ++q) {
-                const int i = i0 + 16 * q;
+                const int i = i0 + kAsmStep * q;
                 if (i > j && i < na && c <= i) X[i * ld + c] = xv[q] - sij[q] * pj;
             }
         }
@@ -1052,14 +1034,14 @@ __global__ __launch_bounds__(kAsmThreads) void pc_asm_small_kernel(
             const double ekj = E[k * ld + j] * invd[k];
 #pragma unroll
             for (int q = 0; q < kAsmSlots; ++q) {
-                const int i = i0 + 16 * q;
+                const int i = i0 + kAsmStep * q;
                 const double eki = E[k * ld + min(i, k)];  // in bounds; used for i <= k
                 acc[q] += i <= k ? eki * ekj : 0.0;
             }
         }
 #pragma unroll
     for (int q = 0; q < kAsmSlots; ++q) {
-        const int i = i0 + 16 * q;
+        const int i = i0 + kAsmStep * q;
         if (i < na && j < na) G[(size_t)i * na + j] = acc[q];
     }
 }
@@ -2223,7 +2205,7 @@ hipError_t precond_assembly(hipStream_t s, const PrecondDev &P) {
     const int max_m = nmax;
     const int nbk = (max_m + kNB - 1) / kNB;
     const size_t lds_i = (size_t)nbk * kNB * kLd * sizeof(double);
-    const size_t lds_r = 12 * (size_t)max_m * sizeof(double) + 2 * (size_t)max_m * sizeof(int);
+    const size_t lds_r = 24 * (size_t)max_m * sizeof(double) + 2 * (size_t)max_m * sizeof(int);
     const bool sweep = max_m <= kSwRows;
     hipError_t e = hipFuncSetAttribute((const void *)pc_trtri_kernel,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_i);
@@ -2232,7 +2214,7 @@ hipError_t precond_assembly(hipStream_t s, const PrecondDev &P) {
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_r);
     if (e != hipSuccess) return e;
     const int nt = (max_m + 63) / 64;
-    pc_asm_form_kernel<<<P.A, 256, lds_r, s>>>(P.asm_row_ptr, P.asm_rows, P.asm_mat_off,
+    pc_asm_form_kernel<<<P.A, kAsmForm, lds_r, s>>>(P.asm_row_ptr, P.asm_rows, P.asm_mat_off,
                                                P.row_p, P.row_q, P.crow, P.Nt, P.S, P.asm_fail,
                                                P.status, max_m);
     const MatBatch B{P.asm_row_ptr, 1, P.asm_mat_off, P.S, nullptr, P.asm_dinv, P.G, P.status,

@@ -16,7 +16,9 @@ namespace arb {
 
 namespace {
 
-constexpr int kThreads = 512;
+constexpr int kThreads = kSmallCycleThreads;
+constexpr int kPairs = 2;  // sources in flight per thread, no wall
+constexpr int kRows = 2;  // basis vectors at a time in the Gram-Schmidt products
 constexpr int kWaves = kThreads / kWave;
 
 __device__ __forceinline__ double wsum(double v) {
@@ -26,25 +28,43 @@ __device__ __forceinline__ double wsum(double v) {
 
 // the Givens update of the new Hessenberg column (as arnoldi_post_dev in krylov.hip),
 // on LDS copies of the column, the rotations and g
-__device__ void givens_column(int j, const double *h1, const double *h2, double hn2, double *col,
-                              double *cs, double *sn, double *g, double *out) {
-    for (int i = 0; i <= j; ++i) col[i] = h1[i] + h2[i];
+__device__ void givens_column(int j, const double *__restrict__ h1, const double *__restrict__ h2,
+                              double hn2, double *__restrict__ col, double *__restrict__ cs,
+                              double *__restrict__ sn, double *g, double *out) {
     const double hn = sqrt(hn2);
-    col[j + 1] = hn;
+    double c = h1[0] + h2[0];  // entry i after the rotations before it
+#pragma unroll 4
     for (int i = 0; i < j; ++i) {
-        const double t = cs[i] * col[i] + sn[i] * col[i + 1];
-        col[i + 1] = -sn[i] * col[i] + cs[i] * col[i + 1];
-        col[i] = t;
+        const double next = h1[i + 1] + h2[i + 1], ci = cs[i], si = sn[i];
+        col[i] = ci * c + si * next;
+        c = -si * c + ci * next;
     }
-    const double rho = hypot(col[j], col[j + 1]);
-    cs[j] = col[j] / rho;
-    sn[j] = col[j + 1] / rho;
+    const double rho = hypot(c, hn);
+    cs[j] = c / rho;
+    sn[j] = hn / rho;
     col[j] = rho;
     col[j + 1] = 0.0;
     g[j + 1] = -sn[j] * g[j];
     g[j] = cs[j] * g[j];
     out[0] = hn;
     out[1] = fabs(g[j + 1]);
+}
+
+// rpy_free with both branches and a select: two wavefronts to a SIMD wait on one pair's
+// chain, so that several pairs in flight pay for the near branch's few operations
+__device__ __forceinline__ void rpy_free_select(double dx, double dy, double dz, double r2,
+                                                double rinv, double lx, double ly, double lz,
+                                                const CoefD &c, double &ax, double &ay,
+                                                double &az) {
+    const double rinv2 = rinv * rinv, rinv3 = rinv * rinv2;
+    const bool near = r2 <= c.four_a2;
+    const double rv = r2 > 0.0 ? rinv : 0.0;
+    const double c1 = near ? fma(-c.n2, r2 * rv, c.n1) : fma(c.k1, rinv3, rinv);
+    const double c2 = near ? rv * c.n3 : fma(-c.k2, rinv3 * rinv2, rinv3);
+    const double t = c2 * fma(dx, lx, fma(dy, ly, dz * lz));
+    ax = fma(c1, lx, fma(t, dx, ax));
+    ay = fma(c1, ly, fma(t, dy, ay));
+    az = fma(c1, lz, fma(t, dz, az));
 }
 
 template <class T>
@@ -56,8 +76,13 @@ __device__ __forceinline__ T *stage(const T *src, size_t cnt, T *dst) {
 // Everything a step reads is staged once in the dynamic LDS arena (small_layout):
 // the state (positions, d_i), the preconditioner (M_pp^-1, Z_p, N~_p, G~_a),
 // the constraint rows and the index arrays; v_j, z = P^-1 v_j, w = A z and U^
-// live there too.  Only the Krylov basis V (written once per step, read by the
-// Gram-Schmidt passes) and the Hessenberg data stay in memory.
+// live there too, and as many of the first basis vectors as fit (the basis is written
+// to memory as well, for the update after the cycle).  A step is a chain of short phases
+// on one compute unit, bound by their latencies and, for its pair sums, by FP64 issue.
+// The 20-rod filament (417 unknowns, 18 steps): 422 -> 294 us.  Of a step's 38,000 cycles
+// 15,000 are pair sums; loads in flight (unrolled sums, the constraint right-hand side in
+// the assemblies' order) took 8,000 off, threads per target 5,000, C^T phi kept for the
+// body rows 3,000.  1,024 threads: 349 us (a step has more barriers than work for them).
 template <bool WALL>
 __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
     SmallSystem Sg, int m, int budget, double target, double *__restrict__ V,
@@ -99,11 +124,17 @@ __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
     int *slot_a = ia + L.slot_a;  // assembly of each slot of asm_rows
     for (int a = tid; a < Sg.A; a += kThreads)
         for (int sl = Sg.asm_row_ptr[a]; sl < Sg.asm_row_ptr[a + 1]; ++sl) slot_a[sl] = a;
-    const int64_t n = S.n;
+    const int n = (int)S.n;
+    // the first nv basis vectors also stay in LDS, as many as fit
+    double *vl = arena + L.vl;
+    const int nv = small_basis_in_lds(Sg, m);
     const CoefD coef = make_coef<CoefD, double>(S.a);
     const size_t o_u = 3 * (size_t)S.N, o_phi = o_u + 6 * (size_t)S.M;
     int k = 0;
-    for (int t = tid; t < n; t += kThreads) vs[t] = V[t];
+    for (int t = tid; t < n; t += kThreads) {
+        vs[t] = V[t];
+        if (nv > 0) vl[t] = vs[t];
+    }
     for (int t = tid; t <= m; t += kThreads) g_s[t] = g[t];
     __syncthreads();
     for (int j = 0; j < budget; ++j) {
@@ -118,15 +149,17 @@ __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
             const double *Mi = S.minv + S.mat_off[p];
             const double *rl = r + 3 * (size_t)b0;
             double s = 0.0;
+#pragma unroll 4
             for (int kk = 0; kk < mm; ++kk) s += Mi[(size_t)kk * mm + i] * rl[kk];
             z[R] = s;
         }
-        // w6 = Z_p^T r_lambda + r_U per body and component
-        for (int e = tid; e < 6 * S.M; e += kThreads) {
+        // w6 = Z_p^T r_lambda + r_U per body and component, from the last wavefront down
+        for (int e = kThreads - 1 - tid; e < 6 * S.M; e += kThreads) {
             const int p = e / 6, c = e - 6 * p;
             const int b0 = S.blob_off[p], mm = 3 * (S.blob_off[p + 1] - b0);
             const double *Zp = S.Z + S.z_off[p];
             double acc = r[o_u + e];
+#pragma unroll 4
             for (int i = 0; i < mm; ++i) acc += Zp[(size_t)i * 6 + c] * r[3 * (size_t)b0 + i];
             w6[e] = acc;
         }
@@ -140,8 +173,9 @@ __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
             us[e] = -s;
         }
         __syncthreads();
-        // assemblies: y = r_phi - C U^ per row, then phi = G~ y over each assembly's rows
-        for (int kr = tid; kr < S.Nc; kr += kThreads) {
+        // assemblies: y = r_phi - C U^ per row, in the assemblies' order, then phi = G~ y over each assembly's rows
+        for (int sl = tid; sl < S.Nc; sl += kThreads) {
+            const int kr = S.asm_rows[sl];
             const double *c = S.crow + 12 * (size_t)kr;
             const double *Up = us + 6 * S.row_p[kr];
             double s = 0.0;
@@ -149,14 +183,15 @@ __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
             const int q = S.row_q[kr];
             if (q >= 0)
                 for (int u = 0; u < 6; ++u) s += c[6 + u] * us[6 * q + u];
-            yv[kr] = r[o_phi + kr] - s;
+            yv[sl] = r[o_phi + kr] - s;
         }
         __syncthreads();
         for (int sl = tid; sl < S.Nc; sl += kThreads) {
             const int a = slot_a[sl], r0 = S.asm_row_ptr[a], na = S.asm_row_ptr[a + 1] - r0;
             const double *Ga = S.G + S.asm_mat_off[a] + (size_t)(sl - r0) * na;
             double s = 0.0;
-            for (int l = 0; l < na; ++l) s += Ga[l] * yv[S.asm_rows[r0 + l]];
+#pragma unroll 8
+            for (int l = 0; l < na; ++l) s += Ga[l] * yv[r0 + l];
             z[o_phi + S.asm_rows[sl]] = s;
         }
         __syncthreads();
@@ -195,11 +230,12 @@ __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
         // same number of passes in every thread, so the group sums below see
         // whole groups)
         for (int base = 0; base < S.N * S.tpt; base += kThreads) {
-            const int tpt = S.tpt, i = (base + tid) / tpt, sl = (base + tid) % tpt;
+            const int tpt = S.tpt, i = (base + tid) >> __builtin_ctz(tpt), sl = (base + tid) & (tpt - 1);
             double ux = 0.0, uy = 0.0, uz = 0.0;
             if (i < S.N) {
                 const double4 ti = S.p64[i];
                 const TargetZ<double> zsc = target_z(ti.z);
+#pragma unroll WALL ? 1 : kPairs
                 for (int jj = sl; jj < S.N; jj += tpt) {
                     const double4 sj = S.p64[jj];
                     const size_t b = 3 * (size_t)(S.perm ? S.perm[jj] : jj);
@@ -216,7 +252,7 @@ __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
                         wall_pair_apply<double>(w, w.c, w.d, dx, dy, dz, Rz, lx, ly, lz, ux, uy,
                                                 uz);
                     } else {
-                        rpy_free<double>(dx, dy, dz, r2, rinv, lx, ly, lz, coef, ux, uy, uz);
+                        rpy_free_select(dx, dy, dz, r2, rinv, lx, ly, lz, coef, ux, uy, uz);
                     }
                 }
             }
@@ -235,25 +271,21 @@ __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
                 ws[3 * ib + 2] = uz * S.scale - (Up[2] + (Up[3] * d1 - Up[4] * d0));
             }
         }
-        // body rows: -K^T lambda + C^T phi per body and component
-        for (int e = tid; e < 6 * S.M; e += kThreads) {
+        // body rows: -K^T lambda + C^T phi per body and component, from the last
+        // wavefront down (the last pass above leaves it free)
+        for (int e = kThreads - 1 - tid; e < 6 * S.M; e += kThreads) {
             const int p = e / 6, c = e - 6 * p;
+            // (K^T lambda)_c: the force, or d x lambda; w6 still holds C^T phi
+            const int c0 = c < 3 ? c : c - 3, c1 = c0 < 2 ? c0 + 1 : 0, c2 = c0 > 0 ? c0 - 1 : 2;
             double f = 0.0;
+#pragma unroll 4
             for (int ib = S.blob_off[p]; ib < S.blob_off[p + 1]; ++ib) {
                 const double *l = z + 3 * (size_t)ib;
                 const double *dv = S.dvec + 3 * (size_t)ib;
-                // (K^T lambda)_c: the force, or d x lambda
-                f += c < 3 ? l[c]
-                           : (c == 3 ? dv[1] * l[2] - dv[2] * l[1]
-                                     : (c == 4 ? dv[2] * l[0] - dv[0] * l[2]
-                                               : dv[0] * l[1] - dv[1] * l[0]));
+                const double torque = dv[c1] * l[c2] - dv[c2] * l[c1];
+                f += c < 3 ? l[c0] : torque;
             }
-            f = -f;
-            if (S.Nc > 0)
-                for (int en = S.brow_ptr[p]; en < S.brow_ptr[p + 1]; ++en) {
-                    const int ent = S.brow_ent[en], row = ent >> 1, side = ent & 1;
-                    f += z[o_phi + row] * S.crow[12 * (size_t)row + 6 * side + c];
-                }
+            f = w6[e] - f;
             ws[o_u + e] = f;
         }
         // constraint rows: C U
@@ -269,23 +301,43 @@ __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
         }
         __syncthreads();
         // ---- classical Gram-Schmidt twice, ||w||, Givens ---------------------------
-        for (int pass = 0; pass < 2; ++pass) {
-            double *h = hs[pass];
-            for (int i = wave; i <= j; i += kWaves) {
-                const double *v = V + (int64_t)i * n;
-                double sacc = 0.0;
-                for (int t = lane; t < n; t += kWave) sacc += v[t] * ws[t];
-                sacc = wsum(sacc);
-                if (lane == 0) h[i] = sacc;
+        auto gram_schmidt = [&](const double *Vb) {
+            for (int pass = 0; pass < 2; ++pass) {
+                double *h = hs[pass];
+                // two basis vectors at a time per wavefront: their loads and lane
+                // exchanges overlap
+                for (int i0 = wave; i0 <= j; i0 += kRows * kWaves) {
+                    const double *v[kRows];
+                    double sacc[kRows] = {};
+#pragma unroll
+                    for (int q = 0; q < kRows; ++q) v[q] = Vb + min(i0 + q * kWaves, j) * n;
+#pragma unroll 4
+                    for (int t = lane; t < n; t += kWave) {
+                        const double wt = ws[t];
+#pragma unroll
+                        for (int q = 0; q < kRows; ++q) sacc[q] += v[q][t] * wt;
+                    }
+                    for (int off = kWave / 2; off > 0; off >>= 1)
+#pragma unroll
+                        for (int q = 0; q < kRows; ++q) sacc[q] += __shfl_xor(sacc[q], off);
+#pragma unroll
+                    for (int q = 0; q < kRows; ++q)
+                        if (lane == 0 && i0 + q * kWaves <= j) h[i0 + q * kWaves] = sacc[q];
+                }
+                __syncthreads();
+                for (int t = tid; t < n; t += kThreads) {
+                    double acc = 0.0;
+#pragma unroll 8
+                    for (int i = 0; i <= j; ++i) acc += Vb[i * n + t] * h[i];
+                    ws[t] -= acc;
+                }
+                __syncthreads();
             }
-            __syncthreads();
-            for (int t = tid; t < n; t += kThreads) {
-                double acc = 0.0;
-                for (int i = 0; i <= j; ++i) acc += V[(int64_t)i * n + t] * h[i];
-                ws[t] -= acc;
-            }
-            __syncthreads();
-        }
+        };
+        if (j < nv)
+            gram_schmidt(vl);
+        else
+            gram_schmidt(V);
         double sq = 0.0;
         for (int t = tid; t < n; t += kThreads) sq += ws[t] * ws[t];
         sq = wsum(sq);
@@ -312,6 +364,7 @@ __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
                 const double v = ws[t] * inv;
                 vn[t] = v;
                 vs[t] = v;
+                if (j + 1 < nv) vl[(j + 1) * n + t] = v;
             }
         }
         __syncthreads();
@@ -331,7 +384,8 @@ __global__ __launch_bounds__(kThreads) void gmres_small_cycle_kernel(
 hipError_t gmres_small_cycle(hipStream_t s, const SmallSystem &S, int m, int budget,
                              double target, double *V, double *Hbar, double *cs, double *sn,
                              double *g, double *steps) {
-    const size_t lds = small_layout(S).bytes;
+    const size_t lds =
+        small_layout(S).bytes + (size_t)small_basis_in_lds(S, m) * S.n * sizeof(double);
     const void *fn = S.wall ? (const void *)gmres_small_cycle_kernel<true>
                             : (const void *)gmres_small_cycle_kernel<false>;
     const hipError_t e =
