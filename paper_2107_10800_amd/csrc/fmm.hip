@@ -96,108 +96,169 @@ __global__ void fmm_gather_lam_kernel(int N, const int *__restrict__ perm,
     slam[k] = vec4<A>((A)lam[3 * i], (A)lam[3 * i + 1], (A)lam[3 * i + 2]);
 }
 
-// qhat of the leaves, one workgroup per leaf, one lane per proxy: the leaf's
-// blobs are staged in LDS in chunks with their 1D Lagrange values, computed
-// once per blob and direction
+// qhat of the leaves (NO points per direction), one workgroup per leaf: the leaf's blobs
+// are staged in LDS in chunks with their 1D Lagrange values, computed once per blob and
+// direction.  A lane takes a column of proxies (kx, ky) and every G-th blob: two reads of
+// 1D values and three broadcasts serve NO proxies.  (A lane per proxy read LDS four times
+// per proxy and blob, which bound it: 1M blobs 176 us, now 86; 256 diatom colonies in FP64
+// 127, now 61.)  The groups' sums meet in LDS in FP64, in group order.
 constexpr int kP2MChunk = 64;
 
-template <class A>
-__global__ __launch_bounds__(kFmmMaxP) void fmm_p2m_kernel(
+template <int NO>
+struct P2MShape {
+    static constexpr int Q = NO * NO, P = Q * NO;
+    static constexpr int G = 256 / Q < 8 ? 256 / Q : 8;      // groups of blobs
+    static constexpr int T = (G * Q + kWave - 1) / kWave * kWave;
+};
+
+template <class A, int NO>
+__global__ __launch_bounds__(P2MShape<NO>::T) void fmm_p2m_kernel(
     Geo g, const float *__restrict__ tabg, const int4 *__restrict__ cc,
     const int2 *__restrict__ rng, int cell0, const float4 *__restrict__ shi,
     const float4 *__restrict__ slo, const Vec4<A> *__restrict__ slam, Vec4<A> *__restrict__ qhat) {
+    constexpr int n = NO, Q = P2MShape<NO>::Q, P = P2MShape<NO>::P, G = P2MShape<NO>::G,
+                  T = P2MShape<NO>::T;
     __shared__ float tab[kTabSize];
     __shared__ float s_l[3][kP2MChunk][kFmmMaxOrder];
     __shared__ Vec4<A> s_lam[kP2MChunk];
+    __shared__ double sum[P][3];
     load_tab(tabg, tab);
     const int c = cell0 + blockIdx.x;
-    const int tid = threadIdx.x;
-    const int n = g.n;
-    const bool act = tid < g.P;
-    const int k = act ? tid : 0;
-    const int kx = k / (n * n), ky = (k / n) % n, kz = k % n;
+    const int tid = threadIdx.x, grp = tid / Q;
+    const int kx = tid % Q / n, ky = tid % n;
     const int4 ci = cc[c];
     const int2 r = rng[c];
     const double side = ldexp(g.S, -ci.w);
     const F2 cd[3] = {split(centre(g.ox, side, ci.x)), split(centre(g.oy, side, ci.y)),
                       split(centre(g.oz, side, ci.z))};
     const float iw = (float)(2.0 / side);
-    double qx = 0.0, qy = 0.0, qz = 0.0;
+    double q[n][3] = {};
     for (int j0 = r.x; j0 < r.y; j0 += kP2MChunk) {
         const int cnt = min(kP2MChunk, r.y - j0);
         __syncthreads();
-        for (int t = tid; t < 3 * cnt; t += blockDim.x) {
+        for (int t = tid; t < 3 * cnt; t += T) {
             const int jj = t / 3, d = t - 3 * jj;
             const float4 h = shi[j0 + jj], l = slo[j0 + jj];
             const float hx = d == 0 ? h.x : (d == 1 ? h.y : h.z);
             const float lx = d == 0 ? l.x : (d == 1 ? l.y : l.z);
             const float u = ((hx - cd[d].h) + (lx - cd[d].l)) * iw;
+#pragma unroll
             for (int kk = 0; kk < n; ++kk) s_l[d][jj][kk] = lag(tab, n, kk, u);
             if (d == 0) s_lam[jj] = slam[j0 + jj];
         }
         __syncthreads();
-        A fx = 0, fy = 0, fz = 0;
-        for (int jj = 0; jj < cnt; ++jj) {
-            const A w = (A)(s_l[0][jj][kx] * s_l[1][jj][ky] * s_l[2][jj][kz]);
+        if (grp >= G) continue;
+        A f[n][3] = {};
+        for (int jj = grp; jj < cnt; jj += G) {
+            const float wxy = s_l[0][jj][kx] * s_l[1][jj][ky];
             const Vec4<A> L = s_lam[jj];
-            fx = fma(w, L.x, fx);
-            fy = fma(w, L.y, fy);
-            fz = fma(w, L.z, fz);
+#pragma unroll
+            for (int kz = 0; kz < n; ++kz) {
+                const A w = (A)(wxy * s_l[2][jj][kz]);
+                f[kz][0] = fma(w, L.x, f[kz][0]);
+                f[kz][1] = fma(w, L.y, f[kz][1]);
+                f[kz][2] = fma(w, L.z, f[kz][2]);
+            }
         }
-        qx += fx;
-        qy += fy;
-        qz += fz;
+#pragma unroll
+        for (int kz = 0; kz < n; ++kz)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) q[kz][d] += f[kz][d];
     }
-    if (act) qhat[(size_t)c * g.P + k] = vec4<A>((A)qx, (A)qy, (A)qz);
+    for (int s = 0; s < G; ++s) {
+        if (s == grp)
+#pragma unroll
+            for (int kz = 0; kz < n; ++kz)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    double &at = sum[tid % Q * n + kz][d];
+                    at = s == 0 ? q[kz][d] : at + q[kz][d];
+                }
+        __syncthreads();
+    }
+    for (int k = tid; k < P; k += T)
+        qhat[(size_t)c * P + k] = vec4<A>((A)sum[k][0], (A)sum[k][1], (A)sum[k][2]);
 }
 
-// qhat of the cells of one level from their children (NO points per direction)
+// qhat of the cells of one level from their children (NO points per direction).  A lane
+// takes a column of the parent's proxies (kx, ky) and one child: a child's weight is read
+// from LDS once for NO proxies (a lane per proxy read it for each: 1M blobs 40 us a level
+// on average, now 27; 256 diatom colonies in FP64 68, now 38).  The children's sums are added
+// in their order.
 template <class A, int NO>
-__global__ __launch_bounds__(kFmmMaxP) void fmm_m2m_kernel(Geo g, const float *__restrict__ tabg,
-                                                           const int4 *__restrict__ cc,
-                                                           const int2 *__restrict__ kids,
-                                                           int cell0, Vec4<A> *__restrict__ qhat) {
+struct M2MShape {
+    static constexpr int Q = NO * NO, P = Q * NO;
+    static constexpr size_t bytes(int c) { return P * (sizeof(Vec4<A>) * c + 24); }
+    static constexpr int C = bytes(8) <= 60 << 10 ? 8 : bytes(4) <= 60 << 10 ? 4 : 2;  // children at a time
+    static constexpr int T = (C * Q + kWave - 1) / kWave * kWave;
+};
+
+template <class A, int NO>
+__global__ __launch_bounds__((M2MShape<A, NO>::T)) void fmm_m2m_kernel(
+    Geo g, const float *__restrict__ tabg, const int4 *__restrict__ cc,
+    const int2 *__restrict__ kids, int cell0, Vec4<A> *__restrict__ qhat) {
+    constexpr int n = NO, Q = M2MShape<A, NO>::Q, P = M2MShape<A, NO>::P, C = M2MShape<A, NO>::C,
+                  T = M2MShape<A, NO>::T;
     __shared__ float tab[kTabSize];
-    __shared__ Vec4<A> sq[kFmmMaxP];  // one child's weights, read by every lane
+    __shared__ Vec4<A> sq[C * P];
+    __shared__ double sum[P][3];
     load_tab(tabg, tab);
     const int c = cell0 + blockIdx.x;
-    const int k = threadIdx.x;
-    constexpr int n = NO, P = NO * NO * NO;
-    const bool act = k < P;
-    const int kx = k / (n * n), ky = (k / n) % n, kz = k % n;
+    const int tid = threadIdx.x, mine = tid / Q;
+    const int kx = tid % Q / n, ky = tid % n;
     const int2 kr = kids[c];
-    double qx = 0.0, qy = 0.0, qz = 0.0;
-    for (int ch = kr.x; ch < kr.y; ++ch) {
+    if (kr.y <= kr.x)
+        for (int k = tid; k < P; k += T) sum[k][0] = sum[k][1] = sum[k][2] = 0.0;
+    for (int ch0 = kr.x; ch0 < kr.y; ch0 += C) {
+        const int cnt = min(C, kr.y - ch0);
         __syncthreads();
-        if (act) sq[k] = qhat[(size_t)ch * P + k];
+        for (int i = tid; i < cnt * P; i += T) sq[i] = qhat[(size_t)ch0 * P + i];
         __syncthreads();
-        if (!act) continue;
-        const int4 cci = cc[ch];
-        // t1[sigma][k][m] = l_k(sigma/2 + xi_m/2): the parent's polynomial at the
-        // child's proxies (sigma = -1 for the lower child, the even coordinate)
-        const float *tx = tab + kTabT1 + (cci.x & 1) * kFmmMaxOrder * kFmmMaxOrder + kx * kFmmMaxOrder;
-        const float *ty = tab + kTabT1 + (cci.y & 1) * kFmmMaxOrder * kFmmMaxOrder + ky * kFmmMaxOrder;
-        const float *tz = tab + kTabT1 + (cci.z & 1) * kFmmMaxOrder * kFmmMaxOrder + kz * kFmmMaxOrder;
-        const Vec4<A> *q = sq;
-        A fx = 0, fy = 0, fz = 0;
-        for (int mx = 0; mx < n; ++mx)
+        A f[n][3] = {};
+        if (mine < cnt) {
+            const int4 cci = cc[ch0 + mine];
+            // t1[sigma][k][m] = l_k(sigma/2 + xi_m/2): the parent's polynomial at the
+            // child's proxies (sigma = -1 for the lower child, the even coordinate)
+            constexpr int kT = kFmmMaxOrder * kFmmMaxOrder;
+            const float *tx = tab + kTabT1 + (cci.x & 1) * kT + kx * kFmmMaxOrder;
+            const float *ty = tab + kTabT1 + (cci.y & 1) * kT + ky * kFmmMaxOrder;
+            const float *tz = tab + kTabT1 + (cci.z & 1) * kT;
+            float z[n][n];
 #pragma unroll
-            for (int my = 0; my < n; ++my) {
-                const float a = tx[mx] * ty[my];
+            for (int kz = 0; kz < n; ++kz)
 #pragma unroll
-                for (int mz = 0; mz < n; ++mz) {
-                    const A w = (A)(a * tz[mz]);
-                    const Vec4<A> Q = q[(mx * n + my) * n + mz];
-                    fx = fma(w, Q.x, fx);
-                    fy = fma(w, Q.y, fy);
-                    fz = fma(w, Q.z, fz);
+                for (int mz = 0; mz < n; ++mz) z[kz][mz] = tz[kz * kFmmMaxOrder + mz];
+            const Vec4<A> *qc = sq + mine * P;
+            for (int mx = 0; mx < n; ++mx)
+                for (int my = 0; my < n; ++my) {
+                    const float a = tx[mx] * ty[my];
+#pragma unroll
+                    for (int mz = 0; mz < n; ++mz) {
+                        const Vec4<A> q = qc[(mx * n + my) * n + mz];
+#pragma unroll
+                        for (int kz = 0; kz < n; ++kz) {
+                            const A w = (A)(a * z[kz][mz]);
+                            f[kz][0] = fma(w, q.x, f[kz][0]);
+                            f[kz][1] = fma(w, q.y, f[kz][1]);
+                            f[kz][2] = fma(w, q.z, f[kz][2]);
+                        }
+                    }
                 }
-            }
-        qx += fx;
-        qy += fy;
-        qz += fz;
+        }
+        for (int s = 0; s < cnt; ++s) {
+            if (s == mine)
+#pragma unroll
+                for (int kz = 0; kz < n; ++kz)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        double &at = sum[tid % Q * n + kz][d];
+                        at = s == 0 && ch0 == kr.x ? f[kz][d] : at + f[kz][d];
+                    }
+            __syncthreads();
+        }
     }
-    if (act) qhat[(size_t)c * P + k] = vec4<A>((A)qx, (A)qy, (A)qz);
+    for (int k = tid; k < P; k += T)
+        qhat[(size_t)c * P + k] = vec4<A>((A)sum[k][0], (A)sum[k][1], (A)sum[k][2]);
 }
 
 // the children at one level gain the parent's interpolant at their proxies (NO
@@ -1259,12 +1320,13 @@ void fmm_run(const FmmState &F, hipStream_t s, const double *lam, double *partia
     Vec4<A> *slam = F.slam.as<Vec4<A>>(), *qhat = F.qhat.as<Vec4<A>>();
     fmm_gather_lam_kernel<A><<<(N + 255) / 256, 256, 0, s>>>(N, F.perm.as<int>(), lam, slam);
     if (L >= 2) {
-        fmm_p2m_kernel<A><<<F.lvl[L + 1] - F.lvl[L], B, 0, s>>>(
-            g, tab, F.cc.as<int4>(), F.rng.as<int2>(), F.lvl[L], F.shi.as<float4>(),
-            F.slo.as<float4>(), slam, qhat);
         with_order(F.n, [&](auto o) {
+            constexpr int n = decltype(o)::value;
+            fmm_p2m_kernel<A, n><<<F.lvl[L + 1] - F.lvl[L], P2MShape<n>::T, 0, s>>>(
+                g, tab, F.cc.as<int4>(), F.rng.as<int2>(), F.lvl[L], F.shi.as<float4>(),
+                F.slo.as<float4>(), slam, qhat);
             for (int l = L - 1; l >= 2; --l)
-                fmm_m2m_kernel<A, decltype(o)::value><<<F.lvl[l + 1] - F.lvl[l], B, 0, s>>>(
+                fmm_m2m_kernel<A, n><<<F.lvl[l + 1] - F.lvl[l], M2MShape<A, n>::T, 0, s>>>(
                     g, tab, F.cc.as<int4>(), F.kids.as<int2>(), F.lvl[l], qhat);
         });
         fmm_m2l(F, s, 1, WALL, std::is_same_v<A, double>);
@@ -1306,15 +1368,15 @@ void fmm_run6(const FmmState &F, hipStream_t s, const double *x6, double inv_a, 
     double *vu = F.v.as<double>(), *vw = F.v2.as<double>();
     fmm_gather6_kernel<A><<<(M + 255) / 256, 256, 0, s>>>(M, F.perm.as<int>(), x6, inv_a, sf, st);
     if (L >= 2) {
-        const int nl = F.lvl[L + 1] - F.lvl[L];
-        for (int ch = 0; ch < 2; ++ch)
-            fmm_p2m_kernel<A><<<nl, B, 0, s>>>(g, tab, F.cc.as<int4>(), F.rng.as<int2>(),
-                                               F.lvl[L], F.shi.as<float4>(), F.slo.as<float4>(),
-                                               ch ? st : sf, ch ? qt : qf);
         with_order(F.n, [&](auto o) {
+            constexpr int n = decltype(o)::value;
+            for (int ch = 0; ch < 2; ++ch)
+                fmm_p2m_kernel<A, n><<<F.lvl[L + 1] - F.lvl[L], P2MShape<n>::T, 0, s>>>(
+                    g, tab, F.cc.as<int4>(), F.rng.as<int2>(), F.lvl[L], F.shi.as<float4>(),
+                    F.slo.as<float4>(), ch ? st : sf, ch ? qt : qf);
             for (int l = L - 1; l >= 2; --l)
                 for (int ch = 0; ch < 2; ++ch)
-                    fmm_m2m_kernel<A, decltype(o)::value><<<F.lvl[l + 1] - F.lvl[l], B, 0, s>>>(
+                    fmm_m2m_kernel<A, n><<<F.lvl[l + 1] - F.lvl[l], M2MShape<A, n>::T, 0, s>>>(
                         g, tab, F.cc.as<int4>(), F.kids.as<int2>(), F.lvl[l], ch ? qt : qf);
         });
         fmm_m2l(F, s, 2, false, std::is_same_v<A, double>);

@@ -398,3 +398,24 @@ def test_single_blob_solve_with_the_fast_product(prec):
     print(f"single-blob fast solve precision {prec}: {info['iterations']} iterations, residual "
           f"{info['rel_residual']:.1e}, velocities vs dense solve {err:.1e}", flush=True)
     assert info["rel_residual"] <= 1e-10 and err <= 1e-3
+
+
+# the upward pass at every order in both types (a parent's children in one, two or four
+# turns): the products share the tree and the weights, so they differ by FP32 rounding only
+@pytest.mark.parametrize("order", range(2, 9))
+def test_upward_pass_in_both_types(order):
+    cl = W.random_blobs(2500, seed=order, box=60.0, zlo=1.2, zhi=60.0)
+    u = {}
+    for prec in (arb.ARB_FP64, arb.ARB_FP32C):
+        ctx = arb.arb_create(precision=prec, wall=True, pair_kernel=arb.ARB_PAIR_FMM,
+                             fmm_order=order, fmm_levels=4)
+        try:
+            u[prec] = arb.arb_rpy_apply(ctx, cl["pos"], cl["lam"])
+        finally:
+            arb.arb_destroy(ctx)
+    uo = rpy.mobility_apply(cl["pos"], cl["lam"], 1.0, 1.0, True)
+    err = np.linalg.norm(u[arb.ARB_FP64] - uo.ravel()) / np.linalg.norm(uo)
+    diff = np.linalg.norm(u[arb.ARB_FP32C] - u[arb.ARB_FP64]) / np.linalg.norm(uo)
+    print(f"order {order}: error {err:.1e}, FP32 against FP64 {diff:.1e}", flush=True)
+    assert diff <= 1e-5
+    assert err <= 10.0 ** (-0.75 * order + 0.5)  # 3e-2 ... 3e-6, as the error by order above
