@@ -21,7 +21,7 @@
 // FP32 (positions in units of a, split hi + lo): float sums over one source
 // tile, promoted to FP64 per tile.  FP64: the same work list with double positions and sums.
 // Target sums are promoted to FP64 after each source tile and added to u at the
-// end of the item.  u is cleared first; FP64 addition order of the atomics
+// end of the item.  u is zero before; FP64 addition order of the atomics
 // varies between runs (results reproducible to FP64 rounding).  Rows beyond N
 // are padded with far-away zero-force blobs.
 #include <algorithm>

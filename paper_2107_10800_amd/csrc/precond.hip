@@ -30,6 +30,7 @@
 //   pc_apply1    t_p = M_pp^-1 r_lam,p;  U^_p = -N~_p (r_U,p + Z_p^T r_lam,p)
 //   pc_apply2    phi_a = G~_a (r_phi,a - C_a U^_a)
 //   pc_apply3    U_p = U^_p + N~_p (C^T phi)_p;  lam_p = t_p + Z_p U_p
+// (one launch, pc_apply_asm, when every assembly is small)
 // which is the exact solution of the body-diagonal saddle problem: row 1 gives
 // lam = M~^-1 (r_lam + K U), row 2 gives N~^-1 U = -r_U - K^T M~^-1 r_lam + C^T phi,
 // row 3 gives (C N~ C^T) phi = r_phi - C U^.
