@@ -1128,14 +1128,16 @@ int dev_norm(arb_ctx *ctx, hipStream_t s, Krylov &K, const double *x, int slot, 
 // from the y already in place with its residual r = rhs - A y in K.r.  Stops
 // when the residual of the operator in `prec` is <= tol_abs, or after the
 // iteration budget.  Returns the final residual norm in *res (same operator).
-// everything the launches of one Arnoldi step depend on besides buffer contents
+// everything the launches of one Arnoldi step depend on besides buffer contents; all of
+// pc_fuse, whose three numbers lay out the LDS of the one-launch apply (changed links can
+// leave the sizes, the number of assemblies and the largest one's rows as they were)
 std::vector<long long> graph_key(arb_ctx *ctx, const Krylov &K, int prec) {
     const int64_t skey = (int64_t)ctx->N * 4 + prec * 2 + (ctx->opt.wall ? 1 : 0);
     auto it = ctx->slice_cache.find(skey);
     return {(long long)arb::alloc_generation().load(), (long long)K.n, K.m, prec,
             ctx->opt.precond, ctx->opt.left_precond, ctx->psorted ? 1 : 0, ctx->pc_learned ? 1 : 0,
-            ctx->pc_lcorr ? 1 : 0, ctx->pc_fuse.rows, ctx->N, ctx->M,
-            ctx->Nc, ctx->n_asm, it == ctx->slice_cache.end() ? 0 : it->second,
+            ctx->pc_lcorr ? 1 : 0, ctx->pc_fuse.rows, ctx->pc_fuse.bodies, ctx->pc_fuse.cons,
+            ctx->N, ctx->M, ctx->Nc, ctx->n_asm, it == ctx->slice_cache.end() ? 0 : it->second,
             (long long)(intptr_t)K.V, (long long)(intptr_t)ctx->pinned, ctx->fmm.version};
 }
 
