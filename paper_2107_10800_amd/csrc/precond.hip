@@ -35,6 +35,7 @@
 // lam = M~^-1 (r_lam + K U), row 2 gives N~^-1 U = -r_U - K^T M~^-1 r_lam + C^T phi,
 // row 3 gives (C N~ C^T) phi = r_phi - C U^.
 #include "rpy_device.h"
+#include "sweep_index.h"
 
 namespace arb {
 
@@ -1753,15 +1754,13 @@ void precond_assemble(hipStream_t s, const PrecondDev &P, const double *pos, dou
 // (a 126- and a 240-row matrix each): 688 -> 399 us, most of it from the order
 // (MatBatch::order).
 constexpr int kSwRows = 256;
-constexpr int kSwLd = 17;
 // matrices of at most kSwSmall tile rows (144 rows) take an instance with fewer
 // registers, two or more workgroups per compute unit
 constexpr int kSwSmall = kSweepSmall / 16;
-constexpr int kSwMaxWaves = 8;
 
 size_t sweep_lds_bytes(int max_m) {
     const int nb = (max_m + 15) / 16;
-    return (size_t)16 * (std::max(3 * nb, kSwMaxWaves) + 6) * kSwLd * sizeof(double);
+    return sweep_lds(nb).end * sizeof(double);
 }
 
 // lane Q of each row of 16 lanes, to the whole row
@@ -1849,10 +1848,8 @@ __global__ __launch_bounds__(64 * WAVES, NBMAX <= kSwSmall ? 4 : 2) void pc_swee
     const int m = mat_rows(B, p);
     const int nb = (m + 15) >> 4, T = nb * (nb + 1) / 2;
     if (nb == 0 || nb > NBMAX) return;
-    const int buf = 16 * nb * kSwLd;
-    // LDS, in doubles: C_r = A_rk of this and the next step, -W_r, P (even and odd
-    // steps), P^T (the same), A_kk of the next step (the same) before its update by this one
-    const int oW = 2 * buf, oP = oW + buf, oT = oP + 32 * kSwLd, oD = oT + 32 * kSwLd;
+    const SweepLds S = sweep_lds(nb);
+    const int buf = S.buf, oW = S.W, oP = S.P, oT = S.T, oD = S.D;
     const double *A = B.mats + B.mat_off[p];
     double *Out = B.out + B.mat_off[p];
     const int tid = threadIdx.x, l = tid & 63, lr = l >> 4, lc = l & 15;
@@ -1862,7 +1859,7 @@ __global__ __launch_bounds__(64 * WAVES, NBMAX <= kSwSmall ? 4 : 2) void pc_swee
     const int per = min(kSwSlots, (T + WAVES - 2) / (WAVES - 1));
     const int t0 = min(T, (w > 0 ? w - 1 : WAVES - 1) * per), nt = min(per, T - t0);
     int tij[kSwSlots];
-    int li = 255, lj = 255;  // lane s: the tile of slot s (255: none)
+    int li = kSwNone, lj = kSwNone;  // lane s: the tile of slot s
     {
         int i = 0, j = t0;
         for (; j > i; ++i) j -= i + 1;
@@ -2016,10 +2013,7 @@ __global__ __launch_bounds__(64 * WAVES, NBMAX <= kSwSmall ? 4 : 2) void pc_swee
         // per tile cost 1,200 cycles a tile, against 256 of its products)
         if (w == 0 && k + 1 < nb) invert(k + 1);
         const uint64_t zero = __ballot(li == k || lj == k);
-        const int offA = oW + 16 * li * kSwLd;
-        const int offB = li != k   ? (k & 1) * buf + 16 * lj * kSwLd
-                         : lj != k ? oW + 16 * lj * kSwLd
-                                   : oT + 16 * (k & 1) * kSwLd;
+        const int offA = sweep_operand_a(S, nb, li), offB = sweep_operand_b(S, nb, li, lj, k);
 #pragma unroll
         for (int s0 = 0; s0 < kSwSlots; s0 += kRun) {
             if (s0 >= nt) continue;
