@@ -273,7 +273,8 @@ int arb_mobility_apply_dev(arb_ctx *ctx, const double *lambda_dev, double *u_dev
 
 /* Stateless pair sum for loose blobs: pos 3N, lambda 3N, u 3N (device
  * pointers), using ctx's a, eta, wall and precision.  Blobs below the wall are
- * not checked here (use arb_check_wall). */
+ * not checked here (use arb_check_wall).  Here and in arb_mobility_apply_dev the
+ * result may overlap an input. */
 int arb_rpy_apply_dev(arb_ctx *ctx, int N, const double *pos_dev,
                       const double *lambda_dev, double *u_dev, void *stream);
 /* Host-pointer version of arb_rpy_apply_dev; checks z > a when the wall is on. */

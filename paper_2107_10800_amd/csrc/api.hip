@@ -420,6 +420,12 @@ bool small_pair(const arb_ctx *ctx, int N) {
 // launch shape of the ring kernel (mid sizes), reported as the symmetric kernel's -1
 constexpr int kRingShape = -1000;
 
+// whether n doubles at x (may be null) and at y share memory
+bool overlap(const double *x, const double *y, size_t n) {
+    const uintptr_t p = (uintptr_t)x, q = (uintptr_t)y, bytes = n * sizeof(double);
+    return x && (p < q ? q - p : p - q) < bytes;
+}
+
 // one pair product; shape > 0: target-parallel kernel with that many source
 // slices; shape < 0: symmetric kernel with -shape source tiles per work item, or the
 // ring kernel; raw_pos: loose blobs whose positions need not be prepared (small_pair)
@@ -435,6 +441,7 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const do
     const bool sym = !small && !ring && shape < 0;
     bool sym_clean = true;
     int used = 1;
+    double *dst = out;
     if (ring) {
         HIPCHK(ctx->partial.ensure((size_t)arb::pair_ring_slices(N) * 3 * N * sizeof(double)));
     } else if (sym) {
@@ -454,6 +461,11 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const do
         ctx->sym_dirty = true;
     } else if (!small) {
         HIPCHK(ctx->partial.ensure((size_t)shape * 3 * N * sizeof(double)));
+    } else if (overlap(lam, out, 3 * (size_t)N) || overlap(raw_pos, out, 3 * (size_t)N)) {
+        // in place: the one launch reads its input while it writes, so it writes to the
+        // scratch of the other kernels, whose inputs are read before the reduction
+        HIPCHK(ctx->partial.ensure((size_t)3 * N * sizeof(double)));
+        dst = ctx->partial.as<double>();
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->prof) {
@@ -463,7 +475,7 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const do
     }
     if (small)
         arb::pair_small(s, precision, wall, N, raw_pos, p64, hi, lo, lam, perm, ctx->opt.a, scale,
-                        out, U, bob, dvec, rows);
+                        dst, U, bob, dvec, rows);
     else if (ring)
         used = arb::pair_ring(s, precision, wall, N, p64, hi, lo, box, lam, perm, ctx->opt.a,
                               ctx->partial.as<double>());
@@ -482,6 +494,8 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const do
         arb::pair_reduce(s, N, used, (sym ? ctx->sym_sums : ctx->partial).as<double>(), sym, scale,
                          out, U, bob, dvec, perm, rows);
     if (sym) ctx->sym_dirty = !sym_clean;
+    if (dst != out)
+        HIPCHK(hipMemcpyAsync(out, dst, (size_t)3 * N * sizeof(double), hipMemcpyDeviceToDevice, s));
     return 0;
 }
 

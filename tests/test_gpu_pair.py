@@ -289,3 +289,52 @@ def test_symmetric_products_in_turn(prec):
             assert rel(arb.arb_rpy_apply(ctx, cl["pos"], cl["lam"]), uo.ravel()) <= TOL[prec]
     finally:
         arb.arb_destroy(ctx)
+
+
+# the result in the place of an input: a product whose kernels write no result before they
+# have read every input (or go through scratch) gives the bits of one with an array of its
+# own; one launch at 300 blobs, the ring at 2,000, the tuned kernels at 8,192; whole
+# overlap, and with the result a few blobs further on
+@pytest.mark.parametrize("n", [300, 1024, 2000, 8192])
+@pytest.mark.parametrize("prec", [arb.ARB_FP64, arb.ARB_FP32C])
+def test_products_in_place(n, prec):
+    import torch
+
+    cl = W.random_blobs(n, seed=500 + n, box=8.0 + n ** 0.5, zlo=1.0, zhi=9.0)
+    c = arb.arb_create(precision=prec, wall=True, pair_kernel=arb.ARB_PAIR_TARGET if n > 8191 else
+                       arb.ARB_PAIR_AUTO)
+    state = arb.context_for(W.loose_blobs(cl["pos"]), precision=prec,
+                            pair_kernel=arb.ARB_PAIR_TARGET if n > 8191 else arb.ARB_PAIR_AUTO)
+    st = torch.cuda.Stream()  # one stream for the copies and the products
+    s = st.cuda_stream
+
+    def room(x, shift):
+        """x in the middle of a larger array, and the result's place beside it."""
+        buf = torch.zeros(3 * n + 60, dtype=torch.float64, device="cuda")
+        v = buf[30:30 + 3 * n]
+        v.copy_(x)
+        return v, buf[30 + shift:30 + shift + 3 * n]
+
+    try:
+        print(f"in place n={n} prec={prec}", flush=True)
+        torch.cuda.set_stream(st)
+        pos, lam = (torch.tensor(np.ravel(cl[k]), dtype=torch.float64, device="cuda")
+                    for k in ("pos", "lam"))
+        want, held = torch.zeros_like(lam), torch.zeros_like(lam)
+        arb.arb_rpy_apply_dev(c, n, pos, lam, want, stream=s)
+        arb.arb_mobility_apply_dev(state, lam, held, stream=s)
+        for shift in (0, 30, -6):
+            x, u = room(lam, shift)
+            arb.arb_rpy_apply_dev(c, n, pos, x, u, stream=s)
+            assert torch.equal(u, want), shift
+            x, u = room(pos, shift)
+            arb.arb_rpy_apply_dev(c, n, x, lam, u, stream=s)
+            assert torch.equal(u, want), shift
+            x, u = room(lam, shift)
+            arb.arb_mobility_apply_dev(state, x, u, stream=s)
+            assert torch.equal(u, held), shift
+    finally:
+        torch.cuda.synchronize()
+        torch.cuda.set_stream(torch.cuda.default_stream())
+        arb.arb_destroy(c)
+        arb.arb_destroy(state)
