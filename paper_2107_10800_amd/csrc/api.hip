@@ -477,7 +477,7 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const do
         arb::pair_small(s, precision, wall, N, raw_pos, p64, hi, lo, lam, perm, ctx->opt.a, scale,
                         dst, U, bob, dvec, rows);
     else if (ring)
-        used = arb::pair_ring(s, precision, wall, N, p64, hi, lo, box, lam, perm, ctx->opt.a,
+        used = arb::pair_ring(s, precision, wall, N, p64, hi, lo, lam, perm, ctx->opt.a,
                               ctx->partial.as<double>());
     else if (sym)
         arb::pair_sym(s, precision, wall, N, p64, hi, lo, box, lam, perm, ctx->opt.a,

@@ -187,8 +187,8 @@ void pair_small(hipStream_t s, int precision, bool wall, int N, const double *ra
 constexpr int kRingPairN = 8192;
 int pair_ring_slices(int N);
 int pair_ring(hipStream_t s, int precision, bool wall, int N, const double4 *p64,
-              const float4 *hi, const float4 *lo, const float4 *box, const double *lam,
-              const int *perm, double a, double *partial);
+              const float4 *hi, const float4 *lo, const double *lam, const int *perm, double a,
+              double *partial);
 // target-parallel sums; returns the number of slices written (clamped to the tile count)
 // positions in the order of perm (may be null), lambda in blob order, partial in
 // the positions' order

@@ -414,6 +414,10 @@ __global__ __launch_bounds__(256) void pair_sym_f64_kernel(int N, const double4 
 // repeat bit for bit.  Float sums run over at most 32 steps.  The target-parallel
 // kernel gave these sizes 160 workgroups or fewer: 5,003 blobs unbounded 98.7 us in
 // FP32, 1,952 above the wall 114 us in FP64, against 26.8 and 13.2 us here.
+// FP32 differences take both parts of the positions in every tile, as the
+// target-parallel kernel does: the far tiles' hi parts alone (the kernel above) would
+// save 2 to 4 % (5,003 ordered blobs above the wall 39.4 -> 38.6 us a product, in random
+// order nothing) and cost up to 2^-20 of a pair's distance.
 struct RingItem {
     int D, d, J, q0, q1;  // half ring, this wavefront's offset and tile, its steps
     bool pair;            // d is a pair of tiles that this target tile sums
@@ -466,8 +470,7 @@ __device__ __forceinline__ void wave_sync() {  // LDS accesses of one wavefront 
 template <bool WALL>
 __global__ __launch_bounds__(256) void pair_ring_f32c_kernel(
     int N, int split, const float4 *__restrict__ hi, const float4 *__restrict__ lo,
-    const float4 *__restrict__ box, const double *__restrict__ lam, const int *__restrict__ perm,
-    double *__restrict__ partial) {
+    const double *__restrict__ lam, const int *__restrict__ perm, double *__restrict__ partial) {
     __shared__ float4 s_tile[4][3][128];
     __shared__ float s_comb[4][2][3][64];
     const int nT = (N + 63) / 64, I = blockIdx.x;
@@ -485,15 +488,11 @@ __global__ __launch_bounds__(256) void pair_ring_f32c_kernel(
         const float zi = t.hi.z + t.lo.z;
         const TargetZ<float> zsc = target_z(zi);
         const int src = (lane + 1) & 63;
-        const bool far = r.d > 0 && far_tiles(box, I, r.J);
         for (int q = r.q0, run = 0; q < r.q1; q += 32, ++run) {
             const int e = min(q + 32, r.q1);
             float fx = 0.f, fy = 0.f, fz = 0.f, ax = 0.f, ay = 0.f, az = 0.f;
             if (r.d == 0)
                 one_way_loop<WALL>(t, zi, zsc, s_hi, s_lo, s_lam, q, e, fx, fy, fz);
-            else if (far)
-                sym_tile_loop<WALL, false>(t, zi, zsc, lane, src, s_hi, s_lo, s_lam, fx, fy, fz,
-                                           ax, ay, az, q, e);
             else
                 sym_tile_loop<WALL, true>(t, zi, zsc, lane, src, s_hi, s_lo, s_lam, fx, fy, fz, ax,
                                           ay, az, q, e);
@@ -558,17 +557,15 @@ int pair_ring_slices(int N) {
 }
 
 int pair_ring(hipStream_t s, int precision, bool wall, int N, const double4 *p64,
-              const float4 *hi, const float4 *lo, const float4 *box, const double *lam,
-              const int *perm, double a, double *partial) {
+              const float4 *hi, const float4 *lo, const double *lam, const int *perm, double a,
+              double *partial) {
     const int nT = (N + 63) / 64, D = nT / 2, split = ring_split(N), G = 4 / split;
     const dim3 grid(nT, (D + G) / G);
     if (precision == ARB_FP32C) {
         if (wall)
-            pair_ring_f32c_kernel<true><<<grid, 256, 0, s>>>(N, split, hi, lo, box, lam, perm,
-                                                              partial);
+            pair_ring_f32c_kernel<true><<<grid, 256, 0, s>>>(N, split, hi, lo, lam, perm, partial);
         else
-            pair_ring_f32c_kernel<false><<<grid, 256, 0, s>>>(N, split, hi, lo, box, lam, perm,
-                                                               partial);
+            pair_ring_f32c_kernel<false><<<grid, 256, 0, s>>>(N, split, hi, lo, lam, perm, partial);
     } else {
         const CoefD c = make_coef<CoefD, double>(a);
         if (wall)

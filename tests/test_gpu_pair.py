@@ -338,3 +338,33 @@ def test_products_in_place(n, prec):
         torch.cuda.set_stream(torch.cuda.default_stream())
         arb.arb_destroy(c)
         arb.arb_destroy(state)
+
+
+# FP32 products below 8,192 blobs keep both parts of every position: one source at about
+# (1000, 1000, 1000) and 1,984 targets about 255 away, in compact tiles, every coordinate
+# just short of half a float step off its rounded value, the source down and the targets
+# up.  The rounded positions alone are 1.7 x 0.98 x 2^-14 off in distance, 4.1e-7 of every
+# velocity; the tensor in float adds errors of about random sign, at most 1 ulp of the
+# reciprocal root (2^-23) and half of three roundings of r^2 (3 x 2^-25) if all of one sign
+def test_mid_size_fp32_keeps_both_parts_of_the_positions():
+    rng = np.random.default_rng(12)
+    step = 2.0 ** -14                    # of floats in [512, 1024)
+    n = 2048
+    pos = 840.0 + np.floor(rng.uniform(0, 20.0, (n, 3)) / step) * step + 0.49 * step
+    pos[:64] = 990.0 + np.floor(rng.uniform(0, 10.0, (64, 3)) / step) * step
+    pos[5] = 1000.0 - 0.49 * step
+    lam = np.zeros((n, 3))
+    lam[5] = (0.7, -1.1, 0.4)
+    uo = rpy.mobility_apply(pos, lam, 1.0, 1.0, False)[64:]
+    err = {}
+    for kind in (arb.ARB_PAIR_AUTO, arb.ARB_PAIR_TARGET):
+        c = arb.arb_create(precision=arb.ARB_FP32C, pair_kernel=kind)
+        try:
+            u = arb.arb_rpy_apply(c, pos, lam).reshape(n, 3)[64:]
+        finally:
+            arb.arb_destroy(c)
+        err[kind] = np.mean(np.sum(u * uo, 1) / np.sum(uo * uo, 1) - 1.0)
+    print(f"mean error {err[arb.ARB_PAIR_AUTO]:.1e}, target-parallel kernel "
+          f"{err[arb.ARB_PAIR_TARGET]:.1e}", flush=True)
+    assert abs(err[arb.ARB_PAIR_AUTO]) <= 2.0 ** -22
+    assert abs(err[arb.ARB_PAIR_TARGET]) <= 2.0 ** -22
