@@ -1187,6 +1187,29 @@ static void near_blocks(const FmmPlan &pl, bool sym, NearBlocks &B) {
     }
 }
 
+// Whether the near field sums both directions of a pair at once: by the steps of its
+// wavefronts over all pairs of adjacent leaves.  A pair of tiles takes 64 steps of 88
+// instructions both ways, however few blobs its tiles hold, and one way a step of 71
+// instructions per source for each direction.
+// Products of order 3 both ways and one way (FP32; FP64 alike), us: leaves of 15 blobs in
+// space 456 and 330, of 34 611 and 571, of 49 629 and 649, of 81 1,176 and 1,256; in a
+// layer above the wall of 49 416 and 367, of 68 532 and 532, of 98 731 and 825.
+static bool near_both_ways(const FmmPlan &pl) {
+    const int leaf0 = pl.lvl[pl.L];
+    int64_t both = 0, one = 0;
+    for (int c = leaf0; c < leaf0 + pl.nleaf; ++c) {
+        const int64_t mc = pl.rng[c].y - pl.rng[c].x, tc = (mc + 63) / 64;
+        for (int e = pl.near_ptr[c - leaf0]; e < pl.near_ptr[c - leaf0 + 1]; ++e) {
+            const int q = pl.nearl[e];
+            if (q <= c) continue;
+            const int64_t mq = pl.rng[q].y - pl.rng[q].x, tq = (mq + 63) / 64;
+            both += 64 * tc * tq;
+            one += tc * mq + tq * mc;
+        }
+    }
+    return 88 * both < 71 * one;
+}
+
 int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const float4 *hi,
               const float4 *lo, double a, int order, int levels, int leaf, int channels, bool wall,
               std::string *msg) {
@@ -1249,7 +1272,7 @@ int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const fl
     // near field: both directions of a pair at once for the 3-component tensor; one way,
     // without slots, with torques or when the slots would outgrow kFmmNearSlots
     NearBlocks &nb = hc.near;
-    bool near_sym = channels == 1;
+    bool near_sym = channels == 1 && near_both_ways(pl);
     near_blocks(pl, near_sym, nb);
     if (near_sym && nb.slots > kFmmNearSlots) {
         near_sym = false;

@@ -17,6 +17,9 @@
 // bacteria 3.54 -> 2.58 ms (issue rate at its limit, 1.46 per clock and CU), diatom
 // colonies with double sums 0.89 -> 0.52 ms.  Blocks of 256 targets with their source
 // sums joined in LDS write a quarter of the slots but wait on barriers: 2.98 ms.
+// Where most leaves fill less than about half a tile, a wavefront's 64 steps both ways
+// cost more than a step per source: such trees are summed one way (near_both_ways in
+// fmm.hip; 100,000 blobs above the wall in leaves of 9: 784 us both ways, 237 one way).
 // Single-blob bodies (6 components) are summed one way, the tensor's few coefficients
 // being a small part of a pair: 4,096 shells 3.19 -> 1.74 ms.  (Two targets per lane,
 // to halve the LDS reads, leave too few blocks: 2.39 against 2.11 ms before the blocks

@@ -122,6 +122,24 @@ def test_near_field_blocks_at_their_edges(wall, L):
         assert np.abs(u[0] - ref).max() <= 1e-5 * np.abs(ref).max()
 
 
+# leaves too small for a wavefront's 64 steps both ways are summed one way, fuller ones both
+# ways, by the tree's steps in all (a row of nearly empty leaves, of leaves just below and
+# just above half a tile, of full tiles, and mixed); orders 2 to 4 also join the sums of
+# many groups of lanes in M2L's sparse part
+@pytest.mark.parametrize("counts", [[1, 7, 30, 2, 5, 3, 64, 20], [39] * 8, [41] * 8, [64] * 8,
+                                    [3, 3, 300, 300, 3, 3, 2, 1]])
+@pytest.mark.parametrize("n,wall", [(2, True), (3, False), (4, True)])
+def test_near_field_one_way_and_both_ways(counts, n, wall):
+    rng = np.random.default_rng(33 + n)
+    pos = leaves_of(counts, rng)
+    lam = rng.standard_normal((len(pos), 3))
+    ref = fastsum.fmm_apply(pos, lam, 1.0, 1.0, wall, n, 3)
+    for prec in (arb.ARB_FP64, arb.ARB_FP32C):
+        u = [fmm(pos, lam, wall, n, 3, precision=prec) for _ in range(2)]
+        assert np.array_equal(u[0], u[1])
+        assert np.abs(u[0] - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
 def test_products_share_a_tree_with_torques():
     """The translational product of single-blob bodies runs on the tree of the
     generalised one (no slots: the near field one way), before and after it."""
