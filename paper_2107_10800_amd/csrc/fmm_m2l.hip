@@ -301,6 +301,8 @@ struct SparseShape {
     static constexpr int lanes = P / KZ;
     static constexpr int block = NO == 6 ? 512 : 256, groups = block / lanes;
     static constexpr int chunk = groups * kFmmRun < block ? groups * kFmmRun : block;
+    // groups whose sums are joined at a time
+    static constexpr int join = NO == 2 ? 16 : (NO == 3 ? 14 : (NO == 4 ? 8 : 1));
 };
 constexpr int kMaxListed = 189;  // cells of an interaction list (6^3 - 3^3)
 static_assert(kMaxListed <= 256, "one list entry per thread");
@@ -456,20 +458,47 @@ void fmm_p2l_kernel(
                 }
         }
     }
-    // the groups' sums, added in group order
-    for (int gr = 0; gr < Sh::groups; ++gr) {
-        if (grp == gr) {
+    // the groups' sums, added in group order; those of the many small groups of low orders
+    // through LDS, several at a time (a barrier per group: 145 us for order 2 on a slab of
+    // 100,000 blobs in leaves of 9, now 61)
+    if constexpr (Sh::join > 1) {
+        __shared__ double s_join[Sh::join][NB * P];
+        for (int g0 = 0; g0 < Sh::groups; g0 += Sh::join) {
+            if (grp >= g0 && grp < min(g0 + Sh::join, Sh::groups)) {
 #pragma unroll
-            for (int kz = 0; kz < KZ; ++kz)
+                for (int kz = 0; kz < KZ; ++kz)
 #pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    if constexpr (F32)
-                        s_sum[i][k0 + kz] += sum[kz][i];
-                    else
-                        s_sum[i][k0 + kz] += run[kz][i];
-                }
+                    for (int i = 0; i < NB; ++i) {
+                        if constexpr (F32)
+                            s_join[grp - g0][i * P + k0 + kz] = sum[kz][i];
+                        else
+                            s_join[grp - g0][i * P + k0 + kz] = run[kz][i];
+                    }
+            }
+            __syncthreads();
+            const int cnt = min(Sh::join, Sh::groups - g0);
+            for (int i = tid; i < NB * P; i += block) {
+                double t = s_sum[i / P][i % P];
+                for (int q = 0; q < cnt; ++q) t += s_join[q][i];
+                s_sum[i / P][i % P] = t;
+            }
+            __syncthreads();
         }
-        __syncthreads();
+    } else {
+        for (int gr = 0; gr < Sh::groups; ++gr) {
+            if (grp == gr) {
+#pragma unroll
+                for (int kz = 0; kz < KZ; ++kz)
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        if constexpr (F32)
+                            s_sum[i][k0 + kz] += sum[kz][i];
+                        else
+                            s_sum[i][k0 + kz] += run[kz][i];
+                    }
+            }
+            __syncthreads();
+        }
     }
     for (int i = tid; i < 3 * P; i += block) {
         if (splits == 1) {
@@ -495,7 +524,7 @@ __global__ __launch_bounds__(256) void fmm_m2l_sum_kernel(int cell0, int c0, int
                                                           double *__restrict__ vw) {
     const int ci = c0 + blockIdx.x, W = P3 * channels;
     const int s0 = slot_ptr[ci] - slot0, s1 = slot_ptr[ci + 1] - slot0;
-    for (int i = blockIdx.y * 256 + threadIdx.x; i < W; i += 256 * gridDim.y) {
+    for (int i = blockIdx.y * blockDim.x + threadIdx.x; i < W; i += blockDim.x * gridDim.y) {
         double *v = (i < P3 ? vu : vw) + (size_t)(cell0 + ci) * P3 + i % P3;
         double t = 0.0;
         if (splits == 1)
@@ -518,6 +547,7 @@ void run_m2l(const FmmState &F, hipStream_t s) {
     const Vec4<A> *qf = F.qhat.as<Vec4<A>>(), *qt = F.qhat2.as<Vec4<A>>();
     double *vu = F.v.as<double>(), *vw = F.v2.as<double>();
     const int cell0 = F.lvl[2], nc = F.lvl[L + 1] - cell0, splits = F.splits;
+    const int W = 3 * P * CH;
     with_order(F.n, [&](auto o) {
         constexpr int NO = decltype(o)::value;
         fmm_p2l_kernel<WALL, CH, A, NO>
@@ -535,8 +565,8 @@ void run_m2l(const FmmState &F, hipStream_t s) {
                         g, tab, F.batches.as<FmmBatch>() + ch.batch0, tasks, items,
                         F.cols.as<int2>(), qf, qt, F.slots.as<double>());
             if (items > 0 || splits > 1)
-                fmm_m2l_sum_kernel<<<dim3(ch.cell1 - ch.cell0, (3 * P * CH + 255) / 256), 256, 0,
-                                     s>>>(cell0, ch.cell0, 3 * P, CH, splits,
+                fmm_m2l_sum_kernel<<<dim3(ch.cell1 - ch.cell0, (W + 255) / 256),
+                                     std::min(256, round_up(W, kWave)), 0, s>>>(cell0, ch.cell0, 3 * P, CH, splits,
                                           F.slot_ptr.as<int>(), ch.slot0, F.slots.as<double>(),
                                           F.vsplit.as<double>(), vu, vw);
         }
