@@ -1269,20 +1269,6 @@ int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const fl
                (F.slam2.ensure((size_t)N * sizeof(double4)) == hipSuccess &&
                 F.qhat2.ensure((size_t)ncell * P * sizeof(double4)) == hipSuccess &&
                 F.v2.ensure((size_t)ncell * P * 3 * sizeof(double)) == hipSuccess));
-    // near field: both directions of a pair at once for the 3-component tensor; one way,
-    // without slots, with torques or when the slots would outgrow kFmmNearSlots
-    NearBlocks &nb = hc.near;
-    bool near_sym = channels == 1 && near_both_ways(pl);
-    near_blocks(pl, near_sym, nb);
-    if (near_sym && nb.slots > kFmmNearSlots) {
-        near_sym = false;
-        near_blocks(pl, false, nb);
-    }
-    ok = ok && up(F.blocks, nb.blocks.data(), nb.blocks.size() * sizeof(int4)) &&
-         up(F.in_ptr, nb.in_ptr.data(), nb.in_ptr.size() * sizeof(int)) &&
-         up(F.in, nb.in.data(), nb.in.size() * sizeof(int)) &&
-         F.own.ensure((size_t)N * 3 * channels * sizeof(double)) == hipSuccess &&
-         F.near_slots.ensure((size_t)nb.slots * 3 * sizeof(double)) == hipSuccess;
     // M2L's batches: 32 columns, 16 with the torque channel; slots of a chunk bounded
     M2LGroups &mg = hc.m2l;
     const int64_t slot_doubles = 3 * (int64_t)P * channels;
@@ -1300,6 +1286,23 @@ int fmm_build(FmmState &F, hipStream_t s, int N, const double *pos_dev, const fl
     ok = ok && (splits == 1 ||
                 F.vsplit.ensure((size_t)nc_m2l * splits * P * 3 * channels * sizeof(double)) ==
                     hipSuccess);
+    ok = ok && F.own.ensure((size_t)N * 3 * channels * sizeof(double)) == hipSuccess;
+    // near field: both directions of a pair at once for the 3-component tensor; one way,
+    // without slots, with torques, where leaves are nearly empty, or when the slots would
+    // outgrow kFmmNearSlots or the memory that the rest leaves
+    NearBlocks &nb = hc.near;
+    bool near_sym = channels == 1 && near_both_ways(pl);
+    near_blocks(pl, near_sym, nb);
+    if (near_sym && ok &&
+        (nb.slots > kFmmNearSlots ||
+         F.near_slots.ensure((size_t)nb.slots * 3 * sizeof(double)) != hipSuccess)) {
+        (void)hipGetLastError();
+        near_sym = false;
+        near_blocks(pl, false, nb);
+    }
+    ok = ok && up(F.blocks, nb.blocks.data(), nb.blocks.size() * sizeof(int4)) &&
+         up(F.in_ptr, nb.in_ptr.data(), nb.in_ptr.size() * sizeof(int)) &&
+         up(F.in, nb.in.data(), nb.in.size() * sizeof(int));
     if (!ok) {
         *msg = "fast product: device allocation or copy failed";
         return ARB_E_DEVICE;

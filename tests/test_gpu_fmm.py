@@ -140,6 +140,37 @@ def test_near_field_one_way_and_both_ways(counts, n, wall):
         assert np.abs(u[0] - ref).max() <= 1e-5 * np.abs(ref).max()
 
 
+def test_near_field_without_room_for_its_slots():
+    """The near field's slots are optional memory (2.9 GB here: 260,000 blobs in 64
+    leaves): with less than that left on the device, everything else (under 0.1 GB)
+    fitting, the product sums the near field one way.  The tensor's floats are the same
+    for both directions and the sums double, over 64,000 near blobs per blob: rounding
+    at most 64,000 x 2^-53 of the sum of the magnitudes, a few hundred times the
+    largest velocity."""
+    import torch
+
+    rng = np.random.default_rng(8)
+    N, left = 260000, 2 << 30
+    pos, lam = rng.uniform(0, 200.0, (N, 3)), rng.standard_normal((N, 3))
+    u = fmm(pos, lam, False, 4, 2)
+    filler = []
+    try:
+        while True:
+            torch.cuda.empty_cache()
+            room = torch.cuda.mem_get_info()[0] - left
+            if room < 64 << 20:
+                break
+            filler.append(torch.empty(min(room, 16 << 30), dtype=torch.uint8, device="cuda"))
+        free = torch.cuda.mem_get_info()[0]
+        print(f"free on the device: {free / 2 ** 30:.2f} GiB", flush=True)
+        assert free < 5 * left // 4
+        v = fmm(pos, lam, False, 4, 2)
+    finally:
+        filler.clear()
+        torch.cuda.empty_cache()
+    assert np.abs(u - v).max() <= 1e-9 * np.abs(u).max()
+
+
 def test_products_share_a_tree_with_torques():
     """The translational product of single-blob bodies runs on the tree of the
     generalised one (no slots: the near field one way), before and after it."""
