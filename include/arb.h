@@ -257,7 +257,8 @@ int arb_fmm_get_stats(const arb_ctx *ctx, arb_fmm_stats *out);
  * would use (a = blob radius; order, levels, leaf as the fmm_* options, 0 for
  * their defaults); build_ms is the host time of the planning, plan_hash a
  * digest of the whole plan.  The planning runs on up to 16 host threads (one
- * per 65,536 blobs); the environment variable ARB_HOST_THREADS (1..16) caps
+ * per 65,536 blobs or entries of the cells' lists); the environment variable
+ * ARB_HOST_THREADS (1..16) caps
  * them, here and in the products' tree builds; the plan does not depend on the
  * count.  Returns ARB_E_ARG for bad sizes or options, ARB_E_NAN for a
  * non-finite position, ARB_E_HOST when host memory or a thread fails. */

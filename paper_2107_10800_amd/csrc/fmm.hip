@@ -53,6 +53,7 @@
 #include <condition_variable>
 #include <functional>
 #include <mutex>
+#include <numeric>
 #include <memory>
 #include <cmath>
 #include <cstdlib>
@@ -60,6 +61,7 @@
 #include <system_error>
 #include <thread>
 #include <type_traits>
+#include <utility>
 
 #include "fmm_device.h"
 
@@ -345,17 +347,21 @@ inline int compact3(uint64_t x) {  // every third bit -> 21 bits (inverse of spr
     return (int)x;
 }
 
-// host threads for the O(N) steps of the tree build: at most 16 (one GPU's
-// share of the host), one per 65,536 blobs; the environment variable
-// ARB_HOST_THREADS (1..16) caps them (the plan does not depend on the count)
-int host_threads(int N) {
+// host threads for a step over `items` items: at most 16 (one GPU's share of the
+// host), one per `each` items; the environment variable ARB_HOST_THREADS (1..16)
+// caps them (the tree does not depend on the count)
+int step_threads(int64_t items, int each) {
     int hw = (int)std::max(1u, std::thread::hardware_concurrency());
     if (const char *e = std::getenv("ARB_HOST_THREADS")) {
         const int v = std::atoi(e);
         if (v >= 1 && v <= 16) hw = std::min(hw, v);
     }
-    return std::max(1, std::min({16, hw, N / 65536}));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(std::min(16, hw), items / each));
 }
+// for the O(N) steps of the tree build
+int host_threads(int N) { return step_threads(N, 65536); }
+// entries of the cells' lists per thread of a step over them
+constexpr int kListStep = 65536;
 
 // FNV-1a over the bytes of a vector
 template <class V>
@@ -580,7 +586,7 @@ struct HostArr {
 // slots of its dense entries, the dense entries grouped into batches, and the
 // chunks of cells that share the slots' memory
 struct M2LGroups {
-    std::vector<int> sp_ptr, sp, sp_order, slot_ptr, count, zidx;
+    std::vector<int> sp_ptr, sp, sp_order, slot_ptr, count, zidx, blobs, sparse, listed, key;
     std::vector<int2> cols;
     std::vector<FmmBatch> batches;
     std::vector<FmmChunk> chunks;
@@ -589,8 +595,9 @@ struct M2LGroups {
 // the near field's work (fmm_near.hip): blocks of targets (leaf, first target,
 // targets, first slot) and, per leaf, the slots that other blocks fill for it
 struct NearBlocks {
-    std::vector<int4> blocks;
-    std::vector<int> in_ptr, in;
+    std::vector<int4> blocks, by_leaf;
+    std::vector<int> in_ptr, in, first, next;
+    std::vector<int64_t> visited, per_block, cost;
     int64_t slots = 0;  // blobs' worth of slots (3 doubles each)
 };
 struct PlanScratch {
@@ -754,9 +761,18 @@ int fmm_plan(FmmPlan &pl, PlanScratch &sc, int N, const double *h, double a, int
     // interaction lists, the adjacent leaves and the work items of leaf level L
     auto build = [&](int L, FmmPlan &q) -> int {
         // cells of every level in Morton order, with their blob ranges
+        std::vector<std::vector<int>> starts_t((size_t)T * (L + 1));
+        parallel_slices(T, N, [&](int t, int i0, int i1) {
+            std::vector<int> *st = starts_t.data() + (size_t)t * (L + 1);
+            for (int j = std::max(i0, 1); j < i1; ++j)
+                for (int l = first[j]; l <= L; ++l) st[l].push_back(j);
+        });
         std::vector<std::vector<int>> starts(L + 1, std::vector<int>(1, 0));
-        for (int j = 1; j < N; ++j)
-            for (int l = first[j]; l <= L; ++l) starts[l].push_back(j);
+        for (int t = 0; t < T; ++t)
+            for (int l = 0; l <= L; ++l) {
+                const std::vector<int> &st = starts_t[(size_t)t * (L + 1) + l];
+                starts[l].insert(starts[l].end(), st.begin(), st.end());
+            }
         std::vector<int4> cc;
         std::vector<int2> rng;
         std::vector<uint64_t> pk;
@@ -824,39 +840,59 @@ int fmm_plan(FmmPlan &pl, PlanScratch &sc, int N, const double *h, double a, int
         std::vector<int2> work;
         for (int c = leaf0; c < leaf0 + nleaf; ++c)
             for (int k0 = rng[c].x; k0 < rng[c].y; k0 += kNearBlock) work.push_back(make_int2(c, k0));
+        // per cell the blobs of its interaction list, and M2L's pair evaluations: n^3 per
+        // proxy of each listed cell, or per blob when it holds fewer blobs than proxies
+        const int Tl = step_threads((int64_t)il.size(), kListStep);
+        std::vector<int64_t> listed((size_t)ncell), m2l((size_t)Tl);
+        parallel_slices(Tl, ncell, [&](int t, int c0, int c1) {
+            int64_t pairs = 0;
+            for (int c = c0; c < c1; ++c) {
+                int64_t m = 0;
+                for (int e = il_ptr[c]; e < il_ptr[c + 1]; ++e) {
+                    const int n = rng[il[e]].y - rng[il[e]].x;
+                    m += n;
+                    pairs += (int64_t)P * std::min(P, n);
+                }
+                listed[c] = m;
+            }
+            m2l[t] = pairs;
+        });
         // every target sees every source exactly once: the adjacent leaves and the
         // interaction lists of its ancestors hold N blobs between them, and every
         // index handed to a kernel is in range
-        for (int c = leaf0; c < leaf0 + nleaf; ++c) {
-            int64_t cnt = 0;
-            for (int e = near_ptr[c - leaf0]; e < near_ptr[c - leaf0 + 1]; ++e) {
-                const int q = nearl[e];
-                if (q < leaf0 || q >= leaf0 + nleaf) {
-                    *msg = "fast product: internal error (near list)";
-                    return ARB_E_ARG;
+        const int Tn = step_threads((int64_t)nearl.size(), kListStep);
+        std::vector<int64_t> pairs((size_t)Tn);
+        std::vector<int> fault((size_t)Tn, 0);
+        parallel_slices(Tn, nleaf, [&](int t, int i0, int i1) {
+            int64_t near = 0;
+            for (int i = i0; i < i1 && !fault[t]; ++i) {
+                const int c = leaf0 + i;
+                int64_t cnt = 0;
+                for (int e = near_ptr[i]; e < near_ptr[i + 1]; ++e) {
+                    const int q = nearl[e];
+                    if (q < leaf0 || q >= leaf0 + nleaf) {
+                        fault[t] = 1;
+                        break;
+                    }
+                    cnt += rng[q].y - rng[q].x;
                 }
-                cnt += rng[q].y - rng[q].x;
+                near += cnt * (rng[c].y - rng[c].x);
+                for (int a2 = c; a2 >= 0 && cc[a2].w >= 2; a2 = parent[a2]) cnt += listed[a2];
+                if (cnt != N && !fault[t]) fault[t] = 2;
             }
-            for (int a2 = c; a2 >= 0 && cc[a2].w >= 2; a2 = parent[a2])
-                for (int e = il_ptr[a2]; e < il_ptr[a2 + 1]; ++e) cnt += rng[il[e]].y - rng[il[e]].x;
-            if (cnt != N) {
-                *msg = "fast product: internal error (cells do not partition the blobs)";
+            pairs[t] = near;
+        });
+        for (int f : fault)
+            if (f) {
+                *msg = f == 1 ? "fast product: internal error (near list)"
+                              : "fast product: internal error (cells do not partition the blobs)";
                 return ARB_E_ARG;
             }
-        }
         q.L = L;
         q.ncell = ncell;
         q.nleaf = nleaf;
-        // M2L pair evaluations: n^3 per proxy of each listed cell, or per blob
-        // when the listed cell holds fewer blobs than proxies
-        q.n_m2l_pairs = 0;
-        for (int e = 0; e < (int)il.size(); ++e)
-            q.n_m2l_pairs += (int64_t)P * std::min(P, rng[il[e]].y - rng[il[e]].x);
-        q.n_near_pairs = 0;
-        for (int c = leaf0; c < leaf0 + nleaf; ++c)
-            for (int e = near_ptr[c - leaf0]; e < near_ptr[c - leaf0 + 1]; ++e)
-                q.n_near_pairs +=
-                    (int64_t)(rng[c].y - rng[c].x) * (rng[nearl[e]].y - rng[nearl[e]].x);
+        q.n_m2l_pairs = std::accumulate(m2l.begin(), m2l.end(), int64_t(0));
+        q.n_near_pairs = std::accumulate(pairs.begin(), pairs.end(), int64_t(0));
         q.lvl = std::move(lvl);
         q.cc = std::move(cc);
         q.rng = std::move(rng);
@@ -1025,15 +1061,25 @@ int fmm_plan(FmmPlan &pl, PlanScratch &sc, int N, const double *h, double a, int
 
 // Work items longest first when there are so few that the last ones to start decide
 // when a launch ends (a few per compute unit; with more, neighbours stay together for
-// the caches): cost[k] of item k, the order in `order`
+// the caches): cost[k] >= 0 of item k, the order in `order`; equal costs keep their order
+// (a stable radix sort, 12 bits a pass)
 constexpr int kSortItems = 16384;
 template <class V>
 static void longest_first(const std::vector<V> &cost, std::vector<int> &order) {
-    order.resize(cost.size());
-    for (size_t k = 0; k < cost.size(); ++k) order[k] = (int)k;
-    if (cost.size() <= kSortItems)
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int a, int b) { return cost[a] > cost[b]; });
+    const size_t n = cost.size();
+    order.resize(n);
+    for (size_t k = 0; k < n; ++k) order[k] = (int)k;
+    if (n > kSortItems || n < 2) return;
+    const V top = *std::max_element(cost.begin(), cost.end());
+    std::vector<int> other(n), count;
+    for (int shift = 0; shift < 63 && (uint64_t)top >> shift; shift += 12) {
+        auto digit = [&](int k) { return (uint64_t)(top - cost[k]) >> shift & 4095; };
+        count.assign(4097, 0);
+        for (int k : order) ++count[digit(k) + 1];
+        for (int d = 0; d < 4096; ++d) count[d + 1] += count[d];
+        for (int k : order) other[count[digit(k)]++] = k;
+        order.swap(other);
+    }
 }
 
 // Groups the interaction lists for M2L.  Entries whose listed cell holds at least P
@@ -1041,42 +1087,60 @@ static void longest_first(const std::vector<V> &cost, std::vector<int> &order) {
 // target cells, and are sorted (counting sort, stable) by the key that fixes the
 // tensor between the two proxy grids: the level, the cells' offset and, above the
 // wall, the target cell's height.  Equal keys make batches of at most max_cols
-// columns.
+// columns.  Host threads take slices of the cells, each with counts of its own, and
+// place their entries in slice order, as one thread would.
 static void group_m2l(const FmmPlan &pl, bool wall, int max_cols, int64_t chunk_slots,
                       M2LGroups &G) {
-    G.sp.clear();
-    G.cols.clear();
     G.batches.clear();
     G.chunks.clear();
     G.max_slots = 0;
     const int cell0 = pl.L >= 2 ? pl.lvl[2] : pl.ncell, nc = pl.ncell - cell0, P = pl.P;
+    const int T = step_threads((int64_t)pl.il.size(), kListStep);
+    // blobs of a cell when it is sparse, 0 when it is dense (the passes over the lists
+    // do not branch on it: both kinds are mixed)
+    G.sparse.resize((size_t)pl.ncell);
+    for (int c = 0; c < pl.ncell; ++c) {
+        const int m = pl.rng[c].y - pl.rng[c].x;
+        G.sparse[c] = m >= P ? 0 : m;
+    }
     G.sp_ptr.assign((size_t)nc + 1, 0);
     G.slot_ptr.assign((size_t)nc + 1, 0);
-    auto dense = [&](int sc) { return pl.rng[sc].y - pl.rng[sc].x >= P; };
-    for (int i = 0; i < nc; ++i) {
-        int d = 0;
-        for (int e = pl.il_ptr[cell0 + i]; e < pl.il_ptr[cell0 + i + 1]; ++e) {
-            if (dense(pl.il[e]))
-                ++d;
-            else
-                G.sp.push_back(pl.il[e]);
+    G.blobs.assign((size_t)nc, 0);
+    parallel_slices(T, nc, [&](int, int i0, int i1) {
+        for (int i = i0; i < i1; ++i) {
+            const int e0 = pl.il_ptr[cell0 + i], e1 = pl.il_ptr[cell0 + i + 1];
+            int d = 0, m = 0;
+            for (int e = e0; e < e1; ++e) {
+                const int n = G.sparse[pl.il[e]];
+                d += n == 0;
+                m += n;
+            }
+            G.slot_ptr[i + 1] = d;
+            G.sp_ptr[i + 1] = e1 - e0 - d;
+            G.blobs[i] = m;
         }
-        G.sp_ptr[i + 1] = (int)G.sp.size();
-        G.slot_ptr[i + 1] = G.slot_ptr[i] + d;
+    });
+    for (int i = 0; i < nc; ++i) {
+        G.sp_ptr[i + 1] += G.sp_ptr[i];
+        G.slot_ptr[i + 1] += G.slot_ptr[i];
     }
-    {
-        std::vector<int> blobs((size_t)nc);
-        for (int i = 0; i < nc; ++i)
-            for (int e = G.sp_ptr[i]; e < G.sp_ptr[i + 1]; ++e)
-                blobs[i] += pl.rng[G.sp[e]].y - pl.rng[G.sp[e]].x;
-        longest_first(blobs, G.sp_order);
-    }
+    // the sparse listed cells, and the dense one of each slot
+    G.sp.resize((size_t)G.sp_ptr[nc]);
+    G.listed.resize((size_t)G.slot_ptr[nc]);
+    G.key.resize((size_t)G.slot_ptr[nc]);
+    parallel_slices(T, nc, [&](int, int i0, int i1) {
+        int *to[2] = {G.sp.data() + G.sp_ptr[i0], G.listed.data() + G.slot_ptr[i0]};
+        for (int e = pl.il_ptr[cell0 + i0]; e < pl.il_ptr[cell0 + i1]; ++e) {
+            const int q = pl.il[e];
+            *to[G.sparse[q] == 0]++ = q;
+        }
+    });
+    longest_first(G.blobs, G.sp_order);
     G.cols.resize((size_t)G.slot_ptr[nc]);
     for (int a = 0; a < nc;) {
         int b = a + 1;
         while (b < nc && G.slot_ptr[b + 1] - G.slot_ptr[a] <= chunk_slots) ++b;
         FmmChunk ch{a, b, (int)G.batches.size(), 0, G.slot_ptr[a]};
-        int out = G.slot_ptr[a];
         for (int x = a; x < b;) {  // the cells of one level
             const int l = pl.cc[cell0 + x].w;
             int y = x + 1;
@@ -1095,40 +1159,46 @@ static void group_m2l(const FmmPlan &pl, bool wall, int max_cols, int64_t chunk_
                     if (zi < 0) zi = nz++;
                 }
             }
-            auto key = [&](const int4 &t, const int4 &s) {
-                const int d = ((t.x - s.x + 3) * 7 + (t.y - s.y + 3)) * 7 + (t.z - s.z + 3);
-                return (wall ? G.zidx[t.z - z0] : 0) * 343 + d;
-            };
-            G.count.assign((size_t)nz * 343 + 1, 0);
-            for (int i = x; i < y; ++i)
-                for (int e = pl.il_ptr[cell0 + i]; e < pl.il_ptr[cell0 + i + 1]; ++e)
-                    if (dense(pl.il[e])) ++G.count[key(pl.cc[cell0 + i], pl.cc[pl.il[e]]) + 1];
-            for (int k = 0; k < nz * 343; ++k) G.count[k + 1] += G.count[k];
-            const int base = out;
-            out += G.count[nz * 343];
-            for (int i = x; i < y; ++i) {
-                int slot = G.slot_ptr[i] - ch.slot0;
-                for (int e = pl.il_ptr[cell0 + i]; e < pl.il_ptr[cell0 + i + 1]; ++e) {
-                    const int sc = pl.il[e];
-                    if (!dense(sc)) continue;
-                    const int at = base + G.count[key(pl.cc[cell0 + i], pl.cc[sc])]++;
-                    G.cols[at] = make_int2(sc, slot++);
+            const int base = G.slot_ptr[x], m = G.slot_ptr[y] - base, keys = nz * 343;
+            // (summing up the counts takes less than placing the entries)
+            const int Tr = std::max(1, std::min(step_threads(m, kListStep / 2), m / keys));
+            G.count.assign((size_t)Tr * keys, 0);
+            parallel_slices(Tr, y - x, [&](int t, int i0, int i1) {
+                int *n = G.count.data() + (size_t)t * keys;
+                for (int i = x + i0; i < x + i1; ++i) {
+                    const int4 c = pl.cc[cell0 + i];
+                    const int k0 = wall ? G.zidx[c.z - z0] * 343 : 0;
+                    for (int e = G.slot_ptr[i]; e < G.slot_ptr[i + 1]; ++e) {
+                        const int4 q = pl.cc[G.listed[e]];
+                        const int k = k0 + ((c.x - q.x + 3) * 7 + (c.y - q.y + 3)) * 7 +
+                                      (c.z - q.z + 3);
+                        G.key[e] = k;
+                        ++n[k];
+                    }
                 }
-            }
-            // count[k] is now the end of key k's entries
-            for (int zi = 0, k0 = 0; zi < nz; ++zi) {
+            });
+            // counts to places: by key, then by slice; the key's batches on the way
+            for (int zi = 0, run = base; zi < nz; ++zi) {
                 int tz = 0;
                 if (wall)
                     while (G.zidx[tz] != zi) ++tz;
                 for (int d = 0; d < 343; ++d) {
-                    const int k1 = G.count[zi * 343 + d];
-                    for (int f = k0; f < k1; f += max_cols)
-                        G.batches.push_back(FmmBatch{base + f, std::min(max_cols, k1 - f), l,
+                    const int k0 = run;
+                    for (int t = 0; t < Tr; ++t) {
+                        int &n = G.count[(size_t)t * keys + zi * 343 + d];
+                        run += std::exchange(n, run);
+                    }
+                    for (int f = k0; f < run; f += max_cols)
+                        G.batches.push_back(FmmBatch{f, std::min(max_cols, run - f), l,
                                                      wall ? z0 + tz : 0, d / 49 - 3,
                                                      (d / 7) % 7 - 3, d % 7 - 3, 0});
-                    k0 = k1;
                 }
             }
+            parallel_slices(Tr, y - x, [&](int t, int i0, int i1) {
+                int *at = G.count.data() + (size_t)t * keys;
+                for (int e = G.slot_ptr[x + i0]; e < G.slot_ptr[x + i1]; ++e)
+                    G.cols[at[G.key[e]]++] = make_int2(G.listed[e], e - ch.slot0);
+            });
             x = y;
         }
         ch.batch1 = (int)G.batches.size();
@@ -1139,52 +1209,83 @@ static void group_m2l(const FmmPlan &pl, bool wall, int max_cols, int64_t chunk_
 }
 
 // Blocks of at most kNearBlock targets of one leaf; with sym, the slots of each block: one
-// per adjacent leaf after its own (in cell order), |leaf| blobs each.
+// per adjacent leaf after its own (in list order), |leaf| blobs each, and per leaf the
+// slots that the blocks before fill for it, in the blocks' order by leaf.
 static void near_blocks(const FmmPlan &pl, bool sym, NearBlocks &B) {
-    const int leaf0 = pl.lvl[pl.L];
-    std::vector<int4> blocks;
-    std::vector<int64_t> cost;
-    B.blocks.clear();
-    B.in.clear();
-    B.in_ptr.assign((size_t)pl.nleaf + 1, 0);
-    B.slots = 0;
-    for (int c = leaf0; c < leaf0 + pl.nleaf; ++c) {
-        int64_t per_block = 0, visited = 0;
-        int after = 0;
-        for (int e = pl.near_ptr[c - leaf0]; e < pl.near_ptr[c - leaf0 + 1]; ++e) {
-            const int q = pl.nearl[e], m = pl.rng[q].y - pl.rng[q].x;
-            if (!sym || q >= c) visited += m;
-            if (sym && q > c) {
-                per_block += m;
-                ++after;
+    const int leaf0 = pl.lvl[pl.L], n = pl.nleaf;
+    const int T = step_threads((int64_t)pl.nearl.size(), kListStep);
+    auto size = [&](int c) { return pl.rng[c].y - pl.rng[c].x; };
+    auto count = [&](int c) { return (size(c) + kNearBlock - 1) / kNearBlock; };
+    B.visited.resize((size_t)n);
+    B.per_block.resize((size_t)n);
+    parallel_slices(T, n, [&](int, int i0, int i1) {
+        for (int i = i0; i < i1; ++i) {
+            int64_t all = 0, after = 0;
+            for (int e = pl.near_ptr[i]; e < pl.near_ptr[i + 1]; ++e) {
+                const int q = pl.nearl[e];
+                all += size(q);
+                if (q > leaf0 + i) after += size(q);
             }
+            B.visited[i] = sym ? after + size(leaf0 + i) : all;
+            B.per_block[i] = sym ? after : 0;
         }
-        const int2 r = pl.rng[c];
-        for (int t = r.x; t < r.y; t += kNearBlock) {
-            blocks.push_back(make_int4(c, t, std::min(kNearBlock, r.y - t), (int)B.slots));
-            cost.push_back(visited);
-            B.slots += per_block;
-            if (after)
-                for (int e = pl.near_ptr[c - leaf0]; e < pl.near_ptr[c - leaf0 + 1]; ++e)
-                    if (pl.nearl[e] > c) ++B.in_ptr[pl.nearl[e] - leaf0 + 1];
+    });
+    B.first.resize((size_t)n + 1);
+    B.first[0] = 0;
+    B.slots = 0;
+    for (int i = 0; i < n; ++i) {
+        B.first[i + 1] = B.first[i] + count(leaf0 + i);
+        B.slots += count(leaf0 + i) * B.per_block[i];
+    }
+    B.in.clear();
+    B.in_ptr.assign((size_t)n + 1, 0);
+    const bool fits = B.slots <= kFmmNearSlots;  // else the caller takes the other form
+    B.by_leaf.resize((size_t)B.first[n]);
+    B.cost.resize((size_t)B.first[n]);
+    for (int64_t i = 0, at = 0; i < n; ++i) {
+        const int2 r = pl.rng[leaf0 + i];
+        for (int b = B.first[i], t = r.x; t < r.y; ++b, t += kNearBlock) {
+            B.by_leaf[b] = make_int4(leaf0 + (int)i, t, std::min(kNearBlock, r.y - t),
+                                     fits ? (int)at : 0);
+            B.cost[b] = B.visited[i];
+            at += B.per_block[i];
         }
     }
     std::vector<int> order;
-    longest_first(cost, order);
-    for (int k : order) B.blocks.push_back(blocks[k]);
-    if (!sym || B.slots > kFmmNearSlots) return;
-    for (int q = 0; q < pl.nleaf; ++q) B.in_ptr[q + 1] += B.in_ptr[q];
-    B.in.resize((size_t)B.in_ptr[pl.nleaf]);
-    std::vector<int> next(B.in_ptr.begin(), B.in_ptr.end() - 1);
-    for (const int4 &b : B.blocks) {
-        int at = b.w;
-        for (int e = pl.near_ptr[b.x - leaf0]; e < pl.near_ptr[b.x - leaf0 + 1]; ++e) {
-            const int q = pl.nearl[e];
-            if (q <= b.x) continue;
-            B.in[next[q - leaf0]++] = at;
-            at += pl.rng[q].y - pl.rng[q].x;
+    longest_first(B.cost, order);
+    B.blocks.resize(order.size());
+    for (size_t k = 0; k < order.size(); ++k) B.blocks[k] = B.by_leaf[order[k]];
+    if (!sym || !fits) return;
+    // per thread the slots its leaves' blocks fill for each leaf, then their places
+    B.next.assign((size_t)T * n, 0);
+    parallel_slices(T, n, [&](int t, int i0, int i1) {
+        int *c = B.next.data() + (size_t)t * n;
+        for (int i = i0; i < i1; ++i)
+            for (int e = pl.near_ptr[i]; e < pl.near_ptr[i + 1]; ++e)
+                if (pl.nearl[e] > leaf0 + i) c[pl.nearl[e] - leaf0] += count(leaf0 + i);
+    });
+    int run = 0;
+    for (int q = 0; q < n; ++q) {
+        for (int t = 0; t < T; ++t) {
+            int &c = B.next[(size_t)t * n + q];
+            run += std::exchange(c, run);
         }
+        B.in_ptr[q + 1] = run;
     }
+    B.in.resize((size_t)run);
+    parallel_slices(T, n, [&](int t, int i0, int i1) {
+        int *c = B.next.data() + (size_t)t * n;
+        for (int b = B.first[i0]; b < B.first[i1]; ++b) {
+            const int leaf = B.by_leaf[b].x;
+            int at = B.by_leaf[b].w;
+            for (int e = pl.near_ptr[leaf - leaf0]; e < pl.near_ptr[leaf - leaf0 + 1]; ++e) {
+                const int q = pl.nearl[e];
+                if (q <= leaf) continue;
+                B.in[c[q - leaf0]++] = at;
+                at += size(q);
+            }
+        }
+    });
 }
 
 // Whether the near field sums both directions of a pair at once: by the steps of its
@@ -1196,16 +1297,28 @@ static void near_blocks(const FmmPlan &pl, bool sym, NearBlocks &B) {
 // layer above the wall of 49 416 and 367, of 68 532 and 532, of 98 731 and 825.
 static bool near_both_ways(const FmmPlan &pl) {
     const int leaf0 = pl.lvl[pl.L];
-    int64_t both = 0, one = 0;
-    for (int c = leaf0; c < leaf0 + pl.nleaf; ++c) {
-        const int64_t mc = pl.rng[c].y - pl.rng[c].x, tc = (mc + 63) / 64;
-        for (int e = pl.near_ptr[c - leaf0]; e < pl.near_ptr[c - leaf0 + 1]; ++e) {
-            const int q = pl.nearl[e];
-            if (q <= c) continue;
-            const int64_t mq = pl.rng[q].y - pl.rng[q].x, tq = (mq + 63) / 64;
-            both += 64 * tc * tq;
-            one += tc * mq + tq * mc;
+    const int T = step_threads((int64_t)pl.nearl.size(), kListStep);
+    std::vector<int64_t> steps(2 * (size_t)T);
+    parallel_slices(T, pl.nleaf, [&](int t, int i0, int i1) {
+        int64_t both = 0, one = 0;
+        for (int i = i0; i < i1; ++i) {
+            const int2 r = pl.rng[leaf0 + i];
+            const int64_t mc = r.y - r.x, tc = (mc + 63) / 64;
+            for (int e = pl.near_ptr[i]; e < pl.near_ptr[i + 1]; ++e) {
+                const int q = pl.nearl[e];
+                if (q <= leaf0 + i) continue;
+                const int64_t mq = pl.rng[q].y - pl.rng[q].x, tq = (mq + 63) / 64;
+                both += 64 * tc * tq;
+                one += tc * mq + tq * mc;
+            }
         }
+        steps[2 * (size_t)t] = both;
+        steps[2 * (size_t)t + 1] = one;
+    });
+    int64_t both = 0, one = 0;
+    for (int t = 0; t < T; ++t) {
+        both += steps[2 * (size_t)t];
+        one += steps[2 * (size_t)t + 1];
     }
     return 88 * both < 71 * one;
 }

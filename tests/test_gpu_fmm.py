@@ -285,6 +285,28 @@ def test_repeated_products_are_bit_identical():
     assert all(np.array_equal(outs[0], o) for o in outs[1:])
 
 
+@pytest.mark.parametrize("N,box,wall,kw", [
+    (1500000, (200, 200, 200), False, dict(fmm_order=2, fmm_levels=5)),   # near field both ways
+    (120000, (300, 300, 10), True, dict(fmm_order=3, fmm_leaf=3))])       # one way, sparse lists
+def test_trees_do_not_depend_on_the_host_threads(N, box, wall, kw, monkeypatch):
+    """The lists behind a product (M2L's batches and slots, the near field's blocks and
+    slots) are counted and filled on several host threads where they are long; products
+    on trees of 1, 3 and 16 threads agree bit for bit."""
+    pos, lam = blobs(N, box, 17)
+    outs = []
+    for threads in ("1", "3", "16"):
+        monkeypatch.setenv("ARB_HOST_THREADS", threads)
+        ctx = arb.arb_create(wall=wall, pair_kernel=arb.ARB_PAIR_FMM, precision=arb.ARB_FP32C, **kw)
+        try:
+            outs.append(arb.arb_rpy_apply(ctx, pos, lam))
+            st = arb.arb_fmm_get_stats(ctx)
+        finally:
+            arb.arb_destroy(ctx)
+        print(f"{threads} threads: {st['leaves']} leaves, {st['interactions']} list entries, tree "
+              f"{st['build_ms']:.1f} ms", flush=True)
+    assert all(np.array_equal(outs[0], o) for o in outs[1:])
+
+
 def test_options_are_checked():
     for bad in (dict(fmm_order=1), dict(fmm_order=9), dict(fmm_levels=-1), dict(fmm_leaf=-2),
                 dict(pair_kernel=4)):
