@@ -202,7 +202,9 @@ void arb_destroy(arb_ctx *ctx);
 const char *arb_last_error(const arb_ctx *ctx);
 /* Pair-kernel launch shape actually used (after autotuning): > 0 source
  * slices of the target-parallel kernel, < 0 the symmetric kernel with -value
- * source tiles per work item. */
+ * source tiles per work item (FP64 atomic sums), 0 the kernel of 1,025 to 8,191
+ * autotuned blobs (each unordered pair once, ordered sums, bitwise
+ * reproducible). */
 int  arb_get_slices(const arb_ctx *ctx, int n_blobs);
 
 /* -------------------------------------------------------------- bodies

@@ -417,8 +417,8 @@ bool small_pair(const arb_ctx *ctx, int N) {
     return N <= arb::kSmallPairN && ctx->opt.pair_kernel != ARB_PAIR_SYMMETRIC;
 }
 
-// launch shape of the ring kernel (mid sizes), reported as the symmetric kernel's -1
-constexpr int kRingShape = -1000;
+// launch shape of the ring kernel (mid sizes), which has no slices and no items
+constexpr int kRingShape = 0;
 
 // whether n doubles at x (may be null) and at y share memory
 bool overlap(const double *x, const double *y, size_t n) {
@@ -427,8 +427,8 @@ bool overlap(const double *x, const double *y, size_t n) {
 }
 
 // one pair product; shape > 0: target-parallel kernel with that many source
-// slices; shape < 0: symmetric kernel with -shape source tiles per work item, or the
-// ring kernel; raw_pos: loose blobs whose positions need not be prepared (small_pair)
+// slices; shape < 0: symmetric kernel with -shape source tiles per work item; kRingShape:
+// the ring kernel; raw_pos: loose blobs whose positions need not be prepared (small_pair)
 int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const double4 *p64,
              const float4 *hi, const float4 *lo, const float4 *box, const int *perm,
              const double *lam, double *out, const double *U, const int *bob, const double *dvec,
@@ -438,7 +438,7 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const do
                          (precision == ARB_FP32C ? ctx->opt.a : 1.0);
     const bool small = small_pair(ctx, N);
     const bool ring = !small && shape == kRingShape;
-    const bool sym = !small && !ring && shape < 0;
+    const bool sym = !small && shape < 0;
     bool sym_clean = true;
     int used = 1;
     double *dst = out;
@@ -531,7 +531,7 @@ int choose_slices(arb_ctx *ctx, hipStream_t s, int N, const double4 *p64, const 
     if (sym_ok)
         for (int R : {1, 2, 4, 8, 16}) cand.push_back(-R);
     int best = cand.empty() ? h : cand[0];
-    if (N >= 8192 && cand.size() > 1) {
+    if (N >= arb::kRingPairN && cand.size() > 1) {
         HIPCHK(ctx->tune_out.ensure(3 * (size_t)N * sizeof(double)));
         hipEvent_t e0, e1;
         HIPCHK(hipEventCreate(&e0));
@@ -1590,8 +1590,7 @@ int arb_get_slices(const arb_ctx *ctx, int n_blobs) {
         const int64_t key = (int64_t)n_blobs * 4 + prec * 2 + (ctx->opt.wall ? 1 : 0);
         if (prec == ctx->opt.precision) {
             auto it = ctx->slice_cache.find(key);
-            if (it != ctx->slice_cache.end())
-                return it->second == kRingShape ? -1 : it->second;
+            if (it != ctx->slice_cache.end()) return it->second;
         }
     }
     return heuristic_slices(n_blobs);
@@ -1838,8 +1837,11 @@ int arb_rpy_apply_dev(arb_ctx *ctx, int N, const double *pos_dev, const double *
     HIPCHK(hipSetDevice(ctx->opt.device));
     hipStream_t s = pick(ctx, stream);
     if (small_pair(ctx, N) && ctx->opt.pair_kernel != ARB_PAIR_FMM) {
+        int sl = 0;  // (for arb_get_slices)
+        TRY(choose_slices(ctx, s, N, nullptr, nullptr, nullptr, nullptr, nullptr, lambda_dev,
+                          ctx->opt.precision, ctx->opt.wall != 0, &sl));
         TRY(run_pair(ctx, s, N, pos_dev, nullptr, nullptr, nullptr, nullptr, nullptr, lambda_dev,
-                     u_dev, nullptr, nullptr, nullptr, ctx->opt.precision, ctx->opt.wall != 0, 1));
+                     u_dev, nullptr, nullptr, nullptr, ctx->opt.precision, ctx->opt.wall != 0, sl));
         HIPCHK(hipGetLastError());
         return ARB_OK;
     }

@@ -182,8 +182,8 @@ void pair_small(hipStream_t s, int precision, bool wall, int N, const double *ra
                 const double4 *p64, const float4 *hi, const float4 *lo, const double *lam,
                 const int *perm, double a, double scale, double *out, const double *U,
                 const int *body_of_blob, const double *dvec, const SaddleRows &R);
-// mid sizes (pair_sym.hip): each unordered pair once, ordered sums in
-// pair_ring_slices(N) slices of partial (returned)
+// mid sizes, kSmallPairN < N < kRingPairN (pair_sym.hip): each unordered pair once, ordered
+// sums in pair_ring_slices(N) slices of partial (returned)
 constexpr int kRingPairN = 8192;
 int pair_ring_slices(int N);
 int pair_ring(hipStream_t s, int precision, bool wall, int N, const double4 *p64,
@@ -541,7 +541,7 @@ struct arb_ctx {
     std::vector<int> h_asm_body_ptr, h_asm_bodies, h_asm_row_ptr, h_asm_rows;
     // autotune cache: key = N*4 + precision*2 + wall -> launch shape; values > 0
     // are source slices of the target-parallel kernel, values < 0 select the
-    // symmetric kernel with -value source tiles per work item
+    // symmetric kernel with -value source tiles per work item, 0 the ring kernel
     std::map<int64_t, int> slice_cache;
     // symmetric-kernel work lists, one per precision [ARB_FP64, ARB_FP32C] (each
     // keyed by size and tiles per item), so that a graph captured for one

@@ -368,3 +368,25 @@ def test_mid_size_fp32_keeps_both_parts_of_the_positions():
           f"{err[arb.ARB_PAIR_TARGET]:.1e}", flush=True)
     assert abs(err[arb.ARB_PAIR_AUTO]) <= 2.0 ** -22
     assert abs(err[arb.ARB_PAIR_TARGET]) <= 2.0 ** -22
+
+
+# the reported launch shape tells ordered sums (>= 0) from atomic ones (< 0), and the
+# slices of the target-parallel kernel from a product without any
+@pytest.mark.parametrize("n,kind,slices,want", [
+    (300, arb.ARB_PAIR_AUTO, 0, lambda k: k > 0), (300, arb.ARB_PAIR_TARGET, 0, lambda k: k > 0),
+    (300, arb.ARB_PAIR_SYMMETRIC, 0, lambda k: k < 0), (2000, arb.ARB_PAIR_AUTO, 0, lambda k: k == 0),
+    (2000, arb.ARB_PAIR_AUTO, 3, lambda k: k == 3), (2000, arb.ARB_PAIR_TARGET, 0, lambda k: k > 0),
+    (2000, arb.ARB_PAIR_SYMMETRIC, 0, lambda k: k < 0),
+    (8191, arb.ARB_PAIR_AUTO, 0, lambda k: k == 0), (8192, arb.ARB_PAIR_AUTO, 0, lambda k: k != 0)])
+def test_reported_launch_shape(n, kind, slices, want):
+    cl = W.random_blobs(n, seed=n, box=8.0 + n ** 0.5)
+    c = arb.arb_create(precision=arb.ARB_FP32C, pair_kernel=kind, slices=slices)
+    try:
+        assert arb.arb_get_slices(c, n) > 0          # before any product: the heuristic
+        u = [arb.arb_rpy_apply(c, cl["pos"], cl["lam"]) for _ in range(3)]
+        k = arb.arb_get_slices(c, n)
+    finally:
+        arb.arb_destroy(c)
+    assert want(k), k
+    if k >= 0:
+        assert np.array_equal(u[1], u[2])
