@@ -1222,7 +1222,9 @@ __global__ __launch_bounds__(kApply) void pc_apply1_kernel(
 // stored to v: GMRES scales its new basis vector here.  Against three kernels and the
 // scaling (launches without their gaps): 16 bacteria 27.0 -> 10.7 us, 100 37.9 -> 18.6
 // (59 MB, 3.2 TB/s), 1,024 150.7 -> 142.0 (600 MB, 4.2 TB/s), 1,000 free 42-blob shells
-// 38.5 -> 26.2.
+// 38.5 -> 26.2.  A chain of 20 bodies with 57 constraint rows: 22.6 us when each step
+// searched bodies and rows one after the other, 14.8 with bisection and a mask of a body's
+// rows (three kernels and the scaling 14.1 + 2.3 and two launches more).
 constexpr int kFuseBlocks = 256;  // workgroups an apply is split into (100 bacteria with
                                   // 500: 26.7 us, with 1,000: 40.5: the chain is repeated)
 constexpr int kFuseRows = 1024, kFuseBodies = 32, kFuseCons = 64;
@@ -1237,6 +1239,7 @@ __global__ __launch_bounds__(kApply) void pc_apply_asm_kernel(
     extern __shared__ double lds[];
     __shared__ int s_p[kFuseBodies], s_row[kFuseBodies + 1], s_b[kFuseBodies];
     __shared__ int s_rows[kFuseCons], s_side[kFuseCons][2];  // rows; their bodies, local
+    __shared__ uint64_t s_mask[kFuseBodies][2];              // rows of a body by side
     const int T = blockDim.x;
     double *x = lds, *part = x + P.fuse.rows, *y = part + T, *ph = y + P.fuse.cons;
     double(*ru)[6] = reinterpret_cast<double(*)[6]>(ph + P.fuse.cons);
@@ -1277,11 +1280,15 @@ __global__ __launch_bounds__(kApply) void pc_apply_asm_kernel(
     __syncthreads();
     const int mt = s_row[nb];
     const int i0 = mt * blockIdx.y / gridDim.y, nr = mt * (blockIdx.y + 1) / gridDim.y - i0;
-    auto body_of = [&](int row) {  // body that holds blob row `row`
-        int b = 0;
-        while (s_row[b + 1] <= row) ++b;
-        return b;
+    // last i < n with a[i] <= v (a ascending, a[0] <= v)
+    auto last_at_most = [](const int *a, int n, int v) {
+        int i = 0;
+#pragma unroll
+        for (int step = kFuseBodies / 2; step > 0; step /= 2)
+            if (i + step < n && a[i + step] <= v) i += step;
+        return i;
     };
+    auto body_of = [&](int row) { return last_at_most(s_row, nb, row); };
     for (int i = tid; i < mt; i += T) {
         const int b = body_of(i);
         x[i] = load((size_t)s_b[b] + (i - s_row[b]), i >= i0 && i < i0 + nr);
@@ -1299,10 +1306,7 @@ __global__ __launch_bounds__(kApply) void pc_apply_asm_kernel(
         cr[e / 12][e % 12] = P.crow[12 * (size_t)s_rows[e / 12] + e % 12];
     for (int e = tid; e < 2 * na; e += T) {
         const int p = (e & 1) ? P.row_q[s_rows[e / 2]] : P.row_p[s_rows[e / 2]];
-        int q = -1;
-        if (p >= 0)
-            for (q = 0; s_p[q] != p;) ++q;
-        s_side[e / 2][e & 1] = q;
+        s_side[e / 2][e & 1] = p >= 0 ? last_at_most(s_p, nb, p) : -1;
     }
     __syncthreads();
     // parts of t = M_pp^-1 r_lam
@@ -1324,6 +1328,12 @@ __global__ __launch_bounds__(kApply) void pc_apply_asm_kernel(
         for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
         if (lane == 0) w6[q][c] = s + ru[q][c];
     }
+    // the rows of each body, a bit per row
+    for (int q = w; q < nb && na > 0; q += T / kWave)
+        for (int side = 0; side < 2; ++side) {
+            const uint64_t m = __ballot(lane < na && s_side[min(lane, kFuseCons - 1)][side] == q);
+            if (lane == 0) s_mask[q][side] = m;
+        }
     __syncthreads();
     if (eb < nb) {  // U^
         double s = 0.0;
@@ -1343,6 +1353,7 @@ __global__ __launch_bounds__(kApply) void pc_apply_asm_kernel(
     __syncthreads();
     if (tid < na) {
         double s = 0.0;
+#pragma unroll 8
         for (int l = 0; l < na; ++l) s += G[tid * na + l] * y[l];
         ph[tid] = s;
         if (first) z[off_phi + s_rows[tid]] = s;
@@ -1350,9 +1361,11 @@ __global__ __launch_bounds__(kApply) void pc_apply_asm_kernel(
     __syncthreads();
     if (eb < nb) {  // f = C^T phi per body
         double s = 0.0;
-        for (int t = 0; t < na; ++t)
-            for (int side = 0; side < 2; ++side)
-                if (s_side[t][side] == eb) s += ph[t] * cr[t][6 * side + ec];
+        const uint64_t q = na > 0 ? s_mask[eb][1] : 0;
+        for (uint64_t m = na > 0 ? s_mask[eb][0] | q : 0; m; m &= m - 1) {
+            const int t = __builtin_ctzll(m);
+            s += ph[t] * cr[t][6 * (int)(q >> t & 1) + ec];
+        }
         w6[eb][ec] = s;
     }
     __syncthreads();
