@@ -1164,7 +1164,7 @@ __device__ __forceinline__ double row_part(const double *__restrict__ Mi, int m,
     return s;
 }
 
-constexpr int kApply = 1024;  // threads of the apply kernels
+constexpr int kApply = 1024;  // most threads of the apply kernels
 
 __global__ __launch_bounds__(kApply) void pc_apply1_kernel(
     int N, const int *__restrict__ order, const int *__restrict__ blob_off, const int64_t *__restrict__ mat_off,
@@ -1174,17 +1174,17 @@ __global__ __launch_bounds__(kApply) void pc_apply1_kernel(
     __shared__ double x[kMaxM];
     __shared__ double part[kApply];
     __shared__ double w6[6];
-    const int p = order ? order[blockIdx.x] : blockIdx.x, tid = threadIdx.x;
+    const int p = order ? order[blockIdx.x] : blockIdx.x, tid = threadIdx.x, T = blockDim.x;
     const int b0 = blob_off[p], m = 3 * (blob_off[p + 1] - b0);
     const double *Mi = minv + mat_off[p];
     const double *Z = Zbuf + z_off[p];
     const double *rl = r + 3 * (size_t)b0;
-    for (int i = tid; i < m; i += kApply) x[i] = rl[i];
+    for (int i = tid; i < m; i += T) x[i] = rl[i];
     __syncthreads();
     // t = Minv r_lam (Minv symmetric: column access is coalesced)
-    const int ks = kApply / m;  // parts per row (0: more rows than threads)
+    const int ks = T / m;  // parts per row (0: more rows than threads)
     if (ks < 2) {
-        for (int i = tid; i < m; i += kApply)
+        for (int i = tid; i < m; i += T)
             z[3 * (size_t)b0 + i] = row_part(Mi, m, i, 0, m, x);
     } else {
         const int g = tid / m, i = tid - g * m;
@@ -1192,11 +1192,11 @@ __global__ __launch_bounds__(kApply) void pc_apply1_kernel(
     }
     // Z^T r_lam + r_U, a wavefront per component
     const int lane = tid % kWave, w = tid / kWave;
-    if (w < 6) {
+    for (int c = w; c < 6; c += T / kWave) {
         double s = 0.0;
-        for (int i = lane; i < m; i += kWave) s += Z[(size_t)i * 6 + w] * x[i];
+        for (int i = lane; i < m; i += kWave) s += Z[(size_t)i * 6 + c] * x[i];
         for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
-        if (lane == 0) w6[w] = s + r[3 * (size_t)N + 6 * (size_t)p + w];
+        if (lane == 0) w6[c] = s + r[3 * (size_t)N + 6 * (size_t)p + c];
     }
     __syncthreads();
     if (ks >= 2 && tid < m) {
@@ -1228,6 +1228,13 @@ __global__ __launch_bounds__(kApply) void pc_apply1_kernel(
 constexpr int kFuseBlocks = 256;  // workgroups an apply is split into (100 bacteria with
                                   // 500: 26.7 us, with 1,000: 40.5: the chain is repeated)
 constexpr int kFuseRows = 1024, kFuseBodies = 32, kFuseCons = 64;
+// from kFuseMany assemblies on, two workgroups to a compute unit, only those of at most
+// kFuseShort rows, a workgroup of 256 threads each: 1,024 threads and the LDS of the
+// largest for every one of them run in turns (2,000 free bodies of 42 blobs and a chain of
+// 8: 78 us, the three kernels 59; 8,000 of 6 blobs and the chain: 143, 37; 1,024 bacteria:
+// 149, 129; all short, 4,000 bodies of 6 blobs: 27, 23 and the scaling's launch; 1,000
+// shells of 42: 28, 36)
+constexpr int kFuseMany = 512, kFuseShort = 256;
 
 __host__ __device__ inline size_t fuse_doubles(const PcFuse &f, int threads) {
     return (size_t)f.rows + threads + 18 * f.bodies + (size_t)f.cons * (14 + f.cons);
@@ -1310,6 +1317,8 @@ __global__ __launch_bounds__(kApply) void pc_apply_asm_kernel(
     }
     __syncthreads();
     // parts of t = M_pp^-1 r_lam
+    // at most 16, whose sums one thread adds up at the end (8, 16, 32 or 64: within 3 % from
+    // 16 to 1,024 bacteria and for chains; 8 and fewer lose up to 14 % where bodies are small)
     const int ks = nr ? min(T / nr, 16) : 0, g = nr ? tid / nr : 0, row = tid - g * nr;
     int b = 0, il = 0;
     if (g < ks) {
@@ -1399,7 +1408,7 @@ PcFuse precond_fuse(int A, const int *body_ptr, const int *bodies, const int *ro
         f.bodies = std::max(f.bodies, nb);
         f.cons = std::max(f.cons, na);
     }
-    return f;
+    return A >= kFuseMany && f.rows > kFuseShort ? PcFuse() : f;
 }
 
 __global__ __launch_bounds__(256) void pc_apply2_kernel(
@@ -2240,15 +2249,28 @@ hipError_t precond_assembly(hipStream_t s, const PrecondDev &P) {
     return hipGetLastError();
 }
 
+// threads of a body's workgroup in the first of three kernels: all of them while the
+// bodies are few, then what gives a mean body's rows about 4 parts, so that more bodies are
+// resident (all three kernels, with 1,024, 8, 4 and 2 parts: 8,000 bodies of 6 and 8 of 42
+// blobs 72, 37, 37 and 37 us, 2,000 of 42 59, 62, 59 and 56, 1,000 of 42 and one of 300
+// 120, 121, 123 and 187)
+static int apply1_threads(int N, int M) {
+    int T = 256;
+    while (T < kApply && (M < kFuseMany || T < 4 * 3 * (N / M))) T *= 2;
+    return T;
+}
+
 void precond_apply(hipStream_t s, const PrecondDev &P, int N, const double *r, double *z,
                    const double *alpha, double *v) {
     if (P.M <= 0) return;
     if (P.fuse.rows) {
-        // a workgroup per compute unit while the assemblies are few.  From two per unit
-        // on, short assemblies take 256 threads each, so that more are resident (1,000
+        // a workgroup per compute unit while the assemblies are few, at most 16 each (a
+        // workgroup's chain is the same however few rows it has: one body of 300 blobs 18,
+        // 14, 13 and 11 us with 8, 16, 32 and 64, one of 8 bodies of 42 15 to 16 with
+        // each).  From two per unit on, 256 threads each, so that more are resident (1,000
         // shells of 42 blobs: 26.2 us, with 1,024 threads 38.5)
         const int split = std::min(16, std::max(1, kFuseBlocks / P.A));
-        const int T = P.A >= 512 && P.fuse.rows <= 256 ? 256 : kApply;
+        const int T = P.A >= kFuseMany ? 256 : kApply;
         pc_apply_asm_kernel<<<dim3(P.A, split), T, fuse_doubles(P.fuse, T) * sizeof(double), s>>>(
             N, P.M, P, r, alpha, v, z);
         return;
@@ -2258,8 +2280,9 @@ void precond_apply(hipStream_t s, const PrecondDev &P, int N, const double *r, d
                                                      P.tminv, P.tZ, P.R9, P.Nt, P.lcorr, r, z,
                                                      P.tmp, P.stmp);
     else
-        pc_apply1_kernel<<<P.M, kApply, 0, s>>>(N, P.order, P.blob_off, P.mat_off, P.z_off, P.minv,
-                                                P.Z, P.Nt, r, z, P.tmp);
+        pc_apply1_kernel<<<P.M, apply1_threads(N, P.M), 0, s>>>(N, P.order, P.blob_off, P.mat_off,
+                                                                P.z_off, P.minv, P.Z, P.Nt, r, z,
+                                                                P.tmp);
     if (P.A > 0)
         pc_apply2_kernel<<<P.A, 256, 0, s>>>(N, P.M, P.asm_row_ptr, P.asm_rows, P.asm_mat_off,
                                              P.row_p, P.row_q, P.crow, P.G, r, P.tmp, z);

@@ -433,6 +433,38 @@ def test_preconditioner_apply_at_its_limits(bodies_, blobs, rows):
         arb.arb_destroy(ctx)
 
 
+@pytest.mark.parametrize("long,free", [(100, 507), (100, 520), (80, 520)])
+def test_preconditioner_apply_of_mixed_assemblies(long, free):
+    # a body of 300 or 240 rows, a chain of three, and free bodies of one blob: 509 and
+    # 522 assemblies around the 512 from which the one-launch apply takes only short ones
+    sizes = np.array([long, 12, 12, 12] + [1] * free)
+    k = np.concatenate([np.arange(n) - 0.5 * (n - 1) for n in sizes])
+    body = np.stack([1.5 * np.cos(k), 1.5 * np.sin(k), 1.1 * k], 1)
+    body[long + 36:] = 0.0
+    M = len(sizes)
+    q = np.zeros((M, 3))
+    q[:, 0], q[:, 1] = 7.0 * (np.arange(M) % 23), 7.0 * (np.arange(M) // 23)
+    L = W._links(2)
+    for n in range(2):
+        L["pq"][n] = (n + 1, n + 2)
+        L["dl_p"][n, 0], L["dl_q"][n, 0], L["nproj"][n] = 3.5, -3.5, 3
+    rng = np.random.default_rng(free)
+    wl = W.Workload("mixed", 1.0, 1.0, False, body,
+                    np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32), q,
+                    np.tile([1.0, 0.0, 0.0, 0.0], (M, 1)), rng.standard_normal((M, 6)), **L)
+    print(f"apply: {M} bodies, {M - 2} assemblies", flush=True)
+    S = system.assemble(wl)
+    P = precond.BlockPreconditioner(wl, S["r"], S["C"])
+    ctx = arb.context_for(wl, precision=arb.ARB_FP64, tol=1e-10)
+    try:
+        arb.arb_precond_build(ctx)
+        for _ in range(2):
+            r = rng.standard_normal(wl.n_unknowns)
+            assert rel(arb.arb_precond_apply(ctx, r), P.apply(r)) <= 1e-11
+    finally:
+        arb.arb_destroy(ctx)
+
+
 @pytest.mark.parametrize("name,prec", [("filament", arb.ARB_FP64), ("bacteria4", arb.ARB_FP32C),
                                        ("diatoms2", arb.ARB_FP64)])
 def test_graph_replays_match_plain_launches(name, prec):
