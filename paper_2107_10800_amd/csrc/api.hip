@@ -1633,17 +1633,21 @@ int arb_set_bodies(arb_ctx *ctx, int M, const int32_t *blob_offset, const double
     // launches of a workgroup per body take the largest first: in the bodies' order the
     // fixed round of workgroups over XCDs and shader engines can give one engine all of
     // them (alternating sizes: 42- and 80-blob bodies), and the rest waits
-    std::vector<int> order(M);
-    std::iota(order.begin(), order.end(), 0);
+    // (a counting sort; one upload with the blobs' bodies)
     const auto size = [&](int p) { return blob_offset[p + 1] - blob_offset[p]; };
-    const auto larger = [&](int x, int y) { return size(x) > size(y); };
-    ctx->sorted_bodies = !std::is_sorted(order.begin(), order.end(), larger);
-    if (ctx->sorted_bodies) std::stable_sort(order.begin(), order.end(), larger);
-    std::vector<int> bob_order(ctx->h_body_of_blob);  // one upload: the order follows
-    bob_order.insert(bob_order.end(), order.begin(), order.end());
+    std::vector<int> bob_order((size_t)N + M), at(kMaxBodyBlobs + 1, 0);
+    std::copy(ctx->h_body_of_blob.begin(), ctx->h_body_of_blob.end(), bob_order.begin());
+    ctx->sorted_bodies = false;
+    ctx->n_large = 0;
+    for (int p = 0; p < M; ++p) {
+        ++at[kMaxBodyBlobs - size(p) + 1];  // (size >= 1)
+        ctx->sorted_bodies |= p > 0 && size(p) > size(p - 1);
+        ctx->n_large += 3 * size(p) > arb::kSweepSmall;
+    }
+    at[0] = N;
+    for (int k = 1; k <= kMaxBodyBlobs; ++k) at[k] += at[k - 1];
+    for (int p = 0; p < M; ++p) bob_order[at[kMaxBodyBlobs - size(p)]++] = p;
     TRY(upload(ctx, ctx->body_of_blob, bob_order.data(), bob_order.size(), s));
-    ctx->n_large = (int)std::count_if(order.begin(), order.end(),
-                                      [&](int p) { return 3 * size(p) > arb::kSweepSmall; });
     TRY(upload(ctx, ctx->r_ref, ctx->h_r_ref.data(), 3 * (size_t)N, s));
     TRY(upload(ctx, ctx->body_type_d, ctx->h_body_type.data(), M, s));
     HIPCHK(hipStreamSynchronize(s));
