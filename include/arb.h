@@ -28,6 +28,9 @@
  *  - Return value: 0 success, > 0 warning (result usable), < 0 error (result
  *    undefined).  arb_last_error() gives the message of the last non-zero code.
  *  - One context per host thread; calls on one context are not thread safe.
+ *    They share its workspaces: calls on different streams are ordered by the
+ *    caller (results of calls that overlap are undefined; later ones are not
+ *    affected).
  */
 #ifndef ARB_H
 #define ARB_H

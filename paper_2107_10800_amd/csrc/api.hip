@@ -493,7 +493,8 @@ int run_pair(arb_ctx *ctx, hipStream_t s, int N, const double *raw_pos, const do
     if (!small)
         arb::pair_reduce(s, N, used, (sym ? ctx->sym_sums : ctx->partial).as<double>(), sym, scale,
                          out, U, bob, dvec, perm, rows);
-    if (sym) ctx->sym_dirty = !sym_clean;
+    // (a reduction that was not launched left the sums)
+    if (sym) ctx->sym_dirty = !sym_clean || hipPeekAtLastError() != hipSuccess;
     if (dst != out)
         HIPCHK(hipMemcpyAsync(out, dst, (size_t)3 * N * sizeof(double), hipMemcpyDeviceToDevice, s));
     return 0;
