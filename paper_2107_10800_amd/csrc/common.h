@@ -73,6 +73,9 @@ constexpr int kFmmMaxOrder = 8;                                          // Cheb
 constexpr int kFmmMaxP = kFmmMaxOrder * kFmmMaxOrder * kFmmMaxOrder;   // proxies per cell
 constexpr int kFmmMaxLevel = 16;
 constexpr int kFmmDefaultOrder = 6;
+// order whose dense listed cells M2L strings together with the sparse ones: 8 proxies fill
+// half of a matrix tile, and a batch, its slots and their sum cost more than the pairs
+constexpr int kFmmStrungOrder = 2;
 
 // octree and proxy buffers of the fast product; cells of all levels 0..L in
 // Morton order, level l at [lvl[l], lvl[l+1])

@@ -1097,11 +1097,12 @@ static void group_m2l(const FmmPlan &pl, bool wall, int max_cols, int64_t chunk_
     const int cell0 = pl.L >= 2 ? pl.lvl[2] : pl.ncell, nc = pl.ncell - cell0, P = pl.P;
     const int T = step_threads((int64_t)pl.il.size(), kListStep);
     // blobs of a cell when it is sparse, 0 when it is dense (the passes over the lists
-    // do not branch on it: both kinds are mixed)
+    // do not branch on it: both kinds are mixed); strung: proxies, every cell counts as sparse
+    const bool strung = pl.n == kFmmStrungOrder;
     G.sparse.resize((size_t)pl.ncell);
     for (int c = 0; c < pl.ncell; ++c) {
         const int m = pl.rng[c].y - pl.rng[c].x;
-        G.sparse[c] = m >= P ? 0 : m;
+        G.sparse[c] = m < P ? m : (strung ? P : 0);
     }
     G.sp_ptr.assign((size_t)nc + 1, 0);
     G.slot_ptr.assign((size_t)nc + 1, 0);

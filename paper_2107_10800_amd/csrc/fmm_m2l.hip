@@ -24,8 +24,13 @@
 //  * sparse entries (P2L): the blobs of a cell's sparse listed cells, strung
 //    together and dealt evenly to lane groups of n^2 lanes, each lane holding the
 //    KZ target proxies of one (x, y), so that the differences in the plane are
-//    formed once per blob and lane.  VALU-bound: 2.05 ms for 1.48e9 pairs of the
-//    bacteria (7.2e11 pairs/s).
+//    formed once per blob and lane.  VALU-bound: 1.87 ms for 1.48e9 pairs of the
+//    bacteria (7.9e11 pairs/s).
+//
+// At order 2 (8 proxies: half a matrix tile, and results as many as weights) every listed
+// cell is strung, the dense ones with their proxies, and a cell takes one wavefront: 150,000
+// blobs in clusters 212 us, in a thin layer 35, against 391 and 81 with batches (and 311 and
+// 47 before there were any).
 //
 // Every pair is well separated (r > 2a: cells at least a side apart, side >= 2a, and
 // proxies inside their cells), so the overlap branch is left out.
@@ -294,18 +299,20 @@ void fmm_m2l_dense_kernel(
 // three of them side by side (2.05 ms on the bacteria) but not six, which the
 // compiler then runs one after the other (2.60 ms; so do 5 or 6 wavefronts per SIMD:
 // 2.47 ms).  Workgroups are whole multiples of 4 wavefronts: 6 load two of the four
-// SIMDs twice as much (3.30 ms).
+// SIMDs twice as much (3.30 ms).  (Order 2, with little to do per cell: one wavefront;
+// 150,000 blobs in clusters and strays with 4 754 us, with 1 428.)
 template <int NO>
 struct SparseShape {
     static constexpr int P = NO * NO * NO, KZ = NO == 6 || NO == 8 ? NO / 2 : NO;
     static constexpr int lanes = P / KZ;
-    static constexpr int block = NO == 6 ? 512 : 256, groups = block / lanes;
+    static constexpr int block = NO == 6 ? 512 : (NO == 2 ? 64 : 256), groups = block / lanes;
     static constexpr int chunk = groups * kFmmRun < block ? groups * kFmmRun : block;
     // groups whose sums are joined at a time
     static constexpr int join = NO == 2 ? 16 : (NO == 3 ? 14 : (NO == 4 ? 8 : 1));
+    // order 2: dense listed cells are strung too, with their proxies
+    static constexpr bool all = NO == kFmmStrungOrder;
 };
 constexpr int kMaxListed = 189;  // cells of an interaction list (6^3 - 3^3)
-static_assert(kMaxListed <= 256, "one list entry per thread");
 
 // the blobs of the sparse listed cells of one target cell; a cell's blobs may be
 // split over `splits` consecutive items, each with a place of its own in vpart
@@ -317,7 +324,8 @@ void fmm_p2l_kernel(
     const int *__restrict__ sp_ptr, const int *__restrict__ sp, const int *__restrict__ order,
     int cell0, int items, int splits,
     const int2 *__restrict__ rng, const float4 *__restrict__ shi, const float4 *__restrict__ slo,
-    const Vec4<A> *__restrict__ sf, const Vec4<A> *__restrict__ st, double *__restrict__ vu,
+    const Vec4<A> *__restrict__ sf, const Vec4<A> *__restrict__ st,
+    const Vec4<A> *__restrict__ qf, const Vec4<A> *__restrict__ qt, double *__restrict__ vu,
     double *__restrict__ vw, double *__restrict__ vpart) {
     using Sh = SparseShape<NO>;
     constexpr int P = Sh::P, C = Sh::chunk, NB = 3 * CH, KZ = Sh::KZ, block = Sh::block;
@@ -329,6 +337,7 @@ void fmm_p2l_kernel(
     __shared__ float4 s_off[C];
     __shared__ Vec4<A> s_f[C], s_t[CH == 2 ? C : 1];
     __shared__ double s_sum[NB][P];
+    __shared__ unsigned char s_id[Sh::all ? C : 1];
     load_tab(tabg, tab);
     const int tid = threadIdx.x;
     const int ci = order[item / splits], part = item % splits, c = cell0 + ci;
@@ -336,25 +345,38 @@ void fmm_p2l_kernel(
     const double side = ldexp(g.S, -ct.w), w = 0.5 * side;
     const int e0 = sp_ptr[ci], ne = sp_ptr[ci + 1] - e0;
     for (int i = tid; i < NB * P; i += block) s_sum[i / P][i % P] = 0.0;
-    // prefix sums of the listed cells' blob counts (one list entry per thread)
-    {
+    // prefix sums of the listed cells' source counts, an entry per thread (a wavefront alone
+    // in turns)
+    static_assert(block == kWave || block >= kMaxListed);
+    if (tid == 0) s_pre[0] = 0;
+    __syncthreads();
+    for (int i0 = 0; i0 < ne; i0 += block) {
+        const int i = i0 + tid;
         int v = 0;
-        if (tid < ne) {
-            const int2 r = rng[sp[e0 + tid]];
-            s_start[tid] = r.x;
+        if (i < ne) {
+            const int q = sp[e0 + i];
+            const int2 r = rng[q];
+            s_start[i] = r.x;
             v = r.y - r.x;
+            if (Sh::all && v >= P) {  // proxies: ~cell in place of the first blob
+                s_start[i] = ~q;
+                v = P;
+            }
         }
         for (int off = 1; off < kWave; off <<= 1) {
             const int u = __shfl_up(v, off);
             if ((tid & 63) >= off) v += u;
         }
-        if ((tid & 63) == 63) s_wave[tid >> 6] = v;
+        if constexpr (block > kWave) {
+            if ((tid & 63) == 63) s_wave[tid >> 6] = v;
+            __syncthreads();
+            for (int q = 0; q < (tid >> 6); ++q) v += s_wave[q];
+        } else {
+            v += s_pre[i0];
+        }
+        if (i < ne) s_pre[i + 1] = v;
         __syncthreads();
-        for (int q = 0; q < (tid >> 6); ++q) v += s_wave[q];
-        if (tid < ne) s_pre[tid + 1] = v;
-        if (tid == 0) s_pre[0] = 0;
     }
-    __syncthreads();
     const int total = s_pre[ne];
     if (total == 0 && splits == 1) {
         for (int i = tid; i < 3 * P; i += block) {
@@ -384,23 +406,48 @@ void fmm_p2l_kernel(
     for (int j0 = (int)((int64_t)total * part / splits); j0 < j1; j0 += C) {
         const int cnt = min(C, j1 - j0);
         __syncthreads();
+        if constexpr (Sh::all) {  // at most P = 8 sources a cell: each marks its own
+            for (int i = tid; i < ne; i += block)
+                for (int k = max(s_pre[i], j0); k < min(s_pre[i + 1], j0 + cnt); ++k)
+                    s_id[k - j0] = (unsigned char)i;
+            __syncthreads();
+        }
         if (tid < cnt) {
             // the listed cell that holds blob j0 + tid of the string
-            int lo = 0, up = ne;
-            while (up - lo > 1) {
-                const int mid = (lo + up) >> 1;
-                if (s_pre[mid] <= j0 + tid)
-                    lo = mid;
-                else
-                    up = mid;
+            int lo = 0;
+            if constexpr (Sh::all) {
+                lo = s_id[tid];
+            } else {
+                int up = ne;
+                while (up - lo > 1) {
+                    const int mid = (lo + up) >> 1;
+                    if (s_pre[mid] <= j0 + tid)
+                        lo = mid;
+                    else
+                        up = mid;
+                }
             }
-            const int j = s_start[lo] + (j0 + tid - s_pre[lo]);
-            const float4 h = shi[j], l = slo[j];
-            // offset from the target cell's centre, and the blob's height
-            s_off[tid] = make_float4((h.x - hx.h) + (l.x - hx.l), (h.y - hy.h) + (l.y - hy.l),
-                                     (h.z - hz.h) + (l.z - hz.l), h.z + l.z);
-            s_f[tid] = sf[j];
-            if constexpr (CH == 2) s_t[tid] = st[j];
+            const int k = j0 + tid - s_pre[lo], first = s_start[lo];
+            if (Sh::all && first < 0) {
+                const int q = ~first;
+                const int4 cs = cc[q];
+                const float oz = (float)(w * tab[kTabNode + k % NO]);
+                s_off[tid] = make_float4(
+                    (float)((double)(cs.x - ct.x) * side) + (float)(w * tab[kTabNode + k / (NO * NO)]),
+                    (float)((double)(cs.y - ct.y) * side) + (float)(w * tab[kTabNode + (k / NO) % NO]),
+                    (float)((double)(cs.z - ct.z) * side) + oz,
+                    (float)centre(g.oz, side, cs.z) + oz);
+                s_f[tid] = qf[(size_t)q * P + k];
+                if constexpr (CH == 2) s_t[tid] = qt[(size_t)q * P + k];
+            } else {
+                const int j = first + k;
+                const float4 h = shi[j], l = slo[j];
+                // offset from the target cell's centre, and the blob's height
+                s_off[tid] = make_float4((h.x - hx.h) + (l.x - hx.l), (h.y - hy.h) + (l.y - hy.l),
+                                         (h.z - hz.h) + (l.z - hz.l), h.z + l.z);
+                s_f[tid] = sf[j];
+                if constexpr (CH == 2) s_t[tid] = st[j];
+            }
         }
         __syncthreads();
         if (!act) continue;
@@ -459,8 +506,8 @@ void fmm_p2l_kernel(
         }
     }
     // the groups' sums, added in group order; those of the many small groups of low orders
-    // through LDS, several at a time (a barrier per group: 145 us for order 2 on a slab of
-    // 100,000 blobs in leaves of 9, now 61)
+    // through LDS, several at a time (a barrier per group: 945 us for order 3 on a slab of
+    // 100,000 blobs in leaves of 2, 28 groups; now 827)
     if constexpr (Sh::join > 1) {
         __shared__ double s_join[Sh::join][NB * P];
         for (int g0 = 0; g0 < Sh::groups; g0 += Sh::join) {
@@ -554,7 +601,7 @@ void run_m2l(const FmmState &F, hipStream_t s) {
             <<<round_up(nc * splits, 8 * kXcdChunk), SparseShape<NO>::block, 0, s>>>(
                 g, tab, F.cc.as<int4>(), F.sp_ptr.as<int>(), F.sp.as<int>(), F.sp_order.as<int>(), cell0,
                 nc * splits,
-                splits, F.rng.as<int2>(), F.shi.as<float4>(), F.slo.as<float4>(), sf, st, vu, vw,
+                splits, F.rng.as<int2>(), F.shi.as<float4>(), F.slo.as<float4>(), sf, st, qf, qt, vu, vw,
                 F.vsplit.as<double>());
         for (const FmmChunk &ch : F.chunks) {
             const int tasks = (ch.batch1 - ch.batch0) * ((NO * NO * NO + 15) / 16);

@@ -140,6 +140,34 @@ def test_near_field_one_way_and_both_ways(counts, n, wall):
         assert np.abs(u[0] - ref).max() <= 1e-5 * np.abs(ref).max()
 
 
+# order 2: every listed cell of M2L strung together, cells of at most 7 blobs with those,
+# the others with their 8 proxies; lists of more than a wavefront's 64 entries (in space)
+# and of a few (a row of cells), both channels
+@pytest.mark.parametrize("N,box,wall,L", [(4000, (60, 60, 60), False, 3), (900, (40, 40, 40), True, 3),
+                                          (700, (200, 6, 6), True, 4)])
+def test_strung_lists_of_order_two(N, box, wall, L):
+    rng = np.random.default_rng(N)
+    pos = rng.uniform(0, 1, (N, 3))
+    pos[:, 0] **= 2
+    pos = pos * np.array(box, float) + np.array([0, 0, 1.5])
+    F = rng.standard_normal((N, 6))
+    ref = fastsum.fmm_apply(pos, F[:, :3], 1.0, 1.0, wall, 2, L)
+    ref6 = fastsum.fmm_apply(pos, F, 1.0, 1.0, False, 2, L, kernel=rot_kernel(1.0, 1.0))
+    wl = W.Workload("loose", 1.0, 1.0, False, np.zeros((N, 3)), np.arange(N + 1, dtype=np.int32),
+                    pos, np.tile([1.0, 0, 0, 0], (N, 1)), F, extra=dict(single_blob=True))
+    for prec in (arb.ARB_FP64, arb.ARB_FP32C):
+        u = [fmm(pos, F[:, :3], wall, 2, L, precision=prec) for _ in range(2)]
+        assert np.array_equal(u[0], u[1])
+        assert np.abs(u[0] - ref).max() <= 1e-5 * np.abs(ref).max()
+        ctx = arb.context_for(wl, precision=prec, pair_kernel=arb.ARB_PAIR_FMM, fmm_order=2,
+                              fmm_levels=L)
+        try:
+            uw = arb.arb_body_mobility_apply(ctx, F)
+        finally:
+            arb.arb_destroy(ctx)
+        assert np.abs(uw - ref6).max() <= 1e-5 * np.abs(ref6).max()
+
+
 def test_near_field_without_room_for_its_slots():
     """The near field's slots are optional memory (2.9 GB here: 260,000 blobs in 64
     leaves): with less than that left on the device, everything else (under 0.1 GB)
