@@ -1293,9 +1293,10 @@ static void near_blocks(const FmmPlan &pl, bool sym, NearBlocks &B) {
 // wavefronts over all pairs of adjacent leaves.  A pair of tiles takes 64 steps of 88
 // instructions both ways, however few blobs its tiles hold, and one way a step of 71
 // instructions per source for each direction.
-// Products of order 3 both ways and one way (FP32; FP64 alike), us: leaves of 15 blobs in
-// space 456 and 330, of 34 611 and 571, of 49 629 and 649, of 81 1,176 and 1,256; in a
-// layer above the wall of 49 416 and 367, of 68 532 and 532, of 98 731 and 825.
+// Products of order 3 both ways and one way in FP32, us: leaves of 15 blobs in space 443
+// and 310, of 34 605 and 553, of 49 626 and 628, of 98 in a layer above the wall 710 and 794,
+// of 68 516 and 512, of 49 406 and 345.  (With double sums alike above the wall; in space
+// one way still wins at leaves of 81, 1,567 and 1,301.)
 static bool near_both_ways(const FmmPlan &pl) {
     const int leaf0 = pl.lvl[pl.L];
     const int T = step_threads((int64_t)pl.nearl.size(), kListStep);

@@ -19,7 +19,10 @@
 // sums joined in LDS write a quarter of the slots but wait on barriers: 2.98 ms.
 // Where most leaves fill less than about half a tile, a wavefront's 64 steps both ways
 // cost more than a step per source: such trees are summed one way (near_both_ways in
-// fmm.hip; 100,000 blobs above the wall in leaves of 9: 784 us both ways, 237 one way).
+// fmm.hip), by an instance of its own without the second copy of the tile and the source
+// sums, whose LDS and registers left a third of the wavefronts (100,000 blobs above the
+// wall in leaves of 9: 784 us both ways, 237 one way; 500,000 in space in leaves of 15 with
+// double sums: 1,149 us in the two-way instance, 854 in its own).
 // Single-blob bodies (6 components) are summed one way, the tensor's few coefficients
 // being a small part of a pair: 4,096 shells 3.19 -> 1.74 ms.  (Two targets per lane,
 // to halve the LDS reads, leave too few blocks: 2.39 against 2.11 ms before the blocks
@@ -121,12 +124,12 @@ __device__ __forceinline__ double next_lane(double v, int src) {
 }
 
 // work[item] = (leaf, first target, targets, first slot); near: the adjacent leaves;
-// own[c][k]: the sums of sorted blob k over its own leaf and (sym) the adjacent leaves
-// after it, or (!sym) all adjacent leaves; slots: per block, for each adjacent leaf
+// own[c][k]: the sums of sorted blob k over its own leaf and (SYM) the adjacent leaves
+// after it, or (!SYM) all adjacent leaves; slots: per block, for each adjacent leaf
 // after its own in list order, 3 x |leaf| source-side sums (component-major)
-template <bool WALL, int CH, class A>
+template <bool WALL, int CH, bool SYM, class A>
 __global__ __launch_bounds__(64 * kNearWaves) void fmm_near_kernel(
-    int N, int sym, const int2 *__restrict__ rng, const int *__restrict__ near_ptr,
+    int N, const int2 *__restrict__ rng, const int *__restrict__ near_ptr,
     const int *__restrict__ near, int leaf0, const int4 *__restrict__ work, int items,
     const float4 *__restrict__ shi, const float4 *__restrict__ slo,
     const Vec4<A> *__restrict__ sf, const Vec4<A> *__restrict__ st, double *__restrict__ own,
@@ -134,12 +137,12 @@ __global__ __launch_bounds__(64 * kNearWaves) void fmm_near_kernel(
     constexpr int NB = 3 * CH, W = kNearWaves;
     const int item = xcd_item(items);
     if (item < 0) return;
-    // a source tile per wavefront, twice over for the rotation (CH = 1)
-    constexpr int TS = CH == 1 ? 128 : 64;
+    // a source tile per wavefront, twice over for the rotation (SYM)
+    constexpr int TS = SYM ? 128 : 64;
     __shared__ float4 s_pos[(2 * W * TS * 16 > W * NB * 64 * 8 ? 2 * W * TS : W * NB * 32)];
     float4(*s_hi)[TS] = reinterpret_cast<float4(*)[TS]>(s_pos), (*s_lo)[TS] = s_hi + W;
     __shared__ Vec4<A> s_f[W][TS], s_t[CH == 2 ? W : 1][64];
-    __shared__ A s_comb[CH == 1 ? W : 1][2][3][64];
+    __shared__ A s_comb[SYM ? W : 1][2][3][SYM ? 64 : 1];
     __shared__ int s_beg[kMaxNear], s_cnt[kMaxNear], s_first[kMaxNear + 1], s_slot[kMaxNear];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int4 it = work[item];
@@ -151,7 +154,7 @@ __global__ __launch_bounds__(64 * kNearWaves) void fmm_near_kernel(
         if (lane < ne) {
             q = near[e0 + lane];
             const int2 r = rng[q];
-            cnt = sym && q < c ? 0 : r.y - r.x;
+            cnt = SYM && q < c ? 0 : r.y - r.x;
             s_beg[lane] = r.x;
             s_cnt[lane] = cnt;
         }
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(64 * kNearWaves) void fmm_near_kernel(
         }
         if (lane < ne) {
             s_first[lane + 1] = tiles;
-            s_slot[lane] = sym && q > c ? it.w + sl - own_sl : -1;
+            s_slot[lane] = SYM && q > c ? it.w + sl - own_sl : -1;
         }
         if (lane == 0) s_first[0] = 0;
         if (lane >= ne && lane < kMaxNear) s_first[lane + 1] = tiles;
@@ -178,7 +181,7 @@ __global__ __launch_bounds__(64 * kNearWaves) void fmm_near_kernel(
     if (act) {
         th = shi[i];
         tl = slo[i];
-        if (CH == 1) lt = sf[i];
+        if (SYM) lt = sf[i];
     }
     const float zi = th.z + tl.z;
     const TargetZ<float> zsc = target_z(zi);
@@ -210,16 +213,15 @@ __global__ __launch_bounds__(64 * kNearWaves) void fmm_near_kernel(
             s_hi[w][lane] = h;
             s_lo[w][lane] = l;
             s_f[w][lane] = f;
-            if constexpr (CH == 1) {
+            if constexpr (SYM) {
                 s_hi[w][lane + 64] = h;
                 s_lo[w][lane + 64] = l;
                 s_f[w][lane + 64] = f;
-            } else {
-                s_t[w][lane] = ok ? st[j] : vec4<A>(0, 0, 0);
             }
+            if constexpr (CH == 2) s_t[w][lane] = ok ? st[j] : vec4<A>(0, 0, 0);
         }
         sync();
-        const int slot = CH == 1 ? s_slot[e] : -1;
+        const int slot = SYM ? s_slot[e] : -1;
         {
             const float4 *ph = s_hi[w], *pl = s_lo[w];
             const Vec4<A> *pf = s_f[w];
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(64 * kNearWaves) void fmm_near_kernel(
 #pragma unroll
                     for (int q = 0; q < NB; ++q) u[q] += (double)f[q];
                 }
-            } else if constexpr (CH == 1) {
+            } else if constexpr (SYM) {
                 // lane l meets source l + s; after 32 steps it holds the sums of
                 // source l + 32, after 64 those of source l
 #pragma unroll 1
@@ -268,7 +270,7 @@ __global__ __launch_bounds__(64 * kNearWaves) void fmm_near_kernel(
                 }
             }
         }
-        if constexpr (CH == 1) {
+        if constexpr (SYM) {
             if (slot < 0) continue;
             sync();
             if (j0 + lane < cnt) {
@@ -385,11 +387,18 @@ void run_near(const FmmState &F, hipStream_t s, double *partial) {
     const int N = F.N, leaf0 = F.lvl[F.L];
     const Geo g{F.o[0], F.o[1], F.o[2], F.S, F.n, F.P};
     const bool sym = CH == 1 && F.near_sym;
-    fmm_near_kernel<WALL, CH, A><<<round_up(F.n_blocks, 8 * kXcdChunk), 64 * kNearWaves, 0, s>>>(
-        N, sym, F.rng.as<int2>(), F.near_ptr.as<int>(), F.nearl.as<int>(), leaf0,
-        F.blocks.as<int4>(), F.n_blocks, F.shi.as<float4>(), F.slo.as<float4>(),
-        F.slam.as<Vec4<A>>(), F.slam2.as<Vec4<A>>(), F.own.as<double>(),
-        F.near_slots.as<double>());
+    auto go = [&](auto both) {
+        fmm_near_kernel<WALL, CH, decltype(both)::value, A>
+            <<<round_up(F.n_blocks, 8 * kXcdChunk), 64 * kNearWaves, 0, s>>>(
+                N, F.rng.as<int2>(), F.near_ptr.as<int>(), F.nearl.as<int>(), leaf0,
+                F.blocks.as<int4>(), F.n_blocks, F.shi.as<float4>(), F.slo.as<float4>(),
+                F.slam.as<Vec4<A>>(), F.slam2.as<Vec4<A>>(), F.own.as<double>(),
+                F.near_slots.as<double>());
+    };
+    if (sym)
+        go(std::bool_constant<CH == 1>());
+    else
+        go(std::false_type());
     with_order(F.n, [&](auto o) {
         fmm_finish_kernel<CH, decltype(o)::value><<<round_up(F.nwork, 8 * kXcdChunk), 64, 0, s>>>(
             g, F.tab.as<float>(), N, F.L >= 2 ? 1 : 0, F.cc.as<int4>(), F.rng.as<int2>(), leaf0,
