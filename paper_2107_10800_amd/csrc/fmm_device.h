@@ -1,5 +1,5 @@
 // Device helpers of the fast product shared by its translation units (fmm.hip:
-// tree, P2M, M2M, L2L, near field; fmm_m2l.hip: M2L).
+// tree, P2M, M2M, L2L; fmm_m2l.hip: M2L; fmm_near.hip: near field, L2P).
 #pragma once
 #include <type_traits>
 

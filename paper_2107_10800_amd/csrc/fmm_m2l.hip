@@ -296,11 +296,11 @@ void fmm_m2l_dense_kernel(
 // lanes per group, as many groups as fill the workgroup's wavefronts, at most
 // kFmmRun staged blobs per group.  KZ = n, but half of it at n = 6 and 8: the KZ
 // pairs are independent chains, and the 128 registers of 4 wavefronts per SIMD hold
-// three of them side by side (2.05 ms on the bacteria) but not six, which the
-// compiler then runs one after the other (2.60 ms; so do 5 or 6 wavefronts per SIMD:
-// 2.47 ms).  Workgroups are whole multiples of 4 wavefronts: 6 load two of the four
-// SIMDs twice as much (3.30 ms).  (Order 2, with little to do per cell: one wavefront;
-// 150,000 blobs in clusters and strays with 4 754 us, with 1 428.)
+// three of them side by side (2.05 ms on the bacteria; 1.87 with the longest lists
+// first) but not six, which the compiler then runs one after the other (2.60 ms; so do 5
+// or 6 wavefronts per SIMD: 2.47 ms).  Workgroups are whole multiples of 4 wavefronts: 6
+// load two of the four SIMDs twice as much (3.30 ms).  (Order 2, with little to do per
+// cell: one wavefront; 150,000 blobs in clusters and strays with 4 754 us, with 1 428.)
 template <int NO>
 struct SparseShape {
     static constexpr int P = NO * NO * NO, KZ = NO == 6 || NO == 8 ? NO / 2 : NO;

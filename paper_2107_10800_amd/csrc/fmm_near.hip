@@ -4,15 +4,16 @@
 // A workgroup takes a block of up to 64 targets of one leaf against the leaves adjacent
 // to it, its 4 wavefronts taking the source tiles (64 blobs of one adjacent leaf, each
 // staged in the wavefront's own LDS) in turn, without barriers, so that small leaves
-// and small trees still fill the chip.  The host lists the blocks longest first: with
-// 12 per compute unit the last ones left 19 % of the time idle.
+// and small trees still fill the chip.  The host lists up to 16,384 blocks longest first:
+// with 12 per compute unit the last ones left 19 % of the time idle.
 //
 // Forces (3 components): the tensor of a pair serves both directions (M_ji = M_ij^T),
 // so a block visits only the adjacent leaves after its own in cell order (and its
 // own, one way) and sums both sides: as in the dense symmetric kernel the source-side
 // sums follow their sources around the wavefront, lane l meeting source l + s at step
 // s.  A block's source-side sums go to a slot of their own per (block, leaf); the
-// last pass adds a blob's slots in block order, so products repeat bit for bit.
+// last pass adds a blob's slots in the order of the blocks' leaves, so products repeat bit
+// for bit.
 // VALU-bound: 88 instructions per unordered pair against 2 x 71 one way; 8,192
 // bacteria 3.54 -> 2.58 ms (issue rate at its limit, 1.46 per clock and CU), diatom
 // colonies with double sums 0.89 -> 0.52 ms.  Blocks of 256 targets with their source

@@ -250,7 +250,7 @@ __device__ void arnoldi_post_dev(const PostArgs &p, double hn2, double *sh) {
 // The whole orthogonalisation of one Arnoldi step for a system of at most
 // kSmallArnoldi unknowns in one workgroup: w against V_0..V_j by classical
 // Gram-Schmidt twice (w held in LDS), ||w||, then the Givens update of
-// arnoldi_post.  One launch instead of nine; the same steps with a different
+// arnoldi_post.  One launch instead of four; the same steps with a different
 // summation order (one wave per dot product, lanes strided over the rows).
 __global__ __launch_bounds__(1024) void arnoldi_small_kernel(
     int n, const double *__restrict__ V, int64_t ldv, double *__restrict__ w, PostArgs post) {

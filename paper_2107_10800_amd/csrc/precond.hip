@@ -990,7 +990,7 @@ __global__ __launch_bounds__(kAsmThreads) void pc_asm_small_kernel(
         tol = 1e-12 * dmax;
     }
     __syncthreads();
-    // thread tid owns column c = tid % 64 of rows i = tid / 64 + 16 q (q < kAsmSlots):
+    // thread tid owns column c = tid % 16 of rows i = tid / 16 + 16 q (q < kAsmSlots):
     // the column-c entries of row j are read once per pivot, the rows' entries all
     // issued before they are updated
     const int c = tid % kAsmSmall, i0 = tid / kAsmSmall;
@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__(kAsmThreads) void pc_asm_small_kernel(
     if (tid < na) invd[tid] = 1.0 / S[tid * ld + tid];
     __syncthreads();
     // G~_ij = sum_k E_ki E_kj / D_k over k >= max(i, j): thread tid takes column
-    // j = tid % 64 of rows i = tid / 64 + 16 q, one pass over k
+    // j = tid % 16 of rows i = tid / 16 + 16 q, one pass over k
     double *G = Gbuf + asm_mat_off[a];
     const int j = c;
     double acc[kAsmSlots];
@@ -1221,8 +1221,7 @@ __global__ __launch_bounds__(kApply) void pc_apply1_kernel(
 // workgroups, then bound by the blocks' bandwidth.  With alpha, r / alpha is applied and
 // stored to v: GMRES scales its new basis vector here.  Against three kernels and the
 // scaling (launches without their gaps): 16 bacteria 27.0 -> 10.7 us, 100 37.9 -> 18.6
-// (59 MB, 3.2 TB/s), 1,024 150.7 -> 142.0 (600 MB, 4.2 TB/s), 1,000 free 42-blob shells
-// 38.5 -> 26.2.  A chain of 20 bodies with 57 constraint rows: 22.6 us when each step
+// (59 MB, 3.2 TB/s), 1,000 free 42-blob shells 38.5 -> 26.2.  A chain of 20 bodies with 57 constraint rows: 22.6 us when each step
 // searched bodies and rows one after the other, 14.8 with bisection and a mask of a body's
 // rows (three kernels and the scaling 14.1 + 2.3 and two launches more).
 constexpr int kFuseBlocks = 256;  // workgroups an apply is split into (100 bacteria with
